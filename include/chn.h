@@ -146,7 +146,11 @@ chn_status chn_reduce_axis_static(int op, const chn_array *in, int axis, int kee
  * y = x @ W.T + b with W (n_out, n_in), is A = x, B = the (n_in, n_out) view of W with strides
  * swapped, epilogue CHN_EPI_BIAS.  A and B must each have one unit-stride dimension; C (and
  * `preact_out`, `aux`) must be row-major (unit stride along N).
- * dtypes: A,B F32 -> C F32 (fp32 matrix cores); A,B BF16 -> C BF16 or F32 (fp32 accumulation).
+ * dtypes: A,B F32 -> C F32; A,B BF16 -> C BF16 or F32 (fp32 accumulation).  F32 products run on the fp32 matrix
+ * instruction or, where that is faster, on the bfloat16 one with every operand value split into three bfloat16 parts
+ * that carry all its 24 bits: six partial products, fp32 accumulation, an error no larger than the instruction's (tiles
+ * whose operands hold infinities or magnitudes beyond 2^48, or rows with nothing above 2^-90, are computed on the fp32
+ * instruction).
  * Epilogue, applied to v = alpha*acc + beta*C in fp32 before the single final rounding:
  *   BIAS       v + bias[n]                         bias (N,) F32
  *   BIAS_RELU  max(0, v + bias[n])
@@ -490,14 +494,17 @@ int chn_elementwise_plan(int op, int n_in, const chn_array *const *in, const chn
 /* The same for chn_gemm: bits 0-1 macro tile (0: 64x64, 1: 128x128, 2: 256x256, 3: 256x128 - bfloat16
  * products with both operands unit-stride along K whose N is too small for 256 blocks of the square tile),
  * bit 2 set when a kernel that copies operand tiles straight from global memory into LDS is taken, bit 3 when that
- * is the kernel that works on the tile with eight waves (bfloat16 products), bits 4 and up the number of
- * K splits (1 = none;
+ * is the kernel that works on the tile with eight waves (bfloat16 products) or, for an F32 product, when it runs on
+ * the bfloat16 matrix cores, each operand as the sum of three bfloat16 parts (same accuracy; bits 0-2 then tell what
+ * the plan on the fp32 matrix instruction would be), bits 4 and up the number of K splits (1 = none;
  * have_workspace = 0 plans as chn_gemm does without workspace). */
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);
 /* Test hook: replace the planner's choice for every later chn_gemm / chn_gemm_plan of the process.
  * tile: 0 .. 3 as above, or -1 for the planner's own; splits: a number of K splits >= 1 (used when a
  * workspace allows it), or -1; direct_copy: 0 keeps products off the direct-copy kernels, -1 or 1 lets
- * the planner take them where they fit, 2 / 3 additionally fix the four-wave / eight-wave kernel.  A forced value that the operands do not allow (the large tiles
+ * the planner take them where they fit, 2 / 3 additionally fix the four-wave / eight-wave kernel; 4 puts F32
+ * products on the three-part kernel (its 64x64 tile with tile = 0, its 128x128 tile with tile = 1), any other value but
+ * -1 and any forced tile keep them off it.  A forced value that the operands do not allow (the large tiles
  * need 8-byte pieces) is ignored.  Results do not depend on the plan beyond summation order; the tests
  * use this to run short products on the large tiles.  (-1, -1, -1) restores normal planning. */
 void chn_gemm_plan_override(int tile, int splits, int direct_copy);

@@ -25,6 +25,7 @@ using gemm::GemmArgs;
 std::atomic<int> g_force_tile{-1}, g_force_splits{-1}, g_force_direct{-1};
 constexpr double kNarrowStep = 0.92, kNarrowFixed = 12.0;   // microseconds per tile step / per block of the 256 x 128 tile
 std::atomic<int> g_force_w8{-1};
+std::atomic<int> g_force_parts{-1};   // 1: fp32 products on the three-part kernel, on the forced tile
 
 // Largest load piece (bytes) that is aligned for every row start of the operand and divides its
 // extent along the unit-stride dimension, so that a piece is never partly out of range.
@@ -85,7 +86,7 @@ bool direct_copy_fits(const GemmArgs &g, int isz, bool a_kc, bool b_kc) {
 // compute units but a long K is cut along K: every split writes fp32 partial sums to the workspace and
 // a second kernel adds them in a fixed order and runs the epilogue (its traffic and launch are charged
 // to the split candidates).
-void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
+double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit) {
   // microseconds per tile step [tile][0: both operands K-contiguous, 1: one, 2: none] and per block
   static const double step_bf16[3][3] = {{0.27, 0.33, 0.56}, {0.57, 0.68, 1.12}, {1.90, 2.25, 2.70}};
   static const double step_f32[3][3] = {{0.52, 0.62, 0.65}, {1.95, 2.40, 2.10}, {6.90, 7.50, 7.90}};
@@ -148,6 +149,62 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   g->tiles_n = (g->N + bn - 1) / bn;
   g->ldp = (g->N + 3) & ~3;
   g->dma = (g->tile == 2 || g->tile == 3) && direct;
+  g->parts = 0;
+  return best;
+}
+
+// fp32 products on the bfloat16 matrix cores (gemm_split.h): the 128x128 tile in two groups of waves or the 64x64 tile
+// in four, against the best plan on the fp32 matrix instruction, by the same kind of model (microseconds, a launch not
+// counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 plus its tile
+// steps (32 k on the large tile, 64 on the small one); a step takes longer when all 256 compute units pull operands out of
+// the L2s than when a quarter of them does, and with operands that allow 8- or 4-byte pieces only.  Each compute
+// unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 21 on the
+// small tile, 4480x2688x672 153 -> 100 and 4480x10000x672 478 -> 350 on the large one, 672x2688x4480 both stored along
+// M/N 178 -> 111 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
+void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
+  double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
+  const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
+  const bool other_forced = force_tile >= 0 || g_force_direct.load(std::memory_order_relaxed) >= 0 || g_force_w8.load(std::memory_order_relaxed) >= 0;
+  constexpr int64_t kMaxLd = 1 << 22;                       // 32-bit byte offsets inside a tile
+  if (isz != 4 || big_unsplit || g->K == 0 || g->lda >= kMaxLd || g->ldb >= kMaxLd || (other_forced && force != 1)) return;
+  static const double step_large[3] = {1.0, 1.25, 1.2}, step_small[3] = {0.78, 1.1, 0.95};   // both along K, one, none
+  const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
+  auto narrow = [](int piece, bool kc, bool large) {
+    if (piece == 16) return 1.0;
+    if (piece == 8) return large ? (kc ? 1.05 : 1.35) : 1.1;
+    return large ? (kc ? 3.2 : 1.9) : (kc ? 3.7 : 3.0);
+  };
+  if (g->splits > 1) best -= 5e-6;                          // (a finishing launch is charged 5 us here, on both sides)
+  static const int split_choices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
+  const int forced_splits = g_force_splits.load(std::memory_order_relaxed);
+  if (force == 1) best = 1e300;
+  GemmArgs p = *g;
+  for (int large = 1; large >= 0; --large) {
+    if (force == 1 && force_tile >= 0 && force_tile != large) continue;
+    const int b = large ? 128 : 64, bk = large ? 32 : 64;
+    const int64_t tiles = (int64_t)((g->M + b - 1) / b) * ((g->N + b - 1) / b);
+    const int nk = (g->K + bk - 1) / bk;
+    const double na = narrow(g->piece_a, a_kc, large), nb = narrow(g->piece_b, b_kc, large);
+    const double step = (large ? step_large : step_small)[lay] * (na > nb ? na : nb);
+    for (int s : split_choices) {
+      if (s > 1 && (!allow_split || s > nk / 4)) break;
+      if (forced_splits >= 1 && allow_split && forced_splits <= nk) s = forced_splits;
+      const int64_t blocks = tiles * s, rounds = (blocks + 255) / 256;
+      const double fill = blocks < 256 ? (double)blocks / 256 : 1.0;
+      const int steps = (nk + s - 1) / s;
+      double t = (double)rounds * (5.6 + steps * step * (large ? 0.9 + 0.25 * fill : 0.6 + 0.4 * fill)) * 1e-6;
+      if (s > 1) t += 5e-6 + (double)(s + 1) * g->M * g->N * 4.0 / 4e12;
+      if (t < best * 0.97) {
+        best = t;
+        p.parts = large ? 2 : 1;
+        p.splits = s;
+        p.tiles_m = (g->M + b - 1) / b;
+        p.tiles_n = (g->N + b - 1) / b;
+      }
+      if (s == forced_splits) break;
+    }
+  }
+  if (p.parts) *g = p;
 }
 
 // Which of the two direct-copy kernels takes a bf16 product on the 256x256 tile: the eight-wave one.  Both
@@ -188,8 +245,9 @@ size_t chn_gemm_workspace_bytes(const chn_array *A, const chn_array *B, const ch
 void chn_gemm_plan_override(int tile, int splits, int direct_copy) {
   chn::g_force_tile.store(tile, std::memory_order_relaxed);
   chn::g_force_splits.store(splits, std::memory_order_relaxed);
-  chn::g_force_direct.store(direct_copy >= 2 ? 1 : direct_copy, std::memory_order_relaxed);
+  chn::g_force_direct.store(direct_copy == 4 ? -1 : direct_copy >= 2 ? 1 : direct_copy, std::memory_order_relaxed);
   chn::g_force_w8.store(direct_copy == 2 ? 0 : direct_copy == 3 ? 1 : -1, std::memory_order_relaxed);
+  chn::g_force_parts.store(direct_copy == 4 ? 1 : -1, std::memory_order_relaxed);
 }
 
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace) {
@@ -206,7 +264,7 @@ int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, in
   CHN_TRY(classify(A, B, &g, &a_kc, &b_kc));
   const int isz = dtype_size(A->dtype);
   plan(&g, isz, a_kc, b_kc, have_workspace != 0);
-  return g.tile | (g.dma ? 4 : 0) | (eight_waves(g, isz, CHN_EPI_NONE) ? 8 : 0) | (g.splits << 4);
+  return g.tile | (g.dma ? 4 : 0) | (eight_waves(g, isz, CHN_EPI_NONE) || g.parts ? 8 : 0) | (g.splits << 4);
 }
 
 chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, float alpha, float beta,

@@ -1,0 +1,450 @@
+// fp32 products on the bfloat16 matrix cores, at fp32 accuracy.
+//
+// A float x is the sum of three bfloat16 numbers: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), every
+// difference exact (8 + 8 + 8 significant bits, round to nearest even at each step, |m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|).  A product a b is then
+//     ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + [am bl + al bm + al bl],
+// and what stands in brackets is below 2^-24 |a b|, of random sign: less than the rounding of the product itself.
+// Six products of v_mfma_f32_32x32x16_bf16 (32 cycles for 16 k) replace eight of v_mfma_f32_32x32x2_f32
+// (64 cycles for 2 k each): 192 instead of 512 cycles of the matrix pipe for the same part of C, with fewer
+// roundings of the fp32 accumulator on the way: the error against 64 bits (2-norm) falls from 5.7e-7 to 1.0e-7 at
+// K = 1000 and from 1.15e-6 to 2.7e-7 at K = 4096.
+//
+// Measured (us, fp32 instruction -> here): 1024x1000x1000 27.2 -> 20.6, 4480x2688x672 153 -> 100, 4480x10000x672
+// 478 -> 350, 4096x4096x4096 919 -> 667 (206 TFLOP/s, where the instruction's peak is 157).  What bounds the large
+// tile at 4096^3: the matrix pipes are busy half of the cycles at the 1.97 GHz the chip holds; without staging (loads,
+// splitting, LDS writes) the same loop takes 516, with the matrix work alone 483.  The small tile waits for the chip-wide
+// stream of operand tiles out of the L2s (20.6 -> 12.9 without staging).
+#pragma once
+#include "gemm_kernel.h"
+
+namespace chn {
+namespace gemm {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
+  const floatx2 v = {x, y};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The three parts of two neighbouring values, packed (first value in the low half).
+__device__ __forceinline__ void split2(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) {
+  h = pack_bf16(x, y);
+  x -= __uint_as_float(h << 16);
+  y -= __uint_as_float(h & 0xffff0000u);
+  m = pack_bf16(x, y);
+  x -= __uint_as_float(m << 16);
+  y -= __uint_as_float(m & 0xffff0000u);
+  l = pack_bf16(x, y);
+}
+
+// max(|x|, |y|, m) in one instruction (a NaN operand drops out: such a row is NaN on either path)
+__device__ __forceinline__ float absmax3(float x, float y, float m) {
+  float r;
+  asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(x), "v"(y), "v"(m));
+  return r;
+}
+
+// One operand tile in LDS: sub-tiles of 32 k, each three planes (h, m, l) of ROWS rows, 32 k of bfloat16 = 64 bytes =
+// four 16-byte chunks per row.  Chunk q holds k = 4q .. 4q+3 and 16+4q .. 16+4q+3 of the sub-tile (the sum over k is
+// order-free as long as both operands agree; this order lets four lanes fetch 64 contiguous bytes of a row per load).
+// Four rows share the 256 bytes of the 64 LDS banks; rows and chunks are XORed with (row / 4) % 4 so that 16 lanes
+// touch 16 different 16-byte slots in each access pattern: fragment reads (16 rows, one chunk), row-wise writes
+// (4 rows x 4 chunks) and transposing writes (rows 4 apart x 4 chunks).
+__device__ __forceinline__ int split_off(int row, int q) {
+  const int s = (row >> 2) & 3;
+  return (row ^ s) * 64 + ((q ^ s) << 4);
+}
+template <int ROWS> constexpr int kSplitSub = 3 * ROWS * 64;       // bytes of one operand's sub-tile
+
+// Global memory -> registers -> planes in LDS for one operand tile of ROWS rows and SUBS sub-tiles, T threads.
+template <int ROWS, int SUBS, bool KC, int T>
+struct SplitLoader {
+  // unit stride along K: a thread has NU units of eight k of a row (two 16-byte loads each); along M/N: one unit of
+  // R rows of k by four m
+  static constexpr int NU = KC ? ROWS * SUBS * 4 / T : 1;
+  static constexpr int R = ROWS * SUBS * 8 / T;           // 16-byte loads per thread
+  static_assert(R == 2 || R == 4, "the tile is dealt out evenly");
+  const char *base;                                       // uniform: the tile's first row (KC) / column (MC) at k = 0
+  uint32_t off[NU];                                       // byte offset of the unit's first element
+  int lim, K, koff;
+  float top[KC ? NU : 4];                                 // largest magnitude seen, per row
+  int64_t kstride;                                        // bytes between consecutive k (MC)
+  int lds;                                                // where the first unit goes inside a stage
+  int sw;                                                 // MC: swizzle of the unit's rows
+
+  __device__ __forceinline__ void init(int t, const float *p, int64_t ld, int rows_total, int row0, int K_) {
+    K = K_;
+    kstride = ld * 4;
+#pragma unroll
+    for (int i = 0; i < (KC ? NU : 4); ++i) top[i] = 0.0f;
+    if constexpr (KC) {
+      const int q = t & 3, row = (t >> 2) % ROWS, sub = t / (4 * ROWS);
+      koff = sub * 32 + q * 4;
+      base = reinterpret_cast<const char *>(p + (int64_t)row0 * ld);
+      // (rows past the end re-read the last one: they only feed rows or columns of C that are not stored)
+#pragma unroll
+      for (int u = 0; u < NU; ++u) off[u] = (uint32_t)((min(row + u * (T / 4), rows_total - 1 - row0) * ld + koff) * 4);
+      lim = K - koff;
+      lds = sub * kSplitSub<ROWS> + split_off(row, q);    // (units T / 4 rows apart: whole periods of the swizzle)
+    } else {
+      constexpr int PAIRS = 4 / R;                        // units that share a group of four k
+      const int pair = t % PAIRS, kg = (t / PAIRS) & 7, mc = (t / (8 * PAIRS)) % (ROWS / 4), sub = t / (2 * PAIRS * ROWS);
+      koff = sub * 32 + (kg >> 2) * 16 + (kg & 3) * 4 + pair * 2;
+      base = reinterpret_cast<const char *>(p + row0);
+      lim = rows_total - row0 - mc * 4;
+      off[0] = (uint32_t)((koff * ld + (lim > 0 ? mc * 4 : 0)) * 4);
+      sw = mc & 3;
+      // (rows 4 mc .. 4 mc + 3 share their swizzle; row 4 mc + e sits (e ^ sw) rows behind the group's start)
+      lds = sub * kSplitSub<ROWS> + mc * 256 + (((kg & 3) ^ sw) << 4) + (kg >> 2) * 8 + pair * 4;
+    }
+  }
+
+  // The loads of the tile step whose first k is k0; what lies past K (the last, ragged step and those requested beyond
+  // it) is redirected to zeros.  Along K a step whose k all exist (uniform) needs a scalar address and the thread's
+  // constant offsets only.
+  template <int PB, bool UNIFORM>
+  __device__ __forceinline__ void issue(uint4 (&reg)[R], int k0) const {
+    if constexpr (KC) {
+      const char *p = base + (int64_t)k0 * 4;
+      if (UNIFORM && k0 + SUBS * 32 <= K) {
+        constexpr int PE = PB / 4;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          uint32_t *w = &reg[j].x;
+#pragma unroll
+          for (int i = 0; i < 4 / PE; ++i) {
+            const uintptr_t a = reinterpret_cast<uintptr_t>(p + (j & 1) * 64 + i * PB) + off[j >> 1];
+            if constexpr (PB == 16) { const u32x4 v = global_load<u32x4>(a); w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3]; }
+            else if constexpr (PB == 8) { const u32x2 v = global_load<u32x2>(a); w[2 * i] = v[0]; w[2 * i + 1] = v[1]; }
+            else w[i] = global_load<uint32_t>(a);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+          reg[j] = load_chunk<float, PB>(reinterpret_cast<uintptr_t>(p) + off[j >> 1] + (j & 1) * 64, lim - k0 - 16 * (j & 1));
+      }
+    } else {
+      const uintptr_t a = reinterpret_cast<uintptr_t>(base) + off[0];
+#pragma unroll
+      for (int j = 0; j < R; ++j) reg[j] = load_chunk<float, PB>(a + (int64_t)(k0 + j) * kstride, k0 + koff + j < K ? lim : 0);
+    }
+  }
+
+  __device__ __forceinline__ void store(const uint4 (&reg)[R], char *stage) {
+    constexpr int PLANE = ROWS * 64;
+    if constexpr (KC) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const uint4 a = reg[2 * u], b = reg[2 * u + 1];
+        const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                            __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+        uint4 h, m, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          split2(f[2 * e], f[2 * e + 1], (&h.x)[e], (&m.x)[e], (&l.x)[e]);
+          top[u] = absmax3(f[2 * e], f[2 * e + 1], top[u]);
+        }
+        char *p = stage + lds + u * (T / 4) * 64;
+        *reinterpret_cast<uint4 *>(p) = h;
+        *reinterpret_cast<uint4 *>(p + PLANE) = m;
+        *reinterpret_cast<uint4 *>(p + 2 * PLANE) = l;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        uint32_t h[R / 2], m[R / 2], l[R / 2];
+#pragma unroll
+        for (int j = 0; j < R / 2; ++j) {
+          const float x = __uint_as_float((&reg[2 * j].x)[e]), y = __uint_as_float((&reg[2 * j + 1].x)[e]);
+          split2(x, y, h[j], m[j], l[j]);
+          top[e] = absmax3(x, y, top[e]);
+        }
+        char *p = stage + lds + ((e ^ sw) << 6);
+        if constexpr (R == 4) {
+          *reinterpret_cast<uint2 *>(p) = make_uint2(h[0], h[1]);
+          *reinterpret_cast<uint2 *>(p + PLANE) = make_uint2(m[0], m[1]);
+          *reinterpret_cast<uint2 *>(p + 2 * PLANE) = make_uint2(l[0], l[1]);
+        } else {
+          *reinterpret_cast<uint32_t *>(p) = h[0];
+          *reinterpret_cast<uint32_t *>(p + PLANE) = m[0];
+          *reinterpret_cast<uint32_t *>(p + 2 * PLANE) = l[0];
+        }
+      }
+    }
+  }
+
+  // Whether a row of the tile cannot be carried by the three parts: its largest magnitude is so large that a part or
+  // a sum of products could overflow where fp32 would not (infinities included), or so small that the last parts would
+  // fall out of bfloat16's range.  Rows of zeros are fine.
+  __device__ __forceinline__ bool out_of_range() const {
+    constexpr float kMost = 0x1p48f, kLeast = 0x1p-90f;
+    constexpr int LANES = KC ? 4 : 8 * (4 / R);           // neighbouring lanes hold parts of the same row
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < (KC ? NU : 4); ++e) {
+      float t = top[e];
+#pragma unroll
+      for (int o = 1; o < LANES; o <<= 1) t = fmaxf(t, __shfl_xor(t, o, 64));
+      if (!KC && e >= lim) t = 0.0f;                      // what follows the operand's last row never reaches C
+      bad = bad || t > kMost || (t > 0.0f && t < kLeast);
+    }
+    return bad;
+  }
+};
+
+// Workgroup of 4 KG waves: KG groups of 2 x 2 waves, a wave owns 32 TM x 32 TN of the (64 TM) x (64 TN) tile and every
+// KG-th 16 k of the contraction; the groups' sums meet in LDS at the end, in group order.  A tile step is 16 KG k.
+// The groups exist because a product this small has one tile per compute unit: KG waves on every SIMD
+// instead of one, so that loads, splitting, LDS traffic and matrix work of different waves overlap.  Even groups
+// multiply first and then split and store their part of the next tile, odd groups the other way round: the matrix pipe
+// and the vector pipe of a SIMD are both busy between two barriers.
+// The products with a low part go to an accumulator of their own (they are 2^-8 of the others), so the main sum is
+// rounded once per 16 k instead of six times.
+template <int TM, int TN, int KG>
+constexpr int kSplitStage = (KG / 2) * (kSplitSub<64 * TM> + kSplitSub<64 * TN>);
+
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
+__global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
+  constexpr int BM = 64 * TM, BN = 64 * TN, BK = 16 * KG, SUBS = KG / 2;
+  constexpr int A_BYTES = SUBS * kSplitSub<BM>, STAGE = kSplitStage<TM, TN, KG>;
+  constexpr int SETS = KG == 4 ? 2 : 1, NT = 256 * KG;    // (the large tile has no registers for a second set)
+  extern __shared__ __align__(16) char lds[];
+  __shared__ int redo;
+
+  const TilePos tp = tile_pos(g);
+  const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BN;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  const int r = lane & 31, h = lane >> 5;
+  const int nk_all = (g.K + BK - 1) / BK;
+  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int kt0 = split * per_split;
+  const int nk = min(nk_all, kt0 + per_split);
+
+  floatx16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.0f;
+  if (threadIdx.x == 0) redo = 0;
+  {
+    // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
+    // by all threads together, so that every wave has the same mixture of work.
+    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || KG == 4;
+    using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
+    using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
+    LA la;
+    LB lb;
+    const bool do_a = wave < 2 * KG;                      // (uniform over a wave)
+    const int t = kHalves ? (int)threadIdx.x & (NT / 2 - 1) : (int)threadIdx.x;
+    if constexpr (kAlike) {
+      la.init(t, static_cast<const float *>(do_a ? g.A : g.B), do_a ? g.lda : g.ldb, do_a ? g.M : g.N, do_a ? m0 : n0, g.K);
+    } else {
+      if (do_a || !kHalves) la.init(t, static_cast<const float *>(g.A), g.lda, g.M, m0, g.K);
+      if (!do_a || !kHalves) lb.init(t, static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K);
+    }
+    // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
+    uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
+    auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
+      if constexpr (!kHalves) { la.template issue<PBA, kAlike>(xa, kt * BK); lb.template issue<PBB, kAlike>(xb, kt * BK); }
+      else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
+      else if constexpr (kAlike) { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else la.template issue<PBB, kAlike>(xa, kt * BK); }
+      else { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else lb.template issue<PBB, kAlike>(xa, kt * BK); }
+    };
+    auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage) __attribute__((always_inline)) {
+      if constexpr (!kHalves) { la.store(xa, stage); lb.store(xb, stage + A_BYTES); }
+      else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES));
+      else { if (do_a) la.store(xa, stage); else lb.store(xa, stage + A_BYTES); }
+    };
+    // this group's 16 k inside a stage: sub-tile grp / 2, k-step grp % 2
+    const int off = split_off(r, (grp & 1) * 2 + h);
+    const int a_at = (grp >> 1) * kSplitSub<BM> + wm * TM * (32 * 64) + off;
+    const int b_at = A_BYTES + (grp >> 1) * kSplitSub<BN> + wn * TN * (32 * 64) + off;
+    auto product = [&](floatx16 (&d)[TM][TN], const uint4 (&a)[TM], const uint4 (&b)[TN]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          d[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[j]), d[i][j], 0, 0, 0);
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    uint4 a[3][TM], b[3][TN];                             // the fragments of this wave's 16 k: parts h, m, l
+    auto read_a = [&](const char *stage, int p) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[p][i] = *reinterpret_cast<const uint4 *>(stage + a_at + p * (BM * 64) + i * (32 * 64));
+    };
+    auto read_b = [&](const char *stage, int p) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[p][j] = *reinterpret_cast<const uint4 *>(stage + b_at + p * (BN * 64) + j * (32 * 64));
+    };
+    // the first two tiles are fetched together
+    issue(ra, rb, kt0);
+    issue(ra1, rb1, kt0 + 1);
+    store(ra, rb, lds);
+    issue(ra, rb, kt0 + 2);
+    store(ra1, rb1, lds + STAGE);
+    if constexpr (SETS == 2) issue(ra1, rb1, kt0 + 3);
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) { read_a(lds, p); read_b(lds, p); }
+    // One tile step.  Its fragments are in registers when it starts; behind its barrier the next tile lies in `nxt`
+    // and nobody reads `cur` any more.  The parts are used in an order that frees them one after the other: each is
+    // replaced by the next tile's as soon as its last product has been issued, the two that are needed longest (both h)
+    // while the first product of the next step (m m) does without them.  Meanwhile the tile after the next is split
+    // and stored into `cur`, by the odd groups before the products, by the even ones after them.
+    auto step = [&](auto set_c, int kt) __attribute__((always_inline)) {
+      constexpr int SET = decltype(set_c)::value;
+      char *cur = lds + (SET == 0 ? 0 : STAGE);
+      const char *nxt = lds + (SET == 0 ? STAGE : 0);
+      const bool early = grp & 1;
+      auto stage_next = [&]() __attribute__((always_inline)) {
+        if constexpr (SETS == 2 && SET == 1) { store(ra1, rb1, cur); issue(ra1, rb1, kt + 4); }
+        else { store(ra, rb, cur); issue(ra, rb, kt + SETS + 2); }
+      };
+      __syncthreads();
+      if (early) stage_next();
+      product(low, a[1], b[1]);
+      product(low, a[1], b[0]);
+      read_a(nxt, 1);
+      product(low, a[0], b[1]);
+      read_b(nxt, 1);
+      product(low, a[2], b[0]);
+      read_a(nxt, 2);
+      product(low, a[0], b[2]);
+      read_b(nxt, 2);
+      product(acc, a[0], b[0]);
+      read_a(nxt, 0);
+      read_b(nxt, 0);
+      if (!early) stage_next();
+    };
+    int kt = kt0;
+    for (; kt + 1 < nk; kt += 2) {
+      step(S0{}, kt);
+      step(S1{}, kt + 1);
+    }
+    if (kt < nk) step(S0{}, kt);
+    __syncthreads();
+    if (((kAlike || do_a || !kHalves) && la.out_of_range()) || (!kAlike && (!do_a || !kHalves) && lb.out_of_range())) redo = 1;
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+  // Parts of the accumulators pass between the groups through LDS: [part][wave of the group][value][lane].
+  float *meet = reinterpret_cast<float *>(lds) + (wave & 3) * (TN * 16 * 64) + lane;
+  constexpr int PART = 4 * TN * 16 * 64;                  // floats of 32 rows of every wave
+  auto put = [&](int part, const floatx16 (&x)[TN]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) meet[part * PART + (j * 16 + v) * 64] = x[j][v];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto get = [&](int part, floatx16 (&x)[TN], bool add) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float y = meet[part * PART + (j * 16 + v) * 64];
+        x[j][v] = add ? x[j][v] + y : y;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  static_assert(3 * PART * 4 <= 2 * STAGE, "the parts fit the stages");
+  if constexpr (KG == 2) {                                // each group ends up with one of the tile's two 32-row blocks per wave
+    static_assert(TM == 2, "one block per group");
+    if (grp == 0) put(0, acc[1]); else put(1, acc[0]);
+    __syncthreads();
+    if (grp == 0) get(1, acc[0], true); else get(0, acc[1], true);
+  } else {                                                // the first group takes everything, in group order
+    static_assert(TM == 1, "three parts");
+    if (grp > 0) put(grp - 1, acc[0]);
+    __syncthreads();
+    if (grp == 0) { get(0, acc[0], true); get(1, acc[0], true); get(2, acc[0], true); }
+  }
+  if (redo) {
+    // Some row of this tile's operands is outside what the parts can carry: the first group multiplies the tile again
+    // on the fp32 matrix instruction, without ceremony (BM + BN rows of 128 bytes, loaded, stored, multiplied).
+    TileLoader<float, BM, A_KC, PBA> la;
+    TileLoader<float, BN, B_KC, PBB> lb;
+    la.init(static_cast<const float *>(g.A), g.lda, g.M, m0, g.K);
+    lb.init(static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K);
+    const int rp = lds_row<float>(r), sw = (r >> 1) & 7;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+#pragma unroll 1
+    for (int k0 = kt0 * BK; k0 < nk * BK; k0 += 32) {
+      if (grp == 0) { la.issue(k0); lb.issue(k0); }
+      __syncthreads();
+      if (grp == 0) { la.store(lds); lb.store(lds + BM * 128); }
+      __syncthreads();
+      if (grp == 0) {
+        Frags<TM, TN> f;
+#pragma unroll 1
+        for (int ks = 0; ks < 4; ++ks) {
+          f.read(lds + (wm * TM * 32 + rp) * 128, lds + BM * 128 + (wn * TN * 32 + rp) * 128, ((ks * 2 + h) ^ sw) << 4);
+          mma<float, TM, TN>(acc, f);
+        }
+      }
+    }
+    __syncthreads();
+    if constexpr (KG == 2) {
+      if (grp == 0) put(0, acc[1]);
+      __syncthreads();
+      if (grp == 1) get(0, acc[1], false);
+    }
+  }
+  __syncthreads();                                        // nobody reads the parts any more
+  if constexpr (KG == 2) {
+    floatx16 own[1][TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) own[0][j] = grp == 0 ? acc[0][j] : acc[1][j];
+    // (write_out takes wave / 2 for the wave's 32-row block: 2 grp + wm here, where it is 2 wm + grp of the tile)
+    write_out<1, TN>(g, own, lds + wave * kEpiStageBytes<1, TN>, m0 + (wm - grp) * 32, n0, split);
+  } else {
+    if (grp != 0) return;
+    write_out<TM, TN>(g, acc, lds + wave * kEpiStageBytes<TM, TN>, m0, n0, split);
+  }
+}
+
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
+chn_status launch_split_piece(const GemmArgs &g, hipStream_t st) {
+  constexpr int LDS = 2 * kSplitStage<TM, TN, KG>;
+  static_assert(4 * KG * kEpiStageBytes<1, TN> <= LDS && (64 * TM + 64 * TN) * 128 <= LDS, "the stages are reused by what follows the loop");
+  auto kern = gemm_split_kernel<TM, TN, KG, A_KC, B_KC, PBA, PBB>;
+  static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "gemm: cannot reserve %d bytes of LDS: %s", LDS, hipGetErrorString(e));
+  hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256 * KG), LDS, st, g);
+  CHN_TRY(check_launch("gemm (split fp32)"));
+  if (g.splits > 1) {
+    const int64_t n = (int64_t)g.M * (g.ldp / 4);
+    hipLaunchKernelGGL(gemm_splitk_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g);
+    return check_launch("gemm split-K finish");
+  }
+  return CHN_OK;
+}
+
+template <int TM, int TN, int KG, bool A_KC, bool B_KC>
+chn_status launch_split(const GemmArgs &g, hipStream_t st) {
+  if (g.piece_a == 4 && g.piece_b == 16) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, 16>(g, st);
+  if (g.piece_a == 16 && g.piece_b == 4) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 16, 4>(g, st);
+  if (g.piece == 16) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 16, 16>(g, st);
+  if (g.piece == 8) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 8, 8>(g, st);
+  return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, 4>(g, st);
+}
+
+}  // namespace gemm
+}  // namespace chn

@@ -1,0 +1,128 @@
+"""fp32 products on the bfloat16 matrix cores: every operand value as the sum of three bfloat16 parts.
+
+Small integers come out bit for bit (their parts beyond the first are zero), random operands with an error
+against 64 bits no larger than the fp32 matrix instruction's, and operands that the parts cannot carry (infinities,
+magnitudes beyond 2^48, rows with nothing above 2^-90) exactly as the instruction computes them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1908_00213_amd import binding as B
+from oracle import oracle as O
+from tests.util import TOL_SUM, check, dev, empty, host, ws
+
+pytestmark = pytest.mark.gpu
+RNG = np.random.default_rng(19080)
+
+
+def operand(a, unit_along_k, pad):
+    """`a` (rows, k) as a device view with the wanted unit stride; pad: extra elements per stored row"""
+    stored = a if unit_along_k else a.T
+    buf = torch.full((stored.shape[0], stored.shape[1] + pad), float("nan"), device="cuda")
+    view = buf[:, :stored.shape[1]]
+    view.copy_(torch.from_numpy(np.ascontiguousarray(stored)))
+    return view if unit_along_k else view.t()
+
+
+def product(a, b, layout, tile, splits=1, pad=0, **kw):
+    """a (m, k) @ b (n, k).T on the three-part kernel (tile 0 / 1) or, tile None, off it"""
+    A, Bm = operand(a, layout[0] == "k", pad), operand(b, layout[1] == "k", pad).t()
+    B.gemm_plan_override(-1 if tile is None else tile, splits, 0 if tile is None else 4)
+    try:
+        C = kw.pop("C", None)
+        C = empty((a.shape[0], b.shape[0])) if C is None else C
+        need = B.gemm_workspace_bytes(A, Bm, C)
+        assert (need > 0) == (splits > 1)
+        return host(B.gemm(A, Bm, C, ws=ws(need), **kw))
+    finally:
+        B.gemm_plan_override()
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 64, 64), (65, 63, 33), (128, 128, 32), (130, 260, 95), (129, 127, 260), (200, 72, 129)])
+@pytest.mark.parametrize("pad", [0, 1, 2, 4])
+def test_exact_integers(tile, layout, shape, pad):
+    # edges of tiles, one to five tile steps with and without a remainder, rows that allow 16-, 8- and 4-byte
+    # pieces; the padding holds NaN, which must never reach C
+    m, n, k = shape
+    a, b = (RNG.integers(-9, 10, size=s).astype(np.float32) for s in ((m, k), (n, k)))
+    got = product(a, b, layout, tile, pad=pad)
+    assert np.array_equal(got, a.astype(np.float64) @ b.T.astype(np.float64))
+    if k >= 129:
+        assert np.array_equal(product(a, b, layout, tile, splits=2, pad=pad), got)
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mm"])
+@pytest.mark.parametrize("k", [64, 650, 3000])
+def test_error_no_larger_than_the_instruction(tile, layout, k):
+    # wide spread of magnitudes along k, so that large and small terms meet in one sum
+    a, b = (RNG.standard_normal(s).astype(np.float32) * np.exp2(RNG.integers(-12, 13, size=(1, k))).astype(np.float32) for s in ((150, k), (140, k)))
+    ref = a.astype(np.float64) @ b.T.astype(np.float64)
+    err = lambda x: np.linalg.norm(x - ref) / np.linalg.norm(ref)
+    got = product(a, b, layout, tile)
+    assert err(got) <= err(product(a, b, layout, None))
+    check(got, O.gemm(a, b.T), TOL_SUM, O.gemm(np.abs(a), np.abs(b).T), "against the oracle")
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+def test_values_the_parts_cannot_carry(tile, layout):
+    a, b = RNG.standard_normal((200, 100)).astype(np.float32), RNG.standard_normal((150, 100)).astype(np.float32)
+    b[:, 7] = np.float32(1.5)                       # exact in bfloat16: its lower parts are zero
+    for place in ("inf", "nan", "both", "huge", "tiny row", "tiny", "zero row"):
+        x = a.copy()
+        if place in ("inf", "both"):
+            x[3, 7], x[150, 0] = np.inf, -np.inf
+        if place in ("nan", "both"):
+            x[70, 5] = np.nan
+        if place == "huge":
+            x[199, 99], x[10, 3] = 3.4e38, -1e30
+        if place == "tiny row":
+            x[5] *= np.float32(1e-36)
+        if place == "tiny":
+            x *= np.float32(1e-30)
+        if place == "zero row":
+            x[140] = 0
+        got, want = product(x, b, layout, tile), product(x, b, layout, None)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), place
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)]) and np.array_equal(np.isinf(got), np.isinf(want)), place
+        fin = np.isfinite(want) & np.isfinite(got)
+        # both sum 100 terms in fp32: each within 100 * 2^-24 of the sum of magnitudes
+        xs = np.nan_to_num(np.abs(x), nan=0.0, posinf=0.0).astype(np.float64)
+        S = xs @ np.abs(b).T.astype(np.float64)
+        assert np.all(np.abs(got[fin] - want[fin]) <= 2 * 100 * 2.0 ** -24 * S[fin]), place
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("splits", [1, 3])
+def test_epilogues(tile, splits):
+    # vector and element-wise epilogue paths (an interior of full 16-byte groups and ragged edges), cut along K or not
+    m, n, k = 190, 205, 800
+    a, b = RNG.standard_normal((m, k)).astype(np.float32), RNG.standard_normal((n, k)).astype(np.float32) / 28
+    bias, aux, c0 = (RNG.standard_normal(s).astype(np.float32) for s in ((n,), (m, n), (m, n)))
+    lin, S = O.gemm(a, b.T), O.gemm(np.abs(a), np.abs(b).T)
+    run = lambda **kw: product(a, b, "km", tile, splits, **kw)
+    for C in (lambda: empty((m, n)), lambda: empty((m, n + 3))[:, :n]):
+        pre = C()
+        z = lin + bias
+        check(run(C=C(), epilogue="bias_gelu", bias=dev(bias), preact_out=pre), O.elementwise("gelu", [z]), TOL_SUM, S + np.abs(bias), "bias_gelu")
+        check(host(pre), z, TOL_SUM, S + np.abs(bias), "pre-activation")
+        check(run(C=C(), epilogue="bias_relu", bias=dev(bias)), np.maximum(z, 0), TOL_SUM, S + np.abs(bias), "bias_relu")
+        check(run(C=C(), epilogue="relu_bwd", aux=dev(aux)), np.where(aux > 0, lin, 0.0), TOL_SUM, S, "relu_bwd")
+        old = C()
+        old.copy_(dev(c0))
+        check(run(C=old, alpha=0.5, beta=-2.0), 0.5 * lin - 2.0 * c0, TOL_SUM, S + 2 * np.abs(c0), "alpha beta")
+
+
+def test_planner_takes_the_kernel_and_results_repeat():
+    # mid-size and large products without any override; the same call twice gives the same bits
+    for m, n, k in ((1024, 1000, 1000), (1100, 1300, 700)):
+        A, Bm = torch.randn(m, k, device="cuda"), torch.randn(n, k, device="cuda").t()
+        assert B.gemm_plan_eight_waves(A, Bm, empty((m, n)), True)
+        need = B.gemm_workspace_bytes(A, Bm, empty((m, n)))
+        x, y = (B.gemm(A, Bm, empty((m, n)), ws=ws(need)) for _ in range(2))
+        assert torch.equal(x, y)
+        ref = A.double() @ Bm.double()
+        assert float((x.double() - ref).norm() / ref.norm()) < 6e-7
