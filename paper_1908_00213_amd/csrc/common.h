@@ -147,6 +147,41 @@ template <> struct Vec16<bf16_raw> {
   }
 };
 
+// The same sixteen bytes at any element address: global memory takes a 16-byte access at any byte address, so a row that
+// starts between two 16-byte boundaries is still moved in whole vectors.
+typedef chn_u32x4 chn_u32x4_any __attribute__((aligned(2)));
+template <typename T>
+__device__ __forceinline__ Vec16<T> load16_any(const T *p) {
+  const chn_u32x4 v = *reinterpret_cast<const chn_u32x4_any *>(p);
+  Vec16<T> r;
+  __builtin_memcpy(&r.raw, &v, 16);
+  return r;
+}
+template <typename T>
+__device__ __forceinline__ void store16_any(T *p, const Vec16<T> &x) {
+  chn_u32x4 v;
+  __builtin_memcpy(&v, &x.raw, 16);
+  *reinterpret_cast<chn_u32x4_any *>(p) = v;
+}
+// The first n (0 .. whole vector) elements only; the others read as zero / stay untouched.
+template <typename T>
+__device__ __forceinline__ Vec16<T> load16_part(const T *p, int64_t n) {
+  if (n >= Vec16<T>::N) return load16_any(p);
+  Vec16<T> r;
+  r.raw = {};
+#pragma unroll
+  for (int i = 0; i < Vec16<T>::N; ++i)
+    if (i < n) r.set(i, Elem<T>::load(p + i));
+  return r;
+}
+template <typename T>
+__device__ __forceinline__ void store16_part(T *p, const Vec16<T> &x, int64_t n) {
+  if (n >= Vec16<T>::N) { store16_any(p, x); return; }
+#pragma unroll
+  for (int i = 0; i < Vec16<T>::N; ++i)
+    if (i < n) Elem<T>::store(p + i, x.get(i));
+}
+
 // erfc with a relative error of about 1e-6 everywhere, tails included: the Chebyshev fit
 // erfc(z) ~ t exp(-z^2 + P(t)), t = 1 / (1 + z/2), z >= 0, of Numerical Recipes' "erfcc" (fractional
 // error below 1.2e-7 in exact arithmetic; the fp32 evaluation of the exponent adds up to a few 1e-6

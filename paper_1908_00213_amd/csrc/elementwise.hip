@@ -7,7 +7,7 @@
 //   0  flat      output and full-size inputs contiguous; other inputs repeat with a fixed period
 //                (row broadcast, e.g. a bias) or are scalars.  16-byte vector loads and stores.
 //   1  rows      every operand has inner stride 1 or 0; outer dimensions arbitrary (pitched rows,
-//                column broadcast, sliced views).  Coalesced scalar accesses.
+//                column broadcast, sliced views).  16-byte accesses at any element address.
 //   2  transpose 2-d; some inputs are unit-stride along dimension 0 (transposed views).  Those go
 //                through a 64x64 LDS tile so that both their reads and the output writes coalesce.
 //   3  general   anything else: one thread per element, full index decomposition.
@@ -323,34 +323,51 @@ struct StridedArgs {
   int64_t istr[3][CHN_MAX_NDIM];
 };
 
-constexpr int kRowsThreads = 256;
-constexpr int kRowsUnroll = 4;
-
-// family 1: inner dimension has stride 1 or 0 in every operand; one block covers a chunk of one row
-template <typename Tin, typename Tout>
-__global__ __launch_bounds__(kRowsThreads) void ew_rows_kernel(StridedArgs a, int64_t chunks_per_row) {
+// family 1: inner dimension has stride 1 or 0 in every operand.  HBM-bound: a thread moves E neighbouring elements of one
+// row in 16-byte accesses at whatever address the row has; 1 << tpr threads share a row and a block takes 256 >> tpr
+// rows, so that rows shorter than a block's width do not leave most of it idle.  (One element per thread and
+// access, with the operation picked at run time, took 60.6 us for relu(a * b + c) on 4999 x 3001 bf16 slices and 304 us
+// on 8001 x 8001 fp32 ones: 17.3 and 138 us now, 5.6 TB/s.)
+template <int OP, typename Tin, typename Tout, int NIN>
+__global__ __launch_bounds__(256) void ew_rows_kernel(StridedArgs a, int tpr, int64_t chunks, int64_t rows) {
+  constexpr int E = (sizeof(Tin) == 2 || sizeof(Tout) == 2) ? 8 : 4, NI = E / Vec16<Tin>::N, NO = E / Vec16<Tout>::N;
   const int last = a.nd - 1;
   const int64_t n = a.shape[last];
-  int64_t row = (int64_t)blockIdx.x / chunks_per_row;
-  const int64_t chunk = (int64_t)blockIdx.x % chunks_per_row;
+  int64_t row = ((int64_t)blockIdx.x / chunks) * (256 >> tpr) + (threadIdx.x >> tpr);
+  const int64_t c = ((((int64_t)blockIdx.x % chunks) << tpr) + (threadIdx.x & ((1 << tpr) - 1))) * E;
+  if (row >= rows || c >= n) return;
   int64_t ooff = 0, ioff[3] = {0, 0, 0};
   for (int d = last - 1; d >= 0; --d) {
-    const int64_t i = row % a.shape[d];
-    row /= a.shape[d];
+    int64_t i = row;
+    if (d > 0) { row = i / a.shape[d]; i -= row * a.shape[d]; }
     ooff += i * a.ostr[d];
-    for (int k = 0; k < a.n_in; ++k) ioff[k] += i * a.istr[k][d];
-  }
-  Tout *o = static_cast<Tout *>(a.out) + ooff;
 #pragma unroll
-  for (int u = 0; u < kRowsUnroll; ++u) {
-    const int64_t c = (chunk * kRowsUnroll + u) * kRowsThreads + threadIdx.x;
-    if (c < n) {
-      float f[3] = {0.0f, 0.0f, 0.0f};
-      for (int k = 0; k < a.n_in; ++k)
-        f[k] = Elem<Tin>::load(static_cast<const Tin *>(a.in[k]) + ioff[k] + c * a.istr[k][last]);
-      Elem<Tout>::store(o + c, ew_apply_rt<sizeof(Tout) == 2>(a.op, f[0], f[1], f[2], a.s0));
+    for (int k = 0; k < NIN; ++k) ioff[k] += i * a.istr[k][d];
+  }
+  Vec16<Tin> x[NIN > 0 ? NIN : 1][NI > 0 ? NI : 1];
+#pragma unroll
+  for (int k = 0; k < NIN; ++k) {
+    const Tin *p = static_cast<const Tin *>(a.in[k]) + ioff[k];
+    if (a.istr[k][last] == 0) {
+      const float v = Elem<Tin>::load(p);
+#pragma unroll
+      for (int i = 0; i < E; ++i) x[k][i / Vec16<Tin>::N].set(i % Vec16<Tin>::N, v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) x[k][i] = load16_part(p + c + i * Vec16<Tin>::N, n - c - i * Vec16<Tin>::N);
     }
   }
+  Vec16<Tout> o[NO];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    float f[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < NIN; ++k) f[k] = x[k][i / Vec16<Tin>::N].get(i % Vec16<Tin>::N);
+    o[i / Vec16<Tout>::N].set(i % Vec16<Tout>::N, ew_apply<OP, sizeof(Tout) == 2>(f[0], f[1], f[2], a.s0));
+  }
+  Tout *q = static_cast<Tout *>(a.out) + ooff + c;
+#pragma unroll
+  for (int i = 0; i < NO; ++i) store16_part(q + i * Vec16<Tout>::N, o[i], n - c - i * Vec16<Tout>::N);
 }
 
 // family 3: one thread per element
@@ -430,7 +447,10 @@ __global__ __launch_bounds__(256) void ew_transpose_kernel(TransArgs a, int64_t 
 // element reads along a column are free of bank conflicts.  The compute phase then walks rows:
 // each lane produces E consecutive columns of one row, gathering the transposed operands element by
 // element from LDS and everything else with 16-byte global loads, and stores 16 bytes.
-template <int OP, typename T, int NIN, int TC>
+// ALIGNED: extents, strides and bases are whole vectors.  Otherwise the same accesses start at any element address and
+// the last vector of a row or column may be partial (relu(a.T * b + c) with one
+// element per access: 4999 x 3001 bf16 89 us, now 30; 8001 x 8001 fp32 417, now 200).
+template <int OP, typename T, int NIN, int TC, bool ALIGNED>
 __global__ __launch_bounds__(256) void ew_transpose_vec_kernel(TransArgs a, int64_t tiles_c) {
   constexpr int E = 16 / (int)sizeof(T);
   constexpr int TR = 16 * E;
@@ -456,7 +476,10 @@ __global__ __launch_bounds__(256) void ew_transpose_vec_kernel(TransArgs a, int6
         const int c = cl + 16 * j;
         Vec16<T> v;
         v.raw = {};
-        if (r < a.rows && c0 + c < a.cols) v.load_nt(p + r + (c0 + c) * a.istr1[k]);
+        if (r < a.rows && c0 + c < a.cols) {
+          const T *q = p + r + (c0 + c) * a.istr1[k];
+          if constexpr (ALIGNED) v.load_nt(q); else v = load16_part(q, a.rows - r);
+        }
         const int key = (c / E) & 15;
         *reinterpret_cast<decltype(v.raw) *>(tiles + a.slot[k] * (TC * 256) + c * 256 + ((rchunk ^ key) << 4)) = v.raw;
       }
@@ -481,7 +504,8 @@ __global__ __launch_bounds__(256) void ew_transpose_vec_kernel(TransArgs a, int6
           const float v = Elem<T>::load(p + r * a.istr0[k]);
 #pragma unroll
           for (int i = 0; i < E; ++i) d[k][pass].set(i, v);
-        } else if (a.istr0[k] == 0) d[k][pass].load(p + c);
+        } else if constexpr (!ALIGNED) d[k][pass] = load16_part(p + r * a.istr0[k] + c, a.cols - c);
+        else if (a.istr0[k] == 0) d[k][pass].load(p + c);
         else d[k][pass].load_nt(p + r * a.istr0[k] + c);
       }
     }
@@ -508,7 +532,8 @@ __global__ __launch_bounds__(256) void ew_transpose_vec_kernel(TransArgs a, int6
 #pragma unroll
       for (int i = 0; i < E; ++i)
         o.set(i, ew_apply<OP, sizeof(T) == 2>(f[0][i], NIN > 1 ? f[1][i] : 0.0f, NIN > 2 ? f[2][i] : 0.0f, a.s0));
-      o.store_nt(static_cast<T *>(a.out) + r * a.ostr0 + c);
+      T *q = static_cast<T *>(a.out) + r * a.ostr0 + c;
+      if constexpr (ALIGNED) o.store_nt(q); else store16_part(q, o, a.cols - c);
     }
   }
 }
@@ -530,6 +555,23 @@ chn_status launch_fast(const Plan &p, const chn_array *const *in, const chn_arra
     hipLaunchKernelGGL((ew_flat_kernel<OP, Tin, Tout, NIN>), dim3((unsigned)blocks), dim3(kFlatThreads), 0, st, a);
     return check_launch("elementwise flat");
   }
+  if (p.family == 1) {
+    constexpr int E = (sizeof(Tin) == 2 || sizeof(Tout) == 2) ? 8 : 4;
+    StridedArgs a{};
+    a.out = out->data; a.nd = p.nd; a.n_in = NIN; a.op = OP; a.s0 = s0; a.total = p.total;
+    for (int d = 0; d < p.nd; ++d) {
+      a.shape[d] = p.shape[d]; a.ostr[d] = p.ostr[d];
+      for (int k = 0; k < NIN; ++k) a.istr[k][d] = p.istr[k][d];
+    }
+    for (int k = 0; k < NIN; ++k) a.in[k] = in[k]->data;
+    const int64_t n = p.shape[p.nd - 1], rows = p.total / n, vecs = (n + E - 1) / E;
+    int tpr = 0;                                            // log2 of the threads that share a row
+    while (tpr < 8 && (1 << tpr) < vecs) ++tpr;
+    const int64_t chunks = (vecs + (1 << tpr) - 1) >> tpr, blocks = (rows + (256 >> tpr) - 1) / (256 >> tpr) * chunks;
+    if (blocks > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
+    hipLaunchKernelGGL((ew_rows_kernel<OP, Tin, Tout, NIN>), dim3((unsigned)blocks), dim3(256), 0, st, a, tpr, chunks, rows);
+    return check_launch("elementwise rows");
+  }
   // family 2
   TransArgs a{};
   a.out = out->data; a.rows = p.shape[0]; a.cols = p.shape[1]; a.ostr0 = p.ostr[0]; a.s0 = s0;
@@ -540,31 +582,32 @@ chn_status launch_fast(const Plan &p, const chn_array *const *in, const chn_arra
   if (tr * tc > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
   if constexpr (NIN > 0) {
     if constexpr (std::is_same<Tin, Tout>::value) {
-      if (p.tvec) {
-        constexpr int TRV = 16 * (16 / (int)sizeof(Tin));
-        const int64_t trv = (a.rows + TRV - 1) / TRV;
-        if (trv * tc > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
-        int nslots = 0;
-        for (int k = 0; k < NIN; ++k) a.slot[k] = a.transposed[k] ? nslots++ : 0;
-        // fp32: tiles of 128 columns where the LDS tiles fit (rows of the other operands and of the output
-        // are then touched in 512-byte pieces: +4 % at 8192 x 8192; bf16 gains nothing from it)
-        if (sizeof(Tin) == 4 && nslots * 128 * 256 <= 65536) {
-          const int64_t tcw = (a.cols + 127) / 128;
-          hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 128>), dim3((unsigned)(trv * tcw)), dim3(256), nslots * 128 * 256, st, a, tcw);
-        } else {
-          hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 64>), dim3((unsigned)(trv * tc)), dim3(256), nslots * 64 * 256, st, a, tc);
-        }
-        return check_launch("elementwise transpose (vector)");
-      }
+      constexpr int TRV = 16 * (16 / (int)sizeof(Tin));
+      const int64_t trv = (a.rows + TRV - 1) / TRV;
+      if (trv * tc > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
+      int nslots = 0;
+      for (int k = 0; k < NIN; ++k) a.slot[k] = a.transposed[k] ? nslots++ : 0;
+      // fp32: tiles of 128 columns where the LDS tiles fit (rows of the other operands and of the output
+      // are then touched in 512-byte pieces: +4 % at 8192 x 8192; bf16 gains nothing from it)
+      const bool wide = sizeof(Tin) == 4 && nslots * 128 * 256 <= 65536;
+      const int64_t tcv = wide ? (a.cols + 127) / 128 : tc;
+      const dim3 grid((unsigned)(trv * tcv));
+      const int lds = nslots * (wide ? 128 : 64) * 256;
+      if (wide && p.tvec) hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 128, true>), grid, dim3(256), lds, st, a, tcv);
+      else if (wide) hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 128, false>), grid, dim3(256), lds, st, a, tcv);
+      else if (p.tvec) hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 64, true>), grid, dim3(256), lds, st, a, tcv);
+      else hipLaunchKernelGGL((ew_transpose_vec_kernel<OP, Tin, NIN, 64, false>), grid, dim3(256), lds, st, a, tcv);
+      return check_launch("elementwise transpose (vector)");
+    } else {
+      hipLaunchKernelGGL((ew_transpose_kernel<OP, Tin, Tout, NIN>), dim3((unsigned)(tr * tc)), dim3(256), 0, st, a, tc);
     }
-    hipLaunchKernelGGL((ew_transpose_kernel<OP, Tin, Tout, NIN>), dim3((unsigned)(tr * tc)), dim3(256), 0, st, a, tc);
   }
   return check_launch("elementwise transpose");
 }
 
 template <typename Tin, typename Tout>
 chn_status launch_dtype(int op, const Plan &p, const chn_array *const *in, const chn_array *out, float s0, hipStream_t st) {
-  if (p.family == 0 || p.family == 2) {
+  if (p.family != 3) {
     switch (op) {
 #define CHN_CASE(OPC) case OPC: return launch_fast<OPC, Tin, Tout>(p, in, out, s0, st);
       CHN_CASE(CHN_OP_COPY) CHN_CASE(CHN_OP_ADD) CHN_CASE(CHN_OP_SUB) CHN_CASE(CHN_OP_MUL)
@@ -583,14 +626,6 @@ chn_status launch_dtype(int op, const Plan &p, const chn_array *const *in, const
     for (int k = 0; k < p.n_in; ++k) a.istr[k][d] = p.istr[k][d];
   }
   for (int k = 0; k < p.n_in; ++k) a.in[k] = in[k]->data;
-  if (p.family == 1) {
-    int64_t n = p.shape[p.nd - 1];
-    int64_t rows = p.total / n;
-    int64_t cpr = (n + kRowsThreads * kRowsUnroll - 1) / (kRowsThreads * kRowsUnroll);
-    if (rows * cpr > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
-    hipLaunchKernelGGL((ew_rows_kernel<Tin, Tout>), dim3((unsigned)(rows * cpr)), dim3(kRowsThreads), 0, st, a, cpr);
-    return check_launch("elementwise rows");
-  }
   int64_t blocks = (p.total + 255) / 256;
   if (blocks > 0x7fffffff) return fail(CHN_ERR_SHAPE, "elementwise: array too large");
   hipLaunchKernelGGL((ew_general_kernel<Tin, Tout>), dim3((unsigned)blocks), dim3(256), 0, st, a);

@@ -1,0 +1,77 @@
+"""Element-wise maps and reductions over views whose rows do not start on 16-byte boundaries or end in partial
+vectors, against NumPy in fp64 on the same values."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_1908_00213_amd import binding as B
+from tests.util import TOL_EW, TOL_SUM, bf16r, check, dev, host, ws
+
+pytestmark = pytest.mark.gpu
+RNG = np.random.default_rng(82)
+TDT = {"f32": torch.float32, "bf16": torch.bfloat16}
+
+
+def view(a, dt, layout, guard=float("nan")):
+    """`a` on the device as a column slice ("slice"), a transposed slice ("t") or contiguous, inside a guarded buffer"""
+    m, n = a.shape
+    shape = {"plain": (m, n), "slice": (m, n + 5), "t": (n, m + 3)}[layout]
+    buf = torch.full(shape, guard, dtype=TDT[dt], device="cuda")
+    v = {"plain": lambda: buf, "slice": lambda: buf[:, 3:n + 3], "t": lambda: buf[:, 1:m + 1].t()}[layout]()
+    v.copy_(dev(a, dt))
+    return buf, v
+
+
+@pytest.mark.parametrize("dt,odt", [("f32", "f32"), ("bf16", "bf16"), ("f32", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("layouts", [("slice", "plain"), ("t", "slice"), ("t", "t"), ("plain", "t")])
+@pytest.mark.parametrize("shape", [(1, 1), (3, 7), (64, 64), (65, 129), (127, 9), (5, 2051), (300, 515)])
+def test_elementwise_views(dt, odt, layouts, shape):
+    a, b = (bf16r(RNG.uniform(-1, 1, shape)) for _ in range(2))
+    c = bf16r(RNG.uniform(-1, 1, (1, shape[1])))
+    col = bf16r(RNG.uniform(-1, 1, (shape[0], 1)))
+    A, Bm = view(a, dt, layouts[0])[1], view(b, dt, layouts[1])[1]
+    tol = TOL_EW if odt == "f32" else 2.0 ** -8
+    for z in (c, col):
+        obuf, out = view(np.zeros(shape, np.float32), odt, "slice")
+        before = obuf.clone()
+        B.elementwise_broadcast("mad", [A, Bm, dev(z, dt)], out)
+        check(host(out), O.elementwise("mad", [a, b, z]), tol, np.abs(a * b) + np.abs(z), "mad %s" % (layouts,))
+        obuf[:, 3:shape[1] + 3] = before[:, 3:shape[1] + 3]
+        assert torch.equal(torch.isnan(obuf), torch.isnan(before))          # nothing outside the view was written
+    if dt == odt:                                                           # in place
+        buf, x = view(a, dt, "slice")
+        B.elementwise_broadcast("mul", [x, Bm], x)
+        check(host(x), O.elementwise("mul", [a, b]), tol, np.abs(a * b), "in place")
+        assert torch.isnan(buf[:, :3]).all() and torch.isnan(buf[:, shape[1] + 3:]).all()
+
+
+def test_elementwise_three_dimensions_unaligned():
+    a = RNG.standard_normal((3, 5, 70)).astype(np.float32)
+    buf = torch.full((3, 7, 73), float("nan"), device="cuda")
+    v = buf[:, 1:6, 2:72]
+    v.copy_(dev(a))
+    row = RNG.standard_normal((5, 1)).astype(np.float32)
+    out = torch.empty(3, 5, 70, device="cuda")
+    B.elementwise_broadcast("add", [v, dev(row)], out)
+    check(host(out), a.astype(np.float64) + row, TOL_EW, np.abs(a) + np.abs(row), "3-d")
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["plain", "slice", "t"])
+@pytest.mark.parametrize("shape", [(1, 1), (2, 9), (70, 33), (65, 1001), (2500, 77), (4099, 1027)])
+def test_reductions_of_views(dt, layout, shape):
+    a = bf16r(RNG.standard_normal(shape))
+    x = view(a, dt, layout)[1]
+    for axis in (0, 1, None):
+        for op, f in (("sum", np.sum), ("max", np.max)):
+            ref = f(a.astype(np.float64), axis=axis)
+            out = torch.empty(np.shape(ref), device="cuda")
+            got = host(B.reduce_axis(op, x, axis, out, ws=ws(B.reduce_axis_workspace_bytes(x, axis))))
+            check(got, ref, TOL_SUM, np.abs(a.astype(np.float64)).sum(axis=axis), "%s axis %s" % (op, axis))
+    ints = np.round(a * 4).astype(np.float32)
+    x = view(ints, dt, layout)[1]
+    for axis in (0, 1):
+        out = torch.empty(shape[1 - axis], device="cuda")
+        got = host(B.reduce_axis("sum", x, axis, out, ws=ws(B.reduce_axis_workspace_bytes(x, axis))))
+        assert np.array_equal(got, ints.astype(np.float64).sum(axis=axis))
