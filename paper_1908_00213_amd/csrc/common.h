@@ -158,6 +158,13 @@ __device__ __forceinline__ Vec16<T> load16_any(const T *p) {
   return r;
 }
 template <typename T>
+__device__ __forceinline__ Vec16<T> load16_any_nt(const T *p) {
+  const chn_u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const chn_u32x4_any *>(p));
+  Vec16<T> r;
+  __builtin_memcpy(&r.raw, &v, 16);
+  return r;
+}
+template <typename T>
 __device__ __forceinline__ void store16_any(T *p, const Vec16<T> &x) {
   chn_u32x4 v;
   __builtin_memcpy(&v, &x.raw, 16);

@@ -13,6 +13,7 @@
 // A transposed 2-d view simply swaps ROW and COL.  HBM-bound: the input is read exactly once.
 #include "common.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace chn {
@@ -69,8 +70,18 @@ struct RPlan {
   int64_t rows_per_split = 0;
   bool vec = false;
   int tx = 64;               // column groups per block
-  size_t ws_bytes = 0;
+  size_t ws_bytes = 0;       // COL: partial sums of the slices (required)
+  // ROW: a long row that too few blocks would work on is cut in slices whose results a second launch folds, where the
+  // caller's workspace has room for them (optional: without it the row is folded by one block)
+  int slices = 1;
+  int64_t slice = 0;
+  size_t slice_bytes = 0;
 };
+
+// Few long rows (the sum over everything is one): one block moves 16 KB per memory latency, so the sum over 1024 x 1001
+// fp32 took 136 us in a single block, 7.8 us cut in slices; the sum over 16 x 16384 37 and 7.9.  The second launch
+// costs about 3 us: worth it from kCutRow elements on, as long as the rows alone do not fill the chip.
+constexpr int64_t kCutRow = 32768, kCutRows = 256, kSliceElems = 4096;
 
 // COL kernel block shapes (column groups x row lanes = 256 threads): 16 x 16 for the large streaming
 // case (more column blocks, hence fewer row splits and a smaller second pass), 64 x 4 otherwise.
@@ -111,16 +122,32 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
   }
   nk = nk == 0 ? 0 : w + 1;
   p->nk = nk;
-  if ((p->sR == 1 || p->len == 1) && nk <= 1) { p->kind = KIND_ROW; return CHN_OK; }
+  if ((p->sR == 1 || p->len == 1) && nk <= 1) {
+    p->kind = KIND_ROW;
+    const int64_t rows = nk == 1 ? p->kshape[0] : 1;
+    if (rows < kCutRows && p->len >= kCutRow) {
+      int64_t s = (p->len + 2 * kSliceElems - 1) / (2 * kSliceElems);
+      if (s * rows < 256) s = std::min((p->len + kSliceElems - 1) / kSliceElems, (256 + rows - 1) / rows);   // one block per compute unit
+      if (s * rows > 8192) s = 8192 / rows;                   // (rows < 256: at least 32)
+      p->slice = ((p->len + s - 1) / s + 1023) / 1024 * 1024;
+      p->slices = (int)((p->len + p->slice - 1) / p->slice);
+      p->slice_bytes = (size_t)(rows * p->slices) * sizeof(float);
+    }
+    return CHN_OK;
+  }
   if (nk >= 1 && nk <= 2 && p->kstr[nk - 1] == 1) {
     p->kind = KIND_COL;
     p->I = p->kshape[nk - 1];
     p->O = nk == 2 ? p->kshape[0] : 1;
     p->sO = nk == 2 ? p->kstr[0] : 0;
     const int n = 16 / isz;
-    p->vec = reinterpret_cast<uintptr_t>(in->data) % 16 == 0 && p->I % n == 0 && p->sR % n == 0 && p->sO % n == 0;
-    const int64_t groups = p->I / (p->vec ? n : 1);
+    // 16-byte accesses wherever a row holds one: they may start at any element address (10000 x 4001 bf16 column sums
+    // 29.8 -> 19.8 us against one element per access, 12000 x 1500 21.3 -> 15.8)
+    const bool aligned = reinterpret_cast<uintptr_t>(in->data) % 16 == 0 && p->I % n == 0 && p->sR % n == 0 && p->sO % n == 0;
+    p->vec = p->I >= n;
+    const int64_t groups = (p->I + n - 1) / (p->vec ? n : 1);
     p->tx = (p->vec && groups >= 512 && p->len >= 1024) ? (isz == 2 && groups >= 1024 ? kColTXMid : kColTXWide) : kColTXNarrow;
+    if (p->vec && groups <= 32) p->tx = groups <= 4 && p->len >= 1024 ? kColTXShort : groups <= 16 ? kColTXWide : kColTXMid;   // no idle column lanes (16384 x 16 fp32 14.0 -> 7.8 us)
     if (p->vec && groups >= 64 && p->len <= 64) p->tx = kColTXWide;   // 16 row lanes: one batch of loads per thread
     const int64_t cols_per_block = (int64_t)p->tx * (p->vec ? n : 1);
     const int64_t blocks_xy = ((p->I + cols_per_block - 1) / cols_per_block) * p->O;
@@ -129,6 +156,10 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     int64_t s = p->len / (rpt * (256 / p->tx));
     if (blocks_xy * s > 16384) s = 16384 / blocks_xy;
     if (p->len <= 64) s = 1;        // a short stack of rows (e.g. per-row-block sums): one launch, a few loads per thread
+    // (rows off the 16-byte grid: partial sums of at most 4 MiB, which the built-in scratch of
+    // chn_reduce_axis_static holds for every shape)
+    const int64_t most = (4 << 20) / (p->O * p->I * (int64_t)sizeof(float) + 1);
+    if (!aligned && s > most) s = most;
     if (s < 1) s = 1;
     if (s > 1024) s = 1024;
     if (s > 1 && p->len <= kShortRows && p->O * p->len * p->I * isz <= (p->vec ? kShortBytes : kShortBytes / 8)) {
@@ -153,14 +184,20 @@ __global__ __launch_bounds__(256) void fill_kernel(Tout *out, int64_t n, float v
 }
 
 // ROW: G lanes per row, 256 / G rows per block.
+// G = 256: a row may be cut in `slices` slices of `slice` elements, one block each; `rows` then counts slices.
 template <int OP, typename Tin, typename Tout, int G, bool VEC>
-__global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *out, int64_t rows, int64_t len, int64_t pitch) {
+__global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *out, int64_t rows, int64_t len, int64_t pitch, int slices = 1, int64_t slice = 0) {
   constexpr int RPB = 256 / G;
   const int g = threadIdx.x % G;
   const int64_t row = (int64_t)blockIdx.x * RPB + threadIdx.x / G;
   float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
   if (row < rows) {
     const Tin *p = in + row * pitch;
+    if (G == 256 && slices > 1) {
+      const int64_t r = row / slices, first = (row - r * slices) * slice;
+      p = in + r * pitch + first;
+      len = len - first < slice ? len - first : slice;
+    }
     if constexpr (VEC) {
       constexpr int N = Vec16<Tin>::N;
       const int64_t nvec = len / N;
@@ -168,17 +205,16 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
       for (; v + 3 * G < nvec; v += 4 * G) {
         Vec16<Tin> x[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u].load_nt(p + (v + u * G) * N);
+        for (int u = 0; u < 4; ++u) x[u] = load16_any_nt(p + (v + u * G) * N);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < N; ++i) acc[u] = fold<OP>(acc[u], x[u].get(i));
       }
       for (; v < nvec; v += G) {
-        Vec16<Tin> x;
-        x.load(p + v * N);
+        const Vec16<Tin> x = load16_any(p + v * N);
 #pragma unroll
-        for (int i = 0; i < N; ++i) acc[0] = fold<OP>(acc[0], x.get(i));
+        for (int i = 0; i < N; ++i) acc[i & 3] = fold<OP>(acc[i & 3], x.get(i));
       }
       for (int64_t c = nvec * N + g; c < len; c += G) acc[1] = fold<OP>(acc[1], Elem<Tin>::load(p + c));
     } else {
@@ -215,7 +251,9 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
   constexpr int N = VEC ? Vec16<Tin>::N : 1;
   constexpr int kColTY = 256 / kColTX;
   const int tx = threadIdx.x % kColTX, ty = threadIdx.x / kColTX;
-  const int64_t col = ((int64_t)blockIdx.x * kColTX + tx) * N;
+  // (the last vector of a row that is not a whole number of them ends with the row: its first columns are folded
+  // twice, by two threads that write the same values)
+  const int64_t first = ((int64_t)blockIdx.x * kColTX + tx) * N, col = VEC && first < I && first + N > I ? I - N : first;
   const int64_t o = blockIdx.z;
   const int64_t r_begin = (int64_t)blockIdx.y * rows_per_split;
   int64_t r_end = r_begin + rows_per_split;
@@ -234,7 +272,7 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
         for (int u = 0; u < U; ++u) {          // a lane past the end re-reads its first row and drops it
           const int64_t rr = r + u * kColTY;
           const Tin *q = p + (rr < r_end ? rr : r) * sR;
-          if constexpr (VEC) x[u].load(q); else x[u] = Elem<Tin>::load(q);
+          if constexpr (VEC) x[u] = load16_any(q); else x[u] = Elem<Tin>::load(q);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -251,15 +289,14 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
       for (; r + 3 * kColTY < r_end; r += 4 * kColTY) {
         Vec16<Tin> x[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u].load_nt(p + (r + u * kColTY) * sR);
+        for (int u = 0; u < 4; ++u) x[u] = load16_any_nt(p + (r + u * kColTY) * sR);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x[u].get(i));
       }
       for (; r < r_end; r += kColTY) {
-        Vec16<Tin> x;
-        x.load(p + r * sR);
+        const Vec16<Tin> x = load16_any(p + r * sR);
 #pragma unroll
         for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x.get(i));
       }
@@ -296,10 +333,14 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
     Tout *q = out + (int64_t)blockIdx.y * out_split_stride + o * I + col;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      float a = part[0][tx * N + i];
+      float v[kParts];                                       // folded as a tree: fewest roundings at full magnitude
 #pragma unroll
-      for (int y = 1; y < kParts; ++y) a = fold<OP>(a, part[y][tx * N + i]);
-      Elem<Tout>::store(q + i, a);
+      for (int y = 0; y < kParts; ++y) v[y] = part[y][tx * N + i];
+#pragma unroll
+      for (int h = kParts / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int y = 0; y < h; ++y) v[y] = fold<OP>(v[y], v[y + h]);
+      Elem<Tout>::store(q + i, v[0]);
     }
   }
 }
@@ -347,13 +388,20 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     const int64_t rows = p.nk == 1 ? p.kshape[0] : 1;
     const int64_t pitch = p.nk == 1 ? p.kstr[0] : 0;
     const int n = 16 / (int)sizeof(Tin);
-    const bool vec = reinterpret_cast<uintptr_t>(src) % 16 == 0 && pitch % n == 0 && p.len >= 4 * n;
+    const bool vec = p.len >= 4 * n;                        // (16-byte accesses at any element address)
+    if (p.slices > 1 && ws) {
+      float *part = static_cast<float *>(ws);
+      hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, float, 256, true>), dim3((unsigned)(rows * p.slices)), dim3(256), 0, st, src, part, rows * p.slices, p.len, pitch, p.slices, p.slice);
+      CHN_TRY(check_launch("reduce row slices"));
+      hipLaunchKernelGGL((reduce_row_kernel<OP, float, Tout, 256, true>), dim3((unsigned)rows), dim3(256), 0, st, part, dst, rows, (int64_t)p.slices, (int64_t)p.slices, 1, (int64_t)0);
+      return check_launch("reduce row");
+    }
 #define CHN_ROW(G)                                                                                          \
   do {                                                                                                      \
     const int64_t blocks = (rows + (256 / G) - 1) / (256 / G);                                              \
     if (blocks > 0x7fffffff) return fail(CHN_ERR_SHAPE, "reduce: too many rows");                           \
-    if (vec) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, true>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch); \
-    else hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, false>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch);    \
+    if (vec) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, true>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0); \
+    else hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, false>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0);    \
   } while (0)
     if (p.len >= 2048 || rows < 512) CHN_ROW(256);
     else if (p.len > 64) CHN_ROW(64);
@@ -369,8 +417,8 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     CHN_TRY((launch_col<OP, Tin, float>(src, part, p, p.O, p.len, p.I, p.sO, p.sR, p.split, p.rows_per_split, OI, p.vec, p.tx, st)));
     // Second pass over the [split, O * I] partials: a small array, so the time is one chain of
     // dependent load batches per lane; the narrow-in-columns block shape keeps that chain short.
-    const bool wide2 = OI % 4 == 0 && OI / 4 >= 512 && p.split >= 16;
-    return launch_col<OP, float, Tout>(part, dst, p, 1, p.split, OI, 0, OI, 1, p.split, 0, OI % 4 == 0, wide2 ? kColTXWide : kColTXNarrow, st);
+    const bool wide2 = OI / 4 >= 512 && p.split >= 16;
+    return launch_col<OP, float, Tout>(part, dst, p, 1, p.split, OI, 0, OI, 1, p.split, 0, OI >= 4, wide2 ? kColTXWide : kColTXNarrow, st);
   }
   GenArgs a{};
   a.nk = p.nk; a.len = p.len; a.sR = p.sR; a.total_out = p.total_out;
@@ -428,6 +476,14 @@ chn_status reduce_one_axis(int op, const chn_array *in, int axis, int keepdims, 
       CHN_TRY(check_ws(ws, ws_bytes, p.ws_bytes, "reduce"));
     }
   }
+  if (p.kind == KIND_ROW && p.slices > 1) {
+    if (static_scratch) {
+      if (p.slice_bytes <= kScratchBytes) CHN_TRY(scratch_of_current_device(&ws));
+      else ws = nullptr;
+    } else if (!ws || reinterpret_cast<uintptr_t>(ws) % 256 || ws_bytes < p.slice_bytes) {
+      ws = nullptr;                                           // (no room for the slices' results: one block per row)
+    }
+  }
   if (in->dtype == CHN_F32 && out->dtype == CHN_F32) return launch_op<float, float>(op, p, in, out, ws, st);
   if (in->dtype == CHN_BF16 && out->dtype == CHN_F32) return launch_op<bf16_raw, float>(op, p, in, out, ws, st);
   if (in->dtype == CHN_BF16 && out->dtype == CHN_BF16) return launch_op<bf16_raw, bf16_raw>(op, p, in, out, ws, st);
@@ -437,9 +493,7 @@ chn_status reduce_one_axis(int op, const chn_array *in, int axis, int keepdims, 
 // ---- several axes at once ---------------------------------------------------------------------------------
 // CHN_AXES(mask) / CHN_AXIS_ALL are carried out as a sequence of single-axis reductions, last axis first,
 // over fp32 intermediates in the caller's workspace: neighbouring reduced dimensions that are jointly
-// contiguous are merged into one axis first (a full sum of a contiguous array is one axis), and an axis that
-// is folded into very few results is cut in two (length = r x c: c elements per row first, then the r row
-// results), because a single-axis reduction gives every result to one workgroup.
+// contiguous are merged into one axis first (a full sum of a contiguous array is one axis: one long row).
 struct Pass {
   chn_array in, out;     // out: contiguous fp32 intermediate, or the caller's out for the last pass
   int axis;
@@ -449,8 +503,11 @@ struct MultiPlan {
   Pass pass[2 * CHN_MAX_NDIM];
   int n = 0;
   size_t tmp_bytes[2] = {0, 0};   // two intermediates that take turns
-  size_t partial_bytes = 0;
-  size_t total() const { return ((tmp_bytes[0] + 255) & ~size_t(255)) + ((tmp_bytes[1] + 255) & ~size_t(255)) + partial_bytes; }
+  size_t partial_bytes = 0;       // partial sums a pass needs ..
+  size_t slice_bytes = 0;         // .. and what cutting long rows would use (optional), at the same place
+  size_t tmp() const { return ((tmp_bytes[0] + 255) & ~size_t(255)) + ((tmp_bytes[1] + 255) & ~size_t(255)); }
+  size_t required() const { return tmp() + partial_bytes; }
+  size_t total() const { return tmp() + (partial_bytes > slice_bytes ? partial_bytes : slice_bytes); }
 };
 
 void set_contiguous(chn_array *a, int dtype) {
@@ -484,20 +541,6 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
     for (int e = d; e + 1 < cur.ndim; ++e) { cur.shape[e] = cur.shape[e + 1]; cur.strides[e] = cur.strides[e + 1]; red[e] = red[e + 1]; }
     --cur.ndim;
   }
-  int64_t kept = 1;
-  for (int d = 0; d < cur.ndim; ++d) if (!red[d]) kept *= cur.shape[d];
-  // cut a long axis with few results in two: (.., L, ..) -> (.., r, c, ..), both reduced
-  for (int d = 0; d < cur.ndim && cur.ndim < CHN_MAX_NDIM; ++d) {
-    if (!red[d] || cur.shape[d] < (1 << 20) || kept >= 512) continue;
-    int64_t c = 0;
-    for (int64_t t = 8192; t >= 1024; t -= 4) if (cur.shape[d] % t == 0) { c = t; break; }
-    if (!c) continue;
-    for (int e = cur.ndim; e > d + 1; --e) { cur.shape[e] = cur.shape[e - 1]; cur.strides[e] = cur.strides[e - 1]; red[e] = red[e - 1]; }
-    ++cur.ndim;
-    cur.shape[d + 1] = c; cur.strides[d + 1] = cur.strides[d]; red[d + 1] = true;
-    cur.shape[d] /= c; cur.strides[d] = cur.strides[d + 1] * c;
-    ++d;
-  }
   // one pass per remaining reduced dimension, last first
   int which = 0;
   for (int d = cur.ndim - 1; d >= 0; --d) {
@@ -517,6 +560,7 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
     CHN_TRY(make_rplan(&probe, d, &rp));
     ps.ws_need = rp.kind == KIND_COL ? rp.ws_bytes : 0;
     if (ps.ws_need > mp->partial_bytes) mp->partial_bytes = ps.ws_need;
+    if (rp.kind == KIND_ROW && rp.slice_bytes > mp->slice_bytes) mp->slice_bytes = rp.slice_bytes;
     const size_t ob = (size_t)numel(&nxt) * sizeof(float);
     if (ob > mp->tmp_bytes[which]) mp->tmp_bytes[which] = ob;
     which ^= 1;
@@ -547,14 +591,14 @@ chn_status reduce_axis_impl(int op, const chn_array *in, int axis, int keepdims,
   }
   if (od != out->ndim) return fail(CHN_ERR_SHAPE, "reduce: out has ndim %d, expected %d", out->ndim, od);
   if (numel(out) == 0) return CHN_OK;
-  const size_t need = static_scratch ? 0 : mp.total();
   if (static_scratch) {
-    if (mp.total() > kScratchBytes)
+    if (mp.required() > kScratchBytes)
       return fail(CHN_ERR_WORKSPACE, "reduce (static scratch): this reduction needs %zu bytes of intermediates, the built-in buffer holds %zu; use chn_reduce_axis with a workspace",
-                  mp.total(), kScratchBytes);
+                  mp.required(), kScratchBytes);
     if (mp.total() > 0) CHN_TRY(scratch_of_current_device(&ws));
+    ws_bytes = kScratchBytes;
   } else {
-    CHN_TRY(check_ws(ws, ws_bytes, need, "reduce"));
+    CHN_TRY(check_ws(ws, ws_bytes, mp.required(), "reduce"));
   }
   char *base = static_cast<char *>(ws);
   char *tmp[2] = {base, base ? base + ((mp.tmp_bytes[0] + 255) & ~size_t(255)) : nullptr};
@@ -566,7 +610,7 @@ chn_status reduce_axis_impl(int op, const chn_array *in, int axis, int keepdims,
     const bool last = i == mp.n - 1;
     if (last) { ps.out.data = out->data; set_contiguous(&ps.out, out->dtype); }
     else ps.out.data = tmp[i & 1];
-    CHN_TRY(reduce_one_axis(op, &ps.in, ps.axis, 0, &ps.out, partial, mp.partial_bytes, false, stream));
+    CHN_TRY(reduce_one_axis(op, &ps.in, ps.axis, 0, &ps.out, partial, base ? ws_bytes - mp.tmp() : 0, false, stream));
     src = ps.out.data;
   }
   return CHN_OK;
@@ -585,7 +629,7 @@ size_t chn_reduce_axis_workspace_bytes(const chn_array *in, int axis) {
   }
   chn::RPlan p;
   if (chn::make_rplan(in, axis, &p) != CHN_OK) return 0;
-  return p.kind == chn::KIND_COL ? p.ws_bytes : 0;
+  return p.kind == chn::KIND_COL ? p.ws_bytes : p.kind == chn::KIND_ROW ? p.slice_bytes : 0;
 }
 
 chn_status chn_reduce_axis(int op, const chn_array *in, int axis, int keepdims, const chn_array *out,

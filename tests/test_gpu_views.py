@@ -75,3 +75,21 @@ def test_reductions_of_views(dt, layout, shape):
         out = torch.empty(shape[1 - axis], device="cuda")
         got = host(B.reduce_axis("sum", x, axis, out, ws=ws(B.reduce_axis_workspace_bytes(x, axis))))
         assert np.array_equal(got, ints.astype(np.float64).sum(axis=axis))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 32767), (1, 32768), (3, 100001), (255, 33000), (256, 33000), (1, 3000001)])
+def test_few_long_rows(dt, shape):
+    # rows that are cut in slices: with the workspace asked for, without any (one block per row) and with the built-in scratch
+    a = RNG.integers(-4, 5, size=shape).astype(np.float32)
+    x = view(a, dt, "slice")[1]
+    ref = a.astype(np.float64).sum(axis=1)
+    need = B.reduce_axis_workspace_bytes(x, 1)
+    assert (need > 0) == (shape[0] < 256 and shape[1] >= 32768)
+    new = lambda: torch.full((shape[0],), float("nan"), device="cuda")
+    for kw in ({"ws": ws(need)}, {}, {"ws": ws(need)[256:]}):
+        assert np.array_equal(host(B.reduce_axis("sum", x, 1, new(), **kw)), ref)
+    assert np.array_equal(host(B.reduce_axis_static("sum", x, 1, new())), ref)
+    top = torch.empty((), device="cuda")
+    assert host(B.reduce_axis("max", x, None, top, ws=ws(B.reduce_axis_workspace_bytes(x, None)))) == a.max()
+    assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
