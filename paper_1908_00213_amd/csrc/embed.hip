@@ -2,10 +2,12 @@
 // Section "GPU Support by CuPy", as the language-model workload uses it) and its gradient.
 //
 // Forward: one wave copies one row (bit-exact), 16-byte chunks when the rows are aligned.
-// Backward is written as a gather so that it needs no atomics and no workspace and is
-// bit-reproducible: one block owns eight neighbouring table rows, scans the id list 256 ids at a time
-// (wave ballots give each wave's matches as a bit mask), and adds the matching rows of dout to the
-// table row they belong to in increasing token order.  Rows nobody referenced are written as zeros (or left alone when accumulating).
+// Backward is written as a gather so that it needs no atomics and no workspace and is bit-reproducible: one block owns
+// eight neighbouring table rows, scans the id list (wave ballots give the matches as bit masks), and adds the
+// matching rows of dout to the table row they belong to in increasing token order.  Rows nobody referenced are
+// written as zeros (or left alone when accumulating).  What bounds it is latency: every block reads every id, and few of
+// them match.  So 4096 ids are scanned at once (sixteen loads per thread in flight, two barriers), the masks
+// are searched by a ballot, and the rows of up to four matches are fetched together.
 #include "common.h"
 
 namespace chn {
@@ -26,10 +28,11 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const T *table, int64_t 
   const T *src = table + id * tpitch;
   if constexpr (VEC) {
     constexpr int NV = 16 / sizeof(T);
-    const int64_t nvec = D / NV;
-    for (int64_t v = lane; v < nvec; v += 64)
-      *reinterpret_cast<uint4 *>(dst + v * NV) = *reinterpret_cast<const uint4 *>(src + v * NV);
-    for (int64_t d = nvec * NV + lane; d < D; d += 64) dst[d] = src[d];
+    // (16-byte accesses at whatever element address the rows have; the last one ends with the row)
+    for (int64_t d = lane * NV; d < D; d += 64 * NV) {
+      const int64_t e = d + NV <= D ? d : D - NV;
+      store16_any(dst + e, load16_any(src + e));
+    }
   } else {
     for (int64_t d = lane; d < D; d += 64) dst[d] = src[d];
   }
@@ -38,11 +41,15 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const T *table, int64_t 
 constexpr int kColsPerThread = 4;
 constexpr int kRowsPerBlock = 8;     // table rows one block owns: the id list is scanned once for all of them
 
+constexpr int kScan = 16;            // ids per thread and scan
+constexpr int kTogether = 4;         // matching rows fetched together
+
 template <typename L>
 __global__ __launch_bounds__(256) void embed_bwd_kernel(const L *ids, int64_t N, const float *dout, int64_t dpitch, int64_t D,
                                                         float *dtable, int64_t tpitch, int64_t V, int accumulate) {
-  __shared__ unsigned long long masks[4];
-  __shared__ unsigned char which[256];           // for a matching token: which of the block's rows
+  __shared__ unsigned long long masks[4 * kScan];          // [round][wave]: 64 ids each, in token order
+  __shared__ unsigned char which[256 * kScan];             // for a matching token: which of the block's rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t v0 = (int64_t)blockIdx.x * kRowsPerBlock;
   const int64_t col0 = (int64_t)blockIdx.y * (256 * kColsPerThread) + threadIdx.x;
   float acc[kRowsPerBlock][kColsPerThread];
@@ -50,33 +57,62 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const L *ids, int64_t N,
   for (int r = 0; r < kRowsPerBlock; ++r)
 #pragma unroll
     for (int k = 0; k < kColsPerThread; ++k) acc[r][k] = 0.0f;
-  for (int64_t base = 0; base < N; base += 256) {
-    const int64_t n = base + threadIdx.x;
-    const int64_t d = n < N ? (int64_t)ids[n] - v0 : -1;
-    const bool hit = d >= 0 && d < kRowsPerBlock;
-    const unsigned long long m = __ballot(hit);
-    if ((threadIdx.x & 63) == 0) masks[threadIdx.x >> 6] = m;
-    which[threadIdx.x] = (unsigned char)(hit ? d : 0);
-    __syncthreads();
+  for (int64_t base = 0; base < N; base += 256 * kScan) {
+    int64_t id[kScan];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      unsigned long long mm = masks[w];
-      while (mm) {                                // matches in increasing token order
-        const int b = __ffsll((long long)mm) - 1;
-        mm &= mm - 1;
-        const float *row = dout + (base + w * 64 + b) * dpitch;
-        float x[kColsPerThread];
+    for (int u = 0; u < kScan; ++u) {
+      const int64_t n = base + u * 256 + threadIdx.x;
+      id[u] = n < N ? (int64_t)ids[n] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) {
+      const int64_t d = id[u] - v0;
+      const bool hit = id[u] >= 0 && d >= 0 && d < kRowsPerBlock;
+      const unsigned long long m = __ballot(hit);
+      if (lane == 0) masks[u * 4 + wave] = m;
+      if (hit) which[u * 256 + threadIdx.x] = (unsigned char)d;
+    }
+    __syncthreads();
+    static_assert(4 * kScan == 64, "one mask per lane");
+    unsigned long long words = __ballot(masks[lane] != 0);  // masks with a match (the same on every wave)
+    unsigned long long mm = 0;
+    int w = 0;
+    for (;;) {
+      int hit[kTogether], n_hits = 0;                       // the next matches in token order; uniform over the block
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q) {
+        if (mm == 0 && words != 0) {
+          w = __ffsll((long long)words) - 1;
+          words &= words - 1;
+          mm = masks[w];
+        }
+        hit[q] = -1;
+        if (mm != 0) {
+          hit[q] = w * 64 + __ffsll((long long)mm) - 1;
+          mm &= mm - 1;
+          ++n_hits;
+        }
+      }
+      if (n_hits == 0) break;
+      float x[kTogether][kColsPerThread];
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q) {
+        const float *row = dout + (base + (hit[q] < 0 ? hit[0] : hit[q])) * dpitch;
 #pragma unroll
         for (int k = 0; k < kColsPerThread; ++k) {
           const int64_t c = col0 + (int64_t)k * 256;
-          x[k] = c < D ? row[c] : 0.0f;
+          x[q][k] = c < D ? row[c] : 0.0f;
         }
-        const int r_hit = which[w * 64 + b];      // uniform over the block
+      }
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q) {
+        if (hit[q] < 0) break;
+        const int r_hit = which[hit[q]];
 #pragma unroll
         for (int r = 0; r < kRowsPerBlock; ++r)
           if (r == r_hit) {
 #pragma unroll
-            for (int k = 0; k < kColsPerThread; ++k) acc[r][k] += x[k];
+            for (int k = 0; k < kColsPerThread; ++k) acc[r][k] += x[q][k];
           }
       }
     }
@@ -122,8 +158,7 @@ chn_status chn_embed_fwd(const chn_array *table, const chn_array *ids, const chn
   if (N == 0 || D == 0) return CHN_OK;
   if (V == 0) return fail(CHN_ERR_SHAPE, "embed: empty table");
   const int isz = dtype_size(table->dtype);
-  const bool vec = reinterpret_cast<uintptr_t>(table->data) % 16 == 0 && reinterpret_cast<uintptr_t>(out->data) % 16 == 0 &&
-                   (tp * isz) % 16 == 0 && (op * isz) % 16 == 0;
+  const bool vec = D * isz >= 16;
   const unsigned blocks = (unsigned)((N + 3) / 4);
   hipStream_t st = as_stream(stream);
   const bool i32 = ids->dtype == CHN_I32;

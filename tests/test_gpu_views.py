@@ -93,3 +93,24 @@ def test_few_long_rows(dt, shape):
     top = torch.empty((), device="cuda")
     assert host(B.reduce_axis("max", x, None, top, ws=ws(B.reduce_axis_workspace_bytes(x, None)))) == a.max()
     assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("V,D,N", [(1, 3, 5), (9, 8, 1), (10, 13, 4095), (7, 650, 4096), (40, 1031, 4097), (3000, 33, 9000)])
+def test_embedding_any_width(dt, V, D, N):
+    # rows off the 16-byte grid; one id list shorter than a scan, exactly one, and several; many and few matches per row
+    ids = RNG.integers(-1, V + 1, N).astype(np.int32)                       # (a stray id gathers zeros and receives nothing)
+    table = bf16r(RNG.standard_normal((V, D)))
+    buf, t = view(table, dt, "slice")
+    obuf, out = view(np.zeros((N, D), np.float32), dt, "slice")
+    B.embed_fwd(t, dev(ids), out)
+    ok = (ids >= 0) & (ids < V)
+    want = np.where(ok[:, None], table[np.where(ok, ids, 0)], 0)
+    assert np.array_equal(host(out), want)
+    assert torch.isnan(obuf[:, :3]).all() and torch.isnan(obuf[:, D + 3:]).all()
+    dout = RNG.integers(-3, 4, (N, D)).astype(np.float32)
+    ref = np.zeros((V, D))
+    np.add.at(ref, ids[ok], dout[ok])
+    g = view(np.zeros((V, D), np.float32), "f32", "slice")[1]
+    assert np.array_equal(host(B.embed_bwd(dev(ids), view(dout, "f32", "slice")[1], g)), ref)
+    assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g, accumulate=True)), 2 * ref)
