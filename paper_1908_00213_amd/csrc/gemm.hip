@@ -167,6 +167,18 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   const bool other_forced = force_tile >= 0 || g_force_direct.load(std::memory_order_relaxed) >= 0 || g_force_w8.load(std::memory_order_relaxed) >= 0;
   constexpr int64_t kMaxLd = 1 << 22;                       // 32-bit byte offsets inside a tile
   if (isz != 4 || big_unsplit || g->K == 0 || g->lda >= kMaxLd || g->ldb >= kMaxLd || (other_forced && force != 1)) return;
+  // Few 32x32 blocks and a contraction that one batch of loads per wave covers: the latency-bound kernel of
+  // gemm_tiny.h (us, tiled kernels -> this: 32x10x100 9.5 -> 4.1, 33x65x77 10.5 -> 4.4, 32x100x100 5.8 -> 4.4,
+  // 256x256x256 10.1 -> 6.4, 512x512x512 11.1 -> 7.7).  Beyond 256 blocks (1000x1000x64 5.9, would be 10.0) or 512 k
+  // (64x1000x1000 9.4, would be 11.2) the tiles' reuse of operands wins.
+  const int64_t small_blocks = (int64_t)((g->M + 31) / 32) * ((g->N + 31) / 32);
+  if (!other_forced && g_force_splits.load(std::memory_order_relaxed) < 0 && small_blocks <= 256 && g->K <= 512) {
+    g->parts = 3;
+    g->splits = 1;
+    g->tiles_m = (g->M + 31) / 32;
+    g->tiles_n = (g->N + 31) / 32;
+    return;
+  }
   static const double step_large[3] = {1.0, 1.25, 1.2}, step_small[3] = {0.78, 1.1, 0.95};   // both along K, one, none
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   auto narrow = [](int piece, bool kc, bool large) {
@@ -264,7 +276,7 @@ int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, in
   CHN_TRY(classify(A, B, &g, &a_kc, &b_kc));
   const int isz = dtype_size(A->dtype);
   plan(&g, isz, a_kc, b_kc, have_workspace != 0);
-  return g.tile | (g.dma ? 4 : 0) | (eight_waves(g, isz, CHN_EPI_NONE) || g.parts ? 8 : 0) | (g.splits << 4);
+  return g.tile | (g.dma ? 4 : 0) | (eight_waves(g, isz, CHN_EPI_NONE) || g.parts == 1 || g.parts == 2 ? 8 : 0) | (g.splits << 4);
 }
 
 chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, float alpha, float beta,

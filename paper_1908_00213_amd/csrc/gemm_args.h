@@ -33,7 +33,8 @@ struct GemmArgs {
   float *colsum;          // activation-gradient epilogues, 256x256 tile only: [M / 128][N] column sums of C over
                           // blocks of 128 rows (values as stored), or NULL
   int64_t ldcs;
-  int parts;              // fp32 on the bfloat16 matrix cores (gemm_split.h): 0 no, 1 on 64x64 tiles, 2 on 128x128 tiles
+  int parts;              // fp32 on the bfloat16 matrix cores (gemm_split.h): 0 no, 1 on 64x64 tiles, 2 on 128x128 tiles;
+                          // 3: the latency-bound kernel for few tiles and a short K (gemm_tiny.h)
 };
 
 }  // namespace gemm

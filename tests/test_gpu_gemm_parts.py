@@ -126,3 +126,31 @@ def test_planner_takes_the_kernel_and_results_repeat():
         assert torch.equal(x, y)
         ref = A.double() @ Bm.double()
         assert float((x.double() - ref).norm() / ref.norm()) < 6e-7
+
+
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 7), (32, 10, 100), (33, 65, 255), (100, 64, 256), (64, 70, 257), (500, 512, 512)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_small_products(layout, shape, pad):
+    # few blocks and a short contraction: edges of the 32x32 block and of the chunks and batches along K, any alignment
+    m, n, k = shape
+    a, b = (RNG.integers(-9, 10, size=s).astype(np.float32) for s in ((m, k), (n, k)))
+    bias, aux, c0 = (RNG.integers(-9, 10, size=s).astype(np.float32) for s in ((n,), (m, n), (m, n)))
+    A, Bm = operand(a, layout[0] == "k", pad), operand(b, layout[1] == "k", pad).t()
+    assert B.gemm_plan(A, Bm, empty((m, n)), True) == (0, False, 1) and B.gemm_workspace_bytes(A, Bm, empty((m, n))) == 0
+    lin = a.astype(np.float64) @ b.T.astype(np.float64)
+    new = lambda: operand(c0, True, 1 + pad)
+    assert np.array_equal(host(B.gemm(A, Bm, new())), lin)
+    assert np.array_equal(host(B.gemm(A, Bm, new(), alpha=2.0, beta=-1.0)), 2 * lin - c0)
+    assert np.array_equal(host(B.gemm(A, Bm, new(), epilogue="bias_relu", bias=dev(bias))), np.maximum(lin + bias, 0))
+    assert np.array_equal(host(B.gemm(A, Bm, new(), epilogue="relu_bwd", aux=dev(aux))), np.where(aux > 0, lin, 0))
+    low = torch.empty(m, n, device="cuda", dtype=torch.bfloat16)
+    got = B.gemm(A, Bm, new(), epilogue="bf16_copy", preact_out=low)
+    assert np.array_equal(host(got), lin) and torch.equal(low, got.to(torch.bfloat16))
+    scale = np.float32(0.01)
+    z = lin * 1e-4 + bias
+    pre = empty((m, n))
+    out = B.gemm(operand(a * scale, layout[0] == "k", pad), operand(b * scale, layout[1] == "k", pad).t(), new(), epilogue="bias_gelu", bias=dev(bias), preact_out=pre)
+    S = np.abs(a).astype(np.float64) @ np.abs(b).T * 1e-4 + np.abs(bias)
+    check(host(pre), z, TOL_SUM, S, "pre-activation")
+    check(host(out), O.elementwise("gelu", [z]), TOL_SUM, S, "bias_gelu")
