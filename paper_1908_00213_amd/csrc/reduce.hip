@@ -154,6 +154,8 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     // Measured on 8192 x 8192: many short blocks (8 rows per thread, 16 of bf16) stream best.
     const int rpt = isz == 2 ? 16 : 8;   // rows per thread (bf16: half the partial sums for the second pass, -5 %)
     int64_t s = p->len / (rpt * (256 / p->tx));
+    // (few blocks: down to one batch of loads per thread, as long as the second pass stays one batch, too)
+    if (blocks_xy * s < 256) s = std::max(s, std::min(std::min(256 / blocks_xy, (int64_t)64), p->len / (4 * (256 / p->tx))));
     if (blocks_xy * s > 16384) s = 16384 / blocks_xy;
     if (p->len <= 64) s = 1;        // a short stack of rows (e.g. per-row-block sums): one launch, a few loads per thread
     // (rows off the 16-byte grid: partial sums of at most 4 MiB, which the built-in scratch of
