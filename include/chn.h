@@ -113,7 +113,9 @@ chn_status chn_elementwise_broadcast(int op, int n_in, const chn_array *const *i
  * to run); `out` F32 or BF16.  An empty axis writes 0 (sum) or -inf (max).
  * Several axes are folded one after the other, last first, over fp32 intermediates in the workspace
  * (neighbouring axes of a contiguous array count as one; so does a sum over everything):
- * chn_reduce_axis_workspace_bytes takes the same axis code. */
+ * chn_reduce_axis_workspace_bytes takes the same axis code.  Fewer than 256 rows of 32768 elements or more (a sum over
+ * everything is one row) are cut in slices for the whole chip when the workspace has the bytes that call names; the
+ * part of it that only this needs is optional: with a NULL or smaller workspace one block folds a row. */
 typedef enum { CHN_REDUCE_SUM = 0, CHN_REDUCE_MAX = 1 } chn_reduce_op;
 
 size_t chn_reduce_axis_workspace_bytes(const chn_array *in, int axis);
