@@ -149,10 +149,11 @@ chn_status chn_reduce_axis_static(int op, const chn_array *in, int axis, int kee
  * swapped, epilogue CHN_EPI_BIAS.  A and B must each have one unit-stride dimension; C (and
  * `preact_out`, `aux`) must be row-major (unit stride along N).
  * dtypes: A,B F32 -> C F32; A,B BF16 -> C BF16 or F32 (fp32 accumulation).  F32 products run on the fp32 matrix
- * instruction or, where that is faster, on the bfloat16 one with every operand value split into three bfloat16 parts
- * that carry all its 24 bits: six partial products, fp32 accumulation, an error no larger than the instruction's (tiles
- * whose operands hold infinities or magnitudes beyond 2^48, or rows with nothing above 2^-90, are computed on the fp32
- * instruction).
+ * instruction or, where that is faster, on the bfloat16 one with every operand value, subnormal ones included, split
+ * into three bfloat16 parts that carry all its 24 bits: six of the nine partial products (the three left out come to at
+ * most 2^-24 |a b|), fp32 accumulation.  Per element the error stays within (K + 2) 2^-24 times the sum of magnitudes
+ * (plus half a subnormal step); in the 2-norm over random operands it is no larger than the instruction's.  Tiles with a
+ * sum that is not finite once scaled by 2^48 (infinities, NaN, 2^80 and more) are computed again on the fp32 instruction.
  * Epilogue, applied to v = alpha*acc + beta*C in fp32 before the single final rounding:
  *   BIAS       v + bias[n]                         bias (N,) F32
  *   BIAS_RELU  max(0, v + bias[n])

@@ -40,12 +40,12 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &h, uint32_t &
   l = pack_bf16(x, y);
 }
 
-// max(|x|, |y|, m) in one instruction (a NaN operand drops out: such a row is NaN on either path)
-__device__ __forceinline__ float absmax3(float x, float y, float m) {
-  float r;
-  asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(x), "v"(y), "v"(m));
-  return r;
-}
+// Both operands are multiplied by 2^24 before they are split, and the sums by 2^-48 at the end, all exact: the bits of an
+// fp32 value are multiples of 2^-149, those of a scaled one of 2^-125, so every part of every value, subnormal ones
+// included, is a normal bfloat16 number, whatever else its row holds, and what underflow takes from a product lies below 2^-174 of
+// the result's scale.  (Unscaled, 2^-120 beside a 1 kept 14 bits.)  The price is the other end: sums from 2^80 on
+// overflow; see `redo` below.
+constexpr float kSplitScale = 0x1p24f;
 
 // One operand tile in LDS: sub-tiles of 32 k, each three planes (h, m, l) of ROWS rows, 32 k of bfloat16 = 64 bytes =
 // four 16-byte chunks per row.  Chunk q holds k = 4q .. 4q+3 and 16+4q .. 16+4q+3 of the sub-tile (the sum over k is
@@ -70,7 +70,6 @@ struct SplitLoader {
   const char *base;                                       // uniform: the tile's first row (KC) / column (MC) at k = 0
   uint32_t off[NU];                                       // byte offset of the unit's first element
   int lim, K, koff;
-  float top[KC ? NU : 4];                                 // largest magnitude seen, per row
   int64_t kstride;                                        // bytes between consecutive k (MC)
   int lds;                                                // where the first unit goes inside a stage
   int sw;                                                 // MC: swizzle of the unit's rows
@@ -78,8 +77,6 @@ struct SplitLoader {
   __device__ __forceinline__ void init(int t, const float *p, int64_t ld, int rows_total, int row0, int K_) {
     K = K_;
     kstride = ld * 4;
-#pragma unroll
-    for (int i = 0; i < (KC ? NU : 4); ++i) top[i] = 0.0f;
     if constexpr (KC) {
       const int q = t & 3, row = (t >> 2) % ROWS, sub = t / (4 * ROWS);
       koff = sub * 32 + q * 4;
@@ -140,14 +137,13 @@ struct SplitLoader {
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         const uint4 a = reg[2 * u], b = reg[2 * u + 1];
-        const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
-                            __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+        float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                      __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] *= kSplitScale;
         uint4 h, m, l;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          split2(f[2 * e], f[2 * e + 1], (&h.x)[e], (&m.x)[e], (&l.x)[e]);
-          top[u] = absmax3(f[2 * e], f[2 * e + 1], top[u]);
-        }
+        for (int e = 0; e < 4; ++e) split2(f[2 * e], f[2 * e + 1], (&h.x)[e], (&m.x)[e], (&l.x)[e]);
         char *p = stage + lds + u * (T / 4) * 64;
         *reinterpret_cast<uint4 *>(p) = h;
         *reinterpret_cast<uint4 *>(p + PLANE) = m;
@@ -159,9 +155,8 @@ struct SplitLoader {
         uint32_t h[R / 2], m[R / 2], l[R / 2];
 #pragma unroll
         for (int j = 0; j < R / 2; ++j) {
-          const float x = __uint_as_float((&reg[2 * j].x)[e]), y = __uint_as_float((&reg[2 * j + 1].x)[e]);
+          const float x = __uint_as_float((&reg[2 * j].x)[e]) * kSplitScale, y = __uint_as_float((&reg[2 * j + 1].x)[e]) * kSplitScale;
           split2(x, y, h[j], m[j], l[j]);
-          top[e] = absmax3(x, y, top[e]);
         }
         char *p = stage + lds + ((e ^ sw) << 6);
         if constexpr (R == 4) {
@@ -175,24 +170,6 @@ struct SplitLoader {
         }
       }
     }
-  }
-
-  // Whether a row of the tile cannot be carried by the three parts: its largest magnitude is so large that a part or
-  // a sum of products could overflow where fp32 would not (infinities included), or so small that the last parts would
-  // fall out of bfloat16's range.  Rows of zeros are fine.
-  __device__ __forceinline__ bool out_of_range() const {
-    constexpr float kMost = 0x1p48f, kLeast = 0x1p-90f;
-    constexpr int LANES = KC ? 4 : 8 * (4 / R);           // neighbouring lanes hold parts of the same row
-    bool bad = false;
-#pragma unroll
-    for (int e = 0; e < (KC ? NU : 4); ++e) {
-      float t = top[e];
-#pragma unroll
-      for (int o = 1; o < LANES; o <<= 1) t = fmaxf(t, __shfl_xor(t, o, 64));
-      if (!KC && e >= lim) t = 0.0f;                      // what follows the operand's last row never reaches C
-      bad = bad || t > kMost || (t > 0.0f && t < kLeast);
-    }
-    return bad;
   }
 };
 
@@ -331,12 +308,29 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     }
     if (kt < nk) step(S0{}, kt);
     __syncthreads();
-    if (((kAlike || do_a || !kHalves) && la.out_of_range()) || (!kAlike && (!do_a || !kHalves) && lb.out_of_range())) redo = 1;
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] += low[i][j];
+  // An overflow anywhere on the way (a scaled operand or one of its parts, a product, a sum) leaves an infinity or a NaN in
+  // this wave's sum, and so do infinities and NaN among the operands: the tile is then multiplied again below.  Rows and
+  // columns beyond C, which may hold whatever follows the operands in memory, do not count.
+  float bad = 0.0f;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const bool col = n0 + (wn * TN + j) * 32 + r < g.N;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int rows = col ? g.M - m0 - (wm * TM + i) * 32 - 4 * h : 0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        bad = 8 * (v >> 2) + (v & 3) < rows ? __builtin_fmaf(acc[i][j][v], 0.0f, bad) : bad;
+        acc[i][j][v] *= 1.0f / (kSplitScale * kSplitScale);
+      }
+    }
+  }
+  if (bad != 0.0f) redo = 1;                              // (0 or NaN)
   // Parts of the accumulators pass between the groups through LDS: [part][wave of the group][value][lane].
   float *meet = reinterpret_cast<float *>(lds) + (wave & 3) * (TN * 16 * 64) + lane;
   constexpr int PART = 4 * TN * 16 * 64;                  // floats of 32 rows of every wave
@@ -372,7 +366,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     if (grp == 0) { get(0, acc[0], true); get(1, acc[0], true); get(2, acc[0], true); }
   }
   if (redo) {
-    // Some row of this tile's operands is outside what the parts can carry: the first group multiplies the tile again
+    // Some sum of this tile is not finite, with the scaled operands or at all: the first group multiplies the tile again
     // on the fp32 matrix instruction, without ceremony (BM + BN rows of 128 bytes, loaded, stored, multiplied).
     TileLoader<float, BM, A_KC, PBA> la;
     TileLoader<float, BN, B_KC, PBB> lb;

@@ -1,8 +1,8 @@
 """fp32 products on the bfloat16 matrix cores: every operand value as the sum of three bfloat16 parts.
 
 Small integers come out bit for bit (their parts beyond the first are zero), random operands with an error
-against 64 bits no larger than the fp32 matrix instruction's, and operands that the parts cannot carry (infinities,
-magnitudes beyond 2^48, rows with nothing above 2^-90) exactly as the instruction computes them."""
+against 64 bits no larger than the fp32 matrix instruction's, element by element down to subnormal numbers, and operands
+whose sums overflow when scaled by 2^48 (infinities and NaN among them) exactly as the instruction computes them."""
 import numpy as np
 import pytest
 import torch
@@ -93,6 +93,59 @@ def test_values_the_parts_cannot_carry(tile, layout):
         xs = np.nan_to_num(np.abs(x), nan=0.0, posinf=0.0).astype(np.float64)
         S = xs @ np.abs(b).T.astype(np.float64)
         assert np.all(np.abs(got[fin] - want[fin]) <= 2 * 100 * 2.0 ** -24 * S[fin]), place
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+@pytest.mark.parametrize("exponent", [-90, -112, -120, -126, -135, -149])
+def test_small_values_beside_large_ones(tile, layout, exponent):
+    # a row that holds a 1 and a small value, against a row that is zero where the 1 stands: one product is the whole
+    # result.  Its error: the three partial products left out, 2 * 2^-8 * 2^-17 = 2^-24 of it at most (plus 2^-34), the
+    # rounding of the five small ones' sum, 5 * 2^-8 * 2^-24, and of the result, 2^-24 or half a step of 2^-149
+    m, n, k = 70, 66, 50
+    small = (np.float64(2.0) ** exponent * RNG.uniform(1, 2, m)).astype(np.float32)
+    a, b = np.zeros((m, k), np.float32), np.zeros((n, k), np.float32)
+    a[:, 0], a[:, 19] = 1, small
+    b[:, 19] = RNG.uniform(1, 2, n)
+    ref = a[:, 19:20].astype(np.float64) * b[:, 19].astype(np.float64)
+    bound = (2 + 5 * 2.0 ** -8 + 2.0 ** -10) * 2.0 ** -24 * ref + 2.0 ** -150
+    assert np.all(np.abs(product(a, b, layout, tile) - ref) <= bound)
+    assert np.all(np.abs(product(b, a, layout, tile) - ref.T) <= bound.T)
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+@pytest.mark.parametrize("ea,eb", [(-60, -60), (-20, -100), (-75, -75), (-130, 10), (30, 30), (33, 33), (36, 36), (40, -40), (60, 60)])
+def test_scaled_operands(tile, layout, ea, eb):
+    # operands far from 1 on both sides of the sums that the scaled parts take (2^80); a sum of 100 terms is within
+    # 100 * 2^-24 of the sum of magnitudes, and no step loses more than a subnormal one
+    a, b = (np.ldexp(RNG.standard_normal(s), e).astype(np.float32) for s, e in (((90, 100), ea), ((80, 100), eb)))
+    ref, S = a.astype(np.float64) @ b.T.astype(np.float64), np.abs(a).astype(np.float64) @ np.abs(b).T.astype(np.float64)
+    assert np.all(np.abs(product(a, b, layout, tile) - ref) <= 100 * 2.0 ** -24 * S + 100 * 2.0 ** -149)
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "mm"])
+@pytest.mark.parametrize("k", [1, 129, 4096])
+def test_largest_sums(tile, layout, k):
+    # every value the same, sums on both sides of 2^80 (where the scaled ones overflow) and of fp32's own limit
+    for e in (30, 39.9, 40, 40.1, 48, 63.9, 90, 103, 104, 127):
+        a, b = np.full((70, k), 2.0 ** e, np.float32), np.full((66, k), -(2.0 ** e), np.float32)
+        got, ref = product(a, b, layout, tile), -k * np.float64(a[0, 0]) ** 2
+        if ref < -3.4028235e38:
+            assert np.all(np.isneginf(got)), e
+        else:
+            assert np.all(np.abs(got - ref) <= k * 2.0 ** -24 * -ref), e
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+def test_one_tile_is_computed_again(tile):
+    # a sum beyond the scaled range in one tile (and one half of K) of a larger product, split or not; the others keep theirs
+    a, b = RNG.standard_normal((300, 700)).astype(np.float32), RNG.standard_normal((290, 700)).astype(np.float32)
+    a[140, 650], b[133, 650] = 2.0 ** 45, 2.0 ** 45
+    ref, S = a.astype(np.float64) @ b.T.astype(np.float64), np.abs(a).astype(np.float64) @ np.abs(b).T.astype(np.float64)
+    for splits in (1, 2):
+        assert np.all(np.abs(product(a, b, "km", tile, splits) - ref) <= 700 * 2.0 ** -24 * S)
 
 
 @pytest.mark.parametrize("tile", [0, 1])
