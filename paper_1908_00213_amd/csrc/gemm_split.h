@@ -73,8 +73,10 @@ struct SplitLoader {
   int64_t kstride;                                        // bytes between consecutive k (MC)
   int lds;                                                // where the first unit goes inside a stage
   int sw;                                                 // MC: swizzle of the unit's rows
+  float scale;                                            // +- kSplitScale
 
-  __device__ __forceinline__ void init(int t, const float *p, int64_t ld, int rows_total, int row0, int K_) {
+  // negate: the k of the odd wave groups are staged with the other sign
+  __device__ __forceinline__ void init(int t, const float *p, int64_t ld, int rows_total, int row0, int K_, bool negate) {
     K = K_;
     kstride = ld * 4;
     if constexpr (KC) {
@@ -85,6 +87,7 @@ struct SplitLoader {
 #pragma unroll
       for (int u = 0; u < NU; ++u) off[u] = (uint32_t)((min(row + u * (T / 4), rows_total - 1 - row0) * ld + koff) * 4);
       lim = K - koff;
+      scale = negate && (q & 2) ? -kSplitScale : kSplitScale;
       lds = sub * kSplitSub<ROWS> + split_off(row, q);    // (units T / 4 rows apart: whole periods of the swizzle)
     } else {
       constexpr int PAIRS = 4 / R;                        // units that share a group of four k
@@ -94,6 +97,7 @@ struct SplitLoader {
       lim = rows_total - row0 - mc * 4;
       off[0] = (uint32_t)((koff * ld + (lim > 0 ? mc * 4 : 0)) * 4);
       sw = mc & 3;
+      scale = negate && (kg & 2) ? -kSplitScale : kSplitScale;
       // (rows 4 mc .. 4 mc + 3 share their swizzle; row 4 mc + e sits (e ^ sw) rows behind the group's start)
       lds = sub * kSplitSub<ROWS> + mc * 256 + (((kg & 3) ^ sw) << 4) + (kg >> 2) * 8 + pair * 4;
     }
@@ -140,7 +144,7 @@ struct SplitLoader {
         float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
                       __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] *= kSplitScale;
+        for (int e = 0; e < 8; ++e) f[e] *= scale;
         uint4 h, m, l;
 #pragma unroll
         for (int e = 0; e < 4; ++e) split2(f[2 * e], f[2 * e + 1], (&h.x)[e], (&m.x)[e], (&l.x)[e]);
@@ -155,7 +159,7 @@ struct SplitLoader {
         uint32_t h[R / 2], m[R / 2], l[R / 2];
 #pragma unroll
         for (int j = 0; j < R / 2; ++j) {
-          const float x = __uint_as_float((&reg[2 * j].x)[e]) * kSplitScale, y = __uint_as_float((&reg[2 * j + 1].x)[e]) * kSplitScale;
+          const float x = __uint_as_float((&reg[2 * j].x)[e]) * scale, y = __uint_as_float((&reg[2 * j + 1].x)[e]) * scale;
           split2(x, y, h[j], m[j], l[j]);
         }
         char *p = stage + lds + ((e ^ sw) << 6);
@@ -181,6 +185,11 @@ struct SplitLoader {
 // and the vector pipe of a SIMD are both busy between two barriers.
 // The products with a low part go to an accumulator of their own (they are 2^-8 of the others), so the main sum is
 // rounded once per 16 k instead of six times.
+// The bfloat16 matrix instruction leaves a tiny error of one sign: summed over 10000 k of a softmax gradient times weights,
+// the mean error came to -2.6e-8 of the results' size (fp32 instruction: 4e-10), and where many results are added up while
+// their random errors cancel, it shows (the bias gradient of the LSTM layer was off by 1.1e-6, 0.92e-6 on the fp32
+// instruction).  So the odd groups multiply -A, for nothing: the sign goes in and out with the scale, their error gets the
+// other sign, and the mean is 6e-10 (the bias gradient's error 0.5e-6).
 template <int TM, int TN, int KG>
 constexpr int kSplitStage = (KG / 2) * (kSplitSub<64 * TM> + kSplitSub<64 * TN>);
 
@@ -221,10 +230,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     const bool do_a = wave < 2 * KG;                      // (uniform over a wave)
     const int t = kHalves ? (int)threadIdx.x & (NT / 2 - 1) : (int)threadIdx.x;
     if constexpr (kAlike) {
-      la.init(t, static_cast<const float *>(do_a ? g.A : g.B), do_a ? g.lda : g.ldb, do_a ? g.M : g.N, do_a ? m0 : n0, g.K);
+      la.init(t, static_cast<const float *>(do_a ? g.A : g.B), do_a ? g.lda : g.ldb, do_a ? g.M : g.N, do_a ? m0 : n0, g.K, do_a);
     } else {
-      if (do_a || !kHalves) la.init(t, static_cast<const float *>(g.A), g.lda, g.M, m0, g.K);
-      if (!do_a || !kHalves) lb.init(t, static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K);
+      if (do_a || !kHalves) la.init(t, static_cast<const float *>(g.A), g.lda, g.M, m0, g.K, true);
+      if (!do_a || !kHalves) lb.init(t, static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K, false);
     }
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
@@ -316,6 +325,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
   // An overflow anywhere on the way (a scaled operand or one of its parts, a product, a sum) leaves an infinity or a NaN in
   // this wave's sum, and so do infinities and NaN among the operands: the tile is then multiplied again below.  Rows and
   // columns beyond C, which may hold whatever follows the operands in memory, do not count.
+  const float unscale = (grp & 1 ? -1.0f : 1.0f) / (kSplitScale * kSplitScale);
   float bad = 0.0f;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
@@ -326,7 +336,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         bad = 8 * (v >> 2) + (v & 3) < rows ? __builtin_fmaf(acc[i][j][v], 0.0f, bad) : bad;
-        acc[i][j][v] *= 1.0f / (kSplitScale * kSplitScale);
+        acc[i][j][v] *= unscale;
       }
     }
   }

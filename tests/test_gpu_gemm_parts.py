@@ -68,6 +68,28 @@ def test_error_no_larger_than_the_instruction(tile, layout, k):
 
 @pytest.mark.parametrize("tile", [0, 1])
 @pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+def test_errors_have_no_preferred_sign(tile, layout):
+    # the gradient of a softmax (one -1, the rest small and positive) times weights, a product whose results are summed over
+    # rows afterwards: n independent errors of relative size e average to e / sqrt(n), here within six of those
+    m, n, k = 2048, 640, 10000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    d = torch.softmax(torch.randn(m, k, generator=g, device="cuda"), 1)
+    d[torch.arange(m, device="cuda"), torch.randint(0, k, (m,), generator=g, device="cuda")] -= 1
+    w = torch.randn(n, k, generator=g, device="cuda")
+    A, Bm = (x if l == "k" else x.t().contiguous().t() for x, l in zip((d, w), layout))
+    ref = d.double() @ w.double().t()
+    B.gemm_plan_override(tile, 1, 4)
+    try:
+        err = B.gemm(A, Bm.t(), empty((m, n))).double() - ref
+    finally:
+        B.gemm_plan_override()
+    e = float(err.norm() / ref.norm())
+    assert e < 8e-7                                   # (the fp32 instruction's)
+    assert abs(float(err.mean() / ref.square().mean().sqrt())) < 6 * e / (m * n) ** 0.5
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
 def test_values_the_parts_cannot_carry(tile, layout):
     a, b = RNG.standard_normal((200, 100)).astype(np.float32), RNG.standard_normal((150, 100)).astype(np.float32)
     b[:, 7] = np.float32(1.5)                       # exact in bfloat16: its lower parts are zero
