@@ -495,7 +495,9 @@ chn_status reduce_one_axis(int op, const chn_array *in, int axis, int keepdims, 
 // ---- several axes at once ---------------------------------------------------------------------------------
 // CHN_AXES(mask) / CHN_AXIS_ALL are carried out as a sequence of single-axis reductions, last axis first,
 // over fp32 intermediates in the caller's workspace: neighbouring reduced dimensions that are jointly
-// contiguous are merged into one axis first (a full sum of a contiguous array is one axis: one long row).
+// contiguous are merged into one axis first (a full sum of a contiguous array is one axis: one long row).  A long axis
+// that is no row (strided elements, say) and is folded into few results is cut in two (length = r x c: c elements per row
+// first, then the r row results): the general kernel gives every result to one thread.
 struct Pass {
   chn_array in, out;     // out: contiguous fp32 intermediate, or the caller's out for the last pass
   int axis;
@@ -543,10 +545,27 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
     for (int e = d; e + 1 < cur.ndim; ++e) { cur.shape[e] = cur.shape[e + 1]; cur.strides[e] = cur.strides[e + 1]; red[e] = red[e + 1]; }
     --cur.ndim;
   }
+  int64_t kept = 1;
+  for (int d = 0; d < cur.ndim; ++d) if (!red[d]) kept *= cur.shape[d];
   // one pass per remaining reduced dimension, last first
   int which = 0;
   for (int d = cur.ndim - 1; d >= 0; --d) {
     if (!red[d]) continue;
+    if (cur.shape[d] >= (1 << 20) && kept < 512 && cur.ndim < CHN_MAX_NDIM) {
+      RPlan whole;
+      chn_array probe = cur;
+      if (!probe.data) probe.data = reinterpret_cast<void *>(uintptr_t(256));
+      CHN_TRY(make_rplan(&probe, d, &whole));
+      int64_t c = 0;
+      for (int64_t t = 8192; t >= 1024; t -= 4) if (cur.shape[d] % t == 0) { c = t; break; }
+      if (whole.kind != KIND_ROW && c) {
+        for (int e = cur.ndim; e > d + 1; --e) { cur.shape[e] = cur.shape[e - 1]; cur.strides[e] = cur.strides[e - 1]; red[e] = red[e - 1]; }
+        ++cur.ndim;
+        cur.shape[d + 1] = c; cur.strides[d + 1] = cur.strides[d]; red[d + 1] = true;
+        cur.shape[d] /= c; cur.strides[d] = cur.strides[d + 1] * c;
+        ++d;
+      }
+    }
     Pass &ps = mp->pass[mp->n++];
     ps.in = cur;
     ps.axis = d;

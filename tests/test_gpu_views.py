@@ -95,6 +95,21 @@ def test_few_long_rows(dt, shape):
     assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
 
 
+@pytest.mark.parametrize("shape,step,axis", [((1 << 22,), 2, None), ((1 << 22,), 2, (0,)), ((3, 1 << 20), 3, (1,)), (((1 << 20) + 4096, 3), 1, (0,)),
+                                             ((1 << 22,), 1, None), ((2, 2, 1 << 20), 2, (0, 2))])
+def test_long_axes_of_few_results(shape, step, axis):
+    # no result is one serial chain over a long axis, whatever its stride: chains of at most 8192 elements whose results are
+    # folded in turn (2^22 equal values added one after the other would be off by several per cent)
+    x = torch.full(shape[:-1] + (shape[-1] * step,), 0.1, device="cuda")[..., ::step]
+    ax = tuple(range(len(shape))) if axis is None else axis
+    n = int(np.prod([shape[a] for a in ax]))
+    out = torch.empty([s for i, s in enumerate(shape) if i not in ax], device="cuda")
+    got = host(B.reduce_axis("sum", x, axis, out, ws=ws(B.reduce_axis_workspace_bytes(x, axis))))
+    ref = n * np.float64(np.float32(0.1))
+    assert np.all(np.abs(got - ref) <= (8192 + n // 1024) * 2.0 ** -24 * ref)
+    assert np.all(host(B.reduce_axis_static("sum", x, axis, out)) == got)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("V,D,N", [(1, 3, 5), (9, 8, 1), (10, 13, 4095), (7, 650, 4096), (40, 1031, 4097), (3000, 33, 9000)])
 def test_embedding_any_width(dt, V, D, N):
