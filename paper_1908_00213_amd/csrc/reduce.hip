@@ -54,6 +54,10 @@ template <int OP> __device__ __forceinline__ float fold(float a, float b) {
 template <int OP> __device__ __forceinline__ float identity() {
   if constexpr (OP == CHN_REDUCE_SUM) return 0.0f; else return -INFINITY;
 }
+// four bytes of input elements that hold it
+template <int OP, typename T> __device__ __forceinline__ uint32_t identity_word() {
+  return OP == CHN_REDUCE_SUM ? 0u : sizeof(T) == 2 ? 0xff80ff80u : 0xff800000u;
+}
 
 enum { KIND_EMPTY = 0, KIND_ROW = 1, KIND_COL = 2, KIND_GEN = 3 };
 
@@ -267,25 +271,35 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
     const Tin *p = in + o * sO + col;
     int64_t r = r_begin + ty;
     if constexpr (kColTX == kColTXShort) {
+      // (Addresses by addition and lanes past the end by four selected words, not sixteen 64-bit products and branches:
+      // the kernel is one cold pass over its own code, 1024 x 1000 bf16 between other kernels 5.1 -> 4.1 us, whatever
+      // pages the code lies on.)
       constexpr int U = 16;
-      for (; r < r_end; r += U * kColTY) {
+      const Tin *q = p + r * sR;
+      const int64_t step = kColTY * sR;
+      for (; r < r_end; r += U * kColTY, q += U * step) {
+        const int n = (int)min((r_end - r + kColTY - 1) / kColTY, (int64_t)U);   // this lane's rows of the batch
         std::conditional_t<VEC, Vec16<Tin>, float> x[U];
+        const Tin *at = q;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {          // a lane past the end re-reads its first row and drops it
-          const int64_t rr = r + u * kColTY;
-          const Tin *q = p + (rr < r_end ? rr : r) * sR;
-          if constexpr (VEC) x[u] = load16_any(q); else x[u] = Elem<Tin>::load(q);
+        for (int u = 0; u < U; ++u) {          // a lane past the end re-reads its last row and drops it
+          if constexpr (VEC) x[u] = load16_any(at); else x[u] = Elem<Tin>::load(at);
+          at += u + 1 < n ? step : 0;
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (r + u * kColTY < r_end) {
-            if constexpr (VEC) {
+        for (int u = 0; u < U; ++u) {
+          if constexpr (VEC) {
+            uint32_t w[4];
+            __builtin_memcpy(w, &x[u].raw, 16);
 #pragma unroll
-              for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x[u].get(i));
-            } else {
-              acc[0] = fold<OP>(acc[0], x[u]);
-            }
+            for (int i = 0; i < 4; ++i) w[i] = u < n ? w[i] : identity_word<OP, Tin>();
+            __builtin_memcpy(&x[u].raw, w, 16);
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x[u].get(i));
+          } else {
+            acc[0] = fold<OP>(acc[0], u < n ? x[u] : identity<OP>());
           }
+        }
       }
     } else if constexpr (VEC) {
       for (; r + 3 * kColTY < r_end; r += 4 * kColTY) {

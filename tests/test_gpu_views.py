@@ -95,6 +95,26 @@ def test_few_long_rows(dt, shape):
     assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", [2, 63, 64, 65, 128, 1000, 1023, 1024, 1025, 2048, 70000])
+@pytest.mark.parametrize("cols", [3, 8, 33, 1000])
+def test_stacks_of_rows(dt, rows, cols):
+    # column folds around the batch of 16 x 64 rows that one block has in flight, whole and partial vectors; a column of
+    # nothing but negative values, one of -inf, one with a NaN (which max drops and sum keeps)
+    rows = min(rows, (1 << 22) // cols)
+    a = RNG.integers(-4, 5, size=(rows, cols)).astype(np.float32)
+    a[:, 0] = -np.abs(a[:, 0]) - 1
+    top = a.copy()
+    top[:, 1], top[rows // 2, 2] = -np.inf, np.nan
+    x, out = view(a, dt, "slice")[1], torch.empty(cols, device="cuda")
+    w = ws(B.reduce_axis_workspace_bytes(x, 0))
+    assert np.array_equal(host(B.reduce_axis("sum", x, 0, out, ws=w)), a.astype(np.float64).sum(axis=0))
+    x[:, 1], x[rows // 2, 2] = float("-inf"), float("nan")
+    assert np.array_equal(host(B.reduce_axis("max", x, 0, out, ws=w)), np.fmax.reduce(top, axis=0))
+    got = host(B.reduce_axis("sum", x, 0, out, ws=w))
+    assert np.isneginf(got[1]) and np.isnan(got[2]) and np.array_equal(got[3:], a[:, 3:].astype(np.float64).sum(axis=0))
+
+
 @pytest.mark.parametrize("shape,step,axis", [((1 << 22,), 2, None), ((1 << 22,), 2, (0,)), ((3, 1 << 20), 3, (1,)), (((1 << 20) + 4096, 3), 1, (0,)),
                                              ((1 << 22,), 1, None), ((2, 2, 1 << 20), 2, (0, 2))])
 def test_long_axes_of_few_results(shape, step, axis):
