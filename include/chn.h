@@ -115,7 +115,8 @@ chn_status chn_elementwise_broadcast(int op, int n_in, const chn_array *const *i
  * (neighbouring axes of a contiguous array count as one; so does a sum over everything):
  * chn_reduce_axis_workspace_bytes takes the same axis code.  Fewer than 256 rows of 32768 elements or more (a sum over
  * everything is one row) are cut in slices for the whole chip when the workspace has the bytes that call names; the
- * part of it that only this needs is optional: with a NULL or smaller workspace one block folds a row. */
+ * part of it that only this needs is optional: with a NULL or smaller workspace one block folds the slices of a row in
+ * turn, to the same bits (a sum over 2^20 fp32 elements: 8 and 62 us). */
 typedef enum { CHN_REDUCE_SUM = 0, CHN_REDUCE_MAX = 1 } chn_reduce_op;
 
 size_t chn_reduce_axis_workspace_bytes(const chn_array *in, int axis);
@@ -129,8 +130,8 @@ chn_status chn_reduce_axis(int op, const chn_array *in, int axis, int keepdims,
                            const chn_array *out, void *ws, size_t ws_bytes, chn_stream stream);
 /* chn_reduce_axis for callers that cannot allocate device memory or bring a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and
- * results (bit for bit) as chn_reduce_axis, but the partial sums of a reduction that is cut into
- * slices live in an array built into the library -- CHN_REDUCE_STATIC_SCRATCH_BYTES of device memory
+ * results (bit for bit) as chn_reduce_axis, but the partial results of a reduction that is cut into
+ * slices (of columns, or of few long rows) live in an array built into the library -- CHN_REDUCE_STATIC_SCRATCH_BYTES of device memory
  * that every GPU the library runs on holds until the process ends -- and the call allocates and frees
  * nothing (the array's device address is looked up once per device, on the first call there).
  * A reduction whose chn_reduce_axis_workspace_bytes exceeds that size is refused with

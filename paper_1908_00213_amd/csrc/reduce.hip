@@ -76,7 +76,7 @@ struct RPlan {
   int tx = 64;               // column groups per block
   size_t ws_bytes = 0;       // COL: partial sums of the slices (required)
   // ROW: a long row that too few blocks would work on is cut in slices whose results a second launch folds, where the
-  // caller's workspace has room for them (optional: without it the row is folded by one block)
+  // caller's workspace has room for them (optional: without it one block folds the slices of a row in turn)
   int slices = 1;
   int64_t slice = 0;
   size_t slice_bytes = 0;
@@ -86,6 +86,7 @@ struct RPlan {
 // fp32 took 136 us in a single block, 7.8 us cut in slices; the sum over 16 x 16384 37 and 7.9.  The second launch
 // costs about 3 us: worth it from kCutRow elements on, as long as the rows alone do not fill the chip.
 constexpr int64_t kCutRow = 32768, kCutRows = 256, kSliceElems = 4096;
+constexpr int kMaxSlices = 8192;                            // over all rows
 
 // COL kernel block shapes (column groups x row lanes = 256 threads): 16 x 16 for the large streaming
 // case (more column blocks, hence fewer row splits and a smaller second pass), 64 x 4 otherwise.
@@ -132,7 +133,7 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     if (rows < kCutRows && p->len >= kCutRow) {
       int64_t s = (p->len + 2 * kSliceElems - 1) / (2 * kSliceElems);
       if (s * rows < 256) s = std::min((p->len + kSliceElems - 1) / kSliceElems, (256 + rows - 1) / rows);   // one block per compute unit
-      if (s * rows > 8192) s = 8192 / rows;                   // (rows < 256: at least 32)
+      if (s * rows > kMaxSlices) s = kMaxSlices / rows;                 // (rows < 256: at least 32)
       p->slice = ((p->len + s - 1) / s + 1023) / 1024 * 1024;
       p->slices = (int)((p->len + p->slice - 1) / p->slice);
       p->slice_bytes = (size_t)(rows * p->slices) * sizeof(float);
@@ -189,6 +190,55 @@ __global__ __launch_bounds__(256) void fill_kernel(Tout *out, int64_t n, float v
   if (i < n) Elem<Tout>::store(out + i, v);
 }
 
+// One lane's share of a row of `len` elements: G lanes, four accumulators each, folded in an order that depends on len
+// alone.  BATCHES of four 16-byte loads are in flight at once.
+template <int OP, typename Tin, int G, bool VEC, int BATCHES>
+__device__ __forceinline__ float fold_row(const Tin *p, int64_t len, int g) {
+  float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
+  if constexpr (VEC) {
+    constexpr int N = Vec16<Tin>::N;
+    const int64_t nvec = len / N;
+    int64_t v = g;
+    auto batches = [&](auto count) __attribute__((always_inline)) {
+      constexpr int U = 4 * decltype(count)::value;
+      for (; v + (U - 1) * G < nvec; v += U * G) {
+        Vec16<Tin> x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(p + (v + u * G) * N);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 0; i < N; ++i) acc[u & 3] = fold<OP>(acc[u & 3], x[u].get(i));
+      }
+    };
+    if constexpr (BATCHES > 1) batches(std::integral_constant<int, BATCHES>{});
+    batches(std::integral_constant<int, 1>{});
+    for (; v < nvec; v += G) {
+      const Vec16<Tin> x = load16_any(p + v * N);
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i & 3] = fold<OP>(acc[i & 3], x.get(i));
+    }
+    for (int64_t c = nvec * N + g; c < len; c += G) acc[1] = fold<OP>(acc[1], Elem<Tin>::load(p + c));
+  } else {
+    int64_t c = g;
+    for (; c + 3 * G < len; c += 4 * G) {
+      float x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = Elem<Tin>::load(p + c + u * G);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] = fold<OP>(acc[u], x[u]);
+    }
+    for (; c < len; c += G) acc[0] = fold<OP>(acc[0], Elem<Tin>::load(p + c));
+  }
+  return fold<OP>(fold<OP>(acc[0], acc[1]), fold<OP>(acc[2], acc[3]));
+}
+template <int OP, int W>
+__device__ __forceinline__ float fold_lanes(float a) {
+#pragma unroll
+  for (int o = W / 2; o > 0; o >>= 1) a = fold<OP>(a, __shfl_xor(a, o, 64));
+  return a;
+}
+
 // ROW: G lanes per row, 256 / G rows per block.
 // G = 256: a row may be cut in `slices` slices of `slice` elements, one block each; `rows` then counts slices.
 template <int OP, typename Tin, typename Tout, int G, bool VEC>
@@ -196,7 +246,7 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
   constexpr int RPB = 256 / G;
   const int g = threadIdx.x % G;
   const int64_t row = (int64_t)blockIdx.x * RPB + threadIdx.x / G;
-  float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
+  float a = identity<OP>();
   if (row < rows) {
     const Tin *p = in + row * pitch;
     if (G == 256 && slices > 1) {
@@ -204,41 +254,9 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
       p = in + r * pitch + first;
       len = len - first < slice ? len - first : slice;
     }
-    if constexpr (VEC) {
-      constexpr int N = Vec16<Tin>::N;
-      const int64_t nvec = len / N;
-      int64_t v = g;
-      for (; v + 3 * G < nvec; v += 4 * G) {
-        Vec16<Tin> x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = load16_any_nt(p + (v + u * G) * N);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int i = 0; i < N; ++i) acc[u] = fold<OP>(acc[u], x[u].get(i));
-      }
-      for (; v < nvec; v += G) {
-        const Vec16<Tin> x = load16_any(p + v * N);
-#pragma unroll
-        for (int i = 0; i < N; ++i) acc[i & 3] = fold<OP>(acc[i & 3], x.get(i));
-      }
-      for (int64_t c = nvec * N + g; c < len; c += G) acc[1] = fold<OP>(acc[1], Elem<Tin>::load(p + c));
-    } else {
-      int64_t c = g;
-      for (; c + 3 * G < len; c += 4 * G) {
-        float x[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = Elem<Tin>::load(p + c + u * G);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[u] = fold<OP>(acc[u], x[u]);
-      }
-      for (; c < len; c += G) acc[0] = fold<OP>(acc[0], Elem<Tin>::load(p + c));
-    }
+    a = fold_row<OP, Tin, G, VEC, 1>(p, len, g);
   }
-  float a = fold<OP>(fold<OP>(acc[0], acc[1]), fold<OP>(acc[2], acc[3]));
-  constexpr int W = G < 64 ? G : 64;
-#pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) a = fold<OP>(a, __shfl_xor(a, o, 64));
+  a = fold_lanes<OP, (G < 64 ? G : 64)>(a);
   if constexpr (G == 256) {
     __shared__ float part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
@@ -248,6 +266,39 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
   } else {
     if (g == 0 && row < rows) Elem<Tout>::store(out + row, a);
   }
+}
+
+// ROW without a workspace for the slices' results: one block folds all slices of its row in the same order, so that the
+// result has the same bits.  Bound by the latency of what one block has in flight: four groups of 256 threads take
+// the slices in turn, and their waves' results wait in LDS for kHeld slices at a time.
+template <int OP, typename Tin, typename Tout>
+__global__ __launch_bounds__(1024) void reduce_row_alone_kernel(const Tin *in, Tout *out, int64_t len, int64_t pitch, int slices, int64_t slice) {
+  constexpr int kHeld = 1024;
+  __shared__ __align__(16) float result[kMaxSlices];
+  __shared__ float part[kHeld][4];
+  const Tin *p = in + (int64_t)blockIdx.x * pitch;
+  const int t = threadIdx.x & 255, wave = t >> 6;
+  const bool first_lane = (threadIdx.x & 63) == 0;
+  for (int s0 = 0; s0 < slices; s0 += kHeld) {
+    const int n = min(slices - s0, kHeld);
+    for (int s = threadIdx.x >> 8; s < n; s += 4) {
+      const int64_t first = (s0 + s) * slice;
+      const float a = fold_lanes<OP, 64>(fold_row<OP, Tin, 256, true, 2>(p + first, len - first < slice ? len - first : slice, t));
+      if (first_lane) part[s][wave] = a;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+      const float *w = part[threadIdx.x];
+      result[s0 + threadIdx.x] = fold<OP>(fold<OP>(w[0], w[1]), fold<OP>(w[2], w[3]));
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < 256) {
+    const float a = fold_lanes<OP, 64>(fold_row<OP, float, 256, true, 1>(result, slices, t));
+    if (first_lane) part[0][wave] = a;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) Elem<Tout>::store(out + blockIdx.x, fold<OP>(fold<OP>(part[0][0], part[0][1]), fold<OP>(part[0][2], part[0][3])));
 }
 
 // COL: out[o, i] (or partial[s, o, i]) = fold over r in this block's slice of in[o*sO + r*sR + i].
@@ -405,7 +456,11 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     const int64_t pitch = p.nk == 1 ? p.kstr[0] : 0;
     const int n = 16 / (int)sizeof(Tin);
     const bool vec = p.len >= 4 * n;                        // (16-byte accesses at any element address)
-    if (p.slices > 1 && ws) {
+    if (p.slices > 1 && !ws) {
+      hipLaunchKernelGGL((reduce_row_alone_kernel<OP, Tin, Tout>), dim3((unsigned)rows), dim3(1024), 0, st, src, dst, p.len, pitch, p.slices, p.slice);
+      return check_launch("reduce row");
+    }
+    if (p.slices > 1) {
       float *part = static_cast<float *>(ws);
       hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, float, 256, true>), dim3((unsigned)(rows * p.slices)), dim3(256), 0, st, src, part, rows * p.slices, p.len, pitch, p.slices, p.slice);
       CHN_TRY(check_launch("reduce row slices"));

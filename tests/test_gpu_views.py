@@ -90,6 +90,12 @@ def test_few_long_rows(dt, shape):
     for kw in ({"ws": ws(need)}, {}, {"ws": ws(need)[256:]}):
         assert np.array_equal(host(B.reduce_axis("sum", x, 1, new(), **kw)), ref)
     assert np.array_equal(host(B.reduce_axis_static("sum", x, 1, new())), ref)
+    # the same bits with and without it (values whose sums round)
+    y = torch.randn(shape, device="cuda").to(TDT[dt])
+    first = B.reduce_axis("sum", y, 1, new(), ws=ws(need))
+    assert torch.equal(first, B.reduce_axis("sum", y, 1, new())) and torch.equal(first, B.reduce_axis_static("sum", y, 1, new()))
+    low = lambda **kw: B.reduce_axis("sum", y, 1, new().to(torch.bfloat16), **kw)
+    assert torch.equal(low(ws=ws(need)), low())
     top = torch.empty((), device="cuda")
     assert host(B.reduce_axis("max", x, None, top, ws=ws(B.reduce_axis_workspace_bytes(x, None)))) == a.max()
     assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
