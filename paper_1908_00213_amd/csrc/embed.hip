@@ -1,14 +1,19 @@
 // chn_embed_fwd / chn_embed_bwd: row gather by integer index (the ndarray layer's array indexing,
 // Section "GPU Support by CuPy", as the language-model workload uses it) and its gradient.
 //
-// Forward: one wave copies one row (bit-exact), 16-byte chunks when the rows are aligned.
+// Forward: one wave copies one row (bit-exact), in 16-byte chunks at whatever address the row has.
 // Backward is written as a gather so that it needs no atomics and no workspace and is bit-reproducible: one block owns
 // eight neighbouring table rows, scans the id list (wave ballots give the matches as bit masks), and adds the
 // matching rows of dout to the table row they belong to in increasing token order.  Rows nobody referenced are
-// written as zeros (or left alone when accumulating).  What bounds it is latency: every block reads every id, and few of
-// them match.  So 4096 ids are scanned at once (sixteen loads per thread in flight, two barriers), the masks
-// are searched by a ballot, and the rows of up to four matches are fetched together.
+// written as zeros (or left alone when accumulating).  What bounds it is latency and, where a block has many matches, the
+// instructions per match.  So up to 4096 ids are scanned at once (sixteen loads per thread in flight, two barriers; one
+// or four loads for short lists), everything that finds the next match is scalar (masks read from a lane's register, the
+// row taken from the id by a scalar load), the rows of up to four matches are fetched together, and a thread has
+// as many columns as the width needs.  Measured (us; 256 ids per scan and one match at a time -> here): 2136 x 1152 with
+// 15664 tokens 60.8 -> 32.5, 5105 x 448 with 3776 13.3 -> 7.8, 3264 x 2 with 25 3.3 -> 2.8, 24 x 12 with 1002 85 -> 60.
 #include "common.h"
+
+#include <type_traits>
 
 namespace chn {
 namespace {
@@ -38,83 +43,86 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const T *table, int64_t 
   }
 }
 
-constexpr int kColsPerThread = 4;
+constexpr int kMaxColsPerThread = 4;
 constexpr int kRowsPerBlock = 8;     // table rows one block owns: the id list is scanned once for all of them
 
-constexpr int kScan = 16;            // ids per thread and scan
 constexpr int kTogether = 4;         // matching rows fetched together
 
-template <typename L>
+// S: ids per thread and scan; K: columns per thread
+template <typename L, int S, int K>
 __global__ __launch_bounds__(256) void embed_bwd_kernel(const L *ids, int64_t N, const float *dout, int64_t dpitch, int64_t D,
                                                         float *dtable, int64_t tpitch, int64_t V, int accumulate) {
-  __shared__ unsigned long long masks[4 * kScan];          // [round][wave]: 64 ids each, in token order
-  __shared__ unsigned char which[256 * kScan];             // for a matching token: which of the block's rows
+  static_assert(4 * S <= 64, "one mask per lane");
+  __shared__ unsigned long long masks[64];                 // [round][wave]: 64 ids each, in token order
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t v0 = (int64_t)blockIdx.x * kRowsPerBlock;
-  const int64_t col0 = (int64_t)blockIdx.y * (256 * kColsPerThread) + threadIdx.x;
-  float acc[kRowsPerBlock][kColsPerThread];
+  const int64_t col0 = (int64_t)blockIdx.y * (256 * K) + threadIdx.x;
+  float acc[kRowsPerBlock][K];
 #pragma unroll
   for (int r = 0; r < kRowsPerBlock; ++r)
 #pragma unroll
-    for (int k = 0; k < kColsPerThread; ++k) acc[r][k] = 0.0f;
-  for (int64_t base = 0; base < N; base += 256 * kScan) {
-    int64_t id[kScan];
+    for (int k = 0; k < K; ++k) acc[r][k] = 0.0f;
+  int64_t at[K];                                           // (columns past the last one re-read it and are not stored)
 #pragma unroll
-    for (int u = 0; u < kScan; ++u) {
-      const int64_t n = base + u * 256 + threadIdx.x;
-      id[u] = n < N ? (int64_t)ids[n] : -1;
-    }
+  for (int k = 0; k < K; ++k) at[k] = min(col0 + k * 256, D - 1);
+  for (int64_t base = 0; base < N; base += 256 * S) {
+    const int left = (int)min(N - base, (int64_t)(256 * S));
+    L id[S];
 #pragma unroll
-    for (int u = 0; u < kScan; ++u) {
-      const int64_t d = id[u] - v0;
-      const bool hit = id[u] >= 0 && d >= 0 && d < kRowsPerBlock;
+    for (int u = 0; u < S; ++u) id[u] = ids[base + min(u * 256 + (int)threadIdx.x, left - 1)];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      // (one unsigned comparison: ids below v0, negative ones among them, wrap to large numbers.  v0 is a multiple of
+      // eight, so an id of -2^31 wraps to eight at least)
+      const auto d = (std::make_unsigned_t<L>)id[u] - (std::make_unsigned_t<L>)v0;
+      const bool hit = d < kRowsPerBlock && u * 256 + (int)threadIdx.x < left;
       const unsigned long long m = __ballot(hit);
       if (lane == 0) masks[u * 4 + wave] = m;
-      if (hit) which[u * 256 + threadIdx.x] = (unsigned char)d;
     }
     __syncthreads();
-    static_assert(4 * kScan == 64, "one mask per lane");
-    unsigned long long words = __ballot(masks[lane] != 0);  // masks with a match (the same on every wave)
-    unsigned long long mm = 0;
+    const unsigned long long mine = lane < 4 * S ? masks[lane] : 0;
+    // From here on everything that finds the matches is uniform and runs on the scalar unit.
+    unsigned long long words = __ballot(mine != 0), mm = 0;  // masks with a match (the same on every wave); bits left of the current one
     int w = 0;
-    for (;;) {
-      int hit[kTogether], n_hits = 0;                       // the next matches in token order; uniform over the block
+    while (words | mm) {
+      int hit[kTogether], n_hits = 0;                       // the next matches in token order (past the last: the first again)
 #pragma unroll
       for (int q = 0; q < kTogether; ++q) {
-        if (mm == 0 && words != 0) {
-          w = __ffsll((long long)words) - 1;
-          words &= words - 1;
-          mm = masks[w];
-        }
-        hit[q] = -1;
-        if (mm != 0) {
-          hit[q] = w * 64 + __ffsll((long long)mm) - 1;
-          mm &= mm - 1;
-          ++n_hits;
-        }
-      }
-      if (n_hits == 0) break;
-      float x[kTogether][kColsPerThread];
-#pragma unroll
-      for (int q = 0; q < kTogether; ++q) {
-        const float *row = dout + (base + (hit[q] < 0 ? hit[0] : hit[q])) * dpitch;
-#pragma unroll
-        for (int k = 0; k < kColsPerThread; ++k) {
-          const int64_t c = col0 + (int64_t)k * 256;
-          x[q][k] = c < D ? row[c] : 0.0f;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < kTogether; ++q) {
-        if (hit[q] < 0) break;
-        const int r_hit = which[hit[q]];
-#pragma unroll
-        for (int r = 0; r < kRowsPerBlock; ++r)
-          if (r == r_hit) {
-#pragma unroll
-            for (int k = 0; k < kColsPerThread; ++k) acc[r][k] += x[q][k];
+        hit[q] = q > 0 ? hit[0] : 0;
+        if (words | mm) {
+          if (mm == 0) {
+            w = __builtin_ctzll(words);
+            words &= words - 1;
+            mm = (unsigned int)__builtin_amdgcn_readlane((int)mine, w) |
+                 (unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(mine >> 32), w) << 32;
           }
+          hit[q] = w * 64 + __builtin_ctzll(mm);
+          mm &= mm - 1;
+          n_hits = q + 1;
+        }
       }
+      int row_of[kTogether];                                // (the id again, as a scalar)
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q) row_of[q] = (int)(ids[base + hit[q]] - (L)v0);
+      float x[kTogether][K];
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q) {
+        const float *row = dout + (base + hit[q]) * dpitch;
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[q][k] = row[at[k]];
+      }
+      __builtin_amdgcn_sched_barrier(0);                    // all loads first
+#pragma unroll
+      for (int q = 0; q < kTogether; ++q)
+        if (q < n_hits) {
+#pragma unroll
+          for (int r = 0; r < kRowsPerBlock; ++r)
+            if (r == row_of[q]) {
+              asm("" : "+v"(acc[r][0]));                    // (a branch: eight rows' sums, seven of them dropped, cost more)
+#pragma unroll
+              for (int k = 0; k < K; ++k) acc[r][k] += x[q][k];
+            }
+        }
     }
     __syncthreads();
   }
@@ -122,8 +130,8 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const L *ids, int64_t N,
   for (int r = 0; r < kRowsPerBlock; ++r) {
     if (v0 + r >= V) break;
 #pragma unroll
-    for (int k = 0; k < kColsPerThread; ++k) {
-      const int64_t c = col0 + (int64_t)k * 256;
+    for (int k = 0; k < K; ++k) {
+      const int64_t c = col0 + k * 256;
       if (c < D) {
         float *q = dtable + (v0 + r) * tpitch + c;
         *q = accumulate ? *q + acc[r][k] : acc[r][k];
@@ -189,15 +197,22 @@ chn_status chn_embed_bwd(const chn_array *ids, const chn_array *dout, const chn_
   if (dn != N || dd != D) return fail(CHN_ERR_SHAPE, "embed: dout must have shape (%lld,%lld)", (long long)N, (long long)D);
   if (V == 0 || D == 0) return CHN_OK;
   if (V > 0x7fffffff) return fail(CHN_ERR_SHAPE, "embed: table too large");
-  dim3 grid((unsigned)((V + kRowsPerBlock - 1) / kRowsPerBlock), (unsigned)((D + 256 * kColsPerThread - 1) / (256 * kColsPerThread)));
+  const int cols = (int)min((D + 255) / 256, (int64_t)kMaxColsPerThread);
+  dim3 grid((unsigned)((V + kRowsPerBlock - 1) / kRowsPerBlock), (unsigned)((D + 256 * cols - 1) / (256 * cols)));
   if (grid.y > 65535) return fail(CHN_ERR_SHAPE, "embed: rows too wide");
   hipStream_t st = as_stream(stream);
-  if (ids->dtype == CHN_I32)
-    hipLaunchKernelGGL((embed_bwd_kernel<int32_t>), grid, dim3(256), 0, st, static_cast<const int32_t *>(ids->data), N,
-                       static_cast<const float *>(dout->data), dp, D, static_cast<float *>(dtable->data), tp, V, accumulate);
-  else
-    hipLaunchKernelGGL((embed_bwd_kernel<int64_t>), grid, dim3(256), 0, st, static_cast<const int64_t *>(ids->data), N,
-                       static_cast<const float *>(dout->data), dp, D, static_cast<float *>(dtable->data), tp, V, accumulate);
+#define CHN_BWD(L, S, K) \
+  hipLaunchKernelGGL((embed_bwd_kernel<L, S, K>), grid, dim3(256), 0, st, static_cast<const L *>(ids->data), N, \
+                     static_cast<const float *>(dout->data), dp, D, static_cast<float *>(dtable->data), tp, V, accumulate)
+#define CHN_BWD_K(L, S) \
+  do { if (cols == 1) CHN_BWD(L, S, 1); else if (cols == 2) CHN_BWD(L, S, 2); else if (cols == 3) CHN_BWD(L, S, 3); else CHN_BWD(L, S, 4); } while (0)
+#define CHN_BWD_S(L) \
+  do { if (N <= 256) CHN_BWD_K(L, 1); else if (N <= 1024) CHN_BWD_K(L, 4); else CHN_BWD_K(L, 16); } while (0)
+  if (ids->dtype == CHN_I32) CHN_BWD_S(int32_t);
+  else CHN_BWD_S(int64_t);
+#undef CHN_BWD_S
+#undef CHN_BWD_K
+#undef CHN_BWD
   return check_launch("embed_bwd");
 }
 

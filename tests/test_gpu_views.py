@@ -155,3 +155,22 @@ def test_embedding_any_width(dt, V, D, N):
     g = view(np.zeros((V, D), np.float32), "f32", "slice")[1]
     assert np.array_equal(host(B.embed_bwd(dev(ids), view(dout, "f32", "slice")[1], g)), ref)
     assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g, accumulate=True)), 2 * ref)
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("N", [1, 3, 256, 257, 1024, 1025, 4097])
+@pytest.mark.parametrize("D", [1, 256, 257, 513, 769, 1025])
+def test_embedding_gradient_scan_lengths(N, D, wide):
+    # both sides of the id list lengths and widths at which the kernel changes its scan and its columns per thread; ids
+    # outside the table, the extremes of their type among them, match nothing
+    V = 21
+    ids = RNG.integers(0, V, N).astype(np.int64 if wide else np.int32)
+    stray = [-1, -2 ** 31, 2 ** 31 - 1, V, -8] + ([-2 ** 63, 2 ** 63 - 1, 2 ** 32, -2 ** 32 + 3] if wide else [])
+    ids[::5] = [stray[i % len(stray)] for i in range(len(ids[::5]))]
+    dout = RNG.integers(-3, 4, (N, D)).astype(np.float32)
+    ok = (ids >= 0) & (ids < V)
+    ref = np.zeros((V, D))
+    np.add.at(ref, ids[ok], dout[ok])
+    g = torch.full((V, D), float("nan"), device="cuda")
+    assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g)), ref)
+    assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g, accumulate=True)), 2 * ref)
