@@ -191,6 +191,13 @@ def test_epilogues(tile, splits):
         check(run(C=old, alpha=0.5, beta=-2.0), 0.5 * lin - 2.0 * c0, TOL_SUM, S + 2 * np.abs(c0), "alpha beta")
 
 
+def test_planner_leaves_few_tiles_to_the_instruction():
+    # one or two tiles and a long K: cut along K on the fp32 instruction (44x15x568 9.2 us, here 15.7; 36x80x5127 17.7 and 29.3)
+    for m, n, k, pad in ((44, 15, 568, 0), (36, 80, 5127, 2), (336, 53, 578, 0)):
+        A, Bm = (torch.empty(r, k + pad, device="cuda")[:, :k] for r in (m, n))
+        assert not B.gemm_plan_eight_waves(A, Bm.t(), empty((m, n)), True) and B.gemm_plan(A, Bm.t(), empty((m, n)), True)[2] > 1
+
+
 def test_planner_takes_the_kernel_and_results_repeat():
     # mid-size and large products without any override; the same call twice gives the same bits
     for m, n, k in ((1024, 1000, 1000), (1100, 1300, 700)):
