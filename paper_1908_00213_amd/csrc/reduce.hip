@@ -83,10 +83,15 @@ struct RPlan {
 };
 
 // Few long rows (the sum over everything is one): one block moves 16 KB per memory latency, so the sum over 1024 x 1001
-// fp32 took 136 us in a single block, 7.8 us cut in slices; the sum over 16 x 16384 37 and 7.9.  The second launch
-// costs about 3 us: worth it from kCutRow elements on, as long as the rows alone do not fill the chip.
+// fp32 took 136 us in a single block, 7.8 us cut in slices; the sum over 16 x 16384 37 and 7.9.  Worth it from kCutRow
+// elements on, as long as the rows alone do not fill the chip; but the second launch costs a microsecond, so the shortest of
+// these stay whole (whatever workspace there is): one row of 32768 bf16 2.9 us against 4.4 in slices, 60000 3.8 and 4.4, 80000
+// 4.6 and 4.4; fp32 40000 3.8 and 4.4, 60000 4.6 and 4.4, but 32 rows of 40000 5.5 and 4.9.
 constexpr int64_t kCutRow = 32768, kCutRows = 256, kSliceElems = 4096;
 constexpr int kMaxSlices = 8192;                            // over all rows
+bool cut_pays(int64_t rows, int64_t len, int isz) {
+  return len >= (isz == 2 ? 65536 : rows <= 8 ? 57344 : rows <= 16 ? 45056 : kCutRow);
+}
 
 // COL kernel block shapes (column groups x row lanes = 256 threads): 16 x 16 for the large streaming
 // case (more column blocks, hence fewer row splits and a smaller second pass), 64 x 4 otherwise.
@@ -456,11 +461,12 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     const int64_t pitch = p.nk == 1 ? p.kstr[0] : 0;
     const int n = 16 / (int)sizeof(Tin);
     const bool vec = p.len >= 4 * n;                        // (16-byte accesses at any element address)
-    if (p.slices > 1 && !ws) {
+    const bool cut = p.slices > 1 && cut_pays(rows, p.len, (int)sizeof(Tin));
+    if (cut && !ws) {
       hipLaunchKernelGGL((reduce_row_alone_kernel<OP, Tin, Tout>), dim3((unsigned)rows), dim3(1024), 0, st, src, dst, p.len, pitch, p.slices, p.slice);
       return check_launch("reduce row");
     }
-    if (p.slices > 1) {
+    if (cut) {
       float *part = static_cast<float *>(ws);
       hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, float, 256, true>), dim3((unsigned)(rows * p.slices)), dim3(256), 0, st, src, part, rows * p.slices, p.len, pitch, p.slices, p.slice);
       CHN_TRY(check_launch("reduce row slices"));

@@ -78,7 +78,8 @@ def test_reductions_of_views(dt, layout, shape):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [(1, 32767), (1, 32768), (3, 100001), (255, 33000), (256, 33000), (1, 3000001)])
+@pytest.mark.parametrize("shape", [(1, 32767), (1, 32768), (3, 100001), (255, 33000), (256, 33000), (1, 3000001), (1, 57343), (8, 57344), (9, 45055), (16, 45056),
+                                   (17, 40000), (5, 65535), (200, 65536)])
 def test_few_long_rows(dt, shape):
     # rows that are cut in slices: with the workspace asked for, without any (one block per row) and with the built-in scratch
     a = RNG.integers(-4, 5, size=shape).astype(np.float32)
