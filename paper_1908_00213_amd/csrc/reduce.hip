@@ -151,11 +151,16 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     p->O = nk == 2 ? p->kshape[0] : 1;
     p->sO = nk == 2 ? p->kstr[0] : 0;
     const int n = 16 / isz;
-    // 16-byte accesses wherever a row holds one: they may start at any element address (10000 x 4001 bf16 column sums
-    // 29.8 -> 19.8 us against one element per access, 12000 x 1500 21.3 -> 15.8)
+    // 16-byte accesses wherever a row holds one; they may start at any element address (10000 x 4001 bf16 column sums
+    // 29.8 -> 19.8 us against one element per access, 12000 x 1500 21.3 -> 15.8).  Off the 16-byte grid one element per
+    // access stays the better where it gives the more blocks and a short chain per thread: small stacks of rows
+    // (376 x 8 bf16 2.5 against 3.7 us, 256 x 1109 3.0 and 4.2) and mid-size widths (9340 x 451 bf16 8.2 and 10.7, 2657 x 179
+    // fp32 5.8 and 6.5).
     const bool aligned = reinterpret_cast<uintptr_t>(in->data) % 16 == 0 && p->I % n == 0 && p->sR % n == 0 && p->sO % n == 0;
-    p->vec = p->I >= n;
-    const int64_t groups = (p->I + n - 1) / (p->vec ? n : 1);
+    const bool stack = p->len <= kShortRows && p->O * p->len * p->I * isz <= kShortBytes / 8 && (isz == 2 || p->len > 128);
+    const bool mid = isz == 2 ? p->I > 128 && p->I < 1280 && p->len > kShortRows : p->I > 128 && p->I < 256;
+    p->vec = p->I >= n && (aligned || !(stack || mid));
+    const int64_t groups = p->vec ? (p->I + n - 1) / n : p->I;
     p->tx = (p->vec && groups >= 512 && p->len >= 1024) ? (isz == 2 && groups >= 1024 ? kColTXMid : kColTXWide) : kColTXNarrow;
     if (p->vec && groups <= 32) p->tx = groups <= 4 && p->len >= 1024 ? kColTXShort : groups <= 16 ? kColTXWide : kColTXMid;   // no idle column lanes (16384 x 16 fp32 14.0 -> 7.8 us)
     if (p->vec && groups >= 64 && p->len <= 64) p->tx = kColTXWide;   // 16 row lanes: one batch of loads per thread
@@ -401,18 +406,21 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
     for (int i = 0; i < N; ++i) part[ty][tx * N + i] = acc[i];
   }
   __syncthreads();
-  if (ty == 0 && col < I) {
-    Tout *q = out + (int64_t)blockIdx.y * out_split_stride + o * I + col;
+  // All threads fold: a column each (with eight bf16 columns per thread of one row lane, 32 threads had 64 values to read
+  // one after the other: 64 x 179 bf16 2.7 us, 2.2 like this).
+  Tout *q = out + (int64_t)blockIdx.y * out_split_stride + o * I;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
+  for (int c = threadIdx.x; c < kColTX * N; c += 256) {
+    const int64_t f = ((int64_t)blockIdx.x * kColTX + c / N) * N, at = VEC && f < I && f + N > I ? I - N : f;
+    if (at < I) {
       float v[kParts];                                       // folded as a tree: fewest roundings at full magnitude
 #pragma unroll
-      for (int y = 0; y < kParts; ++y) v[y] = part[y][tx * N + i];
+      for (int y = 0; y < kParts; ++y) v[y] = part[y][c];
 #pragma unroll
       for (int h = kParts / 2; h > 0; h /= 2)
 #pragma unroll
         for (int y = 0; y < h; ++y) v[y] = fold<OP>(v[y], v[y + h]);
-      Elem<Tout>::store(q + i, v[0]);
+      Elem<Tout>::store(q + at + c % N, v[0]);
     }
   }
 }
@@ -494,8 +502,9 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     CHN_TRY((launch_col<OP, Tin, float>(src, part, p, p.O, p.len, p.I, p.sO, p.sR, p.split, p.rows_per_split, OI, p.vec, p.tx, st)));
     // Second pass over the [split, O * I] partials: a small array, so the time is one chain of
     // dependent load batches per lane; the narrow-in-columns block shape keeps that chain short.
+    // Off the 16-byte grid it takes vectors from 2048 columns on only (9340 x 451 bf16 in all 10.1 us with, 8.2 without).
     const bool wide2 = OI / 4 >= 512 && p.split >= 16;
-    return launch_col<OP, float, Tout>(part, dst, p, 1, p.split, OI, 0, OI, 1, p.split, 0, OI >= 4, wide2 ? kColTXWide : kColTXNarrow, st);
+    return launch_col<OP, float, Tout>(part, dst, p, 1, p.split, OI, 0, OI, 1, p.split, 0, OI % 4 == 0 || OI >= 2048, wide2 ? kColTXWide : kColTXNarrow, st);
   }
   GenArgs a{};
   a.nk = p.nk; a.len = p.len; a.sR = p.sR; a.total_out = p.total_out;
