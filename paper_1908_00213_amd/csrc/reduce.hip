@@ -666,7 +666,9 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
     ps.ws_need = rp.kind == KIND_COL ? rp.ws_bytes : 0;
     if (ps.ws_need > mp->partial_bytes) mp->partial_bytes = ps.ws_need;
     if (rp.kind == KIND_ROW && rp.slice_bytes > mp->slice_bytes) mp->slice_bytes = rp.slice_bytes;
-    const size_t ob = (size_t)numel(&nxt) * sizeof(float);
+    bool last = true;                        // (the last pass writes the caller's array)
+    for (int e = 0; e < d; ++e) last = last && !red[e];
+    const size_t ob = last ? 0 : (size_t)numel(&nxt) * sizeof(float);
     if (ob > mp->tmp_bytes[which]) mp->tmp_bytes[which] = ob;
     which ^= 1;
     cur = nxt;

@@ -100,6 +100,9 @@ def test_few_long_rows(dt, shape):
     top = torch.empty((), device="cuda")
     assert host(B.reduce_axis("max", x, None, top, ws=ws(B.reduce_axis_workspace_bytes(x, None)))) == a.max()
     assert host(B.reduce_axis("max", dev(a, dt), None, top, ws=ws(256))) == a.max()
+    # everything of a contiguous array is one row: no workspace is required, and the bits do not depend on it
+    total = lambda **kw: B.reduce_axis("sum", y, None, torch.empty((), device="cuda"), **kw)
+    assert torch.equal(total(ws=ws(B.reduce_axis_workspace_bytes(y, None))), total())
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
