@@ -31,7 +31,7 @@ EXPORTS = ["chn_elementwise_broadcast", "chn_reduce_axis_workspace_bytes", "chn_
            "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit",
            "chn_softmax_ce_workspace_bytes", "chn_softmax_ce_fwd", "chn_softmax_ce_bwd", "chn_softmax_ce_bwd2", "chn_softmax_ce_fwd_bwd",
            "chn_sgd_update", "chn_sgd_update_multi", "chn_adam_update_multi", "chn_embed_fwd", "chn_embed_bwd",
-           "chn_status_string", "chn_last_error", "chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_override",
+           "chn_status_string", "chn_last_error", "chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel", "chn_gemm_plan_override",
            "chn_user_kernel_config", "chn_user_kernel_stats", "chn_user_kernel_destroy",
            "chn_elementwise_kernel_create", "chn_elementwise_kernel_prepare", "chn_elementwise_kernel_launch",
            "chn_reduction_kernel_create", "chn_reduction_kernel_workspace_bytes", "chn_reduction_kernel_prepare",
@@ -87,6 +87,7 @@ def lib():
     L.chn_gemm_workspace_bytes.argtypes = [AP, AP, AP]
     L.chn_gemm_workspace_bytes.restype = C.c_size_t
     L.chn_gemm_plan.argtypes = [AP, AP, AP, C.c_int]
+    L.chn_gemm_plan_kernel.argtypes = [AP, AP, AP, C.c_int]
     L.chn_gemm_plan_override.argtypes = [C.c_int, C.c_int, C.c_int]
     L.chn_gemm_plan_override.restype = None
     L.chn_gemm.argtypes = [AP, AP, AP, C.c_float, C.c_float, C.c_int, AP, AP, AP, vp, C.c_size_t, st]
@@ -138,7 +139,7 @@ def lib():
                                          C.POINTER(C.c_size_t)]
     for name in EXPORTS:
         fn = getattr(L, name)
-        if fn.restype is C.c_int and name not in ("chn_version", "chn_elementwise_plan", "chn_gemm_plan"):  # i.e. not set above
+        if fn.restype is C.c_int and name not in ("chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel"):  # i.e. not set above
             fn.restype = C.c_int32
     _lib = L
     return L
@@ -287,11 +288,23 @@ def gemm_plan(A, B, Cm, have_workspace=False):
 
 
 def gemm_plan_eight_waves(A, B, Cm, have_workspace=False):
-    """Whether the plain product would run on the eight-wave form of the direct-copy kernel."""
+    """Whether the plain product would run on the eight-wave form of the direct-copy kernel (bf16) or on the
+    three-part kernel (fp32)."""
     code = lib().chn_gemm_plan(_ref(desc(A)), _ref(desc(B)), _ref(desc(Cm)), 1 if have_workspace else 0)
     if code < 0:
         _check(code)
     return bool(code & 8)
+
+
+GEMM_KERNELS = ("staged", "direct4", "direct8", "parts", "small")
+
+
+def gemm_plan_kernel(A, B, Cm, have_workspace=False):
+    """The kernel the plain product would run on, one of GEMM_KERNELS."""
+    code = lib().chn_gemm_plan_kernel(_ref(desc(A)), _ref(desc(B)), _ref(desc(Cm)), 1 if have_workspace else 0)
+    if code < 0:
+        _check(code)
+    return GEMM_KERNELS[code]
 
 
 def gemm_plan_override(tile=-1, splits=-1, direct_copy=-1):

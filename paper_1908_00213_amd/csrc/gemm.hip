@@ -237,6 +237,21 @@ bool eight_waves(const GemmArgs &g, int isz, int epilogue) {
   return f < 0 || f != 0;
 }
 
+// What chn_gemm would do with these operands.
+chn_status plan_of(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace, GemmArgs *g) {
+  CHN_TRY(validate(A, "A", false));
+  CHN_TRY(validate(B, "B", false));
+  CHN_TRY(validate(C, "C", true));
+  if (A->ndim != 2 || B->ndim != 2 || C->ndim != 2) return fail(CHN_ERR_NDIM, "gemm: A, B and C must be 2-d");
+  if (!is_float(A->dtype) || A->dtype != B->dtype) return fail(CHN_ERR_DTYPE, "gemm: A and B must share F32 or BF16");
+  if (A->shape[1] != B->shape[0] || C->shape[0] != A->shape[0] || C->shape[1] != B->shape[1]) return fail(CHN_ERR_SHAPE, "gemm: shapes do not match");
+  if (A->shape[0] > 0x3fffffff || A->shape[1] > 0x3fffffff || B->shape[1] > 0x3fffffff) return fail(CHN_ERR_SHAPE, "gemm: dimension too large");
+  bool a_kc, b_kc;
+  CHN_TRY(classify(A, B, g, &a_kc, &b_kc));
+  plan(g, dtype_size(A->dtype), a_kc, b_kc, have_workspace != 0);
+  return CHN_OK;
+}
+
 size_t split_bytes(const GemmArgs &g) {
   return g.splits > 1 ? (size_t)g.splits * g.M * g.ldp * sizeof(float) : 0;
 }
@@ -267,20 +282,18 @@ void chn_gemm_plan_override(int tile, int splits, int direct_copy) {
 }
 
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace) {
-  using namespace chn;
-  CHN_TRY(validate(A, "A", false));
-  CHN_TRY(validate(B, "B", false));
-  CHN_TRY(validate(C, "C", true));
-  if (A->ndim != 2 || B->ndim != 2 || C->ndim != 2) return fail(CHN_ERR_NDIM, "gemm: A, B and C must be 2-d");
-  if (!is_float(A->dtype) || A->dtype != B->dtype) return fail(CHN_ERR_DTYPE, "gemm: A and B must share F32 or BF16");
-  if (A->shape[1] != B->shape[0] || C->shape[0] != A->shape[0] || C->shape[1] != B->shape[1]) return fail(CHN_ERR_SHAPE, "gemm: shapes do not match");
-  if (A->shape[0] > 0x3fffffff || A->shape[1] > 0x3fffffff || B->shape[1] > 0x3fffffff) return fail(CHN_ERR_SHAPE, "gemm: dimension too large");
-  GemmArgs g{};
-  bool a_kc, b_kc;
-  CHN_TRY(classify(A, B, &g, &a_kc, &b_kc));
-  const int isz = dtype_size(A->dtype);
-  plan(&g, isz, a_kc, b_kc, have_workspace != 0);
-  return g.tile | (g.dma ? 4 : 0) | (eight_waves(g, isz, CHN_EPI_NONE) || g.parts == 1 || g.parts == 2 ? 8 : 0) | (g.splits << 4);
+  chn::GemmArgs g{};
+  CHN_TRY(chn::plan_of(A, B, C, have_workspace, &g));
+  return g.tile | (g.dma ? 4 : 0) | (chn::eight_waves(g, chn::dtype_size(A->dtype), CHN_EPI_NONE) || g.parts == 1 || g.parts == 2 ? 8 : 0) | (g.splits << 4);
+}
+
+int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace) {
+  chn::GemmArgs g{};
+  CHN_TRY(chn::plan_of(A, B, C, have_workspace, &g));
+  if (g.parts == 3) return CHN_GEMM_KERNEL_SMALL;
+  if (g.parts) return CHN_GEMM_KERNEL_PARTS;
+  if (!g.dma) return CHN_GEMM_KERNEL_STAGED;
+  return chn::eight_waves(g, chn::dtype_size(A->dtype), CHN_EPI_NONE) ? CHN_GEMM_KERNEL_DIRECT8 : CHN_GEMM_KERNEL_DIRECT4;
 }
 
 chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, float alpha, float beta,

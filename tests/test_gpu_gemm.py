@@ -55,6 +55,22 @@ def test_gemm_layouts(dt, layout, shape):
         check(host(outb), ref, TOL_BF16, S, "gemm bf16 out")
 
 
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_gemm_layouts_staged_through_registers(tile, layout, shape):
+    """The fp32 tiles that are staged through registers, at sizes the planner gives to the small-product kernel."""
+    M, N, K = shape
+    A, Bm, Ad, Bd = operands(M, N, K, layout, "f32")
+    B.gemm_plan_override(tile, 1, 0)
+    try:
+        assert B.gemm_plan_kernel(Ad, Bd, empty((M, N))) == "staged"
+        out = B.gemm(Ad, Bd, empty((M, N)))
+    finally:
+        B.gemm_plan_override()
+    check(host(out), O.gemm(A, Bm), TOL_SUM, O.gemm(np.abs(A), np.abs(Bm)), "gemm %s" % layout)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(10, 1000, 1024), (10, 37, 200), (77, 130, 96), (203, 5, 64), (1, 3, 40)])
 def test_gemm_transposed_operands_with_padded_rows(dt, shape):
@@ -233,6 +249,15 @@ def test_gemm_alpha_beta_and_epilogues(dt):
         B.gemm(Ad, Bd, bd[M:2 * M], beta=1.0)
         want = big.astype(np.float64); want[M:2 * M] += O.gemm(A, Bm)
         check(host(bd), want, tol, np.concatenate([np.zeros((M, N)), S + np.abs(big[M:2 * M]), np.zeros((M, N))]), "beta=1 slice")
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+def test_gemm_epilogues_staged_through_registers(tile):
+    B.gemm_plan_override(tile, 1, 0)
+    try:
+        test_gemm_alpha_beta_and_epilogues("f32")
+    finally:
+        B.gemm_plan_override()
 
 
 def test_gemm_misaligned_leading_dimensions():

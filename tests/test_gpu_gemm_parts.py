@@ -202,7 +202,7 @@ def test_planner_takes_the_kernel_and_results_repeat():
     # mid-size and large products without any override; the same call twice gives the same bits
     for m, n, k in ((1024, 1000, 1000), (1100, 1300, 700)):
         A, Bm = torch.randn(m, k, device="cuda"), torch.randn(n, k, device="cuda").t()
-        assert B.gemm_plan_eight_waves(A, Bm, empty((m, n)), True)
+        assert B.gemm_plan_eight_waves(A, Bm, empty((m, n)), True) and B.gemm_plan_kernel(A, Bm, empty((m, n)), True) == "parts"
         need = B.gemm_workspace_bytes(A, Bm, empty((m, n)))
         x, y = (B.gemm(A, Bm, empty((m, n)), ws=ws(need)) for _ in range(2))
         assert torch.equal(x, y)
@@ -219,6 +219,7 @@ def test_small_products(layout, shape, pad):
     a, b = (RNG.integers(-9, 10, size=s).astype(np.float32) for s in ((m, k), (n, k)))
     bias, aux, c0 = (RNG.integers(-9, 10, size=s).astype(np.float32) for s in ((n,), (m, n), (m, n)))
     A, Bm = operand(a, layout[0] == "k", pad), operand(b, layout[1] == "k", pad).t()
+    assert B.gemm_plan_kernel(A, Bm, empty((m, n)), True) == "small"
     assert B.gemm_plan(A, Bm, empty((m, n)), True) == (0, False, 1) and B.gemm_workspace_bytes(A, Bm, empty((m, n))) == 0
     lin = a.astype(np.float64) @ b.T.astype(np.float64)
     new = lambda: operand(c0, True, 1 + pad)
