@@ -10,7 +10,7 @@ namespace gemm {
 
 chn_status CHN_GEMM_NAME(GemmArgs &g, hipStream_t st) {
   if constexpr (sizeof(CHN_GEMM_T) == 4) {
-    if (g.parts == 3) return launch_tiny<CHN_GEMM_T, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
+    if (g.parts == 3) return launch_tiny<CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
     if (g.parts == 2) return launch_split<2, 2, 2, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
     if (g.parts == 1) return launch_split<1, 1, 4, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
   }
