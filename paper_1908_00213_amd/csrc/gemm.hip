@@ -158,9 +158,9 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
 // counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 plus its tile
 // steps (32 k on the large tile, 64 on the small one); a step takes longer when all 256 compute units pull operands out of
 // the L2s than when a quarter of them does, and with operands that allow 8- or 4-byte pieces only.  Each compute
-// unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 21 on the
-// small tile, 4480x2688x672 153 -> 100 and 4480x10000x672 478 -> 350 on the large one, 672x2688x4480 both stored along
-// M/N 178 -> 111 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
+// unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 22 on the
+// small tile, 4480x2688x672 143 -> 101 and 4480x10000x672 499 -> 361 on the large one, 672x2688x4480 both stored along
+// M/N 178 -> 115 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
   double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);

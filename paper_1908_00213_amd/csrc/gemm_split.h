@@ -1,20 +1,20 @@
 // fp32 products on the bfloat16 matrix cores, at fp32 accuracy.
 //
-// A float x is the sum of three bfloat16 numbers: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), every
-// difference exact (8 + 8 + 8 significant bits, round to nearest even at each step, |m| <= 2^-8 |x|,
-// |l| <= 2^-17 |x|).  A product a b is then
+// The scheme is that of G. Henry, P. T. P. Tang and A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype
+// For Higher-Precision Computations", ARITH 2019.  A float x is the sum of three bfloat16 numbers: h = bf16(x),
+// m = bf16(x - h), l = bf16(x - h - m), every difference exact (8 + 8 + 8 significant bits, round to nearest even at each
+// step, |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), once x is scaled so that l stays in bfloat16's range (kSplitScale).  A product a b is then
 //     ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + [am bl + al bm + al bl],
-// and what stands in brackets is below 2^-24 |a b|, of random sign: less than the rounding of the product itself.
+// and what stands in brackets, at most 2^-24 |a b| and of random sign, is left out: less than the rounding of the product itself.
 // Six products of v_mfma_f32_32x32x16_bf16 (32 cycles for 16 k) replace eight of v_mfma_f32_32x32x2_f32
 // (64 cycles for 2 k each): 192 instead of 512 cycles of the matrix pipe for the same part of C, with fewer
-// roundings of the fp32 accumulator on the way: the error against 64 bits (2-norm) falls from 5.7e-7 to 1.0e-7 at
-// K = 1000 and from 1.15e-6 to 2.7e-7 at K = 4096.
+// roundings of the fp32 accumulator on the way: the error against 64 bits (2-norm) falls from 5.0e-7 to 0.9e-7 at
+// K = 784 and from 9.1e-7 to 2.1e-7 at K = 2600.
 //
-// Measured (us, fp32 instruction -> here): 1024x1000x1000 27.2 -> 20.6, 4480x2688x672 153 -> 100, 4480x10000x672
-// 478 -> 350, 4096x4096x4096 919 -> 667 (206 TFLOP/s, where the instruction's peak is 157).  What bounds the large
-// tile at 4096^3: the matrix pipes are busy half of the cycles at the 1.97 GHz the chip holds; without staging (loads,
-// splitting, LDS writes) the same loop takes 516, with the matrix work alone 483.  The small tile waits for the chip-wide
-// stream of operand tiles out of the L2s (20.6 -> 12.9 without staging).
+// Measured (us, fp32 instruction -> here, both operands along K): 1024x1000x1000 27.2 -> 22.0, 4480x2688x672 142.8 -> 101.3,
+// 4480x10000x672 499 -> 361, 4096x4096x4096 961 -> 688 (200 TFLOP/s, where the instruction's peak is 157).  What bounds the
+// large tile is the vector work of the split beside the matrix work (13 instructions per pair of values staged: scaling
+// took it from 667 to 688 at 4096^3); the small tile, one per compute unit, waits for the chip-wide stream of operand tiles.
 #pragma once
 #include "gemm_kernel.h"
 
