@@ -170,23 +170,39 @@ __device__ __forceinline__ void store16_any(T *p, const Vec16<T> &x) {
   __builtin_memcpy(&v, &x.raw, 16);
   *reinterpret_cast<chn_u32x4_any *>(p) = v;
 }
-// The first n (0 .. whole vector) elements only; the others read as zero / stay untouched.
+// The first n (0 .. whole vector) elements only; the others read as zero / stay untouched.  The elements are moved as they
+// are.  In two-byte types a partial load takes the last one again in place of those beyond n, so that its eight loads are in
+// flight together (behind conditions, each waits for the word it shares: 1392 x 7 transposed 7.4 us, 5.2 like this); the
+// four of fp32 are the faster with conditions.
 template <typename T>
 __device__ __forceinline__ Vec16<T> load16_part(const T *p, int64_t n) {
-  if (n >= Vec16<T>::N) return load16_any(p);
-  Vec16<T> r;
-  r.raw = {};
+  constexpr int N = Vec16<T>::N;
+  if (n >= N) return load16_any(p);
+  T e[N] = {};
+  if constexpr (sizeof(T) == 4) {
 #pragma unroll
-  for (int i = 0; i < Vec16<T>::N; ++i)
-    if (i < n) r.set(i, Elem<T>::load(p + i));
+    for (int i = 0; i < N; ++i)
+      if (i < n) e[i] = p[i];
+  } else if (n > 0) {
+    const int last = (int)n - 1;
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = p[min(i, last)];
+#pragma unroll
+    for (int i = 0; i < N; ++i) e[i] = i <= last ? e[i] : T(0);
+  }
+  Vec16<T> r;
+  __builtin_memcpy(&r.raw, e, 16);
   return r;
 }
 template <typename T>
 __device__ __forceinline__ void store16_part(T *p, const Vec16<T> &x, int64_t n) {
-  if (n >= Vec16<T>::N) { store16_any(p, x); return; }
+  constexpr int N = Vec16<T>::N;
+  if (n >= N) { store16_any(p, x); return; }
+  T e[N];
+  __builtin_memcpy(e, &x.raw, 16);
 #pragma unroll
-  for (int i = 0; i < Vec16<T>::N; ++i)
-    if (i < n) Elem<T>::store(p + i, x.get(i));
+  for (int i = 0; i < N; ++i)
+    if (i < n) p[i] = e[i];
 }
 
 // erfc with a relative error of about 1e-6 everywhere, tails included: the Chebyshev fit

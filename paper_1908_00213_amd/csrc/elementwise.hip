@@ -449,7 +449,7 @@ __global__ __launch_bounds__(256) void ew_transpose_kernel(TransArgs a, int64_t 
 // element from LDS and everything else with 16-byte global loads, and stores 16 bytes.
 // ALIGNED: extents, strides and bases are whole vectors.  Otherwise the same accesses start at any element address and
 // the last vector of a row or column may be partial (relu(a.T * b + c) with one
-// element per access: 4999 x 3001 bf16 89 us, now 30; 8001 x 8001 fp32 417, now 200).
+// element per access: 4999 x 3001 bf16 89 us, now 28; 8001 x 8001 fp32 417, now 200).
 template <int OP, typename T, int NIN, int TC, bool ALIGNED>
 __global__ __launch_bounds__(256) void ew_transpose_vec_kernel(TransArgs a, int64_t tiles_c) {
   constexpr int E = 16 / (int)sizeof(T);
