@@ -223,6 +223,9 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
     // by all threads together, so that every wave has the same mixture of work.
     constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || KG == 4;
+    // A mixed pair on the large tile: steps of whole k without checks pay for 8-byte pieces (4480x650x2600 149 -> 145 us,
+    // 2050^3 187 -> 176), not for 16-byte ones (4480x2688x672 120 -> 123).
+    constexpr bool kUniform = PBA == 8;
     using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
     using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
     LA la;
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
-      if constexpr (!kHalves) { la.template issue<PBA, kAlike>(xa, kt * BK); lb.template issue<PBB, kAlike>(xb, kt * BK); }
+      if constexpr (!kHalves) { la.template issue<PBA, kUniform>(xa, kt * BK); lb.template issue<PBB, kUniform>(xb, kt * BK); }
       else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
       else if constexpr (kAlike) { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else la.template issue<PBB, kAlike>(xa, kt * BK); }
       else { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else lb.template issue<PBB, kAlike>(xa, kt * BK); }
