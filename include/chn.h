@@ -268,11 +268,14 @@ chn_status chn_lstm_step_bwd(const chn_array *dz_next, const chn_array *U, const
  * the contraction cut in four; the gate activations on the hardware's exponential and reciprocal, relative
  * error a few 1e-7; agrees with them within the product tolerance).
  *
- * The grid stays on the device for the whole sequence - (H/8) x ceil(B/64) workgroups, each holding its rows
- * of Ut in LDS - and exchanges h between steps through device memory, so every workgroup must be resident at
+ * The grid stays on the device for the whole sequence.  Up to 128 rows and H <= 768: sixteen batch rows to an
+ * XCD, up to 32 workgroups there that hold their units' rows of Ut in registers and exchange h through its L2;
+ * if these do not all come to run within some milliseconds, or beyond those sizes: (H/8) x ceil(B/64) workgroups,
+ * each holding its rows of Ut in LDS, that exchange h through device memory.  Every workgroup must be resident at
  * once: H % 8 == 0 (BF16: % 16), a row of h of at most 3072 bytes (H <= 768 F32, 1536 BF16) and no more
- * workgroups than the device has compute units; otherwise CHN_ERR_SHAPE and the caller uses the per-step
- * calls.  ws: chn_lstm_seq_workspace_bytes(B) bytes, 256-byte aligned, the library's until the work on
+ * of the latter workgroups than the device has compute units; otherwise CHN_ERR_SHAPE and the caller uses the per-step
+ * calls.  ws: chn_lstm_seq_workspace_bytes(B) bytes (512 + 4 * ceil(B/64) are enough to run, without the first kind
+ * of grid), 256-byte aligned, the library's until the work on
  * `stream` is done.  A workgroup waits for the others a bounded number of polls (chn_lstm_seq_spin_limit;
  * the default is worth seconds).  If a wait runs out - another kernel holds compute units the grid needs -
  * every workgroup leaves, the outputs are incomplete, and the first 4 bytes of ws read 1 instead of 0 once
@@ -294,13 +297,14 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
  * each h_t from above; out: the total); gates (n_steps*B, 4H), Cs ((n_steps+1)*B, H), dc_last, dc0 (B, H) F32.
  * All device, row-major, unit inner stride; rows of U on 16-byte, of dZ on 8-byte boundaries.  Same arithmetic
  * as the chain of chn_lstm_step_bwd calls: in mixed precision the cell sees the bf16-rounded total dh and the
- * product reads the bf16-rounded dz; the fp32 sums run in another order (64 gate columns per workgroup on the
- * matrix cores, then the H/16 partial sums in workgroup order).
+ * product reads the bf16-rounded dz; the fp32 sums run in another order (a workgroup's gate columns on the
+ * matrix cores, then the workgroups' partial sums in workgroup order).
  *
- * Resident grid of (H/16) x ceil(B/32) workgroups, each with its columns of U in registers: H % 16 == 0,
- * H <= 768 (F32) / 1536 (BF16), no more workgroups than compute units; otherwise CHN_ERR_SHAPE
- * (chn_lstm_seq_bwd_supported asks beforehand).  ws: chn_lstm_seq_bwd_workspace_bytes(B, H) bytes (the partial
- * sums the workgroups exchange: 2 * ceil(B/32) * (H/16)^2 * 2 KiB), 256-byte aligned.  Waits, the status word
+ * Resident grids as for chn_lstm_seq_fwd; the second kind has (H/16) x ceil(B/32) workgroups, each with its columns
+ * of U in registers: H % 16 == 0, H <= 768 (F32) / 1536 (BF16), no more of those than compute units; otherwise
+ * CHN_ERR_SHAPE (chn_lstm_seq_bwd_supported asks beforehand).  ws: chn_lstm_seq_bwd_workspace_bytes(B, H) bytes (the
+ * partial sums the workgroups exchange; 512 + 2 * ceil(B/32) * (H/16)^2 * 2 KiB are enough to run, without the first
+ * kind of grid where that needs more), 256-byte aligned.  Waits, the status word
  * in the first 4 bytes of ws and chn_lstm_seq_spin_limit as for chn_lstm_seq_fwd. */
 chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype);
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden);

@@ -18,10 +18,12 @@
 // does not fit the device next to other work, say) raises the status word and leaves; every other workgroup
 // sees the status word in its next poll and leaves too.  The kernel always ends; the caller checks the status
 // word after synchronising (chn_lstm_seq_status) and falls back to the per-step calls if it is set.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
 #include "common.h"
+#include "lstm_xcd.h"
 
 namespace chn {
 namespace {
@@ -86,10 +88,11 @@ struct SeqArgs {
   float *gates; int64_t g_pitch;
   unsigned *counters;        // one per batch block, zero at launch
   unsigned *status;          // zero at launch; 1 = a bounded wait ran out
+  const unsigned *state;     // launched behind a kernel of lstm_xcd.hip: its verdict.  Only if nobody walked there is there something to do.
 };
 
-__global__ __launch_bounds__(64) void seq_clear_kernel(unsigned *p, int n) {
-  for (int i = threadIdx.x; i < n; i += 64) p[i] = 0u;
+__global__ __launch_bounds__(256) void seq_clear_kernel(unsigned *p, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) p[i] = 0u;
 }
 
 // Agent-scope store of two neighbouring values of a row of h (one 8-byte or 4-byte access).
@@ -114,6 +117,7 @@ __global__ __launch_bounds__(kThreads) void lstm_seq_fwd_kernel(SeqArgs a) {
   __shared__ __attribute__((aligned(1024))) char stage1[kHStageBytes];
   __shared__ __attribute__((aligned(1024))) char stage2_[kHStageBytes];     // allocated only where referenced
   __shared__ __attribute__((aligned(1024))) char stage3_[kHStageBytes];
+  if (a.state && *a.state != xcd::kCalledOff) return;
   char *stage2 = stage0, *stage3 = stage0;
   if constexpr (NS > 2) stage2 = stage2_;
   if constexpr (NS > 3) stage3 = stage3_;
@@ -339,6 +343,7 @@ struct SeqBwdArgs {
   float *dc0; int64_t dc0_pitch;
   float *xbuf;               // [2][batch blocks][receiver][sender][2][32 rows][8 units]
   unsigned *counters, *status;
+  const unsigned *state;
 };
 
 constexpr int kBwdRows = 32, kBwdUnits = 16, kBwdCols = 4 * kBwdUnits;
@@ -353,6 +358,7 @@ __global__ __launch_bounds__(kThreads) void lstm_seq_bwd_kernel(SeqBwdArgs a) {
   constexpr int kSwz = kTileRow / 16 - 1;
   __shared__ __attribute__((aligned(16))) char tile[kBwdRows * kTileRow];
   __shared__ int give_up;
+  if (a.state && *a.state != xcd::kCalledOff) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 31, q = lane >> 5;
   const int64_t j0 = (int64_t)blockIdx.x * kBwdUnits, b0 = (int64_t)blockIdx.y * kBwdRows;
@@ -581,6 +587,21 @@ size_t bwd_exchange_bytes(int64_t B, int64_t H) {
   return (size_t)(2 * nbb * nub * nub) * kBlockFloats * sizeof(float);
 }
 size_t bwd_counter_bytes(int64_t B) { return (size_t)((((B + kBwdRows - 1) / kBwdRows) * sizeof(unsigned) + 255) / 256 * 256); }
+// what the kernels here need by themselves, and with those of lstm_xcd.hip before them
+size_t fwd_workspace(int64_t B) { return 256 + (size_t)((B + 63) / 64) * sizeof(unsigned) + 256; }
+size_t fwd_workspace_xcd(int64_t B) { return xcd::kFwdWords * sizeof(unsigned) + xcd::fwd_messages(B); }
+size_t bwd_workspace(int64_t B, int64_t H) { return 256 + bwd_counter_bytes(B) + bwd_exchange_bytes(B, H); }
+size_t bwd_workspace_xcd(int64_t B, int64_t H) { return std::max(bwd_workspace(B, H), xcd::kBwdWords * sizeof(unsigned) + xcd::bwd_messages(B, H)); }
+
+// Whether a pass goes to the kernels that exchange inside an XCD (lstm_xcd.hip): batches of up to 128 rows (sixteen per XCD),
+// widths of up to 768, a step's rows (`extent` elements at most) within 32-bit offsets, a workspace that holds their messages.
+// They were the faster at every size they take; a caller with the smaller workspace of the kernels here gets these.
+bool exchanges_in_xcd(int64_t B, int64_t H, int64_t extent, size_t have, size_t need) {
+  int dev = 0, cus = 0;
+  if (have < need || extent >= (int64_t(1) << 28)) return false;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
+  return xcd::takes(B, H, cus);
+}
 
 }  // namespace
 }  // namespace chn
@@ -591,7 +612,7 @@ chn_status chn_lstm_seq_supported(int64_t batch, int64_t hidden, int dtype) { re
 
 size_t chn_lstm_seq_workspace_bytes(int64_t batch) {
   if (batch <= 0) return 0;
-  return 256 + (size_t)((batch + 63) / 64) * sizeof(unsigned) + 256;
+  return chn::xcd::sizes_fit(batch, 0) ? chn::fwd_workspace_xcd(batch) : chn::fwd_workspace(batch);
 }
 
 void chn_lstm_seq_spin_limit(int64_t polls) { chn::g_spin_limit.store(polls < 0 ? 0 : polls > (1 << 30) ? (1 << 30) : (int)polls); }
@@ -624,7 +645,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
   // 8-byte (F32) / 4-byte (BF16) stores of two neighbouring units: rows of h on such boundaries
   if ((a.h_pitch * dtype_size(t)) % 8 && t == CHN_F32) return fail(CHN_ERR_STRIDE, "lstm_seq: rows of Hs must start on 8-byte boundaries");
   const int64_t nbb = (a.B + 63) / 64, nub = a.H / 8;
-  CHN_TRY(check_ws(ws, ws_bytes, chn_lstm_seq_workspace_bytes(a.B), "lstm_seq"));
+  CHN_TRY(check_ws(ws, ws_bytes, fwd_workspace(a.B), "lstm_seq"));
   a.n_steps = (int)n_steps; a.nub = (int)nub; a.spin_limit = g_spin_limit.load();
   a.zx = static_cast<const float *>(zx->data);
   a.Ut = Ut->data;
@@ -635,8 +656,25 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
   a.status = static_cast<unsigned *>(ws);
   a.counters = reinterpret_cast<unsigned *>(static_cast<char *>(ws) + 256);
   hipStream_t st = as_stream(stream);
-  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(64), 0, st, a.status, (int)(64 + nbb));
+  const int64_t extent = std::max({a.B * a.h_pitch, a.B * a.c_pitch, a.B * a.zx_pitch, a.B * a.g_pitch, 4 * a.H * a.ut_pitch, a.B * 4 * a.H});
+  const bool in_xcd = exchanges_in_xcd(a.B, a.H, extent, ws_bytes, fwd_workspace_xcd(a.B));
+  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kFwdWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq clear"));
+  if (in_xcd) {
+    xcd::FwdArgs x{};
+    x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_of(a.H);
+    x.spin_limit = a.spin_limit; x.patience = std::min(a.spin_limit, xcd::kPatience);
+    x.zx = a.zx; x.zx_pitch = a.zx_pitch;
+    x.Ut = a.Ut; x.ut_pitch = a.ut_pitch;
+    x.bias = a.bias;
+    x.Hs = a.Hs; x.h_pitch = a.h_pitch;
+    x.Cs = a.Cs; x.c_pitch = a.c_pitch;
+    x.gates = a.gates; x.g_pitch = a.g_pitch;
+    x.status = a.status; x.state = a.status + xcd::kStateWord; x.ids = a.status + xcd::kFirstId;
+    x.xbuf = reinterpret_cast<char *>(a.status + xcd::kFwdWords);
+    CHN_TRY(xcd::launch_fwd(x, t == CHN_BF16, st));
+    a.state = x.state;
+  }
   const dim3 grid((unsigned)nub, (unsigned)nbb);
   const int64_t chunks = (a.H * dtype_size(t) + kRowBytes - 1) / kRowBytes;
 #define CHN_SEQ_FWD(UC, NS)                                                                                            \
@@ -656,7 +694,7 @@ chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype) 
 
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden) {
   if (batch <= 0 || hidden <= 0 || hidden % chn::kBwdUnits) return 0;
-  return 256 + chn::bwd_counter_bytes(batch) + chn::bwd_exchange_bytes(batch, hidden);
+  return chn::xcd::sizes_fit(batch, hidden) ? chn::bwd_workspace_xcd(batch, hidden) : chn::bwd_workspace(batch, hidden);
 }
 
 chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_array *gates, const chn_array *Cs,
@@ -686,8 +724,7 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
   // dz leaves in pairs of neighbouring units (8 bytes F32, 4 bytes BF16)
   if (reinterpret_cast<uintptr_t>(dZ->data) % 8 || (a.dz_pitch * dtype_size(t)) % 8)
     return fail(CHN_ERR_STRIDE, "lstm_seq_bwd: rows of dZ must start on 8-byte boundaries");
-  const size_t need = chn_lstm_seq_bwd_workspace_bytes(a.B, a.H);
-  CHN_TRY(check_ws(ws, ws_bytes, need, "lstm_seq_bwd"));
+  CHN_TRY(check_ws(ws, ws_bytes, bwd_workspace(a.B, a.H), "lstm_seq_bwd"));
   const int64_t nbb = (a.B + kBwdRows - 1) / kBwdRows, nub = a.H / kBwdUnits;
   a.n_steps = (int)n_steps; a.nub = (int)nub; a.spin_limit = g_spin_limit.load();
   a.U = U->data;
@@ -701,8 +738,28 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
   a.counters = reinterpret_cast<unsigned *>(static_cast<char *>(ws) + 256);
   a.xbuf = reinterpret_cast<float *>(static_cast<char *>(ws) + 256 + bwd_counter_bytes(a.B));
   hipStream_t st = as_stream(stream);
-  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(64), 0, st, a.status, (int)(64 + nbb));
+  const int64_t extent = std::max({a.B * a.dh_pitch, a.B * a.c_pitch, a.B * a.dz_pitch, a.B * a.g_pitch, a.H * a.u_pitch, a.B * 4 * a.H});
+  // (pairs of bfloat16 gradients are read in one access there)
+  const bool pairs = t == CHN_F32 || (reinterpret_cast<uintptr_t>(dHs->data) % 4 == 0 && a.dh_pitch % 2 == 0);
+  const bool in_xcd = pairs && exchanges_in_xcd(a.B, a.H, extent, ws_bytes, bwd_workspace_xcd(a.B, a.H));
+  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kBwdWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq_bwd clear"));
+  if (in_xcd) {
+    xcd::BwdArgs x{};
+    x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_of(a.H);
+    x.spin_limit = a.spin_limit; x.patience = std::min(a.spin_limit, xcd::kPatience);
+    x.U = a.U; x.u_pitch = a.u_pitch;
+    x.dHs = a.dHs; x.dh_pitch = a.dh_pitch;
+    x.gates = a.gates; x.g_pitch = a.g_pitch;
+    x.Cs = a.Cs; x.c_pitch = a.c_pitch;
+    x.dc_last = a.dc_last; x.dcl_pitch = a.dcl_pitch;
+    x.dZ = a.dZ; x.dz_pitch = a.dz_pitch;
+    x.dc0 = a.dc0; x.dc0_pitch = a.dc0_pitch;
+    x.status = a.status; x.state = a.status + xcd::kStateWord; x.ids = a.status + xcd::kFirstId; x.flags = a.status + xcd::kFirstFlag;
+    x.xbuf = reinterpret_cast<float *>(a.status + xcd::kBwdWords);
+    CHN_TRY(xcd::launch_bwd(x, t == CHN_BF16, st));
+    a.state = x.state;
+  }
   const dim3 grid((unsigned)nub, (unsigned)nbb);
   if (t == CHN_BF16) hipLaunchKernelGGL((lstm_seq_bwd_kernel<bf16_raw, 12>), grid, dim3(kThreads), 0, st, a);
   else hipLaunchKernelGGL((lstm_seq_bwd_kernel<float, 6>), grid, dim3(kThreads), 0, st, a);

@@ -1,0 +1,65 @@
+// The recurrent layer's whole-sequence kernels whose workgroups exchange inside one XCD's L2 (lstm_xcd.hip), as
+// lstm_seq.hip's entry points see them.
+#pragma once
+#include "common.h"
+
+namespace chn {
+namespace xcd {
+
+constexpr int kXcds = 8;                               // batch groups, one per XCD
+constexpr int kRows = 16;                              // batch rows of a group
+constexpr int kMaxPeers = 32;                          // workgroups of a group: one per compute unit of the XCD
+constexpr int kMaxHidden = 24 * kMaxPeers;
+constexpr int kPatience = 1 << 14;                     // polls (about 0.6 us each) after which a walk that has not begun is called off
+// how the workgroups met: a bit for every group that shares an XCD beside the first, or nobody walks
+constexpr unsigned kOpen = 1u << 30, kCalledOff = 1u << 31;
+
+// The words of a workspace that are zero at launch: the status block of the kernels of lstm_seq.hip, with the state among it, their
+// counters, then what they use for messages and these kernels for the members' ids, the flags (backward: one per sender wave) and
+// messages of their own.
+constexpr int kStateWord = 32, kFirstId = 128, kIdWords = kXcds * kMaxPeers, kFirstFlag = kFirstId + kIdWords, kFlagWords = kXcds * 4 * kMaxPeers;
+constexpr int kFwdWords = kFirstFlag, kBwdWords = kFirstFlag + kFlagWords;
+
+struct FwdArgs {
+  int B, H, n_steps, peers, spin_limit, patience;
+  const float *zx; int64_t zx_pitch;
+  const void *Ut; int64_t ut_pitch;
+  const float *bias;
+  void *Hs; int64_t h_pitch;
+  float *Cs; int64_t c_pitch;
+  float *gates; int64_t g_pitch;
+  unsigned *status, *state, *ids;
+  char *xbuf;
+};
+struct BwdArgs {
+  int B, H, n_steps, peers, spin_limit, patience;
+  const void *U; int64_t u_pitch;
+  void *dHs; int64_t dh_pitch;
+  const float *gates; int64_t g_pitch;
+  const float *Cs; int64_t c_pitch;
+  const float *dc_last; int64_t dcl_pitch;
+  void *dZ; int64_t dz_pitch;
+  float *dc0; int64_t dc0_pitch;
+  unsigned *status, *state, *ids, *flags;
+  float *xbuf;
+};
+
+// units of a workgroup: eight per 256 of the hidden width, so that at most 32 workgroups share a group's units
+inline int units_of(int64_t H) { return H <= 256 ? 8 : H <= 512 ? 16 : 24; }
+inline int peers_of(int64_t H) { return (int)((H + units_of(H) - 1) / units_of(H)); }
+// whether the sizes fit
+inline bool sizes_fit(int64_t B, int64_t H) { return B <= kXcds * kRows && H <= kMaxHidden; }
+inline bool takes(int64_t B, int64_t H, int cus) { return sizes_fit(B, H) && cus >= kXcds * peers_of(H); }
+// bytes of the messages: fp32 exchanges the three parts of h through four blocks (of the widest row: the caller of the forward
+// pass names no width), the backward pass its partial sums through two
+inline size_t fwd_messages(int64_t B) { return (size_t)((B + kRows - 1) / kRows * 4 * (kMaxHidden / 32) * 3 * 1024); }
+inline size_t bwd_messages(int64_t B, int64_t H) {
+  const int64_t g = peers_of(H);
+  return 2 * (size_t)((B + kRows - 1) / kRows * g * g * units_of(H) * kRows) * sizeof(float);
+}
+
+chn_status launch_fwd(const FwdArgs &a, bool bf16, hipStream_t st);
+chn_status launch_bwd(const BwdArgs &a, bool bf16, hipStream_t st);
+
+}  // namespace xcd
+}  // namespace chn

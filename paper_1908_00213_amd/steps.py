@@ -221,11 +221,11 @@ class LSTMTrainer:
         """whole_sequence: the T forward steps are ONE launch (chn_lstm_seq_fwd: the grid stays on the device,
         each workgroup keeps its rows of the recurrent matrix in LDS and the workgroups exchange h through
         device memory between steps).  None = wherever the library takes the shape (fused_step only).
-        Measured on workload 4: 12.9 us instead of 14.3 us per step in fp32, 6.7 instead of 8.0 us in
-        mixed precision.  In fp32 the T backward steps are one launch too (chn_lstm_seq_bwd: 14.4 us per
-        step instead of the 41 us of product, partial-sum kernel and cell kernel); in mixed precision the
-        per-step fused call (11.6 us) is as fast as the resident grid's exchange of partial sums (11.9 us)
-        and stays.  `whole_sequence_bwd` overrides that choice.  The kernels' waits are bounded;
+        Measured on workload 4: 5.1 us instead of 14.3 us per step in fp32, 2.5 instead of 8.0 us in
+        mixed precision.  The T backward steps are one launch too (chn_lstm_seq_bwd: 6.0 us per step in
+        fp32, 4.0 in mixed precision, where the per-step fused call takes 11.6; in mixed precision only
+        where the launch walks inside the XCDs).  `whole_sequence_bwd` overrides that choice.  The kernels'
+        waits are bounded;
         `sequence_complete()` tells whether one ran out (then the step's results and the parameters it
         updated are invalid).
 
@@ -269,7 +269,8 @@ class LSTMTrainer:
         fits = fused_step and B.lstm_seq_bwd_supported(Bn, Hp, adt)
         if whole_sequence_bwd and not fits:
             raise ValueError("LSTMTrainer: the whole-sequence backward kernel does not take batch %d, hidden %d: %s" % (Bn, Hp, B.lib().chn_last_error().decode()))
-        self.whole_sequence_bwd = (fits and not lowp and self.whole_sequence) if whole_sequence_bwd is None else bool(whole_sequence_bwd)
+        fits = fits and self.whole_sequence and (not lowp or B.lstm_seq_bwd_in_xcd(Bn, Hp))
+        self.whole_sequence_bwd = fits if whole_sequence_bwd is None else bool(whole_sequence_bwd)
         self.ws_seq_bwd = torch.zeros(B.lstm_seq_bwd_workspace_bytes(Bn, Hp), dtype=torch.uint8, device="cuda") if self.whole_sequence_bwd else None
         # fp32: the two backward products of the output layer read one operand along its strided
         # dimension, which for fp32 goes through registers instead of straight to LDS; a transposed

@@ -101,7 +101,7 @@ class GpuBackend:
         self.B.lstm_step_bwd(dz_next, U, dh, gates, c_prev, c, dc_next, dz, dc_prev)
 
     # A whole sequence of fused steps over time-major buffers: one launch for all steps where the library's
-    # resident-grid kernels take the shape (forward: both precisions; backward: fp32, in mixed precision the
+    # resident-grid kernels take the shape (backward in mixed precision: where they walk inside the XCDs, else the
     # per-step call is as fast), else one launch per step (the marshalling is done once).  The resident
     # kernels' waits are bounded; whether one ran out shows in a status word that `check_sequences` reads.
     def lstm_steps_fwd(self, zx, Hs, Ut, bias, Cs, gates, n_steps):
@@ -113,9 +113,14 @@ class GpuBackend:
         else:
             self.B.lstm_step_fwd_seq(zx, Hs, Ut, bias, Cs, gates, n_steps)
 
+    def lstm_sequence_bwd(self, Bn, hidden, dtype):
+        """Whether the backward pass over all steps is one launch that pays (tensor or tape dtype)."""
+        dtype = {"f32": self.torch.float32, "bf16": self.torch.bfloat16}.get(dtype, dtype)
+        return (dtype == self.torch.float32 or self.B.lstm_seq_bwd_in_xcd(Bn, hidden)) and self.B.lstm_seq_bwd_supported(Bn, hidden, dtype)
+
     def lstm_steps_bwd(self, dZ, U, dHs, gates, Cs, dc_last, dc, n_steps):
         Bn = dZ.shape[0] // max(1, n_steps)
-        if n_steps > 0 and dHs.dtype == self.torch.float32 and self.B.lstm_seq_bwd_supported(Bn, dHs.shape[1], dHs.dtype):
+        if n_steps > 0 and self.lstm_sequence_bwd(Bn, dHs.shape[1], dHs.dtype):
             ws = self._bytes(self.B.lstm_seq_bwd_workspace_bytes(Bn, dHs.shape[1]))
             self.B.lstm_seq_bwd(U, dHs, gates, Cs, dc_last, dZ, dc[0], n_steps, ws)
             self._pending(ws)
@@ -1390,7 +1395,9 @@ class NStepLSTM(FunctionNode):
         dc = [F.empty((Bn, H), "f32"), F.empty((Bn, H), "f32")]
         dh0 = F.empty((Bn, H), adt)
         dc_next = gc
-        fused_bwd = self.lowp and self.fused       # (in fp32 the three separate calls are the faster ones)
+        # in fp32 three separate calls per step are faster than the fused one, the whole sequence in one launch is faster than both
+        whole = getattr(F, "lstm_sequence_bwd", None)
+        fused_bwd = self.fused and (self.lowp or (T > 0 and whole is not None and whole(Bn, H, adt)))
         if fused_bwd:                              # per step: dh_t += dz_{t+1} U^T, then the cell
             F.lstm_steps_bwd(dZ, U, dHs, G, Cs, gc, dc, T)
         else:

@@ -247,3 +247,68 @@ def test_whole_sequence_kernels_are_reproducible_bit_for_bit(dt):
     for _ in range(2):
         again = run_bwd(Ub, dh_in, gates, Cs, dc_last, T, dt)[:3]
         assert all(torch.equal(a, b) for a, b in zip(first, again))
+
+
+# ------------------------------------------------------------- the kernels that exchange inside an XCD: where their tiles end
+# batches around sixteen rows and 128, widths around 8, 16 and 24 units a workgroup and 32 k, one to five steps (marks run three ahead)
+EDGES = [(1, 16, 1), (15, 24, 2), (16, 32, 3), (17, 40, 4), (33, 248, 5), (127, 256, 2), (128, 264, 3), (16, 504, 4), (64, 512, 2),
+         (31, 520, 5), (128, 528, 2), (48, 744, 3), (113, 760, 2), (128, 768, 5)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Bn,H,T", EDGES)
+def test_sequence_edges(Bn, H, T, dt):
+    if H % (8 if dt == "f32" else 16) == 0:
+        zx, bias, h0, c0, U = inputs(Bn, H, T, dt, 41)
+        Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, dt)
+        assert status_word(work) == 0
+        check_against_oracle(zx, bias, U, T, dt, Hs, Cs, gates)
+        # a workspace that holds no messages: the kernels that exchange through device memory, the same results but for the order of sums
+        small = ws(256 + 256 + 256)
+        H2, C2, G2, small = run(zx, bias, h0, c0, U, T, dt, work=small)
+        assert status_word(small) == 0
+        check_against_oracle(zx, bias, U, T, dt, H2, C2, G2)
+    if H % 16 == 0:
+        U, dh_in, gates, Cs, dc_last = bwd_inputs(Bn, H, T, dt, 42)
+        dHs, dZ, dc0, work = run_bwd(U, dh_in, gates, Cs, dc_last, T, dt)
+        assert status_word(work) == 0
+        check_bwd_against_oracle(U, dh_in, gates, Cs, dc_last, T, dt, dHs, dZ, dc0)
+
+
+def test_sequence_values_that_three_parts_do_not_hold():
+    """fp32: infinities, NaN and values whose scaled parts overflow are multiplied again as they are."""
+    Bn, H, T = 40, 272, 3
+    zx, bias, h0, c0, U = inputs(Bn, H, T, "f32", 43)
+    h0 = np.abs(h0) + 0.25
+    U[5, 7] = np.inf                       # gate i of unit 7: 1 in every row whose h is positive
+    U[11, H + 30] = -np.inf                # gate f of unit 30: 0
+    h0[3] *= np.float32(2.0 ** -112)       # against 2^110: a product of about one, each factor scaled out of range or far from its row
+    h0[3, 5] = h0[3, 11] = 1.0
+    U[:, 3 * H + 100] *= np.float32(2.0 ** 110)
+    h0[20, 9] = np.nan                     # this row and no other
+    Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, "f32")
+    assert status_word(work) == 0
+    with np.errstate(all="ignore"):
+        z = zx[:Bn].astype(np.float64) + bias + h0.astype(np.float64) @ U.astype(np.float64)
+        want = 1.0 / (1.0 + np.exp(-z))
+        want[:, 2 * H:3 * H] = np.tanh(z[:, 2 * H:3 * H])
+        S = np.abs(zx[:Bn]) + np.abs(bias) + np.abs(h0).astype(np.float64) @ np.abs(U).astype(np.float64)
+    got = host(gates)[:Bn]
+    assert np.isnan(got[20]).all() and not np.isnan(np.delete(got, 20, 0)).any()
+    rows = [b for b in range(Bn) if b != 20]
+    assert (got[rows, 7] == 1.0).all() and (got[rows, H + 30] == 0.0).all()
+    cols = [j for j in range(4 * H) if j not in (7, H + 30, 3 * H + 100)]
+    check(got[np.ix_(rows, cols)], want[np.ix_(rows, cols)], TOL_SUM, S[np.ix_(rows, cols)] + 1e-1, "gates")
+    check(got[3, 3 * H + 100], want[3, 3 * H + 100], TOL_SUM, 1.0, "a product of 2^110 and 2^-112")
+    # backward: dz scaled out of range against a small U
+    U, dh_in, gates, Cs, _ = bwd_inputs(Bn, H, T, "f32", 44)
+    U *= np.float32(2.0 ** -100)
+    dh_in *= np.float32(2.0 ** 106)
+    dHs, dZ, dc0, work = run_bwd(U, dh_in, gates, Cs, None, T, "f32")
+    assert status_word(work) == 0 and torch.isfinite(dHs).all()
+    dz = host(dZ)
+    for t in range(T - 1):
+        nx = slice((t + 1) * Bn, (t + 2) * Bn)
+        back = host(dHs)[t * Bn:(t + 1) * Bn] - dh_in[t * Bn:(t + 1) * Bn].astype(np.float64)
+        S = np.abs(dz[nx]) @ np.abs(U.T).astype(np.float64) + np.abs(dh_in[t * Bn:(t + 1) * Bn])
+        check(back, dz[nx] @ U.T.astype(np.float64), TOL_SUM, S, "dh of step %d" % t)
