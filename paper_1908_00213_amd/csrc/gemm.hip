@@ -63,8 +63,9 @@ chn_status classify(const chn_array *A, const chn_array *B, GemmArgs *g, bool *a
   const int qa = piece_bytes(A->data, g->lda, *a_kc ? K : M, isz, !*a_kc);
   const int qb = piece_bytes(B->data, g->ldb, *b_kc ? K : N, isz, !*b_kc);
   g->piece = qa < qb ? qa : qb;
-  g->piece_a = qa; g->piece_b = qb;
-  if (K == 0) { *a_kc = *b_kc = true; g->piece = g->piece_exact = g->piece_a = g->piece_b = isz; }  // nothing to multiply: every load is redirected to zeros
+  g->any_a = (*a_kc ? K : M) * isz >= 16;
+  g->any_b = (*b_kc ? K : N) * isz >= 16;
+  if (K == 0) { *a_kc = *b_kc = true; g->piece = g->piece_exact = isz; g->any_a = g->any_b = 0; }  // nothing to multiply: every load is redirected to zeros
   g->M = (int)M; g->N = (int)N; g->K = (int)K;
   return CHN_OK;
 }
@@ -94,16 +95,20 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   const double step_direct = 1.48;                        // bf16 direct-copy kernel, any layout
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   const bool direct = direct_copy_fits(*g, isz, a_kc, b_kc);
-  const bool wide = g->piece >= 8;   // operands that need element-wise loads only get the small tile
-  const double narrow = g->piece >= 16 ? 1.0 : g->piece >= 8 ? 1.15 : 2.0;   // more, smaller loads per step
+  // Operands whose rows start off 8-byte boundaries do not get the 256x256 tile, those with an extent below one piece only the
+  // small one; a step takes longer where pieces straddle cache lines, and longer still element by element.
+  const bool any = g->any_a && g->any_b;
+  const int largest = g->piece >= 8 ? 2 : any ? 1 : 0;
+  // (bf16 in one 64x64 tile per compute unit: 1024x1000x784 9.1, 1024x1001x785 11.3; 7292x423x487 18.4 on that tile, 27.4 on 128x128)
+  auto narrow = [&](int tile) { return g->piece >= 16 ? 1.0 : tile == 2 || (any && isz == 4) ? 1.15 : any ? (tile == 1 ? 2.0 : 1.5) : 2.0; };
   const int nk = (g->K + 128 / isz - 1) / (128 / isz);   // tile steps along K
   static const int split_choices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
   double best = 1e300;
   g->tile = 0; g->splits = 1;
-  for (int tile = wide ? 2 : 0; tile >= 0; --tile) {
+  for (int tile = largest; tile >= 0; --tile) {
     const int b = 64 << tile;
     const int64_t tiles = (int64_t)((g->M + b - 1) / b) * ((g->N + b - 1) / b);
-    double per_step = (isz == 2 ? step_bf16 : step_f32)[tile][lay] * narrow;
+    double per_step = (isz == 2 ? step_bf16 : step_f32)[tile][lay] * narrow(tile);
     if (tile == 2 && direct && isz == 2) per_step = step_direct;
     const double fixed = (isz == 2 ? fixed_bf16 : fixed_f32)[tile];
     for (int s : split_choices) {
@@ -138,9 +143,9 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   }
   {   // chn_gemm_plan_override
     const int force_tile = g_force_tile.load(std::memory_order_relaxed), force_splits = g_force_splits.load(std::memory_order_relaxed);
-    if (force_tile >= 0 && force_tile <= (wide ? 2 : 0)) g->tile = force_tile;
+    if (force_tile >= 0 && force_tile <= largest) g->tile = force_tile;
     if (force_tile == 3 && narrow_ok) g->tile = 3;
-    if (force_tile >= 0 && force_tile != 3 && g->tile == 3) g->tile = wide ? 2 : 0;
+    if (force_tile >= 0 && force_tile != 3 && g->tile == 3) g->tile = largest;
     if (force_splits >= 1 && allow_split && force_splits <= nk) g->splits = force_splits;
   }
   if (big_unsplit) { g->tile = 2; g->splits = 1; }        // (the caller has checked that the operands allow the big tile)
@@ -157,10 +162,12 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
 // in four, against the best plan on the fp32 matrix instruction, by the same kind of model (microseconds, a launch not
 // counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 plus its tile
 // steps (32 k on the large tile, 64 on the small one); a step takes longer when all 256 compute units pull operands out of
-// the L2s than when a quarter of them does, and with operands that allow 8- or 4-byte pieces only.  Each compute
+// the L2s than when a quarter of them does, and element by element (an extent below four).  Each compute
 // unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 22 on the
 // small tile, 4480x2688x672 143 -> 101 and 4480x10000x672 499 -> 361 on the large one, 672x2688x4480 both stored along
 // M/N 178 -> 115 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
+// Rows off the 16-byte grid cost little (4480x650x2600, both along K 131 -> 108, mixed 145 -> 118 against 8-byte pieces; 4097x2351x2041
+// 556 -> 273 against single elements, 8192x4001x651 584 -> 295).
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
   double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
@@ -181,9 +188,9 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   }
   static const double step_large[3] = {1.0, 1.25, 1.2}, step_small[3] = {0.78, 1.1, 0.95};   // both along K, one, none
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
-  auto narrow = [](int piece, bool kc, bool large) {
-    if (piece == 16) return 1.0;
-    if (piece == 8) return large ? (kc ? 1.05 : 1.35) : 1.1;
+  auto narrow = [&](bool any, bool kc, bool large) {
+    if (g->piece == 16) return 1.0;
+    if (any) return large ? 1.05 : 1.1;
     return large ? (kc ? 3.2 : 1.9) : (kc ? 3.7 : 3.0);
   };
   // (A finishing launch is charged 5 us here, on both sides.  Cut along K, the fp32 instruction's element-wise loads
@@ -200,7 +207,7 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
     const int b = large ? 128 : 64, bk = large ? 32 : 64;
     const int64_t tiles = (int64_t)((g->M + b - 1) / b) * ((g->N + b - 1) / b);
     const int nk = (g->K + bk - 1) / bk;
-    const double na = narrow(g->piece_a, a_kc, large), nb = narrow(g->piece_b, b_kc, large);
+    const double na = narrow(g->any_a, a_kc, large), nb = narrow(g->any_b, b_kc, large);
     const double step = (large ? step_large : step_small)[lay] * (na > nb ? na : nb);
     for (int s : split_choices) {
       if (s > 1 && (!allow_split || s > nk / 4)) break;
@@ -366,15 +373,11 @@ chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, 
   if (M == 0 || N == 0) return CHN_OK;
   g.A = A->data; g.B = B->data; g.C = C->data;
   g.alpha = alpha; g.beta = beta; g.epi = epilogue; g.c_bf16 = C->dtype == CHN_BF16;
-  {
-    const int vb = 4 * csz;  // bytes of a 4-element vector of C's dtype
-    auto ok = [&](const void *q, int64_t ld) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) % vb == 0 && ld % 4 == 0); };
-    g.epi_vec = ok(g.C, g.ldc) && ok(g.aux, g.ldaux) && ok(g.pre, g.ldpre) &&
-                (g.bias == nullptr || reinterpret_cast<uintptr_t>(g.bias) % 16 == 0);
-  }
   if (want_colsum) {
     // the sums are taken per wave tile of the 256x256 kernels, unsplit, on the vector path of the epilogue
-    if (!g.epi_vec || g.piece < 8) return fail(CHN_ERR_STRIDE, "gemm: row-block column sums need operands with 8-byte pieces and 16-byte aligned C and aux rows");
+    const int vb = 4 * csz;  // bytes of a 4-element vector of C's dtype
+    auto ok = [&](const void *q, int64_t ld) { return reinterpret_cast<uintptr_t>(q) % vb == 0 && ld % 4 == 0; };
+    if (!ok(g.C, g.ldc) || !ok(g.aux, g.ldaux) || g.piece < 8) return fail(CHN_ERR_STRIDE, "gemm: row-block column sums need operands with 8-byte pieces and 16-byte aligned C and aux rows");
     plan(&g, isz, a_kc, b_kc, false, true);
   } else {
     plan(&g, isz, a_kc, b_kc, true);

@@ -20,14 +20,13 @@ struct GemmArgs {
   void *pre;
   int64_t ldpre;
   int piece;              // bytes per global load piece (16, 8 or the item size), common to A and B
-  int piece_a, piece_b;   // what A and B would allow each (the 64x64 tile takes them apart when one is element-wise and the other whole)
+  int any_a, any_b;       // whether the unit-stride extent of A, of B holds a 16-byte piece (which the smaller tiles read at any address)
   int piece_exact;        // the same when no piece may hang over the end of a row (direct-copy kernels)
   int tiles_m, tiles_n;
   int tile;               // macro tile: 2 = 256x256, 1 = 128x128, 0 = 64x64
   int splits;             // number of K splits (1 = none)
   float *partial;         // split-K: [splits][M][ldp] fp32 partial sums in the caller's workspace
   int64_t ldp;
-  int epi_vec;            // C, aux, preact and bias allow aligned 4-element vector accesses
   int dma;                // big tile: K-contiguous operands go to LDS by direct global-to-LDS loads
   int w8;                 // ... by the kernel that works with eight waves (bf16)
   float *colsum;          // activation-gradient epilogues, 256x256 tile only: [M / 128][N] column sums of C over

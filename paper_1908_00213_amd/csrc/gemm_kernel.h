@@ -78,6 +78,11 @@ template <typename V>
 __device__ __forceinline__ void global_store(uintptr_t addr, V v) {
   *reinterpret_cast<__attribute__((address_space(1))) V *>(addr) = v;
 }
+// Four elements of C, of the arrays beside it or of the bias, at any element address.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 bf16x4_any __attribute__((aligned(2)));
+__device__ __forceinline__ f32x4 load4f(const float *p) { return *reinterpret_cast<const __attribute__((address_space(1))) f32x4_any *>(reinterpret_cast<uintptr_t>(p)); }
+__device__ __forceinline__ u32x2 load4h(const bf16_raw *p) { return *reinterpret_cast<const __attribute__((address_space(1))) bf16x4_any *>(reinterpret_cast<uintptr_t>(p)); }
 
 // Load one 16-byte chunk starting at address p in pieces of PB bytes without any branch: a piece
 // whose first element index is >= n_valid is read from the zero chunk instead.  Along K a piece never
@@ -109,6 +114,27 @@ __device__ __forceinline__ uint4 load_chunk(uintptr_t p, int n_valid) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// The piece size that stands for 16 bytes at any element address: global memory takes a 16-byte access wherever it starts, so
+// an operand whose rows start off 16-byte boundaries is read in the pieces of an aligned one.  The piece that the end of a
+// row cuts (along K in the last tile step, along M/N in the last tile) is read so that it ends with the row, and its elements
+// move down to their places when it is stored; the operand's extent holds a piece at least (the host checks).  Element by
+// element, as such operands used to be read, a tile step waits for 8 (fp32: 4) times as many loads.  bf16, both along K, us, element-wise -> here:
+// 1024x1001x785 35.7 -> 14.5, 4097x2351x2041 464 -> 116, 8192x4001x651 521 -> 152.
+constexpr int kAnyPiece = 1;
+__device__ __forceinline__ uint4 load_any(uintptr_t addr) {
+  const chn_u32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) chn_u32x4_any *>(addr);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+// `bytes` (0 .. 15) lower in memory order; zeros move in at the top
+__device__ __forceinline__ uint4 move_down(const uint4 &v, int bytes) {
+  uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+  if (bytes & 8) { lo = hi; hi = 0; }
+  const int b = (bytes & 7) * 8;
+  lo = lo >> b | hi << 1 << (63 - b);
+  hi >>= b;
+  return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
 // One operand tile: ROWS rows (m or n) x 128 bytes of k, staged in registers between global memory
 // and LDS.  Everything that does not change from tile step to tile step (slot addresses, row
 // validity) is computed once in init().
@@ -128,6 +154,10 @@ struct TileLoader {
   static constexpr int CP = COOP ? 256 / NBLK : 1;
   static constexpr int NSLOT = KC ? NS : NB;
   uint4 reg[2][KC ? NS : COOP ? 2 : NB * EPC];   // two sets of staging registers (the second only where a kernel looks two tiles ahead)
+  static constexpr bool ANY = PB == kAnyPiece;
+  static constexpr int BK = 128 / (int)sizeof(T);
+  int down[ANY && !KC ? NSLOT : 1];   // ANY, MC: bytes by which the slot's pieces were read early
+  bool cut;                           // ANY, MC: whether the tile reaches past the last row (uniform)
   uintptr_t ptr[NSLOT];   // address of the slot's first element for k0 = 0
   int lim[NSLOT];         // KC: K - (k offset of the slot) for valid rows, else 0;  MC: rows_total - m or 0
   int64_t kstride;        // bytes between consecutive k (MC only)
@@ -158,8 +188,9 @@ struct TileLoader {
       for (int i = 0; i < NS; ++i) {
         const int s = threadIdx.x + i * 256;
         const int row = row0 + (s >> 3), kc = (s & 7) * EPC;
-        ptr[i] = reinterpret_cast<uintptr_t>(base + (int64_t)row * ld + kc);
-        lim[i] = row < rows_total ? K - kc : 0;
+        // (ANY: rows past the end repeat the last one, so that whole tile steps load without conditions)
+        ptr[i] = reinterpret_cast<uintptr_t>(base + (int64_t)(ANY ? min(row, rows_total - 1) : row) * ld + kc);
+        lim[i] = ANY || row < rows_total ? K - kc : 0;
       }
     } else if constexpr (COOP) {
       const int m = row0 + coop_mc() * EPC;
@@ -175,6 +206,36 @@ struct TileLoader {
         lim[b] = blk < NBLK ? rows_total - m : 0;
       }
     }
+    if constexpr (ANY && !KC) {
+      cut = row0 + ROWS > rows_total;
+#pragma unroll
+      for (int i = 0; i < NSLOT; ++i) {
+        down[i] = lim[i] > 0 && lim[i] < EPC ? (EPC - lim[i]) * (int)sizeof(T) : 0;
+        ptr[i] -= down[i];
+      }
+    }
+  }
+  // a piece of slot i, the tile's first k being k0, at address p; n: how many of its elements exist
+  __device__ __forceinline__ uint4 load_piece(uintptr_t p, int n, bool whole) const {
+    if constexpr (ANY) {
+      if (whole) return load_any(p);
+      const uintptr_t zero = reinterpret_cast<uintptr_t>(&kZeroChunk);
+      if constexpr (KC) return load_any(n <= 0 ? zero : p - (n < EPC ? (EPC - n) * (int)sizeof(T) : 0));
+      else return load_any(n <= 0 ? zero : p);
+    } else {
+      return load_chunk<T, PB>(p, n);
+    }
+  }
+  // The slot's pieces as they go to LDS (k0: the tile's first k).
+  __device__ __forceinline__ uint4 placed(const uint4 &v, int i, int k0) const {
+    if constexpr (ANY && KC) {
+      const int n = lim[i] - k0;
+      return k0 + BK > K && n > 0 && n < EPC ? move_down(v, (EPC - n) * (int)sizeof(T)) : v;
+    } else if constexpr (ANY) {
+      return cut ? move_down(v, down[i]) : v;
+    } else {
+      return v;
+    }
   }
   // COOP: which quarter (two k-rows) of which block (k-group, m-chunk) the thread handles
   __device__ __forceinline__ int coop_part() const { return threadIdx.x % CP; }
@@ -187,12 +248,12 @@ struct TileLoader {
     if constexpr (KC) {
 #pragma unroll
       for (int i = 0; i < NS; ++i)
-        reg[SET][i] = load_chunk<T, PB>(ptr[i] + (int64_t)k0 * (int64_t)sizeof(T), lim[i] - k0);
+        reg[SET][i] = load_piece(ptr[i] + (int64_t)k0 * (int64_t)sizeof(T), lim[i] - k0, k0 + BK <= K);
     } else if constexpr (COOP) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int k = k0 + coop_kg() * EPC + 2 * coop_part() + j;
-        reg[SET][j] = load_chunk<T, PB>(ptr[0] + (int64_t)(k0 + j) * kstride, k < K ? lim[0] : 0);
+        reg[SET][j] = load_piece(ptr[0] + (int64_t)(k0 + j) * kstride, k < K ? lim[0] : 0, false);
       }
     } else {
 #pragma unroll
@@ -201,7 +262,7 @@ struct TileLoader {
 #pragma unroll
         for (int j = 0; j < EPC; ++j) {
           const int k = k0 + kg * EPC + j;
-          reg[SET][b * EPC + j] = load_chunk<T, PB>(ptr[b] + (int64_t)(k0 + j) * kstride, k < K ? lim[b] : 0);
+          reg[SET][b * EPC + j] = load_piece(ptr[b] + (int64_t)(k0 + j) * kstride, k < K ? lim[b] : 0, false);
         }
       }
     }
@@ -215,25 +276,27 @@ struct TileLoader {
     return global_load<uint32_t>(k0 < pf_lim ? a : zero);
   }
 
+  // move the loaded tile, whose first k is k0, to its part of a stage
   template <int SET = 0>
-  __device__ __forceinline__ void store(char *lds) const {
+  __device__ __forceinline__ void store(char *lds, int k0) const {
     if constexpr (KC) {
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
         const int s = threadIdx.x + i * 256;
-        *reinterpret_cast<uint4 *>(lds + lds_off<T>(s >> 3, s & 7)) = reg[SET][i];
+        *reinterpret_cast<uint4 *>(lds + lds_off<T>(s >> 3, s & 7)) = placed(reg[SET][i], i, k0);
       }
     } else if constexpr (COOP) {
       const int kg = coop_kg(), row0l = coop_mc() * EPC, part = coop_part();
+      const uint4 r0 = placed(reg[SET][0], 0, k0), r1 = placed(reg[SET][1], 0, k0);
 #pragma unroll
       for (int e = 0; e < EPC; ++e) {
         // k = 2 part and 2 part + 1 of row m = e of the block
         char *q = lds + lds_off<T>(row0l + e, kg);
         if constexpr (sizeof(T) == 2) {
-          const uint32_t lo = (&reg[SET][0].x)[e >> 1], hi = (&reg[SET][1].x)[e >> 1];
+          const uint32_t lo = (&r0.x)[e >> 1], hi = (&r1.x)[e >> 1];
           *reinterpret_cast<uint32_t *>(q + part * 4) = __builtin_amdgcn_perm(hi, lo, (e & 1) ? 0x07060302u : 0x05040100u);
         } else {
-          *reinterpret_cast<uint2 *>(q + part * 8) = make_uint2((&reg[SET][0].x)[e], (&reg[SET][1].x)[e]);
+          *reinterpret_cast<uint2 *>(q + part * 8) = make_uint2((&r0.x)[e], (&r1.x)[e]);
         }
       }
     } else {
@@ -244,7 +307,9 @@ struct TileLoader {
           if (blk >= NBLK) continue;       // big tile's loop would split its scheduling region
         }
         const int kg = blk & 7, mc = blk >> 3;
-        const uint4 *r = &reg[SET][b * EPC];
+        uint4 r[EPC];
+#pragma unroll
+        for (int j = 0; j < EPC; ++j) r[j] = placed(reg[SET][b * EPC + j], b, k0);
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
           uint4 o;
@@ -318,21 +383,20 @@ __device__ __forceinline__ void sched_reads_mfma() {
 }
 
 // ---- epilogue helpers ------------------------------------------------------------------------------
-// Two paths.  The fast one handles whole 4-column groups with aligned vector accesses only (the host
-// sets epi_vec when every pointer and leading dimension allows it) and keeps its code small because
-// it is replicated for every row segment a lane owns; a pass that crosses the last row or column of
-// aligned operands runs a rolled loop over the 4-column groups that lie in range, and unaligned views
-// go through a rolled element-by-element loop.
+// Two paths.  The fast one handles whole 4-column groups in vector accesses, at whatever element address C and the arrays
+// beside it have (element by element, as rows off the 16-byte grid used to be finished, 8192x4001x651 in bf16 takes 152 us,
+// so 97) and keeps its code small because it is replicated for every row segment a lane owns; a pass that crosses the
+// last row or column runs a rolled loop over the 4-column groups that lie in range.
 struct Vec4 { float v[4]; };
 
 __device__ __forceinline__ Vec4 load4v(const void *p, int64_t idx, int is_bf16) {
   Vec4 r;
   if (is_bf16) {
-    const u32x2 w = global_load<u32x2>(reinterpret_cast<uintptr_t>(static_cast<const bf16_raw *>(p) + idx));
+    const u32x2 w = load4h(static_cast<const bf16_raw *>(p) + idx);
     r.v[0] = __uint_as_float(w[0] << 16); r.v[1] = __uint_as_float(w[0] & 0xffff0000u);
     r.v[2] = __uint_as_float(w[1] << 16); r.v[3] = __uint_as_float(w[1] & 0xffff0000u);
   } else {
-    const f32x4 w = global_load<f32x4>(reinterpret_cast<uintptr_t>(static_cast<const float *>(p) + idx));
+    const f32x4 w = load4f(static_cast<const float *>(p) + idx);
     r.v[0] = w[0]; r.v[1] = w[1]; r.v[2] = w[2]; r.v[3] = w[3];
   }
   return r;
@@ -343,10 +407,10 @@ __device__ __forceinline__ void store4v(void *p, int64_t idx, int is_bf16, const
     u32x2 w;
     w[0] = (uint32_t)f32_to_bf16(x.v[0]) | ((uint32_t)f32_to_bf16(x.v[1]) << 16);
     w[1] = (uint32_t)f32_to_bf16(x.v[2]) | ((uint32_t)f32_to_bf16(x.v[3]) << 16);
-    global_store<u32x2>(reinterpret_cast<uintptr_t>(static_cast<bf16_raw *>(p) + idx), w);
+    *reinterpret_cast<__attribute__((address_space(1))) bf16x4_any *>(reinterpret_cast<uintptr_t>(static_cast<bf16_raw *>(p) + idx)) = w;
   } else {
     f32x4 w = {x.v[0], x.v[1], x.v[2], x.v[3]};
-    global_store<f32x4>(reinterpret_cast<uintptr_t>(static_cast<float *>(p) + idx), w);
+    *reinterpret_cast<__attribute__((address_space(1))) f32x4_any *>(reinterpret_cast<uintptr_t>(static_cast<float *>(p) + idx)) = w;
   }
 }
 
@@ -399,7 +463,7 @@ __device__ __forceinline__ void finish4(const GemmArgs &g, int row, int col, con
   store4v(g.C, (int64_t)row * g.ldc + col, g.c_bf16, x);
 }
 
-// One element, any alignment (slow path).
+// One element (the last, partial group of a row).
 __device__ __forceinline__ void finish1(const GemmArgs &g, int row, int col, float acc) {
   const int64_t ci = (int64_t)row * g.ldc + col;
   const float c0 = g.beta != 0.0f ? load1(g.C, ci, g.c_bf16) : 0.0f;
@@ -418,8 +482,8 @@ template <bool CB> struct Raw4 { typedef f32x4 type; };
 template <> struct Raw4<true> { typedef u32x2 type; };
 template <bool CB>
 __device__ __forceinline__ typename Raw4<CB>::type load4raw(const void *p, int64_t idx) {
-  if constexpr (CB) return global_load<u32x2>(reinterpret_cast<uintptr_t>(static_cast<const bf16_raw *>(p) + idx));
-  else return global_load<f32x4>(reinterpret_cast<uintptr_t>(static_cast<const float *>(p) + idx));
+  if constexpr (CB) return load4h(static_cast<const bf16_raw *>(p) + idx);
+  else return load4f(static_cast<const float *>(p) + idx);
 }
 __device__ __forceinline__ Vec4 cvt4(const u32x2 w) {
   Vec4 r;
@@ -559,7 +623,7 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *st
         global_store<f32x4>(reinterpret_cast<uintptr_t>(slab + (int64_t)(row0 + rl) * g.ldp + col0 + cl),
                             *reinterpret_cast<const f32x4 *>(stage + L::at(rl, cl)));
     }
-  } else if (g.epi_vec && col0 + W <= g.N && row0 + RP <= g.M) {
+  } else if (col0 + W <= g.N && row0 + RP <= g.M) {
     auto run = [&](auto epi_c) __attribute__((always_inline)) {
       constexpr int EPI = decltype(epi_c)::value;
       constexpr bool kF32Only = EPI == CHN_EPI_BF16_COPY;   // (the host refuses a bf16 C for it)
@@ -587,7 +651,7 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *st
       case CHN_EPI_GELU_BWD: run(std::integral_constant<int, CHN_EPI_GELU_BWD>{}); break;
       default: run(std::integral_constant<int, CHN_EPI_BF16_COPY>{}); break;
     }
-  } else if (g.epi_vec) {                                     // edge tile of aligned operands: whole 4-column groups that lie in range
+  } else {                                                    // edge tile: whole 4-column groups that lie in range
     // (the lanes are dealt out over the groups that exist, so the number of dependent iterations
     // follows the part of the pass that is in range)
     const int nr = max(0, min(RP, g.M - row0)), ncg = max(0, min(CPR, (g.N - col0 + 3) >> 2));   // (a pass may lie wholly outside)
@@ -599,12 +663,6 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *st
       } else {
         for (int e = 0; col + e < g.N; ++e) finish1(g, row, col + e, stage[L::at(rl, cl + e)]);
       }
-    }
-  } else {                                                    // unaligned views: one element at a time
-#pragma unroll 1
-    for (int c = lane; c < RP * W; c += 64) {
-      const int rl = c / W, cl = c % W;
-      if (row0 + rl < g.M && col0 + cl < g.N) finish1(g, row0 + rl, col0 + cl, stage[L::at(rl, cl)]);
     }
   }
 }
@@ -629,7 +687,7 @@ static __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmArgs
 #pragma unroll
     for (int u = 0; u < 8; ++u) a += v[u];
   }
-  if (g.epi_vec && col + 4 <= g.N) {
+  if (col + 4 <= g.N) {
     finish4(g, row, col, a, epi_fetch(g, row, col));
   } else {
     for (int e = 0; e < 4 && col + e < g.N; ++e) finish1(g, row, col + e, a[e]);
@@ -760,8 +818,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   const int nk = min(nk_all, kt0 + per_split);
   la.issue(kt0 * BK);
   lb.issue(kt0 * BK);
-  la.store(lds);
-  lb.store(lds + A_BYTES);
+  la.store(lds, kt0 * BK);
+  lb.store(lds + A_BYTES, kt0 * BK);
   __syncthreads();
   Frags<TM, TN> f0, f1;
   f0.read(lds + a_row, lds + b_row, koff[0]);
@@ -793,8 +851,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
       f0.read(cur + a_row, cur + b_row, koff[2]);
       mma<T, TM, TN>(acc, f1);
       f1.read(cur + a_row, cur + b_row, koff[3]);
-      la.template store<SET>(nxt);                    // tile kt + 1, on its way since the step before
-      lb.template store<SET>(nxt + A_BYTES);
+      la.template store<SET>(nxt, (kt + 1) * BK);     // tile kt + 1, on its way since the step before
+      lb.template store<SET>(nxt + A_BYTES, (kt + 1) * BK);
       la.template issue<SET>((kt + 3) * BK);          // (past the end of K: zeros, never used)
       lb.template issue<SET>((kt + 3) * BK);
       mma<T, TM, TN>(acc, f0);
@@ -841,8 +899,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     // every LDS read ahead of every LDS write (it cannot tell the two stages apart), so the reads
     // pair with the first half of the MFMAs and the writes with the second half.
     f1.read(cur + a_row, cur + b_row, koff[3]);
-    if constexpr (A_KC) la.store(nxt);
-    if constexpr (B_KC) lb.store(nxt + A_BYTES);
+    if constexpr (A_KC) la.store(nxt, (kt + 1) * BK);
+    if constexpr (B_KC) lb.store(nxt + A_BYTES, (kt + 1) * BK);
     mma<T, TM, TN>(acc, f0);
     if constexpr (kSched) {
       constexpr int NW = (A_KC ? TM * 2 : 0) + (B_KC ? TN * 2 : 0);   // 16-byte LDS writes interleaved
@@ -856,8 +914,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
     }
     // A transposed operand's first LDS write needs all of its loads (an 8x8 block is transposed in
     // registers), so its wait would stall the MFMAs queued behind it: those writes go last.
-    if constexpr (!A_KC) la.store(nxt);
-    if constexpr (!B_KC) lb.store(nxt + A_BYTES);
+    if constexpr (!A_KC) la.store(nxt, (kt + 1) * BK);
+    if constexpr (!B_KC) lb.store(nxt + A_BYTES, (kt + 1) * BK);
     __syncthreads();
     // k-step 3, overlapped with the first fragment reads of the next stage
     f0.read(nxt + a_row, nxt + b_row, koff[0]);
@@ -1088,11 +1146,11 @@ __global__ __launch_bounds__(256) void gemm_kernel_dma(GemmArgs g) {
 
   // prologue: first tile into stage 0, second tile on its way into stage 1
   if constexpr (A_DMA) { la.issue(k_of(kt0), stage0); la.issue(k_of(kt0 + 1), stage1); }
-  else { la.issue(k_of(kt0)); la.store(stage0); }
+  else { la.issue(k_of(kt0)); la.store(stage0, k_of(kt0)); }
   if constexpr (B_DMA) {
     lb.issue(k_of(kt0), stage0 + A_BYTES);
     if constexpr (!(A_DMA && B_DMA)) lb.issue(k_of(kt0 + 1), stage1 + A_BYTES);   // (else: in the first step's k-step 0)
-  } else { lb.issue(k_of(kt0)); lb.store(stage0 + A_BYTES); }
+  } else { lb.issue(k_of(kt0)); lb.store(stage0 + A_BYTES, k_of(kt0)); }
   // (the accumulators are cleared while the first copies are in flight)
   __builtin_amdgcn_sched_barrier(0);
   floatx16 acc[TM][TN];
@@ -1154,8 +1212,8 @@ __global__ __launch_bounds__(256) void gemm_kernel_dma(GemmArgs g) {
     mma<T, TM, TN>(acc, f0);
     sched_kstep(IC0{}, IC0{});
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!A_DMA) la.store(nxt);
-    if constexpr (!B_DMA) lb.store(nxt + A_BYTES);
+    if constexpr (!A_DMA) la.store(nxt, k_of(kt + 1));
+    if constexpr (!B_DMA) lb.store(nxt + A_BYTES, k_of(kt + 1));
     // A wave's own copies must have landed before it tells the others so: the counter of the vector
     // memory pipeline (which also tracks copies to LDS) has to be zero ahead of the barrier.
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
@@ -1417,15 +1475,19 @@ chn_status launch_piece(const GemmArgs &g, hipStream_t st) {
 
 template <typename T, int TM, int TN, bool A_KC, bool B_KC>
 chn_status launch_tile(const GemmArgs &g, hipStream_t st) {
-  if constexpr (TM == 1) {
-    // one operand that only allows element-wise loads (a K of 10, say) does not slow down the other's
-    if (g.piece_a == (int)sizeof(T) && g.piece_b == 16) return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T), 16>(g, st);
-    if (g.piece_a == 16 && g.piece_b == (int)sizeof(T)) return launch_piece<T, 1, 1, A_KC, B_KC, 16, (int)sizeof(T)>(g, st);
-  }
   if (g.piece == 16) return launch_piece<T, TM, TN, A_KC, B_KC, 16>(g, st);
-  if (g.piece == 8) return launch_piece<T, TM, TN, A_KC, B_KC, 8>(g, st);
-  if constexpr (TM == 1) return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T)>(g, st);
-  else return fail(CHN_ERR_LAUNCH, "gemm: internal: element-wise loads only exist for the 64x64 tile");
+  if constexpr (TM == 4) {
+    if (g.piece == 8) return launch_piece<T, TM, TN, A_KC, B_KC, 8>(g, st);
+  } else {
+    if (g.any_a && g.any_b) return launch_piece<T, TM, TN, A_KC, B_KC, kAnyPiece>(g, st);
+  }
+  if constexpr (TM == 1) {
+    // one operand whose extent is below a piece (a K of 3, say) does not slow down the other's loads
+    if (g.any_b) return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T), kAnyPiece>(g, st);
+    if (g.any_a) return launch_piece<T, 1, 1, A_KC, B_KC, kAnyPiece, (int)sizeof(T)>(g, st);
+    return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T)>(g, st);
+  }
+  return fail(CHN_ERR_LAUNCH, "gemm: internal: the operands do not allow the planned tile");
 }
 
 template <typename T, bool A_KC, bool B_KC>

@@ -48,6 +48,8 @@ struct SplitLoader {
   int64_t kstride;                                        // bytes between consecutive k (MC)
   int lds;                                                // where the first unit goes inside a stage
   int sw;                                                 // MC: swizzle of the unit's rows
+  int down;                                               // MC, pieces at any address: bytes by which the unit's pieces are read early
+  bool cut;                                               // ... and whether the tile reaches past the last row (uniform)
   float scale;                                            // +- kSplitScale
 
   // negate: the k of the odd wave groups are staged with the other sign
@@ -68,9 +70,11 @@ struct SplitLoader {
       constexpr int PAIRS = 4 / R;                        // units that share a group of four k
       const int pair = t % PAIRS, kg = (t / PAIRS) & 7, mc = (t / (8 * PAIRS)) % (ROWS / 4), sub = t / (2 * PAIRS * ROWS);
       koff = sub * 32 + (kg >> 2) * 16 + (kg & 3) * 4 + pair * 2;
-      base = reinterpret_cast<const char *>(p + row0);
+      base = reinterpret_cast<const char *>(p + row0) - 16;
       lim = rows_total - row0 - mc * 4;
-      off[0] = (uint32_t)((koff * ld + (lim > 0 ? mc * 4 : 0)) * 4);
+      down = lim > 0 && lim < 4 ? (4 - lim) * 4 : 0;
+      cut = row0 + ROWS > rows_total;
+      off[0] = (uint32_t)((koff * ld + (lim > 0 ? mc * 4 : 0)) * 4 + 16);
       sw = mc & 3;
       scale = negate && (kg & 2) ? -kSplitScale : kSplitScale;
       // (rows 4 mc .. 4 mc + 3 share their swizzle; row 4 mc + e sits (e ^ sw) rows behind the group's start)
@@ -85,32 +89,42 @@ struct SplitLoader {
   __device__ __forceinline__ void issue(uint4 (&reg)[R], int k0) const {
     if constexpr (KC) {
       const char *p = base + (int64_t)k0 * 4;
-      if (UNIFORM && k0 + SUBS * 32 <= K) {
-        constexpr int PE = PB / 4;
+      constexpr bool ANY = PB == kAnyPiece;
+      if ((UNIFORM || ANY) && k0 + SUBS * 32 <= K) {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          uint32_t *w = &reg[j].x;
-#pragma unroll
-          for (int i = 0; i < 4 / PE; ++i) {
-            const uintptr_t a = reinterpret_cast<uintptr_t>(p + (j & 1) * 64 + i * PB) + off[j >> 1];
-            if constexpr (PB == 16) { const u32x4 v = global_load<u32x4>(a); w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3]; }
-            else if constexpr (PB == 8) { const u32x2 v = global_load<u32x2>(a); w[2 * i] = v[0]; w[2 * i + 1] = v[1]; }
-            else w[i] = global_load<uint32_t>(a);
-          }
+          const uintptr_t a = reinterpret_cast<uintptr_t>(p + (j & 1) * 64) + off[j >> 1];
+          if constexpr (ANY) reg[j] = load_any(a);
+          else reg[j] = load_chunk<float, PB>(a, 4);
         }
-      } else {
+      } else {                                            // (pieces at any address: the last step goes element by element)
 #pragma unroll
         for (int j = 0; j < R; ++j)
-          reg[j] = load_chunk<float, PB>(reinterpret_cast<uintptr_t>(p) + off[j >> 1] + (j & 1) * 64, lim - k0 - 16 * (j & 1));
+          reg[j] = load_chunk<float, ANY ? 4 : PB>(reinterpret_cast<uintptr_t>(p) + off[j >> 1] + (j & 1) * 64, lim - k0 - 16 * (j & 1));
       }
     } else {
       const uintptr_t a = reinterpret_cast<uintptr_t>(base) + off[0];
 #pragma unroll
-      for (int j = 0; j < R; ++j) reg[j] = load_chunk<float, PB>(a + (int64_t)(k0 + j) * kstride, k0 + koff + j < K ? lim : 0);
+      for (int j = 0; j < R; ++j) {
+        const uintptr_t p = a + (int64_t)(k0 + j) * kstride;
+        const int n = k0 + koff + j < K ? lim : 0;
+        if constexpr (PB == kAnyPiece) reg[j] = load_any(n > 0 ? p - down : reinterpret_cast<uintptr_t>(&kZeroChunk));
+        else reg[j] = load_chunk<float, PB>(p, n);
+      }
     }
   }
 
-  __device__ __forceinline__ void store(const uint4 (&reg)[R], char *stage) {
+  // any: the pieces were read at any address
+  __device__ __forceinline__ void store(const uint4 (&loaded)[R], char *stage, bool any) {
+    uint4 reg[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) reg[j] = loaded[j];
+    if constexpr (!KC) {
+      if (any && cut) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) reg[j] = move_down(reg[j], down);
+      }
+    }
     constexpr int PLANE = ROWS * 64;
     if constexpr (KC) {
 #pragma unroll
@@ -198,9 +212,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
     // by all threads together, so that every wave has the same mixture of work.
     constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || KG == 4;
-    // A mixed pair on the large tile: steps of whole k without checks pay for 8-byte pieces (4480x650x2600 149 -> 145 us,
-    // 2050^3 187 -> 176), not for 16-byte ones (4480x2688x672 120 -> 123).
-    constexpr bool kUniform = PBA == 8;
+    // (a mixed pair of aligned operands: steps of whole k without checks do not pay, 4480x2688x672 120 -> 123 us)
     using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
     using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
     LA la;
@@ -216,15 +228,16 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
-      if constexpr (!kHalves) { la.template issue<PBA, kUniform>(xa, kt * BK); lb.template issue<PBB, kUniform>(xb, kt * BK); }
+      if constexpr (!kHalves) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }
       else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
       else if constexpr (kAlike) { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else la.template issue<PBB, kAlike>(xa, kt * BK); }
       else { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else lb.template issue<PBB, kAlike>(xa, kt * BK); }
     };
     auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage) __attribute__((always_inline)) {
-      if constexpr (!kHalves) { la.store(xa, stage); lb.store(xb, stage + A_BYTES); }
-      else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES));
-      else { if (do_a) la.store(xa, stage); else lb.store(xa, stage + A_BYTES); }
+      constexpr bool any_a = PBA == kAnyPiece, any_b = PBB == kAnyPiece;
+      if constexpr (!kHalves) { la.store(xa, stage, any_a); lb.store(xb, stage + A_BYTES, any_b); }
+      else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES), do_a ? any_a : any_b);
+      else { if (do_a) la.store(xa, stage, any_a); else lb.store(xa, stage + A_BYTES, any_b); }
     };
     // this group's 16 k inside a stage: sub-tile grp / 2, k-step grp % 2
     const int off = split_off(r, (grp & 1) * 2 + h);
@@ -371,7 +384,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     for (int k0 = kt0 * BK; k0 < nk * BK; k0 += 32) {
       if (grp == 0) { la.issue(k0); lb.issue(k0); }
       __syncthreads();
-      if (grp == 0) { la.store(lds); lb.store(lds + BM * 128); }
+      if (grp == 0) { la.store(lds, k0); lb.store(lds + BM * 128, k0); }
       __syncthreads();
       if (grp == 0) {
         Frags<TM, TN> f;
@@ -425,10 +438,10 @@ chn_status launch_split_piece(const GemmArgs &g, hipStream_t st) {
 
 template <int TM, int TN, int KG, bool A_KC, bool B_KC>
 chn_status launch_split(const GemmArgs &g, hipStream_t st) {
-  if (g.piece_a == 4 && g.piece_b == 16) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, 16>(g, st);
-  if (g.piece_a == 16 && g.piece_b == 4) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 16, 4>(g, st);
   if (g.piece == 16) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 16, 16>(g, st);
-  if (g.piece == 8) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 8, 8>(g, st);
+  if (g.any_a && g.any_b) return launch_split_piece<TM, TN, KG, A_KC, B_KC, kAnyPiece, kAnyPiece>(g, st);
+  if (g.any_b) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, kAnyPiece>(g, st);
+  if (g.any_a) return launch_split_piece<TM, TN, KG, A_KC, B_KC, kAnyPiece, 4>(g, st);
   return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, 4>(g, st);
 }
 

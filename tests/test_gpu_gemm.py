@@ -278,6 +278,38 @@ def test_gemm_misaligned_leading_dimensions():
     assert np.all(host(z) == 0)
 
 
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", [(8, 8, 8), (9, 65, 64), (64, 71, 65), (66, 64, 9), (130, 129, 127), (131, 260, 200), (3, 140, 70), (140, 70, 3)])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_gemm_operands_at_any_address(tile, dt, layout, shape, offset):
+    # rows of odd pitch that start `offset` elements behind a 16-byte boundary: the piece that the end of a row cuts, along
+    # K (one to four tile steps with every remainder) and along M / N; what lies around the operands is NaN and never reaches C
+    M, N, K = shape
+
+    def operand(a):
+        rows, cols = a.shape
+        buf = torch.full((offset + rows * (cols + 1) + 64,), float("nan"), device="cuda", dtype=torch.float32 if dt == "f32" else torch.bfloat16)
+        view = buf[offset:offset + rows * (cols + 1)].view(rows, cols + 1)[:, :cols]
+        view.copy_(torch.from_numpy(a))
+        return view
+
+    A, Bm = (RNG.integers(-3, 4, size=s).astype(np.float32) for s in ((M, K), (K, N)))
+    Ad = operand(A) if layout[0] == "n" else operand(np.ascontiguousarray(A.T)).t()
+    Bd = operand(Bm) if layout[1] == "n" else operand(np.ascontiguousarray(Bm.T)).t()
+    want = A.astype(np.float64) @ Bm.astype(np.float64)
+    B.gemm_plan_override(tile, 1, 0)
+    try:
+        assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)))), want)
+        C = dev(np.ones((M, N), np.float32))
+        assert np.array_equal(host(B.gemm(Ad, Bd, C, alpha=2.0, beta=-1.0)), 2 * want - 1)
+    finally:
+        B.gemm_plan_override()
+    need = B.gemm_workspace_bytes(Ad, Bd, empty((M, N)))
+    assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=ws(need))), want)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("layout,shape", [("nt", (128, 650, 2600)), ("nn", (128, 2600, 650)), ("tn", (100, 70, 4099)), ("nt", (33, 10, 3000))])
 def test_gemm_split_k(dt, layout, shape):
