@@ -95,6 +95,7 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   const double step_direct = 1.48;                        // bf16 direct-copy kernel, any layout
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   const bool direct = direct_copy_fits(*g, isz, a_kc, b_kc);
+  const bool small_direct_on = direct && isz == 2 && g_force_w8.load(std::memory_order_relaxed) < 0;   // (forcing one of the 256x256 kernels leaves the other tiles staged)
   // Operands whose rows start off 8-byte boundaries do not get the 256x256 tile, those with an extent below one piece only the
   // small one; a step takes longer where pieces straddle cache lines, and longer still element by element.
   const bool any = g->any_a && g->any_b;
@@ -110,7 +111,10 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
     const int64_t tiles = (int64_t)((g->M + b - 1) / b) * ((g->N + b - 1) / b);
     double per_step = (isz == 2 ? step_bf16 : step_f32)[tile][lay] * narrow(tile);
     if (tile == 2 && direct && isz == 2) per_step = step_direct;
-    const double fixed = (isz == 2 ? fixed_bf16 : fixed_f32)[tile];
+    double fixed = (isz == 2 ? fixed_bf16 : fixed_f32)[tile];
+    // The directly copied smaller tiles (bf16), the same for every layout: fitted on 17 products of 1 to 3000 tiles.
+    const bool small_direct = tile < 2 && small_direct_on;
+    if (small_direct) { per_step = tile == 1 ? 0.62 : 0.215; fixed = tile == 1 ? 4.0 : 2.0; }
     for (int s : split_choices) {
       if (s > 1 && (!allow_split || s > nk / 4)) break;
       const int64_t blocks = tiles * s;
@@ -118,8 +122,8 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
       // Up to `conc` blocks of this tile run on a compute unit at once, each then `conc` times slower
       // per step than the amortised figure; a lone block only `slow` times (it is not that much faster
       // alone), in between linearly.  Full rounds of 256 * conc blocks, then the remainder.
-      const int conc = tile == 2 ? 1 : tile == 1 ? 2 : 4;
-      const double slow = tile == 2 ? 1.0 : tile == 1 ? 1.5 : 1.6;   // (64x64: 2.0 before the kernel looked two tiles ahead)
+      const int conc = small_direct ? 2 - tile : tile == 2 ? 1 : tile == 1 ? 2 : 4;
+      const double slow = small_direct ? (tile == 1 ? 1.0 : 1.15) : tile == 2 ? 1.0 : tile == 1 ? 1.5 : 1.6;   // (64x64: 2.0 before the kernel looked two tiles ahead)
       const int64_t full = blocks / (256 * conc), rem = blocks % (256 * conc);
       double t = (double)full * (fixed + steps * per_step * conc);
       if (rem > 0) {
@@ -128,8 +132,8 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
         t += fixed + steps * per_step * f;
       }
       t *= 1e-6;
-      if (s > 1) t += 10e-6 + (double)(s + 1) * g->M * g->N * 4.0 / 4e12;
-      if (t < best * 0.97) { best = t; g->tile = tile; g->splits = s; }   // prefer larger tiles / fewer splits on near-ties
+      if (s > 1) t += (small_direct ? 5e-6 : 10e-6) + (double)(s + 1) * g->M * g->N * 4.0 / 4e12;
+      if (t < best * (small_direct ? 1.0 : 0.97)) { best = t; g->tile = tile; g->splits = s; }   // prefer larger tiles / fewer splits on near-ties
     }
   }
   // The 256 x 128 tile of the eight-wave kernel (bf16, both operands K-contiguous): taken when it fills the chip
@@ -153,7 +157,7 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   g->tiles_m = (g->M + bm - 1) / bm;
   g->tiles_n = (g->N + bn - 1) / bn;
   g->ldp = (g->N + 3) & ~3;
-  g->dma = (g->tile == 2 || g->tile == 3) && direct;
+  g->dma = g->tile >= 2 ? direct : small_direct_on;
   g->parts = 0;
   return best;
 }
@@ -166,8 +170,8 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
 // unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 22 on the
 // small tile, 4480x2688x672 143 -> 101 and 4480x10000x672 499 -> 361 on the large one, 672x2688x4480 both stored along
 // M/N 178 -> 115 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
-// Rows off the 16-byte grid cost little (4480x650x2600, both along K 131 -> 108, mixed 145 -> 118 against 8-byte pieces; 4097x2351x2041
-// 556 -> 273 against single elements, 8192x4001x651 584 -> 295).
+// Rows off the 16-byte grid cost little: against the 8-byte pieces of before, 4480x650x2600 159 -> 145 and 2600x650x4480 162 -> 136;
+// against single elements, 4097x2351x2041 556 -> 273 and 8192x4001x651 584 -> 295.
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
   double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
@@ -238,7 +242,7 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
 // with an activation-gradient epilogue 3-5 % faster.  The four-wave kernel (a third less LDS traffic per
 // MFMA) stays for fp32 and as the forced alternative of the tests.
 bool eight_waves(const GemmArgs &g, int isz, int epilogue) {
-  if (!g.dma || isz != 2) return false;
+  if (!g.dma || isz != 2 || g.tile < 2) return false;
   const int f = g_force_w8.load(std::memory_order_relaxed);
   (void)epilogue;
   return f < 0 || f != 0;

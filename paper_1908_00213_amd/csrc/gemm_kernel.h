@@ -546,20 +546,25 @@ struct StageLayout {
   }
 };
 
-// Vector path of one pass: RP rows x W columns starting at (row0, col0), every row and column in
-// range and all accesses aligned, so that the loop is free of per-lane conditions.  Lane l handles
-// four consecutive columns; the LDS reads and the dependent global reads (old C, aux) of U row
-// segments are in flight together.
+// One pass: RP rows x W columns starting at (row0, col0).  Lane l handles four consecutive columns; the LDS
+// reads and the dependent global reads (old C, aux) of U row segments are in flight together.  Without EDGE every row and
+// column is in range and the loop is free of per-lane conditions; with it, rows and whole groups of four columns are
+// stored where they exist, and at least one of each does.  The epilogue's kind is fixed at compile time on both: an edge pass
+// that looked it up for every group ran through several times the code, which has to be fetched once per workgroup (bf16
+// 608x304x120 on the 128x128 tile 11.1 us, 640x384x120 6.4).
 // CS: the lane also adds what it stores to cs[0..3], the running sums of its four columns.
-// UMAX bounds the row segments in flight per lane (the eight-wave kernel has half the registers per wave).
-template <int EPI, bool CB, bool BETA, int TN, int RP, bool CS = false, int UMAX = 4>
+// UMAX bounds the row segments in flight per lane (the eight-wave kernel has half the registers per wave; an edge pass needs
+// some for its conditions).
+template <int EPI, bool CB, bool BETA, int TN, int RP, bool CS = false, int UMAX = 4, bool EDGE = false>
 __device__ __forceinline__ void epilogue_pass_vec(const GemmArgs &g, const float *stage, int row0, int col0, int lane, float *cs = nullptr) {
   using L = StageLayout<TN>;
   constexpr int CPR = L::W / 4, RPI = 64 / CPR;            // 16-byte chunks per row, rows per wave-wide access
-  constexpr int NIT = RP / RPI, U0 = NIT >= 8 ? 4 : NIT / 2, U = U0 < UMAX ? U0 : UMAX;
+  constexpr int NIT = RP / RPI, U0 = NIT >= 8 ? 4 : NIT / 2, UM = EDGE ? UMAX / 2 : UMAX, U = U0 < UM ? U0 : UM;
   constexpr bool kAux = EPI == CHN_EPI_RELU_BWD || EPI == CHN_EPI_GELU_BWD;
   // a lane keeps its four columns for the whole pass and walks down the rows
-  const int cl = (lane % CPR) * 4, col = col0 + cl, rl0 = lane / CPR;
+  const int cl = (lane % CPR) * 4, rl0 = lane / CPR;
+  const bool whole = !EDGE || col0 + cl + 4 <= g.N;
+  const int col = whole ? col0 + cl : col0, last = EDGE ? g.M - 1 : 0;   // (EDGE: what lanes without a group or a row read is not used)
   Vec4 bias;
 #pragma unroll
   for (int e = 0; e < 4; ++e) bias.v[e] = 0.0f;
@@ -570,7 +575,7 @@ __device__ __forceinline__ void epilogue_pass_vec(const GemmArgs &g, const float
   auto fetch = [&](EpiRaw<CB> (&in)[U], int base) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int row = row0 + rl0 + (base + u) * RPI;
+      const int at = row0 + rl0 + (base + u) * RPI, row = EDGE ? min(at, last) : at;
       if constexpr (BETA) in[u].c0 = load4raw<CB>(g.C, (int64_t)row * g.ldc + col);
       if constexpr (kAux) in[u].aux = load4raw<CB>(g.aux, (int64_t)row * g.ldaux + col);
     }
@@ -587,7 +592,8 @@ __device__ __forceinline__ void epilogue_pass_vec(const GemmArgs &g, const float
 #pragma unroll
         for (int e = 0; e < 4; ++e) cs[e] += st.v[e];
       } else {
-        finish4_t<EPI, CB, BETA>(g, row0 + rl0 + (base + u) * RPI, col, a[u], in[u], bias);
+        const int row = row0 + rl0 + (base + u) * RPI;
+        if (!EDGE || (whole && row <= last)) finish4_t<EPI, CB, BETA>(g, row, col, a[u], in[u], bias);
       }
     }
   };
@@ -615,31 +621,24 @@ template <int TN, int RP, int UMAX = 4>
 __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *stage, int row0, int col0, int lane, float *slab, float *cs) {
   using L = StageLayout<TN>;
   constexpr int W = L::W, CPR = W / 4;
-  if (slab) {                                                 // split-K: raw sums, always aligned (ldp % 4 == 0)
-#pragma unroll 1
-    for (int c = lane; c < RP * CPR; c += 64) {
-      const int rl = c / CPR, cl = (c % CPR) * 4;
-      if (row0 + rl < g.M && col0 + cl < g.N)
-        global_store<f32x4>(reinterpret_cast<uintptr_t>(slab + (int64_t)(row0 + rl) * g.ldp + col0 + cl),
-                            *reinterpret_cast<const f32x4 *>(stage + L::at(rl, cl)));
-    }
-  } else if (col0 + W <= g.N && row0 + RP <= g.M) {
+  auto passes = [&](auto edge_c) __attribute__((always_inline)) {
+    constexpr bool EDGE = decltype(edge_c)::value;
     auto run = [&](auto epi_c) __attribute__((always_inline)) {
       constexpr int EPI = decltype(epi_c)::value;
       constexpr bool kF32Only = EPI == CHN_EPI_BF16_COPY;   // (the host refuses a bf16 C for it)
-      if constexpr (EPI == CHN_EPI_RELU_BWD || EPI == CHN_EPI_GELU_BWD) {
-        if (g.colsum) {                                     // (the host asks for column sums with beta = 0 only)
+      if constexpr (!EDGE && (EPI == CHN_EPI_RELU_BWD || EPI == CHN_EPI_GELU_BWD)) {
+        if (g.colsum) {                                     // (the host asks for column sums of whole tiles, with beta = 0, only)
           if (g.c_bf16) epilogue_pass_vec<EPI, true, false, TN, RP, true, UMAX>(g, stage, row0, col0, lane, cs);
           else epilogue_pass_vec<EPI, false, false, TN, RP, true, UMAX>(g, stage, row0, col0, lane, cs);
           return;
         }
       }
       if (g.beta != 0.0f) {
-        if (!kF32Only && g.c_bf16) epilogue_pass_vec<EPI, !kF32Only, true, TN, RP, false, UMAX>(g, stage, row0, col0, lane);
-        else epilogue_pass_vec<EPI, false, true, TN, RP, false, UMAX>(g, stage, row0, col0, lane);
+        if (!kF32Only && g.c_bf16) epilogue_pass_vec<EPI, !kF32Only, true, TN, RP, false, UMAX, EDGE>(g, stage, row0, col0, lane);
+        else epilogue_pass_vec<EPI, false, true, TN, RP, false, UMAX, EDGE>(g, stage, row0, col0, lane);
       } else {
-        if (!kF32Only && g.c_bf16) epilogue_pass_vec<EPI, !kF32Only, false, TN, RP, false, UMAX>(g, stage, row0, col0, lane);
-        else epilogue_pass_vec<EPI, false, false, TN, RP, false, UMAX>(g, stage, row0, col0, lane);
+        if (!kF32Only && g.c_bf16) epilogue_pass_vec<EPI, !kF32Only, false, TN, RP, false, UMAX, EDGE>(g, stage, row0, col0, lane);
+        else epilogue_pass_vec<EPI, false, false, TN, RP, false, UMAX, EDGE>(g, stage, row0, col0, lane);
       }
     };
     switch (g.epi) {
@@ -651,9 +650,21 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *st
       case CHN_EPI_GELU_BWD: run(std::integral_constant<int, CHN_EPI_GELU_BWD>{}); break;
       default: run(std::integral_constant<int, CHN_EPI_BF16_COPY>{}); break;
     }
-  } else {                                                    // edge tile: whole 4-column groups that lie in range
-    // (the lanes are dealt out over the groups that exist, so the number of dependent iterations
-    // follows the part of the pass that is in range)
+  };
+  if (slab) {                                                 // split-K: raw sums, always aligned (ldp % 4 == 0)
+#pragma unroll 1
+    for (int c = lane; c < RP * CPR; c += 64) {
+      const int rl = c / CPR, cl = (c % CPR) * 4;
+      if (row0 + rl < g.M && col0 + cl < g.N)
+        global_store<f32x4>(reinterpret_cast<uintptr_t>(slab + (int64_t)(row0 + rl) * g.ldp + col0 + cl),
+                            *reinterpret_cast<const f32x4 *>(stage + L::at(rl, cl)));
+    }
+  } else if (col0 + W <= g.N && row0 + RP <= g.M) {
+    passes(std::false_type{});
+  } else if constexpr (TN == 4) {
+    // The four-wave 256x256 kernels have no registers for edge passes of their own: one rolled loop that looks the epilogue's
+    // kind up (the lanes are dealt out over the groups that exist, so the number of dependent iterations follows the part of
+    // the pass that is in range).
     const int nr = max(0, min(RP, g.M - row0)), ncg = max(0, min(CPR, (g.N - col0 + 3) >> 2));   // (a pass may lie wholly outside)
 #pragma unroll 1
     for (int c = lane; c < nr * ncg; c += 64) {
@@ -662,6 +673,17 @@ __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *st
         finish4(g, row, col, *reinterpret_cast<const f32x4 *>(stage + L::at(rl, cl)), epi_fetch(g, row, col));
       } else {
         for (int e = 0; col + e < g.N; ++e) finish1(g, row, col + e, stage[L::at(rl, cl + e)]);
+      }
+    }
+  } else if (row0 < g.M) {
+    if (col0 + 4 <= g.N) passes(std::true_type{});
+    // the one to three columns behind the last whole group
+    const int rest = g.N & 3, first = g.N - rest;
+    if (rest && first >= col0 && first < col0 + W) {
+#pragma unroll 1
+      for (int c = lane; c < min(RP, g.M - row0) * 4; c += 64) {
+        const int rl = c >> 2, e = c & 3;
+        if (e < rest) finish1(g, row0 + rl, first + e, stage[L::at(rl, first - col0 + e)]);
       }
     }
   }
@@ -1029,6 +1051,47 @@ struct DmaLoaderMC {
   }
 };
 
+// The same for the smaller tiles, whose k-rows are 128 or 256 bytes.  Their 32-byte blocks are XORed so that the four k-rows
+// that 16 lanes read together lie in different banks: two rows of 128 bytes share the 256 bytes of all banks.
+template <int ROWS>
+__device__ __forceinline__ int tr_swizzle(int k) {
+  static_assert(ROWS == 64 || ROWS == 128, "rows of four or eight blocks");
+  return ROWS == 64 ? (k >> 1) & 3 : k & 7;
+}
+template <int ROWS>
+struct DmaLoaderRows {
+  static constexpr int BK = 64, NS = ROWS / 32, CPR = ROWS / 8;   // instructions per wave and tile (four waves); chunks per k-row
+  const char *tile;                        // wave-uniform: element (k = 0, m = row0)
+  uint32_t off[NS];
+  int lim[NS];                             // K - (k-row of the slot)
+  int wave;
+  int64_t kbytes;
+
+  // (rows_total is a multiple of 8; chunks past it re-read the operand's last one)
+  __device__ __forceinline__ void init(const bf16_raw *base, int64_t ld, int rows_total, int row0, int K) {
+    wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    kbytes = ld * 2;
+    tile = reinterpret_cast<const char *>(base + row0);
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int slot = (i * 4 + wave) * 64 + lane;
+      const int k = slot / CPR, p = slot % CPR;
+      const int m = ((p >> 1) ^ tr_swizzle<ROWS>(k)) * 16 + (p & 1) * 8;
+      off[i] = (uint32_t)(((int64_t)k * ld + min(m, rows_total - 8 - row0)) * 2);
+      lim[i] = K - k;
+    }
+  }
+  __device__ __forceinline__ void issue(int k0, char *lds_operand) const {
+    const char *p = tile + (int64_t)k0 * kbytes;
+    const char *zero = reinterpret_cast<const char *>(&kZeroChunk);
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(k0 < lim[i] ? p + off[i] : zero),
+                                       (__attribute__((address_space(3))) void *)(lds_operand + (i * 4 + wave) * 1024), 16, 0, 0);
+  }
+};
+
 // Fragment readers of the direct-copy kernel: read(stage, k-step, 32-row block)
 // returns the lane's 16 bytes (8 bf16 or 4 fp32 along k) for an MFMA.
 // K-packed tile (lds_off layout): one 16-byte read.
@@ -1069,6 +1132,29 @@ struct TrReader {
     typedef __attribute__((address_space(3))) short4v *lds_ptr;
     const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stage + base[i][0] + ks * (16 * 512)));
     const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stage + base[i][1] + ks * (16 * 512)));
+    const uint2 l = __builtin_bit_cast(uint2, lo), u = __builtin_bit_cast(uint2, hi);
+    return make_uint4(l.x, l.y, u.x, u.y);
+  }
+};
+
+// ... and of the smaller tiles (DmaLoaderRows).
+template <int ROWS, int BLOCKS>
+struct TrReaderRows {
+  int base[BLOCKS][2];
+  __device__ __forceinline__ void init(int first_block, int lane, int region) {
+    const int G = lane >> 4, s = lane & 15, e = s >> 2, q = s & 3, h = G >> 1, g1 = G & 1;
+#pragma unroll
+    for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int k = 8 * h + 4 * t + e;                 // (16 k on, the swizzle is the same)
+        base[i][t] = region + k * (ROWS * 2) + ((2 * (first_block + i) + g1) ^ tr_swizzle<ROWS>(k)) * 32 + q * 8;
+      }
+  }
+  __device__ __forceinline__ uint4 read(const char *stage, int ks, int i) const {
+    typedef __attribute__((address_space(3))) short4v *lds_ptr;
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stage + base[i][0] + ks * (16 * ROWS * 2)));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(stage + base[i][1] + ks * (16 * ROWS * 2)));
     const uint2 l = __builtin_bit_cast(uint2, lo), u = __builtin_bit_cast(uint2, hi);
     return make_uint4(l.x, l.y, u.x, u.y);
   }
@@ -1408,6 +1494,108 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
   }
 }
 
+// ---- 64 x 64 and 128 x 128 tiles, copied directly ------------------------------------------------------
+// bfloat16 products too small for the 256 x 256 tile.  One such tile per compute unit has little to multiply (four MFMAs per
+// wave and step of 64 k on the small one): it waits for operands, through the register-staged kernel for one trip to the L2 every
+// other step and, where an operand lies along M/N, for its transposition between registers and LDS.  Here four stages take
+// turns, copies run three tile steps ahead without a register, and an operand along M/N is transposed on its way out of LDS.
+// What is left is the stream of operand tiles: 16 KB a step and compute unit at the 45-50 GB/s each gets when all 256 pull.
+// A step: the wave's share of the copies of its tile has landed (a count: the later tiles' are still on their way),
+// everybody's has (barrier; nobody reads the stage of the step before any more), that stage is filled again, multiply.
+// us, staged through registers -> here, small tile: 1024x1000x784 with both operands along K 9.4 -> 7.0, one 9.6 -> 7.1, none
+// 11.0 -> 7.2 (13.6 -> 8.5 between other kernels); large tile: 2048x2048x2048 29, 37, 45 -> 24, 25, 26.
+template <int TM, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
+  using T = bf16_raw;
+  constexpr int BM = 64 * TM, BK = 64, STAGES = 4;
+  constexpr int A_BYTES = BM * 128, STAGE = 2 * A_BYTES;
+  __shared__ __align__(1024) char stage0[STAGE];
+  __shared__ __align__(1024) char stage1[STAGE];
+  __shared__ __align__(1024) char stage2[STAGE];
+  __shared__ __align__(1024) char stage3[STAGE];
+
+  const TilePos tp = tile_pos(g);
+  const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BM;
+  std::conditional_t<A_KC, DmaLoader<T, BM, true>, DmaLoaderRows<BM>> la;
+  std::conditional_t<B_KC, DmaLoader<T, BM, true>, DmaLoaderRows<BM>> lb;
+  la.init(static_cast<const T *>(g.A), g.lda, g.M, m0, g.K);
+  lb.init(static_cast<const T *>(g.B), g.ldb, g.N, n0, g.K);
+
+  const int nk_all = (g.K + BK - 1) / BK;
+  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int kt0 = split * per_split;
+  const int nk = min(nk_all, kt0 + per_split);
+  auto copy = [&](int kt, char *stage) __attribute__((always_inline)) {   // (past the end of K: zeros, never used)
+    la.issue(kt * BK, stage);
+    lb.issue(kt * BK, stage + A_BYTES);
+  };
+  copy(kt0, stage0);
+  copy(kt0 + 1, stage1);
+  copy(kt0 + 2, stage2);
+
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = wave >> 1, wn = wave & 1;
+  std::conditional_t<A_KC, KcReader<T>, TrReaderRows<BM, TM>> ra;
+  std::conditional_t<B_KC, KcReader<T>, TrReaderRows<BM, TM>> rb;
+  ra.init(wm * TM, lane, 0);
+  rb.init(wn * TM, lane, A_BYTES);
+  floatx16 acc[TM][TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+  constexpr int kAhead = (STAGES - 2) * 4 * TM;            // copies of the two later tiles, per wave
+  constexpr int kWait = (kAhead & 15) | (kAhead >> 4) << 14 | 0x70;   // vmcnt(kAhead), lgkmcnt(0)
+  auto step = [&](const char *cur, char *before, int kt) __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(kWait);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    Frags<TM, TM> f[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) f[ks].a[i] = ra.read(cur, ks, i);
+#pragma unroll
+      for (int j = 0; j < TM; ++j) f[ks].b[j] = rb.read(cur, ks, j);
+    }
+    __builtin_amdgcn_sched_barrier(0);                    // (the copies' addresses are made while the fragments arrive)
+    copy(kt + 3, before);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) mma<T, TM, TM>(acc, f[ks]);
+  };
+  int kt = kt0;
+  for (; kt + 3 < nk; kt += 4) {
+    step(stage0, stage3, kt);
+    step(stage1, stage0, kt + 1);
+    step(stage2, stage1, kt + 2);
+    step(stage3, stage2, kt + 3);
+  }
+  if (kt < nk) step(stage0, stage3, kt);
+  if (kt + 1 < nk) step(stage1, stage0, kt + 1);
+  if (kt + 2 < nk) step(stage2, stage1, kt + 2);
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);                // the epilogue reuses the stages
+  __syncthreads();
+  static_assert(kEpiStageBytes<TM, TM> <= STAGE, "a wave stages its accumulators in one stage");
+  write_out<TM, TM>(g, acc, wave == 0 ? stage0 : wave == 1 ? stage1 : wave == 2 ? stage2 : stage3, m0, n0, split);
+}
+
+template <int TM, bool A_KC, bool B_KC>
+chn_status launch_small_dma(const GemmArgs &g, hipStream_t st) {
+  hipLaunchKernelGGL((gemm_kernel_small_dma<TM, A_KC, B_KC>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), 0, st, g);
+  CHN_TRY(check_launch("gemm (small direct copy)"));
+  if (g.splits > 1) {
+    const int64_t n = (int64_t)g.M * (g.ldp / 4);
+    hipLaunchKernelGGL(gemm_splitk_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g);
+    return check_launch("gemm split-K finish");
+  }
+  return CHN_OK;
+}
+
 template <bool A_KC, bool B_KC>
 chn_status launch_w8(const GemmArgs &g, hipStream_t st) {
   const dim3 grid((unsigned)(g.tiles_m * g.tiles_n * g.splits));
@@ -1495,6 +1683,7 @@ chn_status launch_layout(GemmArgs &g, hipStream_t st) {
   if ((int64_t)g.tiles_m * g.tiles_n * g.splits > 0x7fffffff) return fail(CHN_ERR_SHAPE, "gemm: too many tiles");
   if constexpr (sizeof(T) == 2) {
     if ((g.tile == 2 || g.tile == 3) && g.piece == 16 && g.dma && g.w8) return launch_w8<A_KC, B_KC>(g, st);
+    if (g.tile < 2 && g.dma) return g.tile == 1 ? launch_small_dma<2, A_KC, B_KC>(g, st) : launch_small_dma<1, A_KC, B_KC>(g, st);
     if (g.tile == 3) return fail(CHN_ERR_LAUNCH, "gemm: the 256 x 128 tile needs the eight-wave direct-copy kernel");
   }
   if constexpr (kHasDmaKernel<T, A_KC, B_KC>) {

@@ -446,6 +446,33 @@ def narrow_tile():
     B.gemm_plan_override()
 
 
+@pytest.mark.parametrize("tile", [0, 1])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", [(8, 8, 8), (64, 64, 64), (72, 136, 200), (136, 72, 256), (200, 64, 264), (128, 128, 320), (264, 328, 520), (136, 200, 1032)])
+def test_gemm_small_tiles_direct_copy(tile, layout, shape):
+    # one tile step to seventeen (every remainder of the four stages, with and without a ragged last step), tiles that
+    # reach past M and N, cut along K; integers come out exactly
+    M, N, K = shape
+    gi = lambda s, d: RNG.integers(-3, 4, size=s).astype(np.float32)
+    A, Bm, Ad, Bd = operands(M, N, K, layout, "bf16", gi)
+    want = A.astype(np.float64) @ Bm.astype(np.float64)
+    bias = RNG.integers(-3, 4, size=N).astype(np.float32)
+    for splits in (1, 2, 3):
+        if splits > (K + 63) // 64:
+            continue
+        B.gemm_plan_override(tile, splits, 1)
+        try:
+            assert B.gemm_plan(Ad, Bd, empty((M, N)), True) == (tile, True, splits)
+            assert not B.gemm_plan_eight_waves(Ad, Bd, empty((M, N)), True) and B.gemm_plan_kernel(Ad, Bd, empty((M, N)), True) == "direct4"
+            w = ws(B.gemm_workspace_bytes(Ad, Bd, empty((M, N))))
+            assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=w)), want)
+            assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), epilogue="bias_relu", bias=dev(bias), ws=w)), np.maximum(want + bias, 0))
+            C = dev(np.ones((M, N), np.float32))
+            assert np.array_equal(host(B.gemm(Ad, Bd, C, alpha=2.0, beta=-1.0, ws=w)), 2 * want - 1)
+        finally:
+            B.gemm_plan_override()
+
+
 @pytest.mark.parametrize("cdt", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(300, 200, 128), (513, 129, 200), (1030, 1000, 520), (256, 128, 64), (2, 3, 8)])
 def test_gemm_256x128_tile(shape, cdt, narrow_tile):
