@@ -180,10 +180,15 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   if (isz != 4 || big_unsplit || g->K == 0 || g->lda >= kMaxLd || g->ldb >= kMaxLd || (other_forced && force != 1)) return;
   // Few 32x32 blocks and a contraction that one batch of loads per wave covers: the latency-bound kernel of
   // gemm_tiny.h (us, tiled kernels -> this: 32x10x100 9.5 -> 4.1, 33x65x77 10.5 -> 4.4, 32x100x100 5.8 -> 4.4,
-  // 256x256x256 10.1 -> 6.4, 512x512x512 11.1 -> 7.7).  Beyond 256 blocks (1000x1000x64 5.9, would be 10.0) or 512 k
-  // (64x1000x1000 9.4, would be 11.2) the tiles' reuse of operands wins.
+  // 256x256x256 10.1 -> 6.4, 512x512x512 11.1 -> 7.7).  Beyond 256 blocks (1000x1000x64 5.9, would be 10.0) the tiles'
+  // reuse of operands wins.
   const int64_t small_blocks = (int64_t)((g->M + 31) / 32) * ((g->N + 31) / 32);
-  if (!other_forced && g_force_splits.load(std::memory_order_relaxed) < 0 && small_blocks <= 256 && g->K <= 512) {
+  // Sixteen waves cover up to 1024 k, four on a SIMD: with few blocks the fp32 instruction then bounds them (2 us of 784 k), so a
+  // K above 832 only pays with more blocks than half the compute units, where the cut product has two rounds (32x100x784
+  // 9.3 -> 8.2, 128x128x650 9.9 -> 8.1, 512x512x768 12.7 -> 9.8, 500x512x1000 16.1 -> 10.7; 10x1000x1024 stays: 9.0, would
+  // be 10.1).  From 513 to 639 k the cut product stays, too: not measured.
+  const bool small_k = g->K <= 512 || (g->K >= 640 && g->K <= (small_blocks > 128 ? 1024 : 832));
+  if (!other_forced && g_force_splits.load(std::memory_order_relaxed) < 0 && small_blocks <= 256 && small_k) {
     g->parts = 3;
     g->splits = 1;
     g->tiles_m = (g->M + 31) / 32;

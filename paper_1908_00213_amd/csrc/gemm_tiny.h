@@ -99,13 +99,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_tiny_kernel(GemmArgs g) {
   }
 }
 
-// Four waves while one batch of loads each covers the contraction, else eight (the planner sends K up to 512 here).
+// Four waves while one batch of loads each covers the contraction, else eight or sixteen (the planner sends K up to 1024 here).
 template <bool A_KC, bool B_KC>
 chn_status launch_tiny(const GemmArgs &g, hipStream_t st) {
   constexpr int kPerWave = kTinyBatch * 8;
   const dim3 grid((unsigned)(g.tiles_m * g.tiles_n));
   if (g.K <= 4 * kPerWave) hipLaunchKernelGGL((gemm_tiny_kernel<A_KC, B_KC, 4>), grid, dim3(256), 0, st, g);
   else if (g.K <= 8 * kPerWave) hipLaunchKernelGGL((gemm_tiny_kernel<A_KC, B_KC, 8>), grid, dim3(512), 0, st, g);
+  else if (g.K <= 16 * kPerWave) hipLaunchKernelGGL((gemm_tiny_kernel<A_KC, B_KC, 16>), grid, dim3(1024), 0, st, g);
   else return fail(CHN_ERR_SHAPE, "gemm: K = %d is beyond the small-product kernel", g.K);
   return check_launch("gemm (tiny)");
 }

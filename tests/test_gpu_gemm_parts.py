@@ -211,7 +211,7 @@ def test_planner_takes_the_kernel_and_results_repeat():
 
 
 @pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
-@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 7), (32, 10, 100), (33, 65, 255), (100, 64, 256), (64, 70, 257), (500, 512, 512)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 7), (32, 10, 100), (33, 65, 255), (100, 64, 256), (64, 70, 257), (500, 512, 512), (32, 100, 784), (33, 65, 641), (420, 400, 1021)])
 @pytest.mark.parametrize("pad", [0, 3])
 def test_small_products(layout, shape, pad):
     # few blocks and a short contraction: edges of the 32x32 block and of the chunks and batches along K, any alignment
