@@ -89,6 +89,9 @@ struct RPlan {
 // 4.6 and 4.4; fp32 40000 3.8 and 4.4, 60000 4.6 and 4.4, but 32 rows of 40000 5.5 and 4.9.
 constexpr int64_t kCutRow = 32768, kCutRows = 256, kSliceElems = 4096;
 constexpr int kMaxSlices = 8192;                            // over all rows
+// Many rows of at most this many bytes are a wave's each instead of a block's, eight vectors per lane in flight: 10000 x 4001 bf16
+// 20.3 -> 16.3 us, fp32 28.7 -> 24.3, 8192 x 3200 fp32 20.1 -> 16.8.
+constexpr int64_t kWaveRows = 2048, kWaveRowBytes = 16384;
 bool cut_pays(int64_t rows, int64_t len, int isz) {
   return len >= (isz == 2 ? 65536 : rows <= 8 ? 57344 : rows <= 16 ? 45056 : kCutRow);
 }
@@ -185,6 +188,13 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     }
     p->split = (int)s;
     p->rows_per_split = (p->len + s - 1) / s;
+    // whole batches of eight rows per thread (10000 x 4001 bf16, 65 rows a slice -> 64: 22.0 -> 21.0 us), where the partial sums
+    // stay within what chn_reduce_axis_static holds
+    const int64_t batch = 8 * (256 / p->tx);
+    if (p->vec && (isz == 2 || p->tx != kColTXWide) && p->rows_per_split > batch && blocks_xy * s >= 1024) {
+      const int64_t down = p->rows_per_split / batch * batch, slices = (p->len + down - 1) / down;
+      if (slices <= 1024 && (aligned || slices <= most) && slices * p->O * p->I * (int64_t)sizeof(float) <= (int64_t)kScratchBytes) p->rows_per_split = down;
+    }
     p->split = (int)((p->len + p->rows_per_split - 1) / p->rows_per_split);
     p->ws_bytes = p->split > 1 ? (size_t)p->split * p->O * p->I * sizeof(float) : 0;
     return CHN_OK;
@@ -200,35 +210,51 @@ __global__ __launch_bounds__(256) void fill_kernel(Tout *out, int64_t n, float v
   if (i < n) Elem<Tout>::store(out + i, v);
 }
 
+// A vector's elements, folded as a tree.
+template <int OP, typename T>
+__device__ __forceinline__ float fold_vec(const Vec16<T> &x) {
+  constexpr int N = Vec16<T>::N;
+  float v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = x.get(i);
+#pragma unroll
+  for (int h = N / 2; h > 0; h /= 2)
+#pragma unroll
+    for (int i = 0; i < h; ++i) v[i] = fold<OP>(v[i], v[i + h]);
+  return v[0];
+}
+
 // One lane's share of a row of `len` elements: G lanes, four accumulators each, folded in an order that depends on len
-// alone.  BATCHES of four 16-byte loads are in flight at once.
+// alone.  BATCHES of four 16-byte loads are in flight at once, in the last, partial batch too: there a lane past the end takes
+// the row's last vector and drops it (one by one, each waited for the one before, and with 256 lanes a row of 4001 bf16 is
+// nothing but such a rest).
 template <int OP, typename Tin, int G, bool VEC, int BATCHES>
 __device__ __forceinline__ float fold_row(const Tin *p, int64_t len, int g) {
   float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
   if constexpr (VEC) {
     constexpr int N = Vec16<Tin>::N;
-    const int64_t nvec = len / N;
-    int64_t v = g;
-    auto batches = [&](auto count) __attribute__((always_inline)) {
-      constexpr int U = 4 * decltype(count)::value;
-      for (; v + (U - 1) * G < nvec; v += U * G) {
-        Vec16<Tin> x[U];
+    const int64_t nvec = len / N, at = nvec * N + g;
+    const float rest = at < len ? Elem<Tin>::load(p + at) : identity<OP>();   // (at most N - 1 of them, G >= N lanes)
+    constexpr int U = 4 * BATCHES;
+    for (int64_t v0 = 0; v0 < nvec; v0 += U * G) {
+      const Tin *q = p + v0 * N;
+      Vec16<Tin> x[U];
+      if (v0 + U * G <= nvec) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(p + (v + u * G) * N);
+        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(q + (g + u * G) * N);
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u & 3] = fold<OP>(acc[u & 3], fold_vec<OP>(x[u]));
+      } else {
+        const int left = (int)(nvec - v0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
+          if (u * G < left) x[u] = load16_any(q + min(g + u * G, left - 1) * N);
 #pragma unroll
-          for (int i = 0; i < N; ++i) acc[u & 3] = fold<OP>(acc[u & 3], x[u].get(i));
+        for (int u = 0; u < U; ++u)
+          if (u * G < left) acc[u & 3] = fold<OP>(acc[u & 3], g + u * G < left ? fold_vec<OP>(x[u]) : identity<OP>());
       }
-    };
-    if constexpr (BATCHES > 1) batches(std::integral_constant<int, BATCHES>{});
-    batches(std::integral_constant<int, 1>{});
-    for (; v < nvec; v += G) {
-      const Vec16<Tin> x = load16_any(p + v * N);
-#pragma unroll
-      for (int i = 0; i < N; ++i) acc[i & 3] = fold<OP>(acc[i & 3], x.get(i));
     }
-    for (int64_t c = nvec * N + g; c < len; c += G) acc[1] = fold<OP>(acc[1], Elem<Tin>::load(p + c));
+    acc[3] = fold<OP>(acc[3], rest);
   } else {
     int64_t c = g;
     for (; c + 3 * G < len; c += 4 * G) {
@@ -251,7 +277,7 @@ __device__ __forceinline__ float fold_lanes(float a) {
 
 // ROW: G lanes per row, 256 / G rows per block.
 // G = 256: a row may be cut in `slices` slices of `slice` elements, one block each; `rows` then counts slices.
-template <int OP, typename Tin, typename Tout, int G, bool VEC>
+template <int OP, typename Tin, typename Tout, int G, bool VEC, int BATCHES = 1>
 __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *out, int64_t rows, int64_t len, int64_t pitch, int slices = 1, int64_t slice = 0) {
   constexpr int RPB = 256 / G;
   const int g = threadIdx.x % G;
@@ -264,7 +290,7 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
       p = in + r * pitch + first;
       len = len - first < slice ? len - first : slice;
     }
-    a = fold_row<OP, Tin, G, VEC, 1>(p, len, g);
+    a = fold_row<OP, Tin, G, VEC, BATCHES>(p, len, g);
   }
   a = fold_lanes<OP, (G < 64 ? G : 64)>(a);
   if constexpr (G == 256) {
@@ -363,20 +389,24 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
         }
       }
     } else if constexpr (VEC) {
-      for (; r + 3 * kColTY < r_end; r += 4 * kColTY) {
-        Vec16<Tin> x[4];
+      // Eight rows in flight per lane, then one batch of four and single ones (14795 x 296 fp32 22.7 -> 16.5 us, 16384 x 1024
+      // bf16 14.5 -> 12.2 against four); four where the many narrow blocks of wide fp32 arrays keep memory busy as it is
+      // (4000 x 8000 23.3, would be 24.3).
+      constexpr int kBatch = sizeof(Tin) == 4 && kColTX == kColTXWide ? 4 : 8;
+      auto batch = [&](auto count) __attribute__((always_inline)) {
+        constexpr int U = decltype(count)::value;
+        Vec16<Tin> x[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = load16_any_nt(p + (r + u * kColTY) * sR);
+        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(p + (r + u * kColTY) * sR);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x[u].get(i));
-      }
-      for (; r < r_end; r += kColTY) {
-        const Vec16<Tin> x = load16_any(p + r * sR);
-#pragma unroll
-        for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x.get(i));
-      }
+        r += U * kColTY;
+      };
+      while (r + (kBatch - 1) * kColTY < r_end) batch(std::integral_constant<int, kBatch>{});
+      if (kBatch > 4 && r + 3 * kColTY < r_end) batch(std::integral_constant<int, 4>{});
+      while (r < r_end) batch(std::integral_constant<int, 1>{});
     } else {
       for (; r + 3 * kColTY < r_end; r += 4 * kColTY) {
         float x[4];
@@ -488,7 +518,8 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     if (vec) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, true>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0); \
     else hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, false>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0);    \
   } while (0)
-    if (p.len >= 2048 || rows < 512) CHN_ROW(256);
+    if (p.len * (int64_t)sizeof(Tin) > (rows >= kWaveRows ? kWaveRowBytes : 2048 * (int64_t)sizeof(Tin) - 1) || rows < 512) CHN_ROW(256);
+    else if (p.len > 4 * 64 * n) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, 64, true, 2>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0);
     else if (p.len > 64) CHN_ROW(64);
     else CHN_ROW(8);
 #undef CHN_ROW

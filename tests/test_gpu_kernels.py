@@ -780,3 +780,24 @@ def test_argmax_is_the_accuracy_of_a_classifier_and_its_errors():
         assert e.value.status == status
     with pytest.raises(B.ChnError):
         B.argmax_axis(torch.empty(4, 0, device="cuda"), 1, torch.empty(4, dtype=torch.int64, device="cuda"))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows", [600, 2050])
+@pytest.mark.parametrize("vectors,rest", [(64, 0), (65, 1), (192, 3), (255, 0), (256, 0), (257, 1), (447, 2), (512, 0), (513, 0), (1023, 3), (1024, 0), (1100, 1)])
+def test_rows_of_partial_batches(dt, rows, vectors, rest):
+    # a wave or a block per row: one to eight vectors per lane in the last batch, with and without elements behind the last
+    # vector, on both sides of the lengths where the kernels change; what lies between the rows is NaN
+    n = vectors * (8 if dt == "bf16" else 4) + rest
+    g = torch.Generator(device="cuda").manual_seed(vectors)
+    buf = torch.full((rows, n + 3), float("nan"), device="cuda", dtype=torch.float32 if dt == "f32" else torch.bfloat16)
+    x = buf[:, :n]
+    x.copy_(torch.randn(rows, n, generator=g, device="cuda"))
+    w = torch.empty(max(256, B.reduce_axis_workspace_bytes(x, 1)), dtype=torch.uint8, device="cuda")
+    out = torch.empty(rows, device="cuda")
+    ref, S = x.double().sum(1), x.double().abs().sum(1)
+    B.reduce_axis("sum", x, 1, out, ws=w)
+    # at most 64 values one after the other, then trees: 74 roundings of partial sums
+    assert bool(((out.double() - ref).abs() <= 74 * 2.0 ** -24 * S).all())
+    B.reduce_axis("max", x, 1, out, ws=w)
+    assert torch.equal(out, x.float().amax(1))
