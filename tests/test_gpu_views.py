@@ -178,3 +178,20 @@ def test_embedding_gradient_scan_lengths(N, D, wide):
     g = torch.full((V, D), float("nan"), device="cuda")
     assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g)), ref)
     assert np.array_equal(host(B.embed_bwd(dev(ids), dev(dout), g, accumulate=True)), 2 * ref)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 5), (129, 65), (130, 449), (65, 577), (1001, 515), (300, 1027), (1027, 1100)])
+@pytest.mark.parametrize("pitch", [0, 3])
+def test_tiles_of_transposed_views_off_the_vector_grid(dt, shape, pitch):
+    # one tile to several hundred, numbers of tiles that the eight XCDs share evenly and not; the transposed operand with and
+    # without a gap between its rows, whole kilobytes of pitch among them (513 + 511, 1025 + 1023: another order of tiles)
+    m, n = shape
+    gen = torch.Generator(device="cuda").manual_seed(m * n)
+    ints = lambda *s: torch.randint(-8, 9, s, generator=gen, device="cuda").to(TDT[dt])
+    for gap in (pitch, -m % 512):
+        a, b, c = ints(n, m + gap)[:, :m].t(), ints(m, n + 5)[:, 2:n + 2], ints(1, n)
+        out = torch.full((m, n + gap), float("nan"), device="cuda", dtype=TDT[dt])
+        B.elementwise_broadcast("mad_relu", [a, b, c], out[:, :n])
+        assert torch.equal(out[:, :n].float(), (a.float() * b.float() + c.float()).clamp(min=0))
+        assert bool(out[:, n:].isnan().all())
