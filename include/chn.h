@@ -502,14 +502,14 @@ int chn_version(void);
 int chn_elementwise_plan(int op, int n_in, const chn_array *const *in, const chn_array *out);
 /* The same for chn_gemm: bits 0-1 macro tile (0: 64x64, 1: 128x128, 2: 256x256, 3: 256x128 - bfloat16
  * products with both operands unit-stride along K whose N is too small for 256 blocks of the square tile),
- * bit 2 set when a kernel that copies operand tiles straight from global memory into LDS is taken, bit 3 when that
+ * bit 2 set when a kernel that copies the operands of a 256-row tile straight from global memory into LDS is taken, bit 3 when that
  * is the kernel that works on the tile with eight waves (bfloat16 products) or, for an F32 product, when it runs on
  * the bfloat16 matrix cores, each operand as the sum of three bfloat16 parts (same accuracy; bits 0-2 then tell what
  * the plan on the fp32 matrix instruction would be), bits 4 and up the number of K splits (1 = none;
  * have_workspace = 0 plans as chn_gemm does without workspace). */
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);
 /* The kernel that plan runs on: operand tiles staged through registers, copied straight into LDS by four or eight
- * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K <= 512 straight
+ * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K up to 512 to 1024 straight
  * from memory to the matrix registers (chn_gemm_plan describes those as a 64x64 tile without a cut).  Negative: an error. */
 enum { CHN_GEMM_KERNEL_STAGED = 0, CHN_GEMM_KERNEL_DIRECT4 = 1, CHN_GEMM_KERNEL_DIRECT8 = 2, CHN_GEMM_KERNEL_PARTS = 3, CHN_GEMM_KERNEL_SMALL = 4 };
 int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);
@@ -518,7 +518,7 @@ int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array
  * workspace allows it), or -1; direct_copy: 0 keeps products off the direct-copy kernels, -1 or 1 lets
  * the planner take them where they fit, 2 / 3 additionally fix the four-wave / eight-wave kernel; 4 puts F32
  * products on the three-part kernel (its 64x64 tile with tile = 0, its 128x128 tile with tile = 1), any other value but
- * -1 and any forced tile keep them off it and off the small-product kernel.  A forced value that the operands do not allow (the large tiles
+ * -1 and any forced tile keep them off it and off the small-product kernel.  A forced value that the operands do not allow (the 256-row tiles
  * need 8-byte pieces) is ignored.  Results do not depend on the plan beyond summation order; the tests
  * use this to run short products on the large tiles.  (-1, -1, -1) restores normal planning. */
 void chn_gemm_plan_override(int tile, int splits, int direct_copy);

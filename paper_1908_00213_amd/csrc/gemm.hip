@@ -112,9 +112,10 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
     double per_step = (isz == 2 ? step_bf16 : step_f32)[tile][lay] * narrow(tile);
     if (tile == 2 && direct && isz == 2) per_step = step_direct;
     double fixed = (isz == 2 ? fixed_bf16 : fixed_f32)[tile];
-    // The directly copied smaller tiles (bf16), the same for every layout: fitted on 17 products of 1 to 3000 tiles.
+    // The directly copied smaller tiles (bf16), the same for every layout: fitted on 17 products of 1 to 3000 tiles.  The
+    // steps are those of a long K (0.62 and 0.215 up to 2048 k): 1000x4096x8192 along M/N 93 on it, 78 on the 256x256 tile cut in four.
     const bool small_direct = tile < 2 && small_direct_on;
-    if (small_direct) { per_step = tile == 1 ? 0.62 : 0.215; fixed = tile == 1 ? 4.0 : 2.0; }
+    if (small_direct) { per_step = tile == 1 ? 0.68 : 0.235; fixed = tile == 1 ? 4.0 : 2.0; }
     for (int s : split_choices) {
       if (s > 1 && (!allow_split || s > nk / 4)) break;
       const int64_t blocks = tiles * s;
@@ -300,7 +301,7 @@ void chn_gemm_plan_override(int tile, int splits, int direct_copy) {
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace) {
   chn::GemmArgs g{};
   CHN_TRY(chn::plan_of(A, B, C, have_workspace, &g));
-  return g.tile | (g.dma ? 4 : 0) | (chn::eight_waves(g, chn::dtype_size(A->dtype), CHN_EPI_NONE) || g.parts == 1 || g.parts == 2 ? 8 : 0) | (g.splits << 4);
+  return g.tile | (g.dma && g.tile >= 2 ? 4 : 0) | (chn::eight_waves(g, chn::dtype_size(A->dtype), CHN_EPI_NONE) || g.parts == 1 || g.parts == 2 ? 8 : 0) | (g.splits << 4);
 }
 
 int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace) {
