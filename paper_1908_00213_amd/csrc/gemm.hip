@@ -113,7 +113,8 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
     if (tile == 2 && direct && isz == 2) per_step = step_direct;
     double fixed = (isz == 2 ? fixed_bf16 : fixed_f32)[tile];
     // The directly copied smaller tiles (bf16), the same for every layout: fitted on 17 products of 1 to 3000 tiles.  The
-    // steps are those of a long K (0.62 and 0.215 up to 2048 k): 1000x4096x8192 along M/N 93 on it, 78 on the 256x256 tile cut in four.
+    // steps are those of a long K (0.62 and 0.215 up to 2048 k): 1000x4096x8192 along M/N 93 on 128x128, 78 on the 256x256 tile
+    // cut in four.
     const bool small_direct = tile < 2 && small_direct_on;
     if (small_direct) { per_step = tile == 1 ? 0.68 : 0.235; fixed = tile == 1 ? 4.0 : 2.0; }
     for (int s : split_choices) {
