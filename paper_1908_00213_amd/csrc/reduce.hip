@@ -105,7 +105,8 @@ constexpr int kColTXWide = 16, kColTXMid = 32, kColTXNarrow = 64;
 constexpr int kColTXShort = 4;
 constexpr int64_t kShortRows = 2048, kShortBytes = 8 << 20;
 
-chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
+// alone: not one of several passes that share a workspace (whose size must not grow with this one's partial sums)
+chn_status make_rplan(const chn_array *in, int axis, RPlan *p, bool alone) {
   CHN_TRY(validate(in, "in", false));
   if (!is_float(in->dtype)) return fail(CHN_ERR_DTYPE, "reduce: input must be F32 or BF16");
   if (in->ndim < 1) return fail(CHN_ERR_NDIM, "reduce: input needs at least one dimension");
@@ -191,7 +192,7 @@ chn_status make_rplan(const chn_array *in, int axis, RPlan *p) {
     // whole batches of eight rows per thread (10000 x 4001 bf16, 65 rows a slice -> 64: 22.0 -> 21.0 us), where the partial sums
     // stay within what chn_reduce_axis_static holds
     const int64_t batch = 8 * (256 / p->tx);
-    if (p->vec && (isz == 2 || p->tx != kColTXWide) && p->rows_per_split > batch && blocks_xy * s >= 1024) {
+    if (alone && p->vec && (isz == 2 || p->tx != kColTXWide) && p->rows_per_split > batch && blocks_xy * s >= 1024) {
       const int64_t down = p->rows_per_split / batch * batch, slices = (p->len + down - 1) / down;
       if (slices <= 1024 && (aligned || slices <= most) && slices * p->O * p->I * (int64_t)sizeof(float) <= (int64_t)kScratchBytes) p->rows_per_split = down;
     }
@@ -555,10 +556,10 @@ chn_status launch_op(int op, const RPlan &p, const chn_array *in, const chn_arra
 }  // namespace
 
 chn_status reduce_one_axis(int op, const chn_array *in, int axis, int keepdims, const chn_array *out,
-                           void *ws, size_t ws_bytes, bool static_scratch, chn_stream stream) {
+                           void *ws, size_t ws_bytes, bool static_scratch, bool alone, chn_stream stream) {
   if (op != CHN_REDUCE_SUM && op != CHN_REDUCE_MAX) return fail(CHN_ERR_OP, "reduce: unknown op %d", op);
   RPlan p;
-  CHN_TRY(make_rplan(in, axis, &p));
+  CHN_TRY(make_rplan(in, axis, &p, alone));
   CHN_TRY(validate(out, "out", true));
   if (!is_float(out->dtype)) return fail(CHN_ERR_DTYPE, "reduce: out must be F32 or BF16");
   const int ax = axis < 0 ? axis + in->ndim : axis;
@@ -670,7 +671,7 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
       RPlan whole;
       chn_array probe = cur;
       if (!probe.data) probe.data = reinterpret_cast<void *>(uintptr_t(256));
-      CHN_TRY(make_rplan(&probe, d, &whole));
+      CHN_TRY(make_rplan(&probe, d, &whole, false));
       int64_t c = 0;
       for (int64_t t = 8192; t >= 1024; t -= 4) if (cur.shape[d] % t == 0) { c = t; break; }
       if (whole.kind != KIND_ROW && c) {
@@ -693,7 +694,7 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
     RPlan rp;
     chn_array probe = ps.in;
     if (!probe.data) probe.data = reinterpret_cast<void *>(uintptr_t(256));   // (planning only looks at alignment)
-    CHN_TRY(make_rplan(&probe, d, &rp));
+    CHN_TRY(make_rplan(&probe, d, &rp, false));
     ps.ws_need = rp.kind == KIND_COL ? rp.ws_bytes : 0;
     if (ps.ws_need > mp->partial_bytes) mp->partial_bytes = ps.ws_need;
     if (rp.kind == KIND_ROW && rp.slice_bytes > mp->slice_bytes) mp->slice_bytes = rp.slice_bytes;
@@ -709,7 +710,7 @@ chn_status make_multi(const chn_array *in, int axis_code, MultiPlan *mp) {
 
 chn_status reduce_axis_impl(int op, const chn_array *in, int axis, int keepdims, const chn_array *out,
                             void *ws, size_t ws_bytes, bool static_scratch, chn_stream stream) {
-  if (axis != CHN_AXIS_ALL && axis < CHN_AXES(0)) return reduce_one_axis(op, in, axis, keepdims, out, ws, ws_bytes, static_scratch, stream);
+  if (axis != CHN_AXIS_ALL && axis < CHN_AXES(0)) return reduce_one_axis(op, in, axis, keepdims, out, ws, ws_bytes, static_scratch, true, stream);
   if (op != CHN_REDUCE_SUM && op != CHN_REDUCE_MAX) return fail(CHN_ERR_OP, "reduce: unknown op %d", op);
   MultiPlan mp;
   CHN_TRY(make_multi(in, axis, &mp));
@@ -748,7 +749,7 @@ chn_status reduce_axis_impl(int op, const chn_array *in, int axis, int keepdims,
     const bool last = i == mp.n - 1;
     if (last) { ps.out.data = out->data; set_contiguous(&ps.out, out->dtype); }
     else ps.out.data = tmp[i & 1];
-    CHN_TRY(reduce_one_axis(op, &ps.in, ps.axis, 0, &ps.out, partial, base ? ws_bytes - mp.tmp() : 0, false, stream));
+    CHN_TRY(reduce_one_axis(op, &ps.in, ps.axis, 0, &ps.out, partial, base ? ws_bytes - mp.tmp() : 0, false, false, stream));
     src = ps.out.data;
   }
   return CHN_OK;
@@ -766,7 +767,7 @@ size_t chn_reduce_axis_workspace_bytes(const chn_array *in, int axis) {
     return mp.total();
   }
   chn::RPlan p;
-  if (chn::make_rplan(in, axis, &p) != CHN_OK) return 0;
+  if (chn::make_rplan(in, axis, &p, true) != CHN_OK) return 0;
   return p.kind == chn::KIND_COL ? p.ws_bytes : p.kind == chn::KIND_ROW ? p.slice_bytes : 0;
 }
 

@@ -243,3 +243,12 @@ def test_benchmark_refuses_what_it_cannot_measure():
     if not torch.cuda.is_available():
         r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--quick", "--no-cpu"], capture_output=True, text=True, timeout=300)
         assert r.returncode == 3 and "no GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_passes_that_share_a_workspace_do_not_grow():
+    # column sums by themselves take slices of whole batches (64 rows); one pass of a reduction over a set of axes keeps the
+    # slices (65 rows) that its workspace, and the built-in scratch, have always been sized for
+    L = B.lib()
+    x = B.raw_desc(P, (10000, 4001), (8002, 2), B.BF16)
+    assert L.chn_reduce_axis_workspace_bytes(C.byref(x), 0) == 157 * 4001 * 4
+    assert L.chn_reduce_axis_workspace_bytes(C.byref(x), B._axis_code((0,), 2)) == 154 * 4001 * 4
