@@ -96,12 +96,13 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   const bool direct = direct_copy_fits(*g, isz, a_kc, b_kc);
   const bool small_direct_on = direct && isz == 2 && g_force_w8.load(std::memory_order_relaxed) < 0;   // (forcing one of the 256x256 kernels leaves the other tiles staged)
-  // Operands whose rows start off 8-byte boundaries do not get the 256x256 tile, those with an extent below one piece only the
-  // small one; a step takes longer where pieces straddle cache lines, and longer still element by element.
-  const bool any = g->any_a && g->any_b;
+  // Operands whose rows start off 8-byte boundaries do not get the 256x256 tile; those with an extent below 16 bytes are read in
+  // 8-byte pieces on every tile where their rows allow it (a K of 4, say), else element by element, on the small tile only.
+  // launch_tile follows the same rule.  A step takes longer where pieces straddle cache lines, and longer still element by element.
+  const bool any = g->any_a && g->any_b, halves = g->piece == 8 && !any;
   const int largest = g->piece >= 8 ? 2 : any ? 1 : 0;
   // (bf16 in one 64x64 tile per compute unit: 1024x1000x784 9.1, 1024x1001x785 11.3; 7292x423x487 18.4 on that tile, 27.4 on 128x128)
-  auto narrow = [&](int tile) { return g->piece >= 16 ? 1.0 : tile == 2 || (any && isz == 4) ? 1.15 : any ? (tile == 1 ? 2.0 : 1.5) : 2.0; };
+  auto narrow = [&](int tile) { return g->piece >= 16 ? 1.0 : tile == 2 || halves || (any && isz == 4) ? 1.15 : any ? (tile == 1 ? 2.0 : 1.5) : 2.0; };
   const int nk = (g->K + 128 / isz - 1) / (128 / isz);   // tile steps along K
   static const int split_choices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
   double best = 1e300;
@@ -202,6 +203,7 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   auto narrow = [&](bool any, bool kc, bool large) {
     if (g->piece == 16) return 1.0;
     if (any) return large ? 1.05 : 1.1;
+    if (g->piece == 8) return large ? (kc ? 1.05 : 1.35) : 1.1;
     return large ? (kc ? 3.2 : 1.9) : (kc ? 3.7 : 3.0);
   };
   // (A finishing launch is charged 5 us here, on both sides.  Cut along K, the fp32 instruction's element-wise loads

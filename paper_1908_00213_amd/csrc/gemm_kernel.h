@@ -1664,11 +1664,10 @@ chn_status launch_piece(const GemmArgs &g, hipStream_t st) {
 template <typename T, int TM, int TN, bool A_KC, bool B_KC>
 chn_status launch_tile(const GemmArgs &g, hipStream_t st) {
   if (g.piece == 16) return launch_piece<T, TM, TN, A_KC, B_KC, 16>(g, st);
-  if constexpr (TM == 4) {
-    if (g.piece == 8) return launch_piece<T, TM, TN, A_KC, B_KC, 8>(g, st);
-  } else {
+  if constexpr (TM < 4) {
     if (g.any_a && g.any_b) return launch_piece<T, TM, TN, A_KC, B_KC, kAnyPiece>(g, st);
   }
+  if (g.piece == 8) return launch_piece<T, TM, TN, A_KC, B_KC, 8>(g, st);   // (the smaller tiles: an extent below 16 bytes)
   if constexpr (TM == 1) {
     // one operand whose extent is below a piece (a K of 3, say) does not slow down the other's loads
     if (g.any_b) return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T), kAnyPiece>(g, st);

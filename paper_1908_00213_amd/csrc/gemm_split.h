@@ -440,6 +440,7 @@ template <int TM, int TN, int KG, bool A_KC, bool B_KC>
 chn_status launch_split(const GemmArgs &g, hipStream_t st) {
   if (g.piece == 16) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 16, 16>(g, st);
   if (g.any_a && g.any_b) return launch_split_piece<TM, TN, KG, A_KC, B_KC, kAnyPiece, kAnyPiece>(g, st);
+  if (g.piece == 8) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 8, 8>(g, st);   // (an extent of two or three)
   if (g.any_b) return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, kAnyPiece>(g, st);
   if (g.any_a) return launch_split_piece<TM, TN, KG, A_KC, B_KC, kAnyPiece, 4>(g, st);
   return launch_split_piece<TM, TN, KG, A_KC, B_KC, 4, 4>(g, st);

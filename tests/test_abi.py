@@ -3,6 +3,8 @@ and rejects malformed descriptors on the host before anything is launched (no GP
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -252,3 +254,53 @@ def test_passes_that_share_a_workspace_do_not_grow():
     x = B.raw_desc(P, (10000, 4001), (8002, 2), B.BF16)
     assert L.chn_reduce_axis_workspace_bytes(C.byref(x), 0) == 157 * 4001 * 4
     assert L.chn_reduce_axis_workspace_bytes(C.byref(x), B._axis_code((0,), 2)) == 154 * 4001 * 4
+
+
+_PRODUCTS = r"""
+import ctypes as C, itertools, random
+import torch
+from paper_1908_00213_amd import binding as B
+assert torch.cuda.device_count() == 0                # (the addresses below are made up)
+L = B.lib()
+P, rng = 1 << 20, random.Random(1)
+
+
+def call(isz, M, N, K, transposed, pads, offsets):
+    dt = B.BF16 if isz == 2 else B.F32
+
+    def operand(r, c, tr, pad, off):
+        ld = (r if tr else c) + pad
+        return B.raw_desc(P + off * isz, (r, c), (isz, ld * isz) if tr else (ld * isz, isz), dt)
+    A, Bm = operand(M, K, transposed[0], pads[0], offsets[0]), operand(K, N, transposed[1], pads[1], offsets[1])
+    for csz in {isz, 4}:
+        Cd = B.raw_desc(P << 8, (M, N), (N * csz, csz), B.BF16 if csz == 2 else B.F32)
+        for ws in (0, 1 << 40):
+            rc = L.chn_gemm(C.byref(A), C.byref(Bm), C.byref(Cd), 1.0, 0.0, 0, None, None, None, C.c_void_p(P << 12 if ws else 0), ws, None)
+            message = L.chn_last_error().decode()
+            # every product gets as far as its launch, which finds no device
+            assert rc != 0 and "no ROCm-capable device" in message, (isz, (M, N, K), transposed, pads, offsets, csz, ws, message)
+
+
+calls = 0
+for isz, layout, K in itertools.product((2, 4), itertools.product((0, 1), repeat=2), (1, 2, 3, 4, 6, 8)):
+    for M, N in itertools.product((1, 4, 70, 512, 2048, 8192), (2, 300, 4096, 10000)):
+        call(isz, M, N, K, layout, (0, 0), (0, 0))
+        calls += 1
+for _ in range(1500):
+    size = lambda: rng.randint(1, 9) if rng.random() < 0.4 else int(2 ** rng.uniform(3, 14))
+    isz = rng.choice((2, 4))
+    M, N, K = size(), size(), size()
+    pick = lambda: rng.choice((0, 0, 1, 2, 4, 8))
+    for tile, splits, direct in ((-1, -1, -1), (0, -1, -1), (1, 1, 0), (1, -1, -1), (2, -1, -1), (3, -1, -1), (0, 2, 4), (1, -1, 4)):
+        L.chn_gemm_plan_override(tile, splits, direct)
+        call(isz, M, N, K, (rng.randint(0, 1), rng.randint(0, 1)), (pick(), pick()), (pick(), pick()))
+        calls += 1
+print(calls, "calls")
+"""
+
+
+def test_every_planned_product_has_a_launch():
+    # sizes from one element on, layouts, pitches and offsets, planned freely and with every tile forced, in a process that sees no device
+    r = subprocess.run([sys.executable, "-c", _PRODUCTS], capture_output=True, text=True, timeout=600, cwd=ROOT,
+                       env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"))
+    assert r.returncode == 0 and "calls" in r.stdout, r.stdout + r.stderr[-2000:]

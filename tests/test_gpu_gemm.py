@@ -311,6 +311,46 @@ def test_gemm_operands_at_any_address(tile, dt, layout, shape, offset):
 
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", [(130, 260, "e"), (2048, 4096, "e"), ("e", 300, 1000), (140, "e", 515), ("e", 2000, 4096), ("e", 300, "e")])
+def test_gemm_extents_below_a_piece(dt, layout, shape):
+    # rows on 8-byte boundaries whose extent is 8 bytes or a little more (four or six bf16, two or three fp32), along K and along
+    # M / N: planned freely (the larger results on the larger tiles) and on every tile
+    for extent in ((4, 6) if dt == "bf16" else (2, 3)):
+        M, N, K = (extent if s == "e" else s for s in shape)
+        A, Bm = (RNG.integers(-3, 4, size=s).astype(np.float32) for s in ((M, K), (K, N)))
+
+        def operand(a):
+            rows, cols = a.shape
+            unit = 4 if dt == "bf16" else 2
+            pitch = (cols + unit - 1) // unit * unit
+            buf = torch.zeros(rows, pitch, device="cuda", dtype=torch.float32 if dt == "f32" else torch.bfloat16)
+            buf[:, :cols].copy_(torch.from_numpy(a))
+            return buf[:, :cols]
+        Ad = operand(A) if layout[0] == "n" else operand(np.ascontiguousarray(A.T)).t()
+        Bd = operand(Bm) if layout[1] == "n" else operand(np.ascontiguousarray(Bm.T)).t()
+        want = A.astype(np.float64) @ Bm.astype(np.float64)
+        for tile, splits in ((-1, -1), (0, 1), (1, 1), (2, 1), (0, 2)):
+            if tile >= 0 and M * N > 10 ** 6:
+                continue
+            B.gemm_plan_override(tile, splits, -1)
+            try:
+                w = ws(B.gemm_workspace_bytes(Ad, Bd, empty((M, N))))
+                assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=w)), want), (extent, tile, splits)
+                C = dev(np.ones((M, N), np.float32))
+                assert np.array_equal(host(B.gemm(Ad, Bd, C, alpha=2.0, beta=-1.0, ws=w)), 2 * want - 1), (extent, tile, splits)
+            finally:
+                B.gemm_plan_override()
+        if dt == "f32":                                  # in three bfloat16 parts
+            for tile in (0, 1):
+                B.gemm_plan_override(tile, 1, 4)
+                try:
+                    assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)))), want), (extent, "parts", tile)
+                finally:
+                    B.gemm_plan_override()
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("layout,shape", [("nt", (128, 650, 2600)), ("nn", (128, 2600, 650)), ("tn", (100, 70, 4099)), ("nt", (33, 10, 3000))])
 def test_gemm_split_k(dt, layout, shape):
     # few output tiles and a long K: the product is cut along K when the caller provides the workspace
