@@ -163,11 +163,13 @@ __device__ __forceinline__ unsigned meet(unsigned *state, unsigned *ids, int pee
 // wave reads its k of h_{t-1} straight into the registers the instruction takes, and the sums meet in LDS.
 // h is its own message: what a step will write is filled with a bit pattern that no pair of values takes (kAbsent) three steps
 // ahead, and a reader loads what it needs until no word of it holds the pattern.  No counter, no acknowledged store, no second trip.
-// bf16: the message is the step's block of Hs itself.
+// bf16: the message is the step's block of Hs itself, which nobody reads again after its step.
 //
 // fp32: U and h are multiplied as three bfloat16 parts each (split.h).  The high and middle parts of U stay in registers, the low
 // parts in LDS; h is split by the lane that makes it and exchanged as parts, in the order the instruction reads them, through four
-// blocks of the workspace that take turns (a reader that splits for itself needs more registers than there are).
+// blocks of the workspace that take turns (a reader that splits for itself needs more registers than there are).  Step t fills the
+// block that step t - 1 read, and only behind its first barrier: there the four waves together have seen h_t of every member, which a
+// member sends when it has read the block for the last time.  (One wave's poll does not tell: it covers every fourth 32 k.)
 // Odd waves hold -U, so that the one-sided error of the instruction cancels.  A sum that is not finite (infinities, NaN,
 // 2^80 and more) is taken again on fp32 values.
 template <typename T, int S>
@@ -322,13 +324,13 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_fwd_kernel(FwdArgs a) {
       }
       if (!ok && lane == 0) { word[t & 1] = 1; give_up(a.status); }
       // ---- what the next steps need: their inputs on the way, the marks three steps ahead (acknowledged by this wait one
-      // step on, before the step is published after which a reader may look for them)
+      // step on, before the step is published after which a reader may look for them; fp32: behind the barrier)
       wait_vector_memory();
       u32x2 z[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) z[g] = zn[g];
       fetch(t + 1 < a.n_steps ? t + 1 : t);
-      mark(t + 3);
+      if constexpr (!kSplit) mark(t + 3);
       // ---- the product, two tiles at a time: 8 w .. 8 w + 7 are the units of wave w, to which the others hand their sums
       floatx4 own[2] = {floatx4{0, 0, 0, 0}, floatx4{0, 0, 0, 0}};
 #pragma unroll
@@ -380,6 +382,7 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_fwd_kernel(FwdArgs a) {
       }
       lds_barrier();
       if (word[t & 1]) break;
+      if constexpr (kSplit) mark(t + 3);
       if (wave < S) {
 #pragma unroll
         for (int s = 0; s < 3; ++s) {

@@ -312,3 +312,40 @@ def test_sequence_values_that_three_parts_do_not_hold():
         back = host(dHs)[t * Bn:(t + 1) * Bn] - dh_in[t * Bn:(t + 1) * Bn].astype(np.float64)
         S = np.abs(dz[nx]) @ np.abs(U.T).astype(np.float64) + np.abs(dh_in[t * Bn:(t + 1) * Bn])
         check(back, dz[nx] @ U.T.astype(np.float64), TOL_SUM, S, "dh of step %d" % t)
+
+
+@pytest.mark.parametrize("Bn,H,T", [(40, 272, 9), (128, 656, 12), (17, 40, 10)])
+def test_sequence_of_sums_taken_again(Bn, H, T):
+    """fp32, more steps than blocks of h: infinities and entries of 2^90 to 2^100 in U make the sums of a few units, in one or two
+    workgroups, overflow in every step, which read h again while the other workgroups go on.  Every step from the state that
+    the GPU left for it."""
+    zx, bias, h0, c0, U = inputs(Bn, H, T, "f32", 45)
+    odd = {"i": 7, "f": H // 2, "g": H - 3, "o": H - 9}
+    U[5, odd["i"]] = np.inf
+    U[11, H + odd["f"]] = -np.inf
+    U[13, 2 * H + odd["g"]] = np.float32(2.0 ** 90)
+    U[:, 3 * H + odd["o"]] *= np.float32(2.0 ** 100)
+    Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, "f32")
+    assert status_word(work) == 0
+    # four columns: saturated gates, in every step; all others as ever
+    special = [odd["i"], H + odd["f"], 2 * H + odd["g"], 3 * H + odd["o"]]
+    Hh, Ch, Gh = host(Hs), host(Cs), host(gates)
+    assert np.isfinite(Hh).all() and np.isfinite(Ch).all() and np.isfinite(Gh).all()
+    plain = U.copy()
+    plain[:, special] = 0
+    for t in range(T):
+        hp, cp, z0 = Hh[t * Bn:(t + 1) * Bn], Ch[t * Bn:(t + 1) * Bn], zx[t * Bn:(t + 1) * Bn]
+        z = (z0 + bias).astype(np.float64) + hp @ plain.astype(np.float64)
+        S = np.abs(z0) + np.abs(bias) + np.abs(hp) @ np.abs(plain).astype(np.float64)
+        want = 1.0 / (1.0 + np.exp(-z))
+        want[:, 2 * H:3 * H] = np.tanh(z[:, 2 * H:3 * H])
+        for col in special:
+            with np.errstate(all="ignore"):
+                zc = hp @ U[:, col].astype(np.float64) if np.isfinite(U[:, col]).all() else U[:, col][~np.isfinite(U[:, col])][0] * hp[:, 5 if col == special[0] else 11]
+            assert (np.abs(zc) > 1e3).all()
+            want[:, col] = np.sign(zc) if col == special[2] else (zc > 0).astype(np.float64)
+        got = Gh[t * Bn:(t + 1) * Bn]
+        check(got, want, TOL_SUM, S + 1e-1, "gates of step %d" % t)
+        c = got[:, H:2 * H] * cp + got[:, :H] * got[:, 2 * H:3 * H]
+        check(Ch[(t + 1) * Bn:(t + 2) * Bn], c, TOL_SUM, np.abs(cp) + 1, "c of step %d" % t)
+        check(Hh[(t + 1) * Bn:(t + 2) * Bn], got[:, 3 * H:] * np.tanh(c), TOL_SUM, 1.0, "h of step %d" % t)
