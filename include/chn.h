@@ -315,6 +315,11 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
  * default is 2^20).  With 0 the first wait gives up without looking: tests use it to see the status word
  * raised and the kernel end after its first step. */
 void chn_lstm_seq_spin_limit(int64_t polls);
+/* How the first kind of grid of chn_lstm_seq_fwd / _bwd comes to run (process-wide, for tests; (-1, 1) is the default):
+ * `patience` polls until a walk that has not begun is called off and left to the second kind (0: always; -1: 2^14, or the
+ * spin limit if that is less); share_l2 = 0: its workgroups exchange at device scope though they share an XCD's L2.
+ * Results do not depend on share_l2. */
+void chn_lstm_seq_meeting(int64_t patience, int share_l2);
 
 /* ---- softmax cross-entropy ------------------------------------------------------------------------
  * The classifier loss of the paper's MNIST example (Section "API Design"); textbook definition.

@@ -28,7 +28,7 @@ EPI = {n: i for i, n in enumerate(EPILOGUES)}
 EXPORTS = ["chn_elementwise_broadcast", "chn_reduce_axis_workspace_bytes", "chn_reduce_axis", "chn_reduce_axis_static", "chn_argmax_axis",
            "chn_gemm_workspace_bytes", "chn_gemm", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
            "chn_lstm_seq_workspace_bytes", "chn_lstm_seq_supported", "chn_lstm_seq_fwd",
-           "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit",
+           "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit", "chn_lstm_seq_meeting",
            "chn_softmax_ce_workspace_bytes", "chn_softmax_ce_fwd", "chn_softmax_ce_bwd", "chn_softmax_ce_bwd2", "chn_softmax_ce_fwd_bwd",
            "chn_sgd_update", "chn_sgd_update_multi", "chn_adam_update_multi", "chn_embed_fwd", "chn_embed_bwd",
            "chn_status_string", "chn_last_error", "chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel", "chn_gemm_plan_override",
@@ -105,6 +105,8 @@ def lib():
     L.chn_lstm_seq_bwd.argtypes = [AP, AP, AP, AP, AP, AP, AP, C.c_int64, C.c_void_p, C.c_size_t, st]
     L.chn_lstm_seq_spin_limit.argtypes = [C.c_int64]
     L.chn_lstm_seq_spin_limit.restype = None
+    L.chn_lstm_seq_meeting.argtypes = [C.c_int64, C.c_int]
+    L.chn_lstm_seq_meeting.restype = None
     L.chn_softmax_ce_workspace_bytes.argtypes = [C.c_int64]
     L.chn_softmax_ce_workspace_bytes.restype = C.c_size_t
     L.chn_softmax_ce_fwd.argtypes = [AP, AP, C.c_int64, AP, AP, AP, vp, C.c_size_t, st]
@@ -388,6 +390,10 @@ def lstm_seq_bwd(U, dHs, gates, Cs, dc_last, dZ, dc0, n_steps, ws, stream=None):
 
 def lstm_seq_spin_limit(polls):
     lib().chn_lstm_seq_spin_limit(int(polls))
+
+
+def lstm_seq_meeting(patience=-1, share_l2=True):
+    lib().chn_lstm_seq_meeting(int(patience), int(share_l2))
 
 
 def softmax_ce_workspace_bytes(n_rows):

@@ -532,6 +532,7 @@ __global__ __launch_bounds__(kThreads) void lstm_seq_bwd_kernel(SeqBwdArgs a) {
 }
 
 std::atomic<int> g_spin_limit{1 << 20};
+std::atomic<int> g_patience{-1}, g_share_l2{1};         // chn_lstm_seq_meeting
 
 chn_status view2(const chn_array *x, const char *name, bool out, int64_t rows, int64_t cols, int want_dtype, bool operand, int64_t *pitch) {
   CHN_TRY(validate(x, name, out));
@@ -593,6 +594,11 @@ size_t fwd_workspace_xcd(int64_t B) { return xcd::kFwdWords * sizeof(unsigned) +
 size_t bwd_workspace(int64_t B, int64_t H) { return 256 + bwd_counter_bytes(B) + bwd_exchange_bytes(B, H); }
 size_t bwd_workspace_xcd(int64_t B, int64_t H) { return std::max(bwd_workspace(B, H), xcd::kBwdWords * sizeof(unsigned) + xcd::bwd_messages(B, H)); }
 
+int patience(int spin_limit) {
+  const int p = g_patience.load();
+  return p >= 0 ? p : std::min(spin_limit, xcd::kPatience);
+}
+
 // Whether a pass goes to the kernels that exchange inside an XCD (lstm_xcd.hip): batches of up to 128 rows (sixteen per XCD),
 // widths of up to 768, a step's rows (`extent` elements at most) within 32-bit offsets, a workspace that holds their messages.
 // They were the faster at every size they take; a caller with the smaller workspace of the kernels here gets these.
@@ -616,6 +622,11 @@ size_t chn_lstm_seq_workspace_bytes(int64_t batch) {
 }
 
 void chn_lstm_seq_spin_limit(int64_t polls) { chn::g_spin_limit.store(polls < 0 ? 0 : polls > (1 << 30) ? (1 << 30) : (int)polls); }
+
+void chn_lstm_seq_meeting(int64_t patience, int share_l2) {
+  chn::g_patience.store(patience < 0 ? -1 : patience > (1 << 30) ? (1 << 30) : (int)patience);
+  chn::g_share_l2.store(share_l2);
+}
 
 chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_array *bias, const chn_array *Hs, const chn_array *Cs,
                             const chn_array *gates, int64_t n_steps, void *ws, size_t ws_bytes, chn_stream stream) {
@@ -663,7 +674,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
   if (in_xcd) {
     xcd::FwdArgs x{};
     x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_of(a.H);
-    x.spin_limit = a.spin_limit; x.patience = std::min(a.spin_limit, xcd::kPatience);
+    x.spin_limit = a.spin_limit; x.patience = patience(a.spin_limit); x.share = g_share_l2.load() ? ~0u : 0u;
     x.zx = a.zx; x.zx_pitch = a.zx_pitch;
     x.Ut = a.Ut; x.ut_pitch = a.ut_pitch;
     x.bias = a.bias;
@@ -747,7 +758,7 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
   if (in_xcd) {
     xcd::BwdArgs x{};
     x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_of(a.H);
-    x.spin_limit = a.spin_limit; x.patience = std::min(a.spin_limit, xcd::kPatience);
+    x.spin_limit = a.spin_limit; x.patience = patience(a.spin_limit); x.share = g_share_l2.load() ? ~0u : 0u;
     x.U = a.U; x.u_pitch = a.u_pitch;
     x.dHs = a.dHs; x.dh_pitch = a.dh_pitch;
     x.gates = a.gates; x.g_pitch = a.g_pitch;

@@ -22,6 +22,7 @@ constexpr int kFwdWords = kFirstFlag, kBwdWords = kFirstFlag + kFlagWords;
 
 struct FwdArgs {
   int B, H, n_steps, peers, spin_limit, patience;
+  unsigned share;            // the groups (a bit each) that may exchange through an L2
   const float *zx; int64_t zx_pitch;
   const void *Ut; int64_t ut_pitch;
   const float *bias;
@@ -33,6 +34,7 @@ struct FwdArgs {
 };
 struct BwdArgs {
   int B, H, n_steps, peers, spin_limit, patience;
+  unsigned share;
   const void *U; int64_t u_pitch;
   void *dHs; int64_t dh_pitch;
   const float *gates; int64_t g_pitch;

@@ -118,7 +118,7 @@ __device__ __forceinline__ void give_up(unsigned *status) { __hip_atomic_store(s
 // word decides, so that all see the same: kOpen with a bit for every group that shares an XCD, or kCalledOff, and the kernels
 // launched behind take over (two such grids on one device can each hold compute units the other waits for; then both leave here
 // after some milliseconds).  Run by one wave; returns the word.
-__device__ __forceinline__ unsigned meet(unsigned *state, unsigned *ids, int peers, int n_groups, int group, int idx, int lane, int patience) {
+__device__ __forceinline__ unsigned meet(unsigned *state, unsigned *ids, int peers, int n_groups, int group, int idx, int lane, int patience, unsigned share) {
   const unsigned mine = 1u + (unsigned)__builtin_amdgcn_s_getreg(20 | (3 << 11));      // hardware register 20, four bits: the XCD
   if (lane == 0) __hip_atomic_store(ids + group * kMaxPeers + idx, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const bool first = group == 0 && idx == 0;
@@ -141,7 +141,7 @@ __device__ __forceinline__ unsigned meet(unsigned *state, unsigned *ids, int pee
         const unsigned long long eights = __ballot(same);
         verdict = kOpen;
         for (int i = 0; i < kXcds; ++i)
-          if ((eights >> (8 * i) & 0xff) == 0xff) verdict |= 1u << i;
+          if ((eights >> (8 * i) & 0xff) == 0xff) verdict |= share & 1u << i;
         break;
       }
     } else {
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_fwd_kernel(FwdArgs a) {
   wait_vector_memory();                                // U, the first inputs; the marks are in place
   __syncthreads();
   if (wave == 0) {
-    const unsigned m = meet(a.state, a.ids, a.peers, n_groups, group, idx, lane, a.patience);
+    const unsigned m = meet(a.state, a.ids, a.peers, n_groups, group, idx, lane, a.patience, a.share);
     if (lane == 0) { word[0] = word[1] = 0; word[2] = (int)m; }
   }
   __syncthreads();
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   wait_vector_memory();
   __syncthreads();
   if (wave == 0) {
-    const unsigned m = meet(a.state, a.ids, G, n_groups, group, idx, lane, a.patience);
+    const unsigned m = meet(a.state, a.ids, G, n_groups, group, idx, lane, a.patience, a.share);
     if (lane == 0) { word[0] = word[1] = 0; word[2] = (int)m; }
   }
   __syncthreads();

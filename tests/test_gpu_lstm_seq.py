@@ -349,3 +349,77 @@ def test_sequence_of_sums_taken_again(Bn, H, T):
         c = got[:, H:2 * H] * cp + got[:, :H] * got[:, 2 * H:3 * H]
         check(Ch[(t + 1) * Bn:(t + 2) * Bn], c, TOL_SUM, np.abs(cp) + 1, "c of step %d" % t)
         check(Hh[(t + 1) * Bn:(t + 2) * Bn], got[:, 3 * H:] * np.tanh(c), TOL_SUM, 1.0, "h of step %d" % t)
+
+
+# ------------------------------------------------------------- how the kernels that exchange inside an XCD come to run, and end
+@pytest.fixture
+def meeting():
+    yield B.lstm_seq_meeting
+    B.lstm_seq_meeting()
+    B.lstm_seq_spin_limit(1 << 20)
+
+
+PATHS = [(33, 64, 5), (128, 272, 9), (70, 528, 6), (128, 672, 12)]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Bn,H,T", PATHS)
+def test_sequences_that_are_called_off_are_done_by_the_other_kernels(Bn, H, T, dt, meeting):
+    """Nobody waits for the others: the walk is called off before its first step, with marks where h will be, and the kernels launched
+    behind do the whole of it, bit for bit what they do by themselves."""
+    zx, bias, h0, c0, U = inputs(Bn, H, T, dt, 51)
+    alone = run(zx, bias, h0, c0, U, T, dt, work=ws(256 + 256 + 256))     # (no room for the messages of the first kind)
+    meeting(patience=0)
+    Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, dt)
+    assert status_word(work) == 0
+    check_against_oracle(zx, bias, U, T, dt, Hs, Cs, gates)
+    assert all(torch.equal(a, b) for a, b in zip((Hs, Cs, gates), alone))
+    U, dh_in, gates, Cs, dc_last = bwd_inputs(Bn, H, T, dt, 52)
+    dHs, dZ, dc0, work = run_bwd(U, dh_in, gates, Cs, dc_last, T, dt)
+    assert status_word(work) == 0
+    check_bwd_against_oracle(U, dh_in, gates, Cs, dc_last, T, dt, dHs, dZ, dc0)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Bn,H,T", PATHS)
+def test_sequences_that_exchange_at_device_scope(Bn, H, T, dt, meeting):
+    """As where a group's workgroups do not share an XCD: the same values another way, so the same bits."""
+    zx, bias, h0, c0, U = inputs(Bn, H, T, dt, 53)
+    through_l2 = run(zx, bias, h0, c0, U, T, dt)
+    bwd = bwd_inputs(Bn, H, T, dt, 54)
+    back = run_bwd(*bwd, T, dt)
+    meeting(share_l2=False)
+    for _ in range(2):
+        Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, dt)
+        assert status_word(work) == 0
+        assert all(torch.equal(a, b) for a, b in zip((Hs, Cs, gates), through_l2))
+        dHs, dZ, dc0, work = run_bwd(*bwd, T, dt)
+        assert status_word(work) == 0
+        assert all(torch.equal(a, b) for a, b in zip((dHs, dZ, dc0), back))
+    check_against_oracle(zx, bias, U, T, dt, Hs, Cs, gates)
+    check_bwd_against_oracle(*bwd, T, dt, dHs, dZ, dc0)
+
+
+@pytest.mark.parametrize("share_l2", [True, False])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_a_walk_that_gives_up_on_its_way_ends(dt, share_l2, meeting):
+    """The walk has begun, then its first wait runs out (spin limit 0) or one does somewhere (1): every workgroup leaves, the status word
+    is up and the kernels behind do not touch the outputs; the next call is complete."""
+    Bn, H, T = 128, 528, 9
+    zx, bias, h0, c0, U = inputs(Bn, H, T, dt, 55)
+    bwd = bwd_inputs(Bn, H, T, dt, 56)
+    for polls in (0, 1):
+        meeting(patience=1 << 14, share_l2=share_l2)
+        B.lstm_seq_spin_limit(polls)
+        Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, dt)
+        bufs = run_bwd(*bwd, T, dt)
+        if polls == 0:
+            assert status_word(work) == 1 and status_word(bufs[3]) == 1
+        meeting()
+        B.lstm_seq_spin_limit(1 << 20)
+        Hs, Cs, gates, work = run(zx, bias, h0, c0, U, T, dt, Hs, Cs, gates, work)
+        assert status_word(work) == 0
+        check_against_oracle(zx, bias, U, T, dt, Hs, Cs, gates)
+        dHs, dZ, dc0, work = run_bwd(*bwd, T, dt, bufs)
+        assert status_word(work) == 0
+        check_bwd_against_oracle(*bwd, T, dt, dHs, dZ, dc0)
