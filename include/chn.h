@@ -307,6 +307,9 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
  * kind of grid where that needs more), 256-byte aligned.  Waits, the status word
  * in the first 4 bytes of ws and chn_lstm_seq_spin_limit as for chn_lstm_seq_fwd. */
 chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype);
+/* 1 where that is the first kind of grid on the current device, for contiguous arrays and a whole workspace: there one launch
+ * for all steps is faster than one per step in BF16 too; else 0. */
+int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden);
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden);
 chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_array *gates, const chn_array *Cs,
                             const chn_array *dc_last, const chn_array *dZ, const chn_array *dc0, int64_t n_steps,

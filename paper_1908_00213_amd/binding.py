@@ -28,7 +28,7 @@ EPI = {n: i for i, n in enumerate(EPILOGUES)}
 EXPORTS = ["chn_elementwise_broadcast", "chn_reduce_axis_workspace_bytes", "chn_reduce_axis", "chn_reduce_axis_static", "chn_argmax_axis",
            "chn_gemm_workspace_bytes", "chn_gemm", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
            "chn_lstm_seq_workspace_bytes", "chn_lstm_seq_supported", "chn_lstm_seq_fwd",
-           "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit", "chn_lstm_seq_meeting",
+           "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_in_xcd", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit", "chn_lstm_seq_meeting",
            "chn_softmax_ce_workspace_bytes", "chn_softmax_ce_fwd", "chn_softmax_ce_bwd", "chn_softmax_ce_bwd2", "chn_softmax_ce_fwd_bwd",
            "chn_sgd_update", "chn_sgd_update_multi", "chn_adam_update_multi", "chn_embed_fwd", "chn_embed_bwd",
            "chn_status_string", "chn_last_error", "chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel", "chn_gemm_plan_override",
@@ -100,6 +100,7 @@ def lib():
     L.chn_lstm_seq_supported.argtypes = [C.c_int64, C.c_int64, C.c_int]
     L.chn_lstm_seq_fwd.argtypes = [AP, AP, AP, AP, AP, AP, C.c_int64, C.c_void_p, C.c_size_t, st]
     L.chn_lstm_seq_bwd_supported.argtypes = [C.c_int64, C.c_int64, C.c_int]
+    L.chn_lstm_seq_bwd_in_xcd.argtypes = [C.c_int64, C.c_int64]
     L.chn_lstm_seq_bwd_workspace_bytes.argtypes = [C.c_int64, C.c_int64]
     L.chn_lstm_seq_bwd_workspace_bytes.restype = C.c_size_t
     L.chn_lstm_seq_bwd.argtypes = [AP, AP, AP, AP, AP, AP, AP, C.c_int64, C.c_void_p, C.c_size_t, st]
@@ -372,9 +373,9 @@ def lstm_seq_bwd_supported(batch, hidden, dtype):
 
 
 def lstm_seq_bwd_in_xcd(batch, hidden):
-    """Whether lstm_seq_bwd walks these sizes inside the XCDs: then it is the faster one in bfloat16 too (128 x 672: 3.8 us per
+    """Whether lstm_seq_bwd walks these sizes inside the XCDs of the current device: then it is the faster one in bfloat16 too (128 x 672: 3.8 us per
     step, the fused per-step call 11.5, the kernel that exchanges through device memory 11.9)."""
-    return batch <= 128 and hidden <= 768
+    return lib().chn_lstm_seq_bwd_in_xcd(int(batch), int(hidden)) == 1
 
 
 def lstm_seq_bwd_workspace_bytes(batch, hidden):

@@ -703,6 +703,11 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
 
 chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype) { return chn::fits_bwd(batch, hidden, dtype); }
 
+int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden) {
+  const size_t need = chn_lstm_seq_bwd_workspace_bytes(batch, hidden);
+  return need > 0 && chn::exchanges_in_xcd(batch, hidden, 0, need, need);    // (whatever it takes has extents far below the limit)
+}
+
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden) {
   if (batch <= 0 || hidden <= 0 || hidden % chn::kBwdUnits) return 0;
   return chn::xcd::sizes_fit(batch, hidden) ? chn::bwd_workspace_xcd(batch, hidden) : chn::bwd_workspace(batch, hidden);

@@ -423,3 +423,10 @@ def test_a_walk_that_gives_up_on_its_way_ends(dt, share_l2, meeting):
         dHs, dZ, dc0, work = run_bwd(*bwd, T, dt, bufs)
         assert status_word(work) == 0
         check_bwd_against_oracle(*bwd, T, dt, dHs, dZ, dc0)
+
+
+def test_the_library_says_where_the_backward_pass_stays_inside_the_xcds():
+    """The answer follows the device (32 workgroups on each of eight XCDs need 256 compute units) and the sizes."""
+    whole = torch.cuda.get_device_properties(0).multi_processor_count >= 256
+    for Bn, H, fits in [(1, 16, True), (128, 672, True), (128, 768, True), (129, 672, False), (128, 784, False), (128, 1536, False), (16, 40, False)]:
+        assert B.lstm_seq_bwd_in_xcd(Bn, H) == (fits and whole), (Bn, H)
