@@ -268,9 +268,9 @@ chn_status chn_lstm_step_bwd(const chn_array *dz_next, const chn_array *U, const
  * the contraction cut in four; the gate activations on the hardware's exponential and reciprocal, relative
  * error a few 1e-7; agrees with them within the product tolerance).
  *
- * The grid stays on the device for the whole sequence.  Up to 128 rows and H <= 768: sixteen batch rows to an
+ * The grid stays on the device for the whole sequence.  Up to 128 rows, H <= 768 and from a few steps on: sixteen batch rows to an
  * XCD, up to 32 workgroups there that hold their units' rows of Ut in registers and exchange h through its L2;
- * if these do not all come to run within some milliseconds, or beyond those sizes: (H/8) x ceil(B/64) workgroups,
+ * if these do not all come to run within some milliseconds, or for fewer steps or beyond those sizes: (H/8) x ceil(B/64) workgroups,
  * each holding its rows of Ut in LDS, that exchange h through device memory.  Every workgroup must be resident at
  * once: H % 8 == 0 (BF16: % 16), a row of h of at most 3072 bytes (H <= 768 F32, 1536 BF16) and no more
  * of the latter workgroups than the device has compute units; otherwise CHN_ERR_SHAPE and the caller uses the per-step
@@ -309,7 +309,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
 chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype);
 /* 1 where that is the first kind of grid on the current device, for contiguous arrays and a whole workspace: there one launch
  * for all steps is faster than one per step in BF16 too; else 0. */
-int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden);
+int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden, int64_t n_steps, int dtype);
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden);
 chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_array *gates, const chn_array *Cs,
                             const chn_array *dc_last, const chn_array *dZ, const chn_array *dc0, int64_t n_steps,
@@ -320,7 +320,7 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
 void chn_lstm_seq_spin_limit(int64_t polls);
 /* How the first kind of grid of chn_lstm_seq_fwd / _bwd comes to run (process-wide, for tests; (-1, 1) is the default):
  * `patience` polls until a walk that has not begun is called off and left to the second kind (0: always; -1: 2^14, or the
- * spin limit if that is less); share_l2 = 0: its workgroups exchange at device scope though they share an XCD's L2.
+ * spin limit if that is less; any value but -1 takes sequences of every length to the first kind); share_l2 = 0: its workgroups exchange at device scope though they share an XCD's L2.
  * Results do not depend on share_l2. */
 void chn_lstm_seq_meeting(int64_t patience, int share_l2);
 

@@ -100,7 +100,7 @@ def lib():
     L.chn_lstm_seq_supported.argtypes = [C.c_int64, C.c_int64, C.c_int]
     L.chn_lstm_seq_fwd.argtypes = [AP, AP, AP, AP, AP, AP, C.c_int64, C.c_void_p, C.c_size_t, st]
     L.chn_lstm_seq_bwd_supported.argtypes = [C.c_int64, C.c_int64, C.c_int]
-    L.chn_lstm_seq_bwd_in_xcd.argtypes = [C.c_int64, C.c_int64]
+    L.chn_lstm_seq_bwd_in_xcd.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
     L.chn_lstm_seq_bwd_workspace_bytes.argtypes = [C.c_int64, C.c_int64]
     L.chn_lstm_seq_bwd_workspace_bytes.restype = C.c_size_t
     L.chn_lstm_seq_bwd.argtypes = [AP, AP, AP, AP, AP, AP, AP, C.c_int64, C.c_void_p, C.c_size_t, st]
@@ -372,10 +372,10 @@ def lstm_seq_bwd_supported(batch, hidden, dtype):
     return lib().chn_lstm_seq_bwd_supported(int(batch), int(hidden), _DTYPES[dtype]) == 0
 
 
-def lstm_seq_bwd_in_xcd(batch, hidden):
+def lstm_seq_bwd_in_xcd(batch, hidden, n_steps, dtype):
     """Whether lstm_seq_bwd walks these sizes inside the XCDs of the current device: then it is the faster one in bfloat16 too (128 x 672: 3.8 us per
     step, the fused per-step call 11.5, the kernel that exchanges through device memory 11.9)."""
-    return lib().chn_lstm_seq_bwd_in_xcd(int(batch), int(hidden)) == 1
+    return lib().chn_lstm_seq_bwd_in_xcd(int(batch), int(hidden), int(n_steps), _DTYPES[dtype]) == 1
 
 
 def lstm_seq_bwd_workspace_bytes(batch, hidden):

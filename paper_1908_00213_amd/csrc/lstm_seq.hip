@@ -600,11 +600,12 @@ int patience(int spin_limit) {
 }
 
 // Whether a pass goes to the kernels that exchange inside an XCD (lstm_xcd.hip): batches of up to 128 rows (sixteen per XCD),
-// widths of up to 768, a step's rows (`extent` elements at most) within 32-bit offsets, a workspace that holds their messages.
-// They were the faster at every size they take; a caller with the smaller workspace of the kernels here gets these.
-bool exchanges_in_xcd(int64_t B, int64_t H, int64_t extent, size_t have, size_t need) {
+// widths of up to 768, steps enough, a step's rows (`extent` elements at most) within 32-bit offsets, a workspace that holds their
+// messages; a caller with the smaller workspace of the kernels here gets these.  (A patience that tests have set: whatever the steps.)
+bool exchanges_in_xcd(bool backward, bool bf16, int64_t B, int64_t H, int64_t n_steps, int64_t extent, size_t have, size_t need) {
   int dev = 0, cus = 0;
-  if (have < need || extent >= (int64_t(1) << 28)) return false;
+  if (have < need || extent >= (int64_t(1) << 28) || !xcd::sizes_fit(B, H)) return false;
+  if (n_steps < xcd::least_steps(backward, bf16, B, H) && g_patience.load() < 0) return false;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
   return xcd::takes(B, H, cus);
 }
@@ -668,7 +669,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
   a.counters = reinterpret_cast<unsigned *>(static_cast<char *>(ws) + 256);
   hipStream_t st = as_stream(stream);
   const int64_t extent = std::max({a.B * a.h_pitch, a.B * a.c_pitch, a.B * a.zx_pitch, a.B * a.g_pitch, 4 * a.H * a.ut_pitch, a.B * 4 * a.H});
-  const bool in_xcd = exchanges_in_xcd(a.B, a.H, extent, ws_bytes, fwd_workspace_xcd(a.B));
+  const bool in_xcd = exchanges_in_xcd(false, t == CHN_BF16, a.B, a.H, n_steps, extent, ws_bytes, fwd_workspace_xcd(a.B));
   hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kFwdWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq clear"));
   if (in_xcd) {
@@ -703,9 +704,9 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
 
 chn_status chn_lstm_seq_bwd_supported(int64_t batch, int64_t hidden, int dtype) { return chn::fits_bwd(batch, hidden, dtype); }
 
-int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden) {
+int chn_lstm_seq_bwd_in_xcd(int64_t batch, int64_t hidden, int64_t n_steps, int dtype) {
   const size_t need = chn_lstm_seq_bwd_workspace_bytes(batch, hidden);
-  return need > 0 && chn::exchanges_in_xcd(batch, hidden, 0, need, need);    // (whatever it takes has extents far below the limit)
+  return need > 0 && chn::exchanges_in_xcd(true, dtype == CHN_BF16, batch, hidden, n_steps, 0, need, need);    // (whatever it takes has extents far below the limit)
 }
 
 size_t chn_lstm_seq_bwd_workspace_bytes(int64_t batch, int64_t hidden) {
@@ -757,7 +758,7 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
   const int64_t extent = std::max({a.B * a.dh_pitch, a.B * a.c_pitch, a.B * a.dz_pitch, a.B * a.g_pitch, a.H * a.u_pitch, a.B * 4 * a.H});
   // (pairs of bfloat16 gradients are read in one access there)
   const bool pairs = t == CHN_F32 || (reinterpret_cast<uintptr_t>(dHs->data) % 4 == 0 && a.dh_pitch % 2 == 0);
-  const bool in_xcd = pairs && exchanges_in_xcd(a.B, a.H, extent, ws_bytes, bwd_workspace_xcd(a.B, a.H));
+  const bool in_xcd = pairs && exchanges_in_xcd(true, t == CHN_BF16, a.B, a.H, n_steps, extent, ws_bytes, bwd_workspace_xcd(a.B, a.H));
   hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kBwdWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq_bwd clear"));
   if (in_xcd) {

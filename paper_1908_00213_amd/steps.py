@@ -269,7 +269,7 @@ class LSTMTrainer:
         fits = fused_step and B.lstm_seq_bwd_supported(Bn, Hp, adt)
         if whole_sequence_bwd and not fits:
             raise ValueError("LSTMTrainer: the whole-sequence backward kernel does not take batch %d, hidden %d: %s" % (Bn, Hp, B.lib().chn_last_error().decode()))
-        fits = fits and self.whole_sequence and (not lowp or B.lstm_seq_bwd_in_xcd(Bn, Hp))
+        fits = fits and self.whole_sequence and (not lowp or B.lstm_seq_bwd_in_xcd(Bn, Hp, T, adt))
         self.whole_sequence_bwd = fits if whole_sequence_bwd is None else bool(whole_sequence_bwd)
         self.ws_seq_bwd = torch.zeros(B.lstm_seq_bwd_workspace_bytes(Bn, Hp), dtype=torch.uint8, device="cuda") if self.whole_sequence_bwd else None
         # fp32: the two backward products of the output layer read one operand along its strided

@@ -113,14 +113,16 @@ class GpuBackend:
         else:
             self.B.lstm_step_fwd_seq(zx, Hs, Ut, bias, Cs, gates, n_steps)
 
-    def lstm_sequence_bwd(self, Bn, hidden, dtype):
-        """Whether the backward pass over all steps is one launch that pays (tensor or tape dtype)."""
-        dtype = {"f32": self.torch.float32, "bf16": self.torch.bfloat16}.get(dtype, dtype)
-        return (dtype == self.torch.float32 or self.B.lstm_seq_bwd_in_xcd(Bn, hidden)) and self.B.lstm_seq_bwd_supported(Bn, hidden, dtype)
+    def lstm_sequence_bwd(self, Bn, U, n_steps):
+        """Whether the backward pass over all steps is one launch that pays, and takes U as it lies."""
+        hidden, dtype = U.shape[0], U.dtype
+        if n_steps <= 0 or not self.B.lstm_seq_bwd_supported(Bn, hidden, dtype):
+            return False
+        return dtype == self.torch.float32 or self.B.lstm_seq_bwd_in_xcd(Bn, hidden, n_steps, dtype)
 
     def lstm_steps_bwd(self, dZ, U, dHs, gates, Cs, dc_last, dc, n_steps):
         Bn = dZ.shape[0] // max(1, n_steps)
-        if n_steps > 0 and self.lstm_sequence_bwd(Bn, dHs.shape[1], dHs.dtype):
+        if self.lstm_sequence_bwd(Bn, U, n_steps):
             ws = self._bytes(self.B.lstm_seq_bwd_workspace_bytes(Bn, dHs.shape[1]))
             self.B.lstm_seq_bwd(U, dHs, gates, Cs, dc_last, dZ, dc[0], n_steps, ws)
             self._pending(ws)
@@ -1397,7 +1399,7 @@ class NStepLSTM(FunctionNode):
         dc_next = gc
         # in fp32 three separate calls per step are faster than the fused one, the whole sequence in one launch is faster than both
         whole = getattr(F, "lstm_sequence_bwd", None)
-        fused_bwd = self.fused and (self.lowp or (T > 0 and whole is not None and whole(Bn, H, adt)))
+        fused_bwd = self.fused and (self.lowp or (whole is not None and whole(Bn, U, T)))
         if fused_bwd:                              # per step: dh_t += dz_{t+1} U^T, then the cell
             F.lstm_steps_bwd(dZ, U, dHs, G, Cs, gc, dc, T)
         else:

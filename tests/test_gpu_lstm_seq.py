@@ -426,7 +426,36 @@ def test_a_walk_that_gives_up_on_its_way_ends(dt, share_l2, meeting):
 
 
 def test_the_library_says_where_the_backward_pass_stays_inside_the_xcds():
-    """The answer follows the device (32 workgroups on each of eight XCDs need 256 compute units) and the sizes."""
+    """The answer follows the device (32 workgroups on each of eight XCDs need 256 compute units), the sizes and the steps."""
     whole = torch.cuda.get_device_properties(0).multi_processor_count >= 256
     for Bn, H, fits in [(1, 16, True), (128, 672, True), (128, 768, True), (129, 672, False), (128, 784, False), (128, 1536, False), (16, 40, False)]:
-        assert B.lstm_seq_bwd_in_xcd(Bn, H) == (fits and whole), (Bn, H)
+        for dt in (torch.float32, torch.bfloat16):
+            assert B.lstm_seq_bwd_in_xcd(Bn, H, 6, dt) == (fits and whole), (Bn, H)
+            assert not B.lstm_seq_bwd_in_xcd(Bn, H, 2, dt)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("Bn,H,T", EDGES)
+def test_sequence_edges_inside_the_xcds(Bn, H, T, dt, meeting):
+    """As test_sequence_edges, where few steps are left to the other kernels otherwise; those do the same to the last roundings."""
+    def both(call, check_it):
+        meeting(patience=1 << 14)
+        first = call()
+        assert status_word(first[-1]) == 0
+        check_it(*first[:-1])
+        meeting()
+        usual = call()
+        assert status_word(usual[-1]) == 0
+        check_it(*usual[:-1])
+    if H % (8 if dt == "f32" else 16) == 0:
+        zx, bias, h0, c0, U = inputs(Bn, H, T, dt, 61)
+        both(lambda: run(zx, bias, h0, c0, U, T, dt), lambda Hs, Cs, gates: check_against_oracle(zx, bias, U, T, dt, Hs, Cs, gates))
+    if H % 16 == 0:
+        bwd = bwd_inputs(Bn, H, T, dt, 62)
+        both(lambda: run_bwd(*bwd, T, dt), lambda dHs, dZ, dc0: check_bwd_against_oracle(*bwd, T, dt, dHs, dZ, dc0))
+
+
+def test_overflowing_products_inside_the_xcds(meeting):
+    """As test_sequence_values_that_three_parts_do_not_hold, whose three steps are left to the other kernels otherwise."""
+    meeting(patience=1 << 14)
+    test_sequence_values_that_three_parts_do_not_hold()
