@@ -89,9 +89,11 @@ struct RPlan {
 // 4.6 and 4.4; fp32 40000 3.8 and 4.4, 60000 4.6 and 4.4, but 32 rows of 40000 5.5 and 4.9.
 constexpr int64_t kCutRow = 32768, kCutRows = 256, kSliceElems = 4096;
 constexpr int kMaxSlices = 8192;                            // over all rows
-// Many rows of at most this many bytes are a wave's each instead of a block's, eight vectors per lane in flight: 10000 x 4001 bf16
-// 20.3 -> 16.3 us, fp32 28.7 -> 24.3, 8192 x 3200 fp32 20.1 -> 16.8.
-constexpr int64_t kWaveRows = 2048, kWaveRowBytes = 16384;
+// Many rows of kWaveRowLen elements and more, up to kWaveRowBytes, are a wave's each instead of a block's, eight vectors per lane in
+// flight (us, a block's against a wave's: 8192 x 2048 bf16 6.4 and 4.4, 8192 x 4001 bf16 12.2 and 11.2, 8192 x 2500 fp32 13.4 and 11.4).
+// Fewer rows leave the chip too few loads in flight (1024 x 4001 bf16 3.2 and 3.4, 2000 x 2500 fp32 3.3 and 3.7; at 3000 it depends on
+// the length), and so do longer ones to each wave (16384 x 4096 fp32 38 and 42).
+constexpr int64_t kWaveRows = 4096, kWaveRowLen = 2048, kWaveRowBytes = 10240;
 bool cut_pays(int64_t rows, int64_t len, int isz) {
   return len >= (isz == 2 ? 65536 : rows <= 8 ? 57344 : rows <= 16 ? 45056 : kCutRow);
 }
@@ -211,51 +213,45 @@ __global__ __launch_bounds__(256) void fill_kernel(Tout *out, int64_t n, float v
   if (i < n) Elem<Tout>::store(out + i, v);
 }
 
-// A vector's elements, folded as a tree.
-template <int OP, typename T>
-__device__ __forceinline__ float fold_vec(const Vec16<T> &x) {
-  constexpr int N = Vec16<T>::N;
-  float v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = x.get(i);
-#pragma unroll
-  for (int h = N / 2; h > 0; h /= 2)
-#pragma unroll
-    for (int i = 0; i < h; ++i) v[i] = fold<OP>(v[i], v[i + h]);
-  return v[0];
-}
-
 // One lane's share of a row of `len` elements: G lanes, four accumulators each, folded in an order that depends on len
-// alone.  BATCHES of four 16-byte loads are in flight at once, in the last, partial batch too: there a lane past the end takes
-// the row's last vector and drops it (one by one, each waited for the one before, and with 256 lanes a row of 4001 bf16 is
-// nothing but such a rest).
+// alone.  BATCHES of four 16-byte loads are in flight at once, and so are those of the last vectors, fewer than a batch, and of
+// the elements behind them (one after the other they took a trip to memory each: 10000 x 4001 bf16 16.3 -> 14.5 us, 8192 x 1000 fp32
+// 6.1 -> 5.7; a lane without a vector loads none: with the last one in its place 16384 x 500 bf16 takes 6.1, so 4.5).
 template <int OP, typename Tin, int G, bool VEC, int BATCHES>
 __device__ __forceinline__ float fold_row(const Tin *p, int64_t len, int g) {
   float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
   if constexpr (VEC) {
     constexpr int N = Vec16<Tin>::N;
-    const int64_t nvec = len / N, at = nvec * N + g;
-    const float rest = at < len ? Elem<Tin>::load(p + at) : identity<OP>();   // (at most N - 1 of them, G >= N lanes)
-    constexpr int U = 4 * BATCHES;
-    for (int64_t v0 = 0; v0 < nvec; v0 += U * G) {
-      const Tin *q = p + v0 * N;
-      Vec16<Tin> x[U];
-      if (v0 + U * G <= nvec) {
+    const int64_t nvec = len / N;
+    int64_t v = g;
+    auto batches = [&](auto count) __attribute__((always_inline)) {
+      constexpr int U = 4 * decltype(count)::value;
+      for (; v + (U - 1) * G < nvec; v += U * G) {
+        Vec16<Tin> x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(q + (g + u * G) * N);
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc[u & 3] = fold<OP>(acc[u & 3], fold_vec<OP>(x[u]));
-      } else {
-        const int left = (int)(nvec - v0);
+        for (int u = 0; u < U; ++u) x[u] = load16_any_nt(p + (v + u * G) * N);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          if (u * G < left) x[u] = load16_any(q + min(g + u * G, left - 1) * N);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (u * G < left) acc[u & 3] = fold<OP>(acc[u & 3], g + u * G < left ? fold_vec<OP>(x[u]) : identity<OP>());
+          for (int i = 0; i < N; ++i) acc[u & 3] = fold<OP>(acc[u & 3], x[u].get(i));
       }
-    }
-    acc[3] = fold<OP>(acc[3], rest);
+    };
+    if constexpr (BATCHES > 1) batches(std::integral_constant<int, BATCHES>{});
+    batches(std::integral_constant<int, 1>{});
+    const int left = (int)(nvec - v);
+    Vec16<Tin> x[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (u * G < left) x[u] = load16_any(p + (v + u * G) * N);
+    const int64_t at = nvec * N + g;
+    const float rest = at < len ? Elem<Tin>::load(p + at) : identity<OP>();   // (at most N - 1 of them, G >= N lanes)
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (u * G < left) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i & 3] = fold<OP>(acc[i & 3], x[u].get(i));
+      }
+    acc[1] = fold<OP>(acc[1], rest);
   } else {
     int64_t c = g;
     for (; c + 3 * G < len; c += 4 * G) {
@@ -269,6 +265,38 @@ __device__ __forceinline__ float fold_row(const Tin *p, int64_t len, int g) {
   }
   return fold<OP>(fold<OP>(acc[0], acc[1]), fold<OP>(acc[2], acc[3]));
 }
+// The same for a mid-size row that one wave folds: eight vectors per lane in flight, in the last, partial batch too.
+template <int OP, typename Tin>
+__device__ __forceinline__ float fold_row_by_wave(const Tin *p, int64_t len, int g) {
+  constexpr int N = Vec16<Tin>::N, G = 64, U = 8;
+  float acc[4] = {identity<OP>(), identity<OP>(), identity<OP>(), identity<OP>()};
+  const int64_t nvec = len / N, at = nvec * N + g;
+  int64_t v = 0;
+  for (; v + U * G <= nvec; v += U * G) {
+    Vec16<Tin> x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = load16_any_nt(p + (v + g + u * G) * N);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[u & 3] = fold<OP>(acc[u & 3], x[u].get(i));
+  }
+  const int left = (int)(nvec - v);
+  const Tin *q = p + v * N;
+  Vec16<Tin> x[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (g + u * G < left) x[u] = load16_any(q + (g + u * G) * N);
+  const float rest = at < len ? Elem<Tin>::load(p + at) : identity<OP>();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (g + u * G < left) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[u & 3] = fold<OP>(acc[u & 3], x[u].get(i));
+    }
+  acc[1] = fold<OP>(acc[1], rest);
+  return fold<OP>(fold<OP>(acc[0], acc[1]), fold<OP>(acc[2], acc[3]));
+}
 template <int OP, int W>
 __device__ __forceinline__ float fold_lanes(float a) {
 #pragma unroll
@@ -278,7 +306,7 @@ __device__ __forceinline__ float fold_lanes(float a) {
 
 // ROW: G lanes per row, 256 / G rows per block.
 // G = 256: a row may be cut in `slices` slices of `slice` elements, one block each; `rows` then counts slices.
-template <int OP, typename Tin, typename Tout, int G, bool VEC, int BATCHES = 1>
+template <int OP, typename Tin, typename Tout, int G, bool VEC>
 __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *out, int64_t rows, int64_t len, int64_t pitch, int slices = 1, int64_t slice = 0) {
   constexpr int RPB = 256 / G;
   const int g = threadIdx.x % G;
@@ -291,7 +319,7 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
       p = in + r * pitch + first;
       len = len - first < slice ? len - first : slice;
     }
-    a = fold_row<OP, Tin, G, VEC, BATCHES>(p, len, g);
+    a = fold_row<OP, Tin, G, VEC, 1>(p, len, g);
   }
   a = fold_lanes<OP, (G < 64 ? G : 64)>(a);
   if constexpr (G == 256) {
@@ -303,6 +331,15 @@ __global__ __launch_bounds__(256) void reduce_row_kernel(const Tin *in, Tout *ou
   } else {
     if (g == 0 && row < rows) Elem<Tout>::store(out + row, a);
   }
+}
+
+template <int OP, typename Tin, typename Tout>
+__global__ __launch_bounds__(256) void reduce_row_by_wave_kernel(const Tin *in, Tout *out, int64_t rows, int64_t len, int64_t pitch) {
+  const int g = threadIdx.x % 64;
+  const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+  if (row >= rows) return;
+  const float a = fold_lanes<OP, 64>(fold_row_by_wave<OP, Tin>(in + row * pitch, len, g));
+  if (g == 0) Elem<Tout>::store(out + row, a);
 }
 
 // ROW without a workspace for the slices' results: one block folds all slices of its row in the same order, so that the
@@ -519,8 +556,10 @@ chn_status launch(const RPlan &p, const chn_array *in, const chn_array *out, voi
     if (vec) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, true>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0); \
     else hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, G, false>), dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0);    \
   } while (0)
-    if (p.len * (int64_t)sizeof(Tin) > (rows >= kWaveRows ? kWaveRowBytes : 2048 * (int64_t)sizeof(Tin) - 1) || rows < 512) CHN_ROW(256);
-    else if (p.len > 4 * 64 * n) hipLaunchKernelGGL((reduce_row_kernel<OP, Tin, Tout, 64, true, 2>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, src, dst, rows, p.len, pitch, 1, (int64_t)0);
+    if (rows >= kWaveRows && p.len >= kWaveRowLen && p.len * (int64_t)sizeof(Tin) <= kWaveRowBytes) {
+      if ((rows + 3) / 4 > 0x7fffffff) return fail(CHN_ERR_SHAPE, "reduce: too many rows");
+      hipLaunchKernelGGL((reduce_row_by_wave_kernel<OP, Tin, Tout>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, src, dst, rows, p.len, pitch);
+    } else if (p.len >= 2048 || rows < 512) CHN_ROW(256);
     else if (p.len > 64) CHN_ROW(64);
     else CHN_ROW(8);
 #undef CHN_ROW

@@ -801,3 +801,22 @@ def test_rows_of_partial_batches(dt, rows, vectors, rest):
     assert bool(((out.double() - ref).abs() <= 74 * 2.0 ** -24 * S).all())
     B.reduce_axis("max", x, 1, out, ws=w)
     assert torch.equal(out, x.float().amax(1))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("vectors,rest", [(256, 0), (257, 1), (448, 2), (511, 3), (512, 0), (513, 0), (575, 1), (639, 3), (640, 0), (640, 1)])
+def test_many_mid_size_rows(dt, vectors, rest):
+    # a wave per row: partial and whole batches of eight vectors per lane, with and without elements behind the last vector, on both
+    # sides of the lengths where the kernels change (a last block of rows that is not full); what lies between the rows is NaN
+    rows, n = 4099, vectors * (8 if dt == "bf16" else 4) + rest
+    g = torch.Generator(device="cuda").manual_seed(vectors)
+    buf = torch.full((rows, n + 3), float("nan"), device="cuda", dtype=torch.float32 if dt == "f32" else torch.bfloat16)
+    x = buf[:, :n]
+    x.copy_(torch.randn(rows, n, generator=g, device="cuda"))
+    out = torch.full((rows + 1,), 7.0, device="cuda")
+    ref, S = x.double().sum(1), x.double().abs().sum(1)
+    B.reduce_axis("sum", x, 1, out[:rows])
+    # at most 24 values one after the other and one behind them, then trees: 33 roundings of partial sums
+    assert bool(((out[:rows].double() - ref).abs() <= 33 * 2.0 ** -24 * S).all()) and float(out[rows]) == 7.0
+    B.reduce_axis("max", x, 1, out[:rows])
+    assert torch.equal(out[:rows], x.float().amax(1)) and float(out[rows]) == 7.0
