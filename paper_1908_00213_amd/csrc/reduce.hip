@@ -429,7 +429,8 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
     } else if constexpr (VEC) {
       // Eight rows in flight per lane, then one batch of four and single ones (14795 x 296 fp32 22.7 -> 16.5 us, 16384 x 1024
       // bf16 14.5 -> 12.2 against four); four where the many narrow blocks of wide fp32 arrays keep memory busy as it is
-      // (4000 x 8000 23.3, would be 24.3).
+      // (4000 x 8000 23.3, would be 24.3).  The single ones stay in the caches: where rows start off cache lines, a neighbour
+      // wants the other part of the line (3000 x 2351 bf16 7.8 us, past the caches 9.5).
       constexpr int kBatch = sizeof(Tin) == 4 && kColTX == kColTXWide ? 4 : 8;
       auto batch = [&](auto count) __attribute__((always_inline)) {
         constexpr int U = decltype(count)::value;
@@ -444,7 +445,11 @@ __global__ __launch_bounds__(256) void reduce_col_kernel(const Tin *in, Tout *ou
       };
       while (r + (kBatch - 1) * kColTY < r_end) batch(std::integral_constant<int, kBatch>{});
       if (kBatch > 4 && r + 3 * kColTY < r_end) batch(std::integral_constant<int, 4>{});
-      while (r < r_end) batch(std::integral_constant<int, 1>{});
+      for (; r < r_end; r += kColTY) {
+        const Vec16<Tin> x = load16_any(p + r * sR);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] = fold<OP>(acc[i], x.get(i));
+      }
     } else {
       for (; r + 3 * kColTY < r_end; r += 4 * kColTY) {
         float x[4];
