@@ -116,7 +116,8 @@ class GpuBackend:
     def lstm_sequence_bwd(self, Bn, U, n_steps):
         """Whether the backward pass over all steps is one launch that pays, and takes U as it lies."""
         hidden, dtype = U.shape[0], U.dtype
-        if n_steps <= 0 or not self.B.lstm_seq_bwd_supported(Bn, hidden, dtype):
+        rows16 = U.stride(1) == 1 and U.data_ptr() % 16 == 0 and U.stride(0) * U.element_size() % 16 == 0
+        if n_steps <= 0 or not rows16 or not self.B.lstm_seq_bwd_supported(Bn, hidden, dtype):
             return False
         return dtype == self.torch.float32 or self.B.lstm_seq_bwd_in_xcd(Bn, hidden, n_steps, dtype)
 

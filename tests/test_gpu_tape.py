@@ -414,3 +414,29 @@ def test_tape_function_made_of_two_user_kernels():
     assert abs(got[0] - ref[0]) <= 1e-5 * abs(ref[0])
     for a, b in zip(got[1], ref[1]):
         check(a, b, 1e-4, float(np.max(np.abs(b))), "gradient")
+
+
+@pytest.mark.parametrize("steps_", [2, 6])
+@pytest.mark.parametrize("layout", ["pitched", "off16", "transposed"])
+def test_n_step_lstm_takes_the_recurrent_matrix_as_it_lies(layout, steps_):
+    """fp32: the products take U in any layout, so the whole call does (the kernels of a whole sequence need its rows on 16 bytes)."""
+    n, H = 20, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    U = rnd(H, 4 * H) * 0.1
+    if layout == "transposed":
+        view = U.t().contiguous().t()
+    else:
+        view = torch.empty(H, 4 * H + (4 if layout == "pitched" else 3), device="cuda")[:, (0 if layout == "pitched" else 1):][:, :4 * H]
+        view.copy_(U)
+    c0, h0, zx, b, ghs = rnd(n, H), rnd(n, H) * 0.5, rnd(steps_ * n, 4 * H), rnd(4 * H), rnd(steps_ * n, H)
+
+    def once(matrix):
+        ps = [T.Parameter(a.clone(), None, "p") for a in (c0, h0, zx)] + [T.Parameter(matrix, None, "U"), T.Parameter(b.clone(), None, "b")]
+        c, h, hs = T.n_step_lstm(*ps, steps_)
+        hs.grad = ghs.clone()
+        hs.backward()
+        return [hs.array, c.array] + [p.grad for p in ps]
+    for got, want in zip(once(view), once(U)):
+        cmp(got, host(want), 1e-5, layout)
+    T.backend().check_sequences()
