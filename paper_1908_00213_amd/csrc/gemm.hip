@@ -139,6 +139,20 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
       if (t < best * (small_direct ? 1.0 : 0.97)) { best = t; g->tile = tile; g->splits = s; }   // prefer larger tiles / fewer splits on near-ties
     }
   }
+  // The four stages of the directly copied 64x64 tile leave room for two of its blocks on a compute unit, the two of the staged one for
+  // more.  With more blocks than that and a single tile step, a few where no operand is to be transposed, a block is its first loads and its
+  // epilogue, and the staged kernel has more of them under way (us, direct and staged: 4728x2016x96 19.4 and 15.2, 1000x2728x64 7.0
+  // and 6.0, both along M/N 7176x1248x16 16.7 and 13.1, but 2224x1472x192 8.1 and 10.7, 2176x1456x128 7.6 and 9.6).  Instead of the
+  // 256x256 tile only with both operands along K and up to 3072 blocks (2376x3408x192 19.2 and 16.4; 7928x3704x64 21.0 and 25.4).
+  // Fitted on 149 products of 513 to 7200 blocks, K 8 to 512.
+  bool many_staged = false;
+  const int64_t small_tiles = (int64_t)((g->M + 63) / 64) * ((g->N + 63) / 64);
+  if (small_direct_on && small_tiles > 512 && g->K <= (lay == 0 ? 256 : 64) && (g->tile < 2 || (lay == 0 && small_tiles <= 3072))) {
+    const int64_t full = small_tiles / 1024, rem = small_tiles % 1024;
+    const double step = lay == 0 ? 0.27 : 0.33, shared = 1.6 + 0.8 * (double)((rem + 255) / 256 - 1);
+    const double t = 1e-6 * ((double)full * (2.0 + 4.0 * nk * step) + (rem > 0 ? 2.0 + nk * step * shared : 0.0));
+    if (t < best) { best = t; g->tile = 0; g->splits = 1; many_staged = true; }
+  }
   // The 256 x 128 tile of the eight-wave kernel (bf16, both operands K-contiguous): taken when it fills the chip
   // in one round without a cut along K where the square tile cannot (N near 1000 with a long M).
   const bool narrow_ok = direct && isz == 2 && a_kc && b_kc && !big_unsplit && g_force_w8.load(std::memory_order_relaxed) != 0;
@@ -150,7 +164,7 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   }
   {   // chn_gemm_plan_override
     const int force_tile = g_force_tile.load(std::memory_order_relaxed), force_splits = g_force_splits.load(std::memory_order_relaxed);
-    if (force_tile >= 0 && force_tile <= largest) g->tile = force_tile;
+    if (force_tile >= 0 && force_tile <= largest) { g->tile = force_tile; many_staged = false; }
     if (force_tile == 3 && narrow_ok) g->tile = 3;
     if (force_tile >= 0 && force_tile != 3 && g->tile == 3) g->tile = largest;
     if (force_splits >= 1 && allow_split && force_splits <= nk) g->splits = force_splits;
@@ -160,7 +174,7 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   g->tiles_m = (g->M + bm - 1) / bm;
   g->tiles_n = (g->N + bn - 1) / bn;
   g->ldp = (g->N + 3) & ~3;
-  g->dma = g->tile >= 2 ? direct : small_direct_on;
+  g->dma = g->tile >= 2 ? direct : small_direct_on && !many_staged;
   g->parts = 0;
   return best;
 }

@@ -310,6 +310,22 @@ def test_gemm_operands_at_any_address(tile, dt, layout, shape, offset):
     assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=ws(need))), want)
 
 
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", [(2056, 1032, 8), (1032, 2120, 64), (2112, 1096, 72), (4160, 2056, 256)])
+def test_gemm_short_products_of_many_blocks(layout, shape):
+    # more than two 64x64 blocks per compute unit, one to four tile steps; whole numbers, so every order of the sums gives the same
+    M, N, K = shape
+    A, Bm = (RNG.integers(-3, 4, size=s).astype(np.float32) for s in ((M, K), (K, N)))
+    Ad = dev(A, "bf16") if layout[0] == "n" else dev(np.ascontiguousarray(A.T), "bf16").t()
+    Bd = dev(Bm, "bf16") if layout[1] == "n" else dev(np.ascontiguousarray(Bm.T), "bf16").t()
+    want = A.astype(np.float64) @ Bm.astype(np.float64)
+    if K <= 64 or (K == 72 and layout == "nt"):
+        assert B.gemm_plan_kernel(Ad, Bd, empty((M, N))) == "staged"
+    C = dev(np.ones((M, N), np.float32))
+    assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)))), want)
+    assert np.array_equal(host(B.gemm(Ad, Bd, C, alpha=2.0, beta=-1.0)), 2 * want - 1)
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
 @pytest.mark.parametrize("shape", [(130, 260, "e"), (2048, 4096, "e"), ("e", 300, 1000), (140, "e", 515), ("e", 2000, 4096), ("e", 300, "e")])
