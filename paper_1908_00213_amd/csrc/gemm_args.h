@@ -20,6 +20,7 @@ struct GemmArgs {
   void *pre;
   int64_t ldpre;
   int piece;              // bytes per global load piece (16, 8 or the item size), common to A and B
+  int piece_a, piece_b;   // what A and B allow each
   int any_a, any_b;       // whether the unit-stride extent of A, of B holds a 16-byte piece (which the smaller tiles read at any address)
   int piece_exact;        // the same when no piece may hang over the end of a row (direct-copy kernels)
   int tiles_m, tiles_n;

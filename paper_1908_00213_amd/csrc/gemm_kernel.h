@@ -1661,18 +1661,34 @@ chn_status launch_piece(const GemmArgs &g, hipStream_t st) {
   return CHN_OK;
 }
 
+// Pieces of the register-staged kernel.  On the small tile each operand is read in the largest it allows: 16 aligned bytes, 16 at any
+// address, 8 (both operands), single elements (us, an aligned operand read at any address and in aligned pieces: bf16 2688x3072x6 16.7
+// and 13.2, 1088x256x6 4.9 and 4.3; fp32 3x1760x1520 13.1 and 11.4).  Rows on the 8-byte grid are read in 8-byte pieces where a
+// compute unit has one block at most, which waits for its first loads: those come without the moves of a cut piece.  Time at any
+// address over that in 8-byte pieces, 700 drawn products: bf16 with B along N 1.05-1.10 at every K; along K 1.13 up to 64 k, 1.07 to 256,
+// 1.03 to 512, 0.98 beyond; A along M and B along K 1.11, 1.06, 1.06, 0.98; both along M/N 1.00; with more blocks 0.70-0.95.  fp32 both
+// along K 1.03, else 0.96-1.00.
 template <typename T, int TM, int TN, bool A_KC, bool B_KC>
 chn_status launch_tile(const GemmArgs &g, hipStream_t st) {
+  constexpr int E = (int)sizeof(T);
   if (g.piece == 16) return launch_piece<T, TM, TN, A_KC, B_KC, 16>(g, st);
+  if constexpr (TM == 1) {
+    constexpr bool kHalves = E == 2 ? A_KC || B_KC : A_KC && B_KC;
+    if (kHalves && g.piece == 8 && g.tiles_m * g.tiles_n <= 256 && (E == 4 || (g.splits == 1 && (g.K <= 512 || !B_KC)))) return launch_piece<T, 1, 1, A_KC, B_KC, 8>(g, st);
+    if (g.any_a && g.piece_b == 16) return launch_piece<T, 1, 1, A_KC, B_KC, kAnyPiece, 16>(g, st);
+    if (g.any_b && g.piece_a == 16) return launch_piece<T, 1, 1, A_KC, B_KC, 16, kAnyPiece>(g, st);
+  }
   if constexpr (TM < 4) {
     if (g.any_a && g.any_b) return launch_piece<T, TM, TN, A_KC, B_KC, kAnyPiece>(g, st);
   }
   if (g.piece == 8) return launch_piece<T, TM, TN, A_KC, B_KC, 8>(g, st);   // (the smaller tiles: an extent below 16 bytes)
   if constexpr (TM == 1) {
     // one operand whose extent is below a piece (a K of 3, say) does not slow down the other's loads
-    if (g.any_b) return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T), kAnyPiece>(g, st);
-    if (g.any_a) return launch_piece<T, 1, 1, A_KC, B_KC, kAnyPiece, (int)sizeof(T)>(g, st);
-    return launch_piece<T, 1, 1, A_KC, B_KC, (int)sizeof(T)>(g, st);
+    if (g.piece_b == 16) return launch_piece<T, 1, 1, A_KC, B_KC, E, 16>(g, st);
+    if (g.piece_a == 16) return launch_piece<T, 1, 1, A_KC, B_KC, 16, E>(g, st);
+    if (g.any_b) return launch_piece<T, 1, 1, A_KC, B_KC, E, kAnyPiece>(g, st);
+    if (g.any_a) return launch_piece<T, 1, 1, A_KC, B_KC, kAnyPiece, E>(g, st);
+    return launch_piece<T, 1, 1, A_KC, B_KC, E>(g, st);
   }
   return fail(CHN_ERR_LAUNCH, "gemm: internal: the operands do not allow the planned tile");
 }

@@ -310,6 +310,40 @@ def test_gemm_operands_at_any_address(tile, dt, layout, shape, offset):
     assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=ws(need))), want)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
+@pytest.mark.parametrize("shape", [(130, 264, 72), (64, 40, 3), (3, 136, 640), (104, 5, 264), (70, 72, 1), (9, 264, 1032)])
+@pytest.mark.parametrize("grids", [(16, 4), (4, 16), (16, 1), (1, 16), (8, 16), (8, 8), (4, 1)])
+def test_gemm_operands_on_different_grids(dt, layout, shape, grids):
+    # rows of A and of B on 16-byte boundaries, on 8- or 4-byte ones (grids: bytes), on none (1), extents from one element on: every
+    # pair of piece sizes of the small tile; whole numbers, so every order of the sums gives the same
+    M, N, K = shape
+    A, Bm = (RNG.integers(-3, 4, size=s).astype(np.float32) for s in ((M, K), (K, N)))
+    isz = 4 if dt == "f32" else 2
+
+    def operand(a, grid):
+        rows, cols = a.shape
+        unit = max(1, grid // isz)
+        pitch = (cols + unit - 1) // unit * unit
+        if unit < 16 // isz and pitch * isz % (2 * unit * isz) == 0:
+            pitch += unit                          # (on this grid and on no coarser one)
+        buf = torch.zeros(rows, pitch, device="cuda", dtype=torch.float32 if dt == "f32" else torch.bfloat16)
+        buf[:, :cols].copy_(torch.from_numpy(a))
+        return buf[:, :cols]
+    Ad = operand(A, grids[0]) if layout[0] == "n" else operand(np.ascontiguousarray(A.T), grids[0]).t()
+    Bd = operand(Bm, grids[1]) if layout[1] == "n" else operand(np.ascontiguousarray(Bm.T), grids[1]).t()
+    want = A.astype(np.float64) @ Bm.astype(np.float64)
+    for splits in (1, 2):
+        B.gemm_plan_override(0, splits, -1)
+        try:
+            w = ws(B.gemm_workspace_bytes(Ad, Bd, empty((M, N))))
+            assert np.array_equal(host(B.gemm(Ad, Bd, empty((M, N)), ws=w)), want), splits
+            C = dev(np.ones((M, N), np.float32))
+            assert np.array_equal(host(B.gemm(Ad, Bd, C, alpha=2.0, beta=-1.0, ws=w)), 2 * want - 1), splits
+        finally:
+            B.gemm_plan_override()
+
+
 @pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
 @pytest.mark.parametrize("shape", [(2056, 1032, 8), (1032, 2120, 64), (2112, 1096, 72), (4160, 2056, 256)])
 def test_gemm_short_products_of_many_blocks(layout, shape):
