@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "lstm_cell.h"
 #include "lstm_xcd.h"
 
 namespace chn {
@@ -62,19 +63,6 @@ __device__ __forceinline__ void mma_pair(floatx16 &acc0, floatx16 &acc1, const u
       acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float((&a1.x)[kk]), __uint_as_float((&b.x)[kk]), acc1, 0, 0, 0);
     }
   }
-}
-
-// Activations of the cell on the hardware's exponential and reciprocal (relative error a few 1e-7): between two
-// exchanges the cell is on the critical path of every step, and the library's expf / tanhf are a third of it.
-__device__ __forceinline__ float sigmoid_hw(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-// tanh: (1 - e) / (1 + e) with e = exp(-2 |x|) cancels for small |x|; there the odd series takes over (its first
-// dropped term, 62/2835 x^9, is below 1e-7 of x for |x| < 0.25), so that the relative error stays at a few 1e-7.
-__device__ __forceinline__ float tanh_hw(float x) {
-  const float ax = fabsf(x), e = __expf(-2.0f * ax);
-  const float big = copysignf((1.0f - e) * __builtin_amdgcn_rcpf(1.0f + e), x);
-  const float x2 = x * x;
-  const float small = x * fmaf(x2, fmaf(x2, fmaf(x2, -17.0f / 315.0f, 2.0f / 15.0f), -1.0f / 3.0f), 1.0f);
-  return ax < 0.25f ? small : big;
 }
 
 struct SeqArgs {

@@ -12,6 +12,7 @@
 //
 // Every wait is bounded, as in lstm_seq.hip: after `spin_limit` polls a wave raises the status word and its workgroup leaves; the
 // others run out of polls, or see the word, and leave too.
+#include "lstm_cell.h"
 #include "lstm_xcd.h"
 #include "split.h"
 
@@ -34,16 +35,6 @@ constexpr int kNowhere = 0x7ffffff0;                   // a byte offset past eve
 constexpr unsigned kAbsent = 0xffffffffu;              // what a word of h holds until its value arrives
 constexpr int kMayCross = 0x7f6;                       // sched_barrier: everything but matrix instructions
 constexpr float kUnscale = 1.0f / (kSplitScale * kSplitScale);
-
-__device__ __forceinline__ float sigmoid_hw(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-// (odd series where 1 - exp(-2 |x|) would cancel: relative error a few 1e-7 throughout)
-__device__ __forceinline__ float tanh_hw(float x) {
-  const float ax = fabsf(x), e = __expf(-2.0f * ax);
-  const float big = copysignf((1.0f - e) * __builtin_amdgcn_rcpf(1.0f + e), x);
-  const float x2 = x * x;
-  const float small = x * fmaf(x2, fmaf(x2, fmaf(x2, -17.0f / 315.0f, 2.0f / 15.0f), -1.0f / 3.0f), 1.0f);
-  return ax < 0.25f ? small : big;
-}
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t resource(const void *p, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
