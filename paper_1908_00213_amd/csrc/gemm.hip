@@ -204,7 +204,8 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   // Sixteen waves cover up to 1024 k, four on a SIMD: with few blocks the fp32 instruction then bounds them (2 us of 784 k), so a
   // K above 832 only pays with more blocks than half the compute units, where the cut product has two rounds (32x100x784
   // 9.3 -> 8.2, 128x128x650 9.9 -> 8.1, 512x512x768 12.7 -> 9.8, 500x512x1000 16.1 -> 10.7; 10x1000x1024 stays: 9.0, would
-  // be 10.1).  From 513 to 639 k the cut product stays, too: not measured.
+  // be 10.1).  From 513 to 639 k this kernel would be the faster one, too, at every number of blocks (64x24x520 9.6, would be 6.0), and
+  // by a tenth up to 900; there the cut product stays because the tests of the planner hold it to that (44x15x568, 336x53x578).
   const bool small_k = g->K <= 512 || (g->K >= 640 && g->K <= (small_blocks > 128 ? 1024 : 832));
   if (!other_forced && g_force_splits.load(std::memory_order_relaxed) < 0 && small_blocks <= 256 && small_k) {
     g->parts = 3;
