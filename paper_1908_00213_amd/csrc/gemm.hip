@@ -149,10 +149,22 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   bool many_staged = false;
   const int64_t small_tiles = (int64_t)((g->M + 63) / 64) * ((g->N + 63) / 64);
   if (small_direct_on && small_tiles > 512 && g->K <= (lay == 0 ? 256 : 64) && (g->tile < 2 || (lay == 0 && small_tiles <= 3072))) {
-    const int64_t full = small_tiles / 1024, rem = small_tiles % 1024;
-    const double step = lay == 0 ? 0.27 : 0.33, shared = 1.6 + 0.8 * (double)((rem + 255) / 256 - 1);
-    const double t = 1e-6 * ((double)full * (2.0 + 4.0 * nk * step) + (rem > 0 ? 2.0 + nk * step * shared : 0.0));
-    if (t < best) { best = t; g->tile = 0; g->splits = 1; many_staged = true; }
+    // (four blocks of the staged 64x64 tile at once on a compute unit, or two of the 128x128 one: that where its rounds come out even,
+    // 5700 blocks of 64x64, 1450 of 128x128, 28.6 and 23.8)
+    const int64_t large_tiles = (int64_t)((g->M + 127) / 128) * ((g->N + 127) / 128);
+    auto rounds = [&](int64_t blocks, int at_once, double fixed, double step) {
+      const int64_t full = blocks / (256 * at_once), rem = blocks % (256 * at_once);
+      const double lone = at_once == 4 ? 1.6 : 1.5, more = (at_once - lone) / (at_once - 1);
+      return 1e-6 * ((double)full * (fixed + at_once * nk * step) + (rem > 0 ? fixed + nk * step * (lone + more * (double)((rem + 255) / 256 - 1)) : 0.0));
+    };
+    const double small = rounds(small_tiles, 4, 2.0, lay == 0 ? 0.27 : 0.33);
+    const double large = lay < 2 ? rounds(large_tiles, 2, 5.0, step_bf16[1][lay]) : 1e300;
+    if (small < best) {
+      best = small < large ? small : large;
+      g->tile = small < large ? 0 : 1;
+      g->splits = 1;
+      many_staged = true;
+    }
   }
   // The 256 x 128 tile of the eight-wave kernel (bf16, both operands K-contiguous): taken when it fills the chip
   // in one round without a cut along K where the square tile cannot (N near 1000 with a long M).

@@ -258,14 +258,14 @@ def test_passes_that_share_a_workspace_do_not_grow():
 
 def test_short_bf16_products_of_many_blocks_are_staged_through_registers():
     # more than two 64x64 blocks per compute unit and few tile steps: the direct-copy kernel has too few of them under way
-    for M, N, K, layouts, kernel in [(4728, 2016, 96, "nt", "staged"), (7176, 1248, 16, "tt", "staged"), (1000, 2728, 64, "nt", "staged"),
-                                     (2304, 2224, 24, "tn", "staged"), (824, 4560, 320, "nn", "direct4"), (1024, 1000, 784, "nt", "direct4"),
-                                     (1000, 1000, 64, "nt", "direct4")]:
+    for M, N, K, layouts, kernel, tile in [(4728, 2016, 96, "nt", "staged", 0), (7176, 1248, 16, "tt", "staged", 0), (1000, 2728, 64, "nt", "staged", 0),
+                                           (2304, 2224, 24, "tn", "staged", 0), (5760, 1152, 16, "nn", "staged", 1), (2752, 2696, 32, "nn", "staged", 1),
+                                           (824, 4560, 320, "nn", "direct4", 1), (1024, 1000, 784, "nt", "direct4", 0), (1000, 1000, 64, "nt", "direct4", 0)]:
         A = B.raw_desc(P, (M, K), (K * 2, 2) if layouts[0] == "n" else (2, M * 2), B.BF16)
         Bm = B.raw_desc(P, (K, N), (N * 2, 2) if layouts[1] == "n" else (2, K * 2), B.BF16)
         Cm = B.raw_desc(P, (M, N), (N * 2, 2), B.BF16)
-        got = B.gemm_plan_kernel(A, Bm, Cm, True)
-        assert got == kernel and (got != "staged" or B.gemm_plan(A, Bm, Cm, True) == (0, False, 1)), (M, N, K, got)
+        got = B.gemm_plan_kernel(A, Bm, Cm, True), B.gemm_plan(A, Bm, Cm, True)
+        assert got == (kernel, (tile, False, 1)), (M, N, K, got)
 
 
 _PRODUCTS = r"""

@@ -345,7 +345,7 @@ def test_gemm_operands_on_different_grids(dt, layout, shape, grids):
 
 
 @pytest.mark.parametrize("layout", ["nt", "nn", "tn", "tt"])
-@pytest.mark.parametrize("shape", [(2056, 1032, 8), (1032, 2120, 64), (2112, 1096, 72), (4160, 2056, 256)])
+@pytest.mark.parametrize("shape", [(2056, 1032, 8), (1032, 2120, 64), (2112, 1096, 72), (4160, 2056, 256), (2752, 2696, 32)])
 def test_gemm_short_products_of_many_blocks(layout, shape):
     # more than two 64x64 blocks per compute unit, one to four tile steps; whole numbers, so every order of the sums gives the same
     M, N, K = shape
