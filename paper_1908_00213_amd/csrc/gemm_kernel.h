@@ -119,7 +119,8 @@ __device__ __forceinline__ uint4 load_chunk(uintptr_t p, int n_valid) {
 // row cuts (along K in the last tile step, along M/N in the last tile) is read so that it ends with the row, and its elements
 // move down to their places when it is stored; the operand's extent holds a piece at least (the host checks).  Element by
 // element, as such operands used to be read, a tile step waits for 8 (fp32: 4) times as many loads.  bf16, both along K, us, element-wise -> here:
-// 1024x1001x785 35.7 -> 14.5, 4097x2351x2041 464 -> 116, 8192x4001x651 521 -> 152.
+// 1024x1001x785 35.7 -> 14.5, 4097x2351x2041 464 -> 116, 8192x4001x651 521 -> 152 (98 and 97 with the
+// epilogue at any address).
 constexpr int kAnyPiece = 1;
 __device__ __forceinline__ uint4 load_any(uintptr_t addr) {
   const chn_u32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) chn_u32x4_any *>(addr);

@@ -218,14 +218,15 @@ class LSTMTrainer:
     """
 
     def __init__(self, P, T, Bn, lr=0.01, lowp=False, fused_step=True, whole_sequence=None, whole_sequence_bwd=None):
-        """whole_sequence: the T forward steps are ONE launch (chn_lstm_seq_fwd: the grid stays on the device,
-        each workgroup keeps its rows of the recurrent matrix in LDS and the workgroups exchange h through
-        device memory between steps).  None = wherever the library takes the shape (fused_step only).
-        Measured on workload 4: 5.1 us instead of 14.3 us per step in fp32, 2.5 instead of 8.0 us in
-        mixed precision.  The T backward steps are one launch too (chn_lstm_seq_bwd: 6.0 us per step in
-        fp32, 4.0 in mixed precision, where the per-step fused call takes 11.6; in mixed precision only
-        where the launch walks inside the XCDs).  `whole_sequence_bwd` overrides that choice.  The kernels'
-        waits are bounded;
+        """whole_sequence: the T forward steps are ONE launch (chn_lstm_seq_fwd).  Up to 128 rows, 768 hidden units
+        and from a few steps on every XCD walks through its own sixteen rows, the recurrent matrix in registers
+        and h exchanged through its L2; else, and where that walk cannot begin, the workgroups keep their rows
+        of the recurrent matrix in LDS and exchange h through device memory.  None = wherever the library takes
+        the shape (fused_step only).  Measured on workload 4, inside the XCDs: 5.1 us instead of 14.3 us per step
+        in fp32, 2.5 instead of 8.0 us in mixed precision.  The T backward steps are one launch too
+        (chn_lstm_seq_bwd: 6.0 us per step in fp32, 4.0 in mixed precision, where the per-step fused call takes
+        11.6; in mixed precision only where the launch walks inside the XCDs, chn_lstm_seq_bwd_in_xcd).
+        `whole_sequence_bwd` overrides that choice.  The kernels' waits are bounded;
         `sequence_complete()` tells whether one ran out (then the step's results and the parameters it
         updated are invalid).
 
