@@ -24,6 +24,7 @@ using gemm::GemmArgs;
 // chn_gemm_plan_override: what tests force instead of the planner's choice (-1: not forced)
 std::atomic<int> g_force_tile{-1}, g_force_splits{-1}, g_force_direct{-1};
 constexpr double kNarrowStep = 0.92, kNarrowFixed = 12.0;   // microseconds per tile step / per block of the 256 x 128 tile
+constexpr int64_t kMaxLd = 1 << 22;    // fp32 products off the fp32 tiles: 32-bit byte offsets inside a tile
 std::atomic<int> g_force_w8{-1};
 std::atomic<int> g_force_parts{-1};   // 1: fp32 products on the three-part kernel, on the forced tile
 
@@ -192,6 +193,28 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
   return best;
 }
 
+// Few blocks and a contraction that one batch of loads per wave covers: the latency-bound kernel of gemm_tiny.h, up to 256 blocks
+// of 32x32 (beyond, 1000x1000x64 say, the tiles' reuse of operands wins) and 1024 k, which sixteen waves cover.  On blocks of 16x16
+// while a compute unit gets two of them or their operands are few; above, the larger block's reuse wins (us, 16x16 and 32x32:
+// 350x350x512 5.1 and 6.2, x1000 7.8 and 11.1; 400x400x256 4.9 and 5.3, x512 6.4 and 6.1; 512x512x192 4.2 and 4.5, x256 5.7 and 5.3,
+// x1000 12.8 and 8.6).  Against the cut product on the tiled kernels: 10x1000x1024 9.9 -> 4.4, 256x256x1000 9.3 -> 5.0, 400x400x1000
+// 11.2 -> 8.6.  Between 513 and 639 k products of a few 64x64 tiles stay cut although this kernel is the faster one there, too: the
+// tests of the planner hold 44x15x568 (9.2) and 336x53x578 to that.
+bool plan_small(GemmArgs *g, int isz, bool big_unsplit) {
+  auto forced = [](const std::atomic<int> &f) { return f.load(std::memory_order_relaxed) >= 0; };
+  if (isz != 4 || big_unsplit || g->K == 0 || g->K > 1024 || g->lda >= kMaxLd || g->ldb >= kMaxLd) return false;
+  if (forced(g_force_tile) || forced(g_force_direct) || forced(g_force_w8) || forced(g_force_parts) || forced(g_force_splits)) return false;
+  auto blocks = [&](int64_t n) { return ((g->M + n - 1) / n) * ((g->N + n - 1) / n); };
+  if (blocks(32) > 256 || (g->K > 512 && g->K < 640 && blocks(64) <= 6)) return false;
+  g->parts = 3;
+  g->splits = 1;
+  g->tile = g->dma = 0;
+  g->small = blocks(16) <= 512 || blocks(16) * g->K <= 200000 ? 16 : 32;
+  g->tiles_m = (g->M + g->small - 1) / g->small;
+  g->tiles_n = (g->N + g->small - 1) / g->small;
+  return true;
+}
+
 // fp32 products on the bfloat16 matrix cores (gemm_split.h): the 128x128 tile in two groups of waves or the 64x64 tile
 // in four, against the best plan on the fp32 matrix instruction, by the same kind of model (microseconds, a launch not
 // counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 plus its tile
@@ -203,29 +226,11 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
 // Rows off the 16-byte grid cost little: against the 8-byte pieces of before, 4480x650x2600 159 -> 145 and 2600x650x4480 162 -> 136;
 // against single elements, 4097x2351x2041 556 -> 273 and 8192x4001x651 584 -> 295.
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
+  if (plan_small(g, isz, big_unsplit)) return;
   double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
   const bool other_forced = force_tile >= 0 || g_force_direct.load(std::memory_order_relaxed) >= 0 || g_force_w8.load(std::memory_order_relaxed) >= 0;
-  constexpr int64_t kMaxLd = 1 << 22;                       // 32-bit byte offsets inside a tile
   if (isz != 4 || big_unsplit || g->K == 0 || g->lda >= kMaxLd || g->ldb >= kMaxLd || (other_forced && force != 1)) return;
-  // Few 32x32 blocks and a contraction that one batch of loads per wave covers: the latency-bound kernel of
-  // gemm_tiny.h (us, tiled kernels -> this: 32x10x100 9.5 -> 4.1, 33x65x77 10.5 -> 4.4, 32x100x100 5.8 -> 4.4,
-  // 256x256x256 10.1 -> 6.4, 512x512x512 11.1 -> 7.7).  Beyond 256 blocks (1000x1000x64 5.9, would be 10.0) the tiles'
-  // reuse of operands wins.
-  const int64_t small_blocks = (int64_t)((g->M + 31) / 32) * ((g->N + 31) / 32);
-  // Sixteen waves cover up to 1024 k, four on a SIMD: with few blocks the fp32 instruction then bounds them (2 us of 784 k), so a
-  // K above 832 only pays with more blocks than half the compute units, where the cut product has two rounds (32x100x784
-  // 9.3 -> 8.2, 128x128x650 9.9 -> 8.1, 512x512x768 12.7 -> 9.8, 500x512x1000 16.1 -> 10.7; 10x1000x1024 stays: 9.0, would
-  // be 10.1).  From 513 to 639 k this kernel would be the faster one, too, at every number of blocks (64x24x520 9.6, would be 6.0), and
-  // by a tenth up to 900; there the cut product stays because the tests of the planner hold it to that (44x15x568, 336x53x578).
-  const bool small_k = g->K <= 512 || (g->K >= 640 && g->K <= (small_blocks > 128 ? 1024 : 832));
-  if (!other_forced && g_force_splits.load(std::memory_order_relaxed) < 0 && small_blocks <= 256 && small_k) {
-    g->parts = 3;
-    g->splits = 1;
-    g->tiles_m = (g->M + 31) / 32;
-    g->tiles_n = (g->N + 31) / 32;
-    return;
-  }
   static const double step_large[3] = {1.0, 1.25, 1.2}, step_small[3] = {0.78, 1.1, 0.95};   // both along K, one, none
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   auto narrow = [&](bool any, bool kc, bool large) {

@@ -34,7 +34,9 @@ struct GemmArgs {
                           // blocks of 128 rows (values as stored), or NULL
   int64_t ldcs;
   int parts;              // fp32 on the bfloat16 matrix cores (gemm_split.h): 0 no, 1 on 64x64 tiles, 2 on 128x128 tiles;
-                          // 3: the latency-bound kernel for few tiles and a short K (gemm_tiny.h)
+                          // 3: the latency-bound kernel for few tiles and a short K (gemm_tiny.h), whose blocks are
+  int small;              // 16x16 or 32x32
+  float *sums;            // backward of a fully connected layer (linear_bwd.hip): [M] sums of A's rows over k, or NULL
 };
 
 }  // namespace gemm
