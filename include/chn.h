@@ -214,6 +214,18 @@ chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, 
                     float beta, int epilogue, const chn_array *bias, const chn_array *aux,
                     const chn_array *preact_out, void *ws, size_t ws_bytes, chn_stream stream);
 
+/* The backward of a fully connected layer y = x W^T + b (figure "Examples of model definitions") in one call, for callers that have
+ * the gradient dv (M,N) of y, the weights W (N,K) and the input x (M,K), all F32 or all BF16:
+ *   dW (N,K) F32 = dv^T x    db (N,) F32 = column sums of dv    dx (M,K) = epilogue(dv W)
+ * db and dx may be NULL (W is then not looked at).  epilogue is NONE, RELU_BWD or GELU_BWD, with aux as in chn_gemm.  The same results
+ * up to summation order as
+ *   chn_gemm(dv^T, x, dW), chn_reduce_axis(SUM, dv, 0, db), chn_gemm(dv, W, dx, epilogue, aux)
+ * in this order, which it issues for large products, for layouts other than unit-stride rows of dv and x, and where an output
+ * may overlap another array; otherwise one kernel does all three.  Workspace (optional) and errors as for those calls. */
+size_t chn_linear_bwd_workspace_bytes(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW);
+chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_array *x, int epilogue, const chn_array *aux, const chn_array *dx,
+                          const chn_array *dW, const chn_array *db, void *ws, size_t ws_bytes, chn_stream stream);
+
 /* ---- LSTM cell ------------------------------------------------------------------------------------
  * The paper names LSTMs as a motivating model class (Section "Introduction") and an RNN language
  * model as an application; it prints no equations, so the cell is the textbook one without
@@ -517,7 +529,7 @@ int chn_elementwise_plan(int op, int n_in, const chn_array *const *in, const chn
  * have_workspace = 0 plans as chn_gemm does without workspace). */
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);
 /* The kernel that plan runs on: operand tiles staged through registers, copied straight into LDS by four or eight
- * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K up to 512 to 1024 straight
+ * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K up to 1024 straight
  * from memory to the matrix registers (chn_gemm_plan describes those as a 64x64 tile without a cut).  Negative: an error. */
 enum { CHN_GEMM_KERNEL_STAGED = 0, CHN_GEMM_KERNEL_DIRECT4 = 1, CHN_GEMM_KERNEL_DIRECT8 = 2, CHN_GEMM_KERNEL_PARTS = 3, CHN_GEMM_KERNEL_SMALL = 4 };
 int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);

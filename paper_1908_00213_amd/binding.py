@@ -26,7 +26,7 @@ EPILOGUES = ["none", "bias", "bias_relu", "bias_gelu", "relu_bwd", "gelu_bwd", "
 EPI = {n: i for i, n in enumerate(EPILOGUES)}
 
 EXPORTS = ["chn_elementwise_broadcast", "chn_reduce_axis_workspace_bytes", "chn_reduce_axis", "chn_reduce_axis_static", "chn_argmax_axis",
-           "chn_gemm_workspace_bytes", "chn_gemm", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
+           "chn_gemm_workspace_bytes", "chn_gemm", "chn_linear_bwd_workspace_bytes", "chn_linear_bwd", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
            "chn_lstm_seq_workspace_bytes", "chn_lstm_seq_supported", "chn_lstm_seq_fwd",
            "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_in_xcd", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit", "chn_lstm_seq_meeting",
            "chn_softmax_ce_workspace_bytes", "chn_softmax_ce_fwd", "chn_softmax_ce_bwd", "chn_softmax_ce_bwd2", "chn_softmax_ce_fwd_bwd",
@@ -90,6 +90,9 @@ def lib():
     L.chn_gemm_plan_kernel.argtypes = [AP, AP, AP, C.c_int]
     L.chn_gemm_plan_override.argtypes = [C.c_int, C.c_int, C.c_int]
     L.chn_gemm_plan_override.restype = None
+    L.chn_linear_bwd_workspace_bytes.argtypes = [AP] * 5
+    L.chn_linear_bwd_workspace_bytes.restype = C.c_size_t
+    L.chn_linear_bwd.argtypes = [AP, AP, AP, C.c_int, AP, AP, AP, AP, vp, C.c_size_t, st]
     L.chn_gemm.argtypes = [AP, AP, AP, C.c_float, C.c_float, C.c_int, AP, AP, AP, vp, C.c_size_t, st]
     L.chn_lstm_fwd.argtypes = [AP, AP, AP, AP, AP, AP, st]
     L.chn_lstm_bwd.argtypes = [AP, AP, AP, AP, AP, AP, AP, st]
@@ -323,6 +326,18 @@ def gemm(A, B, Cm, alpha=1.0, beta=0.0, epilogue="none", bias=None, aux=None, pr
                           _ref(desc(bias)), _ref(desc(aux)), _ref(desc(preact_out)), p, n,
                           _stream() if stream is None else stream))
     return Cm
+
+
+def linear_bwd_workspace_bytes(dv, W, x, dx, dW):
+    return lib().chn_linear_bwd_workspace_bytes(_ref(desc(dv)), _ref(desc(W)), _ref(desc(x)), _ref(desc(dx)), _ref(desc(dW)))
+
+
+def linear_bwd(dv, W, x, dW, db=None, dx=None, epilogue="none", aux=None, ws=None, stream=None):
+    """dW = dv^T x, db = column sums of dv, dx = epilogue(dv W): the backward of y = x W^T + b."""
+    p, n = _ws(ws)
+    _check(lib().chn_linear_bwd(_ref(desc(dv)), _ref(desc(W)), _ref(desc(x)), EPI[epilogue] if isinstance(epilogue, str) else epilogue,
+                                _ref(desc(aux)), _ref(desc(dx)), _ref(desc(dW)), _ref(desc(db)), p, n,
+                                _stream() if stream is None else stream))
 
 
 def lstm_fwd(z, bias, c_prev, c, h, gates=None, stream=None):

@@ -1,9 +1,12 @@
 // chn_gemm: host side of the dense product -- validation, layout classification and dispatch to the
 // kernel families in gemm_kernel.h (one object file per dtype and operand layout).
+#include <algorithm>
 #include <atomic>
+#include <utility>
 
 #include "common.h"
 #include "gemm_args.h"
+#include "linear_bwd.h"
 
 namespace chn {
 namespace gemm {
@@ -309,6 +312,127 @@ size_t split_bytes(const GemmArgs &g) {
   return g.splits > 1 ? (size_t)g.splits * g.M * g.ldp * sizeof(float) : 0;
 }
 
+// Validates a product's arrays and fills in everything but the plan (colsum: row-block column sums are wanted).
+chn_status prepare(const chn_array *A, const chn_array *B, const chn_array *C, float alpha, float beta, int epilogue, const chn_array *bias,
+                   const chn_array *aux, const chn_array *preact_out, GemmArgs &g, bool *a_kc, bool *b_kc) {
+  CHN_TRY(validate(A, "A", false));
+  CHN_TRY(validate(B, "B", false));
+  CHN_TRY(validate(C, "C", true));
+  if (A->ndim != 2 || B->ndim != 2 || C->ndim != 2) return fail(CHN_ERR_NDIM, "gemm: A, B and C must be 2-d");
+  if (epilogue < 0 || epilogue >= CHN_EPI_COUNT_) return fail(CHN_ERR_OP, "gemm: unknown epilogue %d", epilogue);
+  if (!is_float(A->dtype) || A->dtype != B->dtype) return fail(CHN_ERR_DTYPE, "gemm: A and B must share F32 or BF16");
+  if (!is_float(C->dtype) || (A->dtype == CHN_F32 && C->dtype != CHN_F32))
+    return fail(CHN_ERR_DTYPE, "gemm: C must be F32 (or BF16 when A and B are BF16)");
+  const int64_t M = A->shape[0], K = A->shape[1], N = B->shape[1];
+  if (B->shape[0] != K) return fail(CHN_ERR_SHAPE, "gemm: A is (%lld,%lld) but B has %lld rows", (long long)M, (long long)K, (long long)B->shape[0]);
+  if (C->shape[0] != M || C->shape[1] != N) return fail(CHN_ERR_SHAPE, "gemm: C must be (%lld,%lld)", (long long)M, (long long)N);
+  if (M > 0x3fffffff || N > 0x3fffffff || K > 0x3fffffff) return fail(CHN_ERR_SHAPE, "gemm: dimension too large");
+  int64_t cr, cc;
+  CHN_TRY(row_major_2d(C, "C", &cr, &cc, &g.ldc));
+  CHN_TRY(classify(A, B, &g, a_kc, b_kc));
+  const bool needs_bias = epilogue >= CHN_EPI_BIAS && epilogue <= CHN_EPI_BIAS_GELU;
+  const bool needs_aux = epilogue == CHN_EPI_RELU_BWD || epilogue == CHN_EPI_GELU_BWD;
+  if (needs_bias) {
+    CHN_TRY(validate(bias, "bias", false));
+    if (bias->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "gemm: bias must be F32");
+    if (bias->ndim != 1 || bias->shape[0] != N || !is_contiguous(bias)) return fail(CHN_ERR_SHAPE, "gemm: bias must be a contiguous (%lld,) array", (long long)N);
+    g.bias = static_cast<const float *>(bias->data);
+  }
+  if (needs_aux) {
+    CHN_TRY(validate(aux, "aux", false));
+    if (aux->dtype != C->dtype) return fail(CHN_ERR_DTYPE, "gemm: aux must have C's dtype");
+    int64_t ar, ac;
+    CHN_TRY(row_major_2d(aux, "aux", &ar, &ac, &g.ldaux));
+    if (ar != M || ac != N) return fail(CHN_ERR_SHAPE, "gemm: aux must have C's shape");
+    g.aux = aux->data;
+  }
+  if (epilogue == CHN_EPI_BF16_COPY && !preact_out) return fail(CHN_ERR_NULL, "gemm: the BF16_COPY epilogue needs preact_out");
+  if (preact_out && needs_aux) {
+    // activation-gradient epilogues: the second output holds column sums of C over blocks of 128 rows
+    CHN_TRY(validate(preact_out, "preact_out", true));
+    if (preact_out->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "gemm: the row-block column sums must be F32");
+    int64_t pr, pc;
+    CHN_TRY(row_major_2d(preact_out, "preact_out", &pr, &pc, &g.ldcs));
+    if (M % 256 || N % 256 || pr != M / 128 || pc != N)
+      return fail(CHN_ERR_SHAPE, "gemm: row-block column sums need M and N to be multiples of 256 and an (M/128, N) array");
+    if (beta != 0.0f) return fail(CHN_ERR_OP, "gemm: row-block column sums are not produced together with beta != 0");
+    if (reinterpret_cast<uintptr_t>(preact_out->data) % 16 || g.ldcs % 4)
+      return fail(CHN_ERR_STRIDE, "gemm: the row-block column sums need 16-byte aligned rows");
+    g.colsum = static_cast<float *>(preact_out->data);
+  } else if (preact_out) {
+    if (epilogue != CHN_EPI_BIAS_GELU && epilogue != CHN_EPI_BF16_COPY)
+      return fail(CHN_ERR_OP, "gemm: preact_out is only produced by the BIAS_GELU and BF16_COPY epilogues");
+    CHN_TRY(validate(preact_out, "preact_out", true));
+    if (epilogue == CHN_EPI_BF16_COPY) {
+      if (C->dtype != CHN_F32 || preact_out->dtype != CHN_BF16) return fail(CHN_ERR_DTYPE, "gemm: BF16_COPY needs an F32 C and a BF16 preact_out");
+    } else if (preact_out->dtype != C->dtype) {
+      return fail(CHN_ERR_DTYPE, "gemm: preact_out must have C's dtype");
+    }
+    int64_t pr, pc;
+    CHN_TRY(row_major_2d(preact_out, "preact_out", &pr, &pc, &g.ldpre));
+    if (pr != M || pc != N) return fail(CHN_ERR_SHAPE, "gemm: preact_out must have C's shape");
+    g.pre = preact_out->data;
+  }
+  g.A = A->data; g.B = B->data; g.C = C->data;
+  g.alpha = alpha; g.beta = beta; g.epi = epilogue; g.c_bf16 = C->dtype == CHN_BF16;
+  return CHN_OK;
+}
+
+// Launches a product as planned, or, if the plan cuts K and the workspace has no room for that, as planned uncut.
+chn_status launch_planned(GemmArgs &g, int isz, bool a_kc, bool b_kc, int epilogue, void *ws, size_t ws_bytes, hipStream_t st) {
+  if (g.splits > 1) {
+    // split-K is an optimisation: without (enough, aligned) workspace the product is planned unsplit
+    if (ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= split_bytes(g)) g.partial = static_cast<float *>(ws);
+    else plan(&g, isz, a_kc, b_kc, false);
+  }
+  g.w8 = eight_waves(g, isz, epilogue);
+  if (isz == 4) {
+    if (a_kc) return b_kc ? gemm::launch_f32_kk(g, st) : gemm::launch_f32_km(g, st);
+    return b_kc ? gemm::launch_f32_mk(g, st) : gemm::launch_f32_mm(g, st);
+  }
+  if (a_kc) return b_kc ? gemm::launch_bf16_kk(g, st) : gemm::launch_bf16_km(g, st);
+  return b_kc ? gemm::launch_bf16_mk(g, st) : gemm::launch_bf16_mm(g, st);
+}
+
+// ---- the backward of a fully connected layer --------------------------------------------------------------------------
+
+chn_array transposed(const chn_array *a) {
+  chn_array t = *a;
+  std::swap(t.shape[0], t.shape[1]);
+  std::swap(t.strides[0], t.strides[1]);
+  return t;
+}
+
+// Whether the memory of two arrays may overlap (the span from first to last element).
+bool may_overlap(const chn_array *a, const chn_array *b) {
+  auto span = [](const chn_array *x, uintptr_t *lo, uintptr_t *hi) {
+    *lo = reinterpret_cast<uintptr_t>(x->data);
+    *hi = *lo + dtype_size(x->dtype);
+    for (int d = 0; d < x->ndim; ++d)
+      if (x->shape[d] > 1) *hi += (x->shape[d] - 1) * x->strides[d];
+  };
+  uintptr_t a0, a1, b0, b1;
+  span(a, &a0, &a1);
+  span(b, &b0, &b1);
+  return a0 < b1 && b0 < a1;
+}
+
+// Which of the one-launch kernels takes the two planned products (dx: NULL where there is none).
+gemm::LinearBwd together(const GemmArgs &w, const GemmArgs *dx, int isz, bool w_mm, bool x_a_kc) {
+  using gemm::LinearBwd;
+  if (!w_mm || w.splits > 1 || (dx && (!x_a_kc || dx->splits > 1))) return LinearBwd::kApart;
+  auto both = [&](auto ok) { return ok(w) && (!dx || ok(*dx)); };
+  const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n + (dx ? (int64_t)dx->tiles_m * dx->tiles_n : 0);
+  if (isz == 4) {
+    if (both([](const GemmArgs &g) { return g.parts == 3 && g.small == 16; })) return LinearBwd::kTiny;
+    if (tiles <= 512 && both([](const GemmArgs &g) { return g.parts == 1; }) &&
+        (both([](const GemmArgs &g) { return g.piece == 16; }) || both([](const GemmArgs &g) { return g.any_a && g.any_b; })))
+      return LinearBwd::kSplit;
+    return LinearBwd::kApart;
+  }
+  return tiles <= 512 && both([](const GemmArgs &g) { return g.tile == 0 && g.dma; }) ? LinearBwd::kDma : LinearBwd::kApart;
+}
+
 }  // namespace
 }  // namespace chn
 
@@ -353,94 +477,67 @@ chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, 
                     int epilogue, const chn_array *bias, const chn_array *aux, const chn_array *preact_out,
                     void *ws, size_t ws_bytes, chn_stream stream) {
   using namespace chn;
-  CHN_TRY(validate(A, "A", false));
-  CHN_TRY(validate(B, "B", false));
-  CHN_TRY(validate(C, "C", true));
-  if (A->ndim != 2 || B->ndim != 2 || C->ndim != 2) return fail(CHN_ERR_NDIM, "gemm: A, B and C must be 2-d");
-  if (epilogue < 0 || epilogue >= CHN_EPI_COUNT_) return fail(CHN_ERR_OP, "gemm: unknown epilogue %d", epilogue);
-  if (!is_float(A->dtype) || A->dtype != B->dtype) return fail(CHN_ERR_DTYPE, "gemm: A and B must share F32 or BF16");
-  if (!is_float(C->dtype) || (A->dtype == CHN_F32 && C->dtype != CHN_F32))
-    return fail(CHN_ERR_DTYPE, "gemm: C must be F32 (or BF16 when A and B are BF16)");
-  const int64_t M = A->shape[0], K = A->shape[1], N = B->shape[1];
-  if (B->shape[0] != K) return fail(CHN_ERR_SHAPE, "gemm: A is (%lld,%lld) but B has %lld rows", (long long)M, (long long)K, (long long)B->shape[0]);
-  if (C->shape[0] != M || C->shape[1] != N) return fail(CHN_ERR_SHAPE, "gemm: C must be (%lld,%lld)", (long long)M, (long long)N);
-  if (M > 0x3fffffff || N > 0x3fffffff || K > 0x3fffffff) return fail(CHN_ERR_SHAPE, "gemm: dimension too large");
-  const int isz = dtype_size(A->dtype), csz = dtype_size(C->dtype);
   GemmArgs g{};
-  int64_t cr, cc;
-  CHN_TRY(row_major_2d(C, "C", &cr, &cc, &g.ldc));
   bool a_kc, b_kc;
-  CHN_TRY(classify(A, B, &g, &a_kc, &b_kc));
-  const bool needs_bias = epilogue >= CHN_EPI_BIAS && epilogue <= CHN_EPI_BIAS_GELU;
-  const bool needs_aux = epilogue == CHN_EPI_RELU_BWD || epilogue == CHN_EPI_GELU_BWD;
-  if (needs_bias) {
-    CHN_TRY(validate(bias, "bias", false));
-    if (bias->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "gemm: bias must be F32");
-    if (bias->ndim != 1 || bias->shape[0] != N || !is_contiguous(bias)) return fail(CHN_ERR_SHAPE, "gemm: bias must be a contiguous (%lld,) array", (long long)N);
-    g.bias = static_cast<const float *>(bias->data);
-  }
-  if (needs_aux) {
-    CHN_TRY(validate(aux, "aux", false));
-    if (aux->dtype != C->dtype) return fail(CHN_ERR_DTYPE, "gemm: aux must have C's dtype");
-    int64_t ar, ac;
-    CHN_TRY(row_major_2d(aux, "aux", &ar, &ac, &g.ldaux));
-    if (ar != M || ac != N) return fail(CHN_ERR_SHAPE, "gemm: aux must have C's shape");
-    g.aux = aux->data;
-  }
-  if (epilogue == CHN_EPI_BF16_COPY && !preact_out) return fail(CHN_ERR_NULL, "gemm: the BF16_COPY epilogue needs preact_out");
-  bool want_colsum = false;
-  if (preact_out && needs_aux) {
-    // activation-gradient epilogues: the second output holds column sums of C over blocks of 128 rows
-    CHN_TRY(validate(preact_out, "preact_out", true));
-    if (preact_out->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "gemm: the row-block column sums must be F32");
-    int64_t pr, pc;
-    CHN_TRY(row_major_2d(preact_out, "preact_out", &pr, &pc, &g.ldcs));
-    if (M % 256 || N % 256 || pr != M / 128 || pc != N)
-      return fail(CHN_ERR_SHAPE, "gemm: row-block column sums need M and N to be multiples of 256 and an (M/128, N) array");
-    if (beta != 0.0f) return fail(CHN_ERR_OP, "gemm: row-block column sums are not produced together with beta != 0");
-    if (reinterpret_cast<uintptr_t>(preact_out->data) % 16 || g.ldcs % 4)
-      return fail(CHN_ERR_STRIDE, "gemm: the row-block column sums need 16-byte aligned rows");
-    g.colsum = static_cast<float *>(preact_out->data);
-    want_colsum = true;
-  } else if (preact_out) {
-    if (epilogue != CHN_EPI_BIAS_GELU && epilogue != CHN_EPI_BF16_COPY)
-      return fail(CHN_ERR_OP, "gemm: preact_out is only produced by the BIAS_GELU and BF16_COPY epilogues");
-    CHN_TRY(validate(preact_out, "preact_out", true));
-    if (epilogue == CHN_EPI_BF16_COPY) {
-      if (C->dtype != CHN_F32 || preact_out->dtype != CHN_BF16) return fail(CHN_ERR_DTYPE, "gemm: BF16_COPY needs an F32 C and a BF16 preact_out");
-    } else if (preact_out->dtype != C->dtype) {
-      return fail(CHN_ERR_DTYPE, "gemm: preact_out must have C's dtype");
-    }
-    int64_t pr, pc;
-    CHN_TRY(row_major_2d(preact_out, "preact_out", &pr, &pc, &g.ldpre));
-    if (pr != M || pc != N) return fail(CHN_ERR_SHAPE, "gemm: preact_out must have C's shape");
-    g.pre = preact_out->data;
-  }
-  if (M == 0 || N == 0) return CHN_OK;
-  g.A = A->data; g.B = B->data; g.C = C->data;
-  g.alpha = alpha; g.beta = beta; g.epi = epilogue; g.c_bf16 = C->dtype == CHN_BF16;
-  if (want_colsum) {
+  CHN_TRY(prepare(A, B, C, alpha, beta, epilogue, bias, aux, preact_out, g, &a_kc, &b_kc));
+  if (g.M == 0 || g.N == 0) return CHN_OK;
+  const int isz = dtype_size(A->dtype);
+  if (g.colsum) {
     // the sums are taken per wave tile of the 256x256 kernels, unsplit, on the vector path of the epilogue
-    const int vb = 4 * csz;  // bytes of a 4-element vector of C's dtype
+    const int vb = 4 * dtype_size(C->dtype);  // bytes of a 4-element vector of C's dtype
     auto ok = [&](const void *q, int64_t ld) { return reinterpret_cast<uintptr_t>(q) % vb == 0 && ld % 4 == 0; };
     if (!ok(g.C, g.ldc) || !ok(g.aux, g.ldaux) || g.piece < 8) return fail(CHN_ERR_STRIDE, "gemm: row-block column sums need operands with 8-byte pieces and 16-byte aligned C and aux rows");
     plan(&g, isz, a_kc, b_kc, false, true);
   } else {
     plan(&g, isz, a_kc, b_kc, true);
   }
-  if (g.splits > 1) {
-    // split-K is an optimisation: without (enough, aligned) workspace the product is planned unsplit
-    if (ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= split_bytes(g)) g.partial = static_cast<float *>(ws);
-    else plan(&g, isz, a_kc, b_kc, false);
+  return launch_planned(g, isz, a_kc, b_kc, epilogue, ws, ws_bytes, as_stream(stream));
+}
+
+size_t chn_linear_bwd_workspace_bytes(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW) {
+  using namespace chn;
+  if (!dv || !x || !dW || dv->ndim != 2) return 0;
+  const chn_array dvt = transposed(dv);
+  size_t need = chn_gemm_workspace_bytes(&dvt, x, dW);
+  if (dx && W) need = std::max(need, chn_gemm_workspace_bytes(dv, W, dx));
+  return std::max(need, chn_reduce_axis_workspace_bytes(dv, 0));
+}
+
+chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_array *x, int epilogue, const chn_array *aux, const chn_array *dx,
+                          const chn_array *dW, const chn_array *db, void *ws, size_t ws_bytes, chn_stream stream) {
+  using namespace chn;
+  CHN_TRY(validate(dv, "dv", false));
+  if (dv->ndim != 2) return fail(CHN_ERR_NDIM, "linear_bwd: dv must be 2-d");
+  if (epilogue != CHN_EPI_NONE && epilogue != CHN_EPI_RELU_BWD && epilogue != CHN_EPI_GELU_BWD)
+    return fail(CHN_ERR_OP, "linear_bwd: the epilogue of the input gradient is NONE, RELU_BWD or GELU_BWD");
+  const chn_array dvt = transposed(dv);
+  GemmArgs gw{}, gx{};
+  bool w_a, w_b, x_a = true, x_b = true;
+  CHN_TRY(prepare(&dvt, x, dW, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, gw, &w_a, &w_b));
+  if (dW->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "linear_bwd: dW must be F32");
+  if (dx) CHN_TRY(prepare(dv, W, dx, 1.0f, 0.0f, epilogue, nullptr, aux, nullptr, gx, &x_a, &x_b));
+  if (db) {
+    CHN_TRY(validate(db, "db", true));
+    if (db->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "linear_bwd: db must be F32");
+    if (db->ndim != 1 || db->shape[0] != gw.M || !is_contiguous(db)) return fail(CHN_ERR_SHAPE, "linear_bwd: db must be a contiguous (%d,) array", gw.M);
   }
-  g.w8 = eight_waves(g, isz, epilogue);
-  hipStream_t st = as_stream(stream);
-  if (A->dtype == CHN_F32) {
-    if (a_kc) return b_kc ? gemm::launch_f32_kk(g, st) : gemm::launch_f32_km(g, st);
-    return b_kc ? gemm::launch_f32_mk(g, st) : gemm::launch_f32_mm(g, st);
+  const int isz = dtype_size(dv->dtype);
+  // one launch: no call may write what another still reads
+  if (gw.M > 0 && gw.N > 0 && gw.K > 0 &&
+      !(dx && (may_overlap(dx, dv) || may_overlap(dx, x) || may_overlap(dx, dW) || (db && may_overlap(dx, db)) || may_overlap(dW, W) || (db && may_overlap(db, W)) ||
+               (aux && (may_overlap(aux, dW) || (db && may_overlap(aux, db)))))) &&
+      !may_overlap(dW, dv) && !may_overlap(dW, x) && !(db && (may_overlap(db, dv) || may_overlap(db, x) || may_overlap(db, dW)))) {
+    plan(&gw, isz, w_a, w_b, true);
+    if (dx) plan(&gx, isz, x_a, x_b, true);
+    const gemm::LinearBwd kind = together(gw, dx ? &gx : nullptr, isz, !w_a && !w_b, x_a);
+    if (kind != gemm::LinearBwd::kApart) {
+      gw.sums = db ? static_cast<float *>(db->data) : nullptr;
+      return gemm::launch_linear_bwd(gw, dx ? &gx : nullptr, x_b, kind, as_stream(stream));
+    }
   }
-  if (a_kc) return b_kc ? gemm::launch_bf16_kk(g, st) : gemm::launch_bf16_km(g, st);
-  return b_kc ? gemm::launch_bf16_mk(g, st) : gemm::launch_bf16_mm(g, st);
+  CHN_TRY(chn_gemm(&dvt, x, dW, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, ws, ws_bytes, stream));
+  if (db) CHN_TRY(chn_reduce_axis(CHN_REDUCE_SUM, dv, 0, 0, db, ws, ws_bytes, stream));
+  return dx ? chn_gemm(dv, W, dx, 1.0f, 0.0f, epilogue, nullptr, aux, nullptr, ws, ws_bytes, stream) : CHN_OK;
 }
 
 }  // extern "C"

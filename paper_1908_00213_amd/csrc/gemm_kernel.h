@@ -367,6 +367,14 @@ __device__ __forceinline__ void mma(floatx16 (&acc)[TM][TN], const Frags<TM, TN>
   }
 }
 
+// The sum of a chunk of eight bfloat16 values.
+__device__ __forceinline__ float sum8_bf16(const uint4 &v) {
+  float t[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t[e] = __uint_as_float((&v.x)[e] << 16) + __uint_as_float((&v.x)[e] & 0xffff0000u);
+  return (t[0] + t[1]) + (t[2] + t[3]);
+}
+
 // Scheduling hints (instruction-class masks of __builtin_amdgcn_sched_group_barrier).
 constexpr int SG_MFMA = 0x008, SG_VMEM = 0x010, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100, SG_DS_WRITE = 0x200;
 // s_waitcnt immediate (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8) that waits
@@ -720,10 +728,10 @@ static __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmArgs
 // Which C tile (and which K split) a workgroup owns: XCD-aware renumbering, then grouped (8 tile rows
 // at a time) ordering.
 struct TilePos { int tm, tn, split; };
-__device__ __forceinline__ TilePos tile_pos(const GemmArgs &g) {
+__device__ __forceinline__ TilePos tile_pos(const GemmArgs &g, int block) {
   const int nb = g.tiles_m * g.tiles_n;
-  int pid = blockIdx.x % nb;
-  const int split = blockIdx.x / nb;
+  int pid = block % nb;
+  const int split = block / nb;
   const int nb8 = nb & ~7;
   if (pid < nb8) pid = (pid & 7) * (nb8 >> 3) + (pid >> 3);
   constexpr int GROUP = 8;
@@ -806,7 +814,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
   constexpr int A_BYTES = BM * 128, B_BYTES = BN * 128, STAGE = A_BYTES + B_BYTES;
   extern __shared__ __align__(16) char lds[];
 
-  const TilePos tp = tile_pos(g);
+  const TilePos tp = tile_pos(g, blockIdx.x);
   const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BN;
 
   TileLoader<T, BM, A_KC, PB> la;
@@ -1201,7 +1209,7 @@ __global__ __launch_bounds__(256) void gemm_kernel_dma(GemmArgs g) {
   __shared__ __align__(1024) char stage0[STAGE + 1024];
   __shared__ __align__(1024) char stage1[STAGE + 1024];
 
-  const TilePos tp = tile_pos(g);
+  const TilePos tp = tile_pos(g, blockIdx.x);
   const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BN;
 
   std::conditional_t<A_KC, DmaLoader<T, BM, RAGGED>, std::conditional_t<kBf16, DmaLoaderMC<BM, RAGGED>, TileLoader<T, BM, false, 16>>> la;
@@ -1377,7 +1385,7 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
   __shared__ __align__(1024) char stage0[STAGE];
   __shared__ __align__(1024) char stage1[STAGE];
 
-  const TilePos tp = tile_pos(g);
+  const TilePos tp = tile_pos(g, blockIdx.x);
   const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BN;
 
   TwoParts<std::conditional_t<A_KC, DmaLoader<T, BM, RAGGED, NW>, DmaLoaderMC<BM, RAGGED, NW>>> la;
@@ -1505,17 +1513,16 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
 // everybody's has (barrier; nobody reads the stage of the step before any more), that stage is filled again, multiply.
 // us, staged through registers -> here, small tile: 1024x1000x784 with both operands along K 9.4 -> 7.0, one 9.6 -> 7.1, none
 // 11.0 -> 7.2 (13.6 -> 8.5 between other kernels); large tile: 2048x2048x2048 29, 37, 45 -> 24, 25, 26.
-template <int TM, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
+template <int TM> constexpr int kSmallDmaStage = 2 * 64 * TM * 128;
+
+// Block `block` of the product (SUMS: and the row sums of A, by the blocks of the first tile column).
+template <int TM, bool A_KC, bool B_KC, bool SUMS>
+__device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, char *stage0, char *stage1, char *stage2, char *stage3) {
   using T = bf16_raw;
   constexpr int BM = 64 * TM, BK = 64, STAGES = 4;
-  constexpr int A_BYTES = BM * 128, STAGE = 2 * A_BYTES;
-  __shared__ __align__(1024) char stage0[STAGE];
-  __shared__ __align__(1024) char stage1[STAGE];
-  __shared__ __align__(1024) char stage2[STAGE];
-  __shared__ __align__(1024) char stage3[STAGE];
+  constexpr int A_BYTES = BM * 128, STAGE = kSmallDmaStage<TM>;
 
-  const TilePos tp = tile_pos(g);
+  const TilePos tp = tile_pos(g, block);
   const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BM;
   std::conditional_t<A_KC, DmaLoader<T, BM, true>, DmaLoaderRows<BM>> la;
   std::conditional_t<B_KC, DmaLoader<T, BM, true>, DmaLoaderRows<BM>> lb;
@@ -1548,6 +1555,10 @@ __global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
+  float sum[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) sum[i] = 0.0f;
+  const bool summing = SUMS && g.sums && tp.tn == 0 && wn == 0;
   constexpr int kAhead = (STAGES - 2) * 4 * TM;            // copies of the two later tiles, per wave
   constexpr int kWait = (kAhead & 15) | (kAhead >> 4) << 14 | 0x70;   // vmcnt(kAhead), lgkmcnt(0)
   auto step = [&](const char *cur, char *before, int kt) __attribute__((always_inline)) {
@@ -1568,6 +1579,17 @@ __global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) mma<T, TM, TM>(acc, f[ks]);
+    if constexpr (SUMS) {
+      if (summing) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          float t[4];
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) t[ks] = sum8_bf16(f[ks].a[i]);
+          sum[i] += (t[0] + t[1]) + (t[2] + t[3]);
+        }
+      }
+    }
   };
   int kt = kt0;
   for (; kt + 3 < nk; kt += 4) {
@@ -1582,7 +1604,26 @@ __global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);                // the epilogue reuses the stages
   __syncthreads();
   static_assert(kEpiStageBytes<TM, TM> <= STAGE, "a wave stages its accumulators in one stage");
+  if constexpr (SUMS) {
+    if (summing) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const float t = sum[i] + __shfl_xor(sum[i], 32, 64);      // (lanes l and l + 32 hold the two halves of every 16 k)
+        const int row = m0 + (wm * TM + i) * 32 + (lane & 31);
+        if (lane < 32 && row < g.M) g.sums[row] = t;
+      }
+    }
+  }
   write_out<TM, TM>(g, acc, wave == 0 ? stage0 : wave == 1 ? stage1 : wave == 2 ? stage2 : stage3, m0, n0, split);
+}
+
+template <int TM, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
+  __shared__ __align__(1024) char stage0[kSmallDmaStage<TM>];
+  __shared__ __align__(1024) char stage1[kSmallDmaStage<TM>];
+  __shared__ __align__(1024) char stage2[kSmallDmaStage<TM>];
+  __shared__ __align__(1024) char stage3[kSmallDmaStage<TM>];
+  small_dma_block<TM, A_KC, B_KC, false>(g, blockIdx.x, stage0, stage1, stage2, stage3);
 }
 
 template <int TM, bool A_KC, bool B_KC>

@@ -114,6 +114,40 @@ struct SplitLoader {
     }
   }
 
+  // Sums over k of what has been loaded, by row: NS of them a thread, to which PARTS threads contribute.
+  static constexpr int NS = KC ? NU : 4, PARTS = KC ? 4 * SUBS : 8 * SUBS * (4 / R);
+  __device__ __forceinline__ void add_up(const uint4 (&reg)[R], float (&s)[NS], bool any) const {
+    if constexpr (KC) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) s[u] += sum4(reg[2 * u]) + sum4(reg[2 * u + 1]);
+    } else {
+      uint4 v[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) v[j] = any && cut ? move_down(reg[j], down) : reg[j];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float x = __uint_as_float((&v[0].x)[e]) + __uint_as_float((&v[1].x)[e]);
+        if constexpr (R == 4) x += __uint_as_float((&v[2].x)[e]) + __uint_as_float((&v[3].x)[e]);
+        s[e] += x;
+      }
+    }
+  }
+  static __device__ __forceinline__ float sum4(const uint4 &v) {
+    return (__uint_as_float(v.x) + __uint_as_float(v.y)) + (__uint_as_float(v.z) + __uint_as_float(v.w));
+  }
+  // t: as for init; rows: PARTS x ROWS floats
+  __device__ __forceinline__ void put_sums(int t, const float (&s)[NS], float *rows) const {
+    if constexpr (KC) {
+      const int q = t & 3, row = (t >> 2) % ROWS, sub = t / (4 * ROWS);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) rows[(sub * 4 + q) * ROWS + row + u * (T / 4)] = s[u];
+    } else {
+      constexpr int PAIRS = 4 / R;
+      const int part = t % (8 * PAIRS), mc = (t / (8 * PAIRS)) % (ROWS / 4), sub = t / (2 * PAIRS * ROWS);
+      *reinterpret_cast<float4 *>(rows + (sub * 8 * PAIRS + part) * ROWS + mc * 4) = make_float4(s[0], s[1], s[2], s[3]);
+    }
+  }
+
   // any: the pieces were read at any address
   __device__ __forceinline__ void store(const uint4 (&loaded)[R], char *stage, bool any) {
     uint4 reg[R];
@@ -182,15 +216,14 @@ struct SplitLoader {
 template <int TM, int TN, int KG>
 constexpr int kSplitStage = (KG / 2) * (kSplitSub<64 * TM> + kSplitSub<64 * TN>);
 
-template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
-__global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
+// Block `block` of the product (SUMS: and the row sums of A, by the blocks of the first tile column).  lds: two stages.
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, bool SUMS>
+__device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *lds, int &redo) {
   constexpr int BM = 64 * TM, BN = 64 * TN, BK = 16 * KG, SUBS = KG / 2;
   constexpr int A_BYTES = SUBS * kSplitSub<BM>, STAGE = kSplitStage<TM, TN, KG>;
-  constexpr int SETS = KG == 4 ? 2 : 1, NT = 256 * KG;    // (the large tile has no registers for a second set)
-  extern __shared__ __align__(16) char lds[];
-  __shared__ int redo;
+  constexpr int SETS = TM == 1 ? 2 : 1, NT = 256 * KG;    // (the large tile has no registers for a second set)
 
-  const TilePos tp = tile_pos(g);
+  const TilePos tp = tile_pos(g, block);
   const int split = tp.split, m0 = tp.tm * BM, n0 = tp.tn * BN;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
@@ -211,7 +244,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
   {
     // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
     // by all threads together, so that every wave has the same mixture of work.
-    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || KG == 4;
+    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || TM == 1;
     // (a mixed pair of aligned operands: steps of whole k without checks do not pay, 4480x2688x672 120 -> 123 us)
     using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
     using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
@@ -227,6 +260,11 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     }
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
+    // row sums of A: what this thread has staged of it, by its rows
+    float sum[LA::NS];
+#pragma unroll
+    for (int e = 0; e < LA::NS; ++e) sum[e] = 0.0f;
+    const bool summing = SUMS && g.sums && tp.tn == 0 && (do_a || !kHalves);
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
       if constexpr (!kHalves) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }
       else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
@@ -235,6 +273,9 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     };
     auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage) __attribute__((always_inline)) {
       constexpr bool any_a = PBA == kAnyPiece, any_b = PBB == kAnyPiece;
+      if constexpr (SUMS) {
+        if (summing) la.add_up(xa, sum, any_a);
+      }
       if constexpr (!kHalves) { la.store(xa, stage, any_a); lb.store(xb, stage + A_BYTES, any_b); }
       else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES), do_a ? any_a : any_b);
       else { if (do_a) la.store(xa, stage, any_a); else lb.store(xa, stage + A_BYTES, any_b); }
@@ -308,6 +349,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     }
     if (kt < nk) step(S0{}, kt);
     __syncthreads();
+    if constexpr (SUMS) {
+      if (g.sums && tp.tn == 0) {                         // (uniform over the workgroup) the threads that share a row add up in LDS
+        float *rows = reinterpret_cast<float *>(lds);     // [part][BM]
+        if (summing) la.put_sums(t, sum, rows);
+        __syncthreads();
+        if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < g.M) {
+          float s = 0.0f;
+#pragma unroll
+          for (int p = 0; p < LA::PARTS; ++p) s += rows[p * BM + threadIdx.x];
+          g.sums[m0 + threadIdx.x] = s;
+        }
+        __syncthreads();
+      }
+    }
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -354,17 +409,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  static_assert(3 * PART * 4 <= 2 * STAGE, "the parts fit the stages");
-  if constexpr (KG == 2) {                                // each group ends up with one of the tile's two 32-row blocks per wave
-    static_assert(TM == 2, "one block per group");
+  static_assert((TM == 2 ? 2 : KG - 1) * PART * 4 <= 2 * STAGE, "the parts fit the stages");
+  if constexpr (TM == 2) {                                // each group ends up with one of the tile's two 32-row blocks per wave
+    static_assert(KG == 2, "one block per group");
     if (grp == 0) put(0, acc[1]); else put(1, acc[0]);
     __syncthreads();
     if (grp == 0) get(1, acc[0], true); else get(0, acc[1], true);
   } else {                                                // the first group takes everything, in group order
-    static_assert(TM == 1, "three parts");
+    static_assert(TM == 1, "a part for every group but the first");
     if (grp > 0) put(grp - 1, acc[0]);
     __syncthreads();
-    if (grp == 0) { get(0, acc[0], true); get(1, acc[0], true); get(2, acc[0], true); }
+    if (grp == 0) {
+#pragma unroll
+      for (int part = 0; part + 1 < KG; ++part) get(part, acc[0], true);
+    }
   }
   if (redo) {
     // Some sum of this tile is not finite, with the scaled operands or at all: the first group multiplies the tile again
@@ -396,14 +454,14 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
       }
     }
     __syncthreads();
-    if constexpr (KG == 2) {
+    if constexpr (TM == 2) {
       if (grp == 0) put(0, acc[1]);
       __syncthreads();
       if (grp == 1) get(0, acc[1], false);
     }
   }
   __syncthreads();                                        // nobody reads the parts any more
-  if constexpr (KG == 2) {
+  if constexpr (TM == 2) {
     floatx16 own[1][TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) own[0][j] = grp == 0 ? acc[0][j] : acc[1][j];
@@ -413,6 +471,13 @@ __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
     if (grp != 0) return;
     write_out<TM, TN>(g, acc, lds + wave * kEpiStageBytes<TM, TN>, m0, n0, split);
   }
+}
+
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
+__global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
+  extern __shared__ __align__(16) char lds[];
+  __shared__ int redo;
+  split_block<TM, TN, KG, A_KC, B_KC, PBA, PBB, false>(g, blockIdx.x, lds, redo);
 }
 
 template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>

@@ -1,0 +1,15 @@
+// The one-launch backward of a fully connected layer (linear_bwd.hip), as gemm.hip's entry point sees it.
+#pragma once
+#include "common.h"
+#include "gemm_args.h"
+
+namespace chn {
+namespace gemm {
+
+enum class LinearBwd { kApart, kTiny, kSplit, kDma };
+// w: the weight gradient dv^T x, both operands along M/N, with `sums`; dx: the input gradient dv W or NULL, W along K (w_kc) or N.
+// Both unsplit, on tiles of the kind's size.
+chn_status launch_linear_bwd(const GemmArgs &w, const GemmArgs *dx, bool w_kc, LinearBwd kind, hipStream_t st);
+
+}  // namespace gemm
+}  // namespace chn

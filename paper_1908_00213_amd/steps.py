@@ -37,6 +37,7 @@ class _Program:
         self.gemm_ws = C.c_void_p(0)
         self.gemm_ws_bytes = C.c_size_t(0)
         self._gemm_need = 0
+        self.operations = 0                # library operations the calls stand for, when issued one by one
 
     def finish(self):
         if self._gemm_need:
@@ -62,8 +63,9 @@ class _Program:
     def ws(self, t):
         return (None, 0) if t is None else (C.c_void_p(t.data_ptr()), t.numel() * t.element_size())
 
-    def add(self, fn, *args):
+    def add(self, fn, *args, operations=1):
         self.calls.append((fn, args))
+        self.operations += operations
 
     def run(self, stream=None):
         s = B._stream() if stream is None else stream
@@ -91,6 +93,13 @@ def _gemm(p, L, A, Bm, Cm, alpha=1.0, beta=0.0, epi="none", bias=None, aux=None,
     p._gemm_need = max(p._gemm_need, L.chn_gemm_workspace_bytes(a, b, c))
     p.add(L.chn_gemm, a, b, c, C.c_float(alpha), C.c_float(beta), B.EPI[epi],
           p.d(bias), p.d(aux), p.d(pre), p.gemm_ws, p.gemm_ws_bytes)
+
+
+def _linear_bwd(p, L, dv, W, x, dW, db, dx=None, epi="none", aux=None):
+    """Weight, bias and (unless dx is None) input gradient of a fully connected layer."""
+    a, w, b, c, d = p.d(dv), p.d(W), p.d(x), p.d(dx), p.d(dW)
+    p._gemm_need = max(p._gemm_need, L.chn_linear_bwd_workspace_bytes(a, w, b, c, d))
+    p.add(L.chn_linear_bwd, a, w, b, B.EPI[epi], p.d(aux), c, d, p.d(db), p.gemm_ws, p.gemm_ws_bytes, operations=2 if dx is None else 3)
 
 
 class MLPTrainer:
@@ -155,12 +164,16 @@ class MLPTrainer:
         rp, rn = p.ws(self.ws_red)
         for l in range(n - 1, -1, -1):
             dv = self.dv[l + 1]
+            aux = (hs[l] if self.act == "relu" else self.z[l]) if l > 0 else None
+            if not self.fused_update and l not in self.rowsums and l + 1 not in self.rowsums:
+                _linear_bwd(p, L, dv, self.Wl[l], hs[l], self.dW[l], self.db[l], *((self.dv[l], bwd_epi, aux) if l > 0 else ()))
+                continue
             if not self.fused_update:
                 _gemm(p, L, dv.t(), hs[l], self.dW[l])
             p.add(L.chn_reduce_axis, B.REDUCE["sum"], p.d(self.rowsums.get(l + 1, dv)), 0, 0, p.d(self.db[l]), rp, rn)
             if l > 0:
                 _gemm(p, L, dv, self.Wl[l], self.dv[l], epi=bwd_epi,
-                      aux=hs[l] if self.act == "relu" else self.z[l], pre=self.rowsums.get(l))
+                      aux=aux, pre=self.rowsums.get(l))
             if self.fused_update:     # after dx: that product still reads this layer's old weights
                 _gemm(p, L, dv.t(), hs[l], self.W[l], alpha=-self.lr, beta=1.0,
                       epi="bf16_copy" if self.lowp else "none", pre=self.Wl[l] if self.lowp else None)
@@ -186,8 +199,9 @@ class MLPTrainer:
         return self.loss
 
     def n_launch_calls(self, x, t):
+        """Library operations of a step (a call that does a layer's whole backward counts as the three it replaces)."""
         self.step(x, t)
-        return len(self._progs[(x.data_ptr(), t.data_ptr())].calls)
+        return self._progs[(x.data_ptr(), t.data_ptr())].operations
 
 
 def _ceil32(n):
@@ -399,4 +413,4 @@ class LSTMTrainer:
 
     def n_launch_calls(self, ids, targets):
         self.step(ids, targets)
-        return len(self._progs[(ids.data_ptr(), targets.data_ptr())].calls)
+        return self._progs[(ids.data_ptr(), targets.data_ptr())].operations
