@@ -217,14 +217,18 @@ chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, 
 /* The backward of a fully connected layer y = x W^T + b (figure "Examples of model definitions") in one call, for callers that have
  * the gradient dv (M,N) of y, the weights W (N,K) and the input x (M,K), all F32 or all BF16:
  *   dW (N,K) F32 = dv^T x    db (N,) F32 = column sums of dv    dx (M,K) = epilogue(dv W)
- * db and dx may be NULL (W is then not looked at).  epilogue is NONE, RELU_BWD or GELU_BWD, with aux as in chn_gemm.  The same results
+ * db and dx may be NULL (without dx, W is not looked at); dW may also be stored by columns (the gradient of a W kept as (K,N)).
+ * epilogue is NONE, RELU_BWD or GELU_BWD, with aux as in chn_gemm.  The same results
  * up to summation order as
  *   chn_gemm(dv^T, x, dW), chn_reduce_axis(SUM, dv, 0, db), chn_gemm(dv, W, dx, epilogue, aux)
- * in this order, which it issues for large products, for layouts other than unit-stride rows of dv and x, and where an output
- * may overlap another array; otherwise one kernel does all three.  Workspace (optional) and errors as for those calls. */
+ * in this order.  Where the products are small one kernel does all three; larger ones are issued apart, the weight gradient leaving
+ * db's sums on its way; the three calls remain for layouts other than unit-stride rows of dv and x, where an output may overlap
+ * another array, and (the sums) without workspace.  Workspace and errors as for those calls. */
 size_t chn_linear_bwd_workspace_bytes(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW);
 chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_array *x, int epilogue, const chn_array *aux, const chn_array *dx,
                           const chn_array *dW, const chn_array *db, void *ws, size_t ws_bytes, chn_stream stream);
+/* Host-only query: 1 if that call would be one kernel (outputs apart from the other arrays), 0 if not, negative: an error. */
+int chn_linear_bwd_plan(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW);
 
 /* ---- LSTM cell ------------------------------------------------------------------------------------
  * The paper names LSTMs as a motivating model class (Section "Introduction") and an RNN language

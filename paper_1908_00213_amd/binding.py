@@ -26,7 +26,7 @@ EPILOGUES = ["none", "bias", "bias_relu", "bias_gelu", "relu_bwd", "gelu_bwd", "
 EPI = {n: i for i, n in enumerate(EPILOGUES)}
 
 EXPORTS = ["chn_elementwise_broadcast", "chn_reduce_axis_workspace_bytes", "chn_reduce_axis", "chn_reduce_axis_static", "chn_argmax_axis",
-           "chn_gemm_workspace_bytes", "chn_gemm", "chn_linear_bwd_workspace_bytes", "chn_linear_bwd", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
+           "chn_gemm_workspace_bytes", "chn_gemm", "chn_linear_bwd_workspace_bytes", "chn_linear_bwd", "chn_linear_bwd_plan", "chn_lstm_fwd", "chn_lstm_bwd", "chn_lstm_step_fwd", "chn_lstm_step_bwd",
            "chn_lstm_seq_workspace_bytes", "chn_lstm_seq_supported", "chn_lstm_seq_fwd",
            "chn_lstm_seq_bwd_supported", "chn_lstm_seq_bwd_in_xcd", "chn_lstm_seq_bwd_workspace_bytes", "chn_lstm_seq_bwd", "chn_lstm_seq_spin_limit", "chn_lstm_seq_meeting",
            "chn_softmax_ce_workspace_bytes", "chn_softmax_ce_fwd", "chn_softmax_ce_bwd", "chn_softmax_ce_bwd2", "chn_softmax_ce_fwd_bwd",
@@ -92,6 +92,7 @@ def lib():
     L.chn_gemm_plan_override.restype = None
     L.chn_linear_bwd_workspace_bytes.argtypes = [AP] * 5
     L.chn_linear_bwd_workspace_bytes.restype = C.c_size_t
+    L.chn_linear_bwd_plan.argtypes = [AP] * 5
     L.chn_linear_bwd.argtypes = [AP, AP, AP, C.c_int, AP, AP, AP, AP, vp, C.c_size_t, st]
     L.chn_gemm.argtypes = [AP, AP, AP, C.c_float, C.c_float, C.c_int, AP, AP, AP, vp, C.c_size_t, st]
     L.chn_lstm_fwd.argtypes = [AP, AP, AP, AP, AP, AP, st]
@@ -145,7 +146,7 @@ def lib():
                                          C.POINTER(C.c_size_t)]
     for name in EXPORTS:
         fn = getattr(L, name)
-        if fn.restype is C.c_int and name not in ("chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel"):  # i.e. not set above
+        if fn.restype is C.c_int and name not in ("chn_version", "chn_elementwise_plan", "chn_gemm_plan", "chn_gemm_plan_kernel", "chn_linear_bwd_plan"):  # i.e. not set above
             fn.restype = C.c_int32
     _lib = L
     return L
@@ -330,6 +331,14 @@ def gemm(A, B, Cm, alpha=1.0, beta=0.0, epilogue="none", bias=None, aux=None, pr
 
 def linear_bwd_workspace_bytes(dv, W, x, dx, dW):
     return lib().chn_linear_bwd_workspace_bytes(_ref(desc(dv)), _ref(desc(W)), _ref(desc(x)), _ref(desc(dx)), _ref(desc(dW)))
+
+
+def linear_bwd_in_one_launch(dv, W, x, dx, dW):
+    """Whether linear_bwd would be one kernel (outputs apart from the other arrays)."""
+    code = lib().chn_linear_bwd_plan(_ref(desc(dv)), _ref(desc(W)), _ref(desc(x)), _ref(desc(dx)), _ref(desc(dW)))
+    if code < 0:
+        _check(code)
+    return bool(code)
 
 
 def linear_bwd(dv, W, x, dW, db=None, dx=None, epilogue="none", aux=None, ws=None, stream=None):

@@ -403,6 +403,45 @@ chn_array transposed(const chn_array *a) {
   return t;
 }
 
+// The weight gradient as a product: dW = dv^T x, or, where dW is stored by columns, its transpose x^T dv.  The workspace of one that
+// leaves parts of the bias gradient's sums: the cut product's slabs, the parts, what adding them up needs.
+struct WeightGradient {
+  chn_array A, B, C;
+  bool transposed;
+  static size_t aligned(size_t n) { return (n + 255) / 256 * 256; }
+  chn_array parts(const GemmArgs &g, void *ws) const {
+    chn_array a{};
+    a.data = static_cast<char *>(ws) + aligned(split_bytes(g));
+    a.ndim = 2;
+    a.dtype = CHN_F32;
+    a.shape[0] = (int64_t)g.splits * (transposed ? g.tiles_m : g.tiles_n);
+    a.shape[1] = transposed ? g.N : g.M;
+    a.strides[0] = a.shape[1] * 4;
+    a.strides[1] = 4;
+    return a;
+  }
+  size_t fold_offset(const GemmArgs &g) const {
+    const chn_array a = parts(g, nullptr);
+    return aligned(split_bytes(g)) + aligned((size_t)(a.shape[0] * a.strides[0]));
+  }
+  size_t workspace_bytes(const GemmArgs &g) const {
+    chn_array a = parts(g, nullptr);
+    a.data = reinterpret_cast<void *>(256);               // (never looked at)
+    return fold_offset(g) + chn_reduce_axis_workspace_bytes(&a, 0);
+  }
+  size_t workspace_bytes() const {
+    GemmArgs g{};
+    bool a_kc, b_kc;
+    if (A.shape[0] <= 0 || A.shape[1] <= 0 || B.shape[1] <= 0 || plan_of(&A, &B, &C, 1, &g) != CHN_OK || classify(&A, &B, &g, &a_kc, &b_kc) != CHN_OK) return 0;
+    return !a_kc && !b_kc && gemm::sums_of_large(g, dtype_size(A.dtype)) ? workspace_bytes(g) : split_bytes(g);
+  }
+};
+WeightGradient weight_gradient(const chn_array *dv, const chn_array *x, const chn_array *dW) {
+  const bool by_columns = dW->strides[0] == dtype_size(dW->dtype) && dW->shape[0] > 1 && dW->shape[1] > 1 && dW->strides[1] != dW->strides[0];
+  if (by_columns) return WeightGradient{transposed(x), *dv, transposed(dW), true};
+  return WeightGradient{transposed(dv), *x, *dW, false};
+}
+
 // Whether the memory of two arrays may overlap (the span from first to last element).
 bool may_overlap(const chn_array *a, const chn_array *b) {
   auto span = [](const chn_array *x, uintptr_t *lo, uintptr_t *hi) {
@@ -496,47 +535,83 @@ chn_status chn_gemm(const chn_array *A, const chn_array *B, const chn_array *C, 
 
 size_t chn_linear_bwd_workspace_bytes(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW) {
   using namespace chn;
-  if (!dv || !x || !dW || dv->ndim != 2) return 0;
-  const chn_array dvt = transposed(dv);
-  size_t need = chn_gemm_workspace_bytes(&dvt, x, dW);
+  if (!dv || !x || !dW || dv->ndim != 2 || x->ndim != 2 || dW->ndim != 2) return 0;
+  size_t need = std::max(weight_gradient(dv, x, dW).workspace_bytes(), chn_reduce_axis_workspace_bytes(dv, 0));
   if (dx && W) need = std::max(need, chn_gemm_workspace_bytes(dv, W, dx));
-  return std::max(need, chn_reduce_axis_workspace_bytes(dv, 0));
+  return need;
+}
+
+int chn_linear_bwd_plan(const chn_array *dv, const chn_array *W, const chn_array *x, const chn_array *dx, const chn_array *dW) {
+  using namespace chn;
+  CHN_TRY(validate(dv, "dv", false));
+  CHN_TRY(validate(x, "x", false));
+  CHN_TRY(validate(dW, "dW", true));
+  if (dv->ndim != 2 || x->ndim != 2 || dW->ndim != 2) return fail(CHN_ERR_NDIM, "linear_bwd: dv, x and dW must be 2-d");
+  const WeightGradient w = weight_gradient(dv, x, dW);
+  GemmArgs gw{}, gx{};
+  bool w_a, w_b, x_a = true, x_b;
+  CHN_TRY(plan_of(&w.A, &w.B, &w.C, 1, &gw));
+  CHN_TRY(classify(&w.A, &w.B, &gw, &w_a, &w_b));
+  if (dx) {
+    CHN_TRY(plan_of(dv, W, dx, 1, &gx));
+    CHN_TRY(classify(dv, W, &gx, &x_a, &x_b));
+  }
+  if (w.transposed || gw.M <= 0 || gw.N <= 0 || gw.K <= 0) return 0;
+  return together(gw, dx ? &gx : nullptr, dtype_size(dv->dtype), !w_a && !w_b, x_a) != gemm::LinearBwd::kApart;
 }
 
 chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_array *x, int epilogue, const chn_array *aux, const chn_array *dx,
                           const chn_array *dW, const chn_array *db, void *ws, size_t ws_bytes, chn_stream stream) {
   using namespace chn;
   CHN_TRY(validate(dv, "dv", false));
-  if (dv->ndim != 2) return fail(CHN_ERR_NDIM, "linear_bwd: dv must be 2-d");
+  CHN_TRY(validate(x, "x", false));
+  CHN_TRY(validate(dW, "dW", true));
+  if (dv->ndim != 2 || x->ndim != 2 || dW->ndim != 2) return fail(CHN_ERR_NDIM, "linear_bwd: dv, x and dW must be 2-d");
   if (epilogue != CHN_EPI_NONE && epilogue != CHN_EPI_RELU_BWD && epilogue != CHN_EPI_GELU_BWD)
     return fail(CHN_ERR_OP, "linear_bwd: the epilogue of the input gradient is NONE, RELU_BWD or GELU_BWD");
-  const chn_array dvt = transposed(dv);
+  if (dW->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "linear_bwd: dW must be F32");
+  const WeightGradient w = weight_gradient(dv, x, dW);
   GemmArgs gw{}, gx{};
   bool w_a, w_b, x_a = true, x_b = true;
-  CHN_TRY(prepare(&dvt, x, dW, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, gw, &w_a, &w_b));
-  if (dW->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "linear_bwd: dW must be F32");
+  CHN_TRY(prepare(&w.A, &w.B, &w.C, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, gw, &w_a, &w_b));
   if (dx) CHN_TRY(prepare(dv, W, dx, 1.0f, 0.0f, epilogue, nullptr, aux, nullptr, gx, &x_a, &x_b));
   if (db) {
     CHN_TRY(validate(db, "db", true));
     if (db->dtype != CHN_F32) return fail(CHN_ERR_DTYPE, "linear_bwd: db must be F32");
-    if (db->ndim != 1 || db->shape[0] != gw.M || !is_contiguous(db)) return fail(CHN_ERR_SHAPE, "linear_bwd: db must be a contiguous (%d,) array", gw.M);
+    if (db->ndim != 1 || db->shape[0] != dv->shape[1] || !is_contiguous(db)) return fail(CHN_ERR_SHAPE, "linear_bwd: db must be a contiguous (%lld,) array", (long long)dv->shape[1]);
   }
   const int isz = dtype_size(dv->dtype);
-  // one launch: no call may write what another still reads
-  if (gw.M > 0 && gw.N > 0 && gw.K > 0 &&
-      !(dx && (may_overlap(dx, dv) || may_overlap(dx, x) || may_overlap(dx, dW) || (db && may_overlap(dx, db)) || may_overlap(dW, W) || (db && may_overlap(db, W)) ||
-               (aux && (may_overlap(aux, dW) || (db && may_overlap(aux, db)))))) &&
-      !may_overlap(dW, dv) && !may_overlap(dW, x) && !(db && (may_overlap(db, dv) || may_overlap(db, x) || may_overlap(db, dW)))) {
+  const bool mm = !w_a && !w_b;
+  bool done = false;
+  if (mm && gw.M > 0 && gw.N > 0 && gw.K > 0 && !(db && (may_overlap(db, dv) || may_overlap(db, x) || may_overlap(db, dW)))) {
     plan(&gw, isz, w_a, w_b, true);
-    if (dx) plan(&gx, isz, x_a, x_b, true);
-    const gemm::LinearBwd kind = together(gw, dx ? &gx : nullptr, isz, !w_a && !w_b, x_a);
-    if (kind != gemm::LinearBwd::kApart) {
-      gw.sums = db ? static_cast<float *>(db->data) : nullptr;
-      return gemm::launch_linear_bwd(gw, dx ? &gx : nullptr, x_b, kind, as_stream(stream));
+    // one launch: no product may write what another still reads
+    const bool apart = may_overlap(dW, dv) || may_overlap(dW, x) ||
+                       (dx && (may_overlap(dx, dv) || may_overlap(dx, x) || may_overlap(dx, dW) || (db && may_overlap(dx, db)) || may_overlap(dW, W) ||
+                               (db && may_overlap(db, W)) || (aux && (may_overlap(aux, dW) || (db && may_overlap(aux, db))))));
+    if (!w.transposed && !apart) {
+      if (dx) plan(&gx, isz, x_a, x_b, true);
+      const gemm::LinearBwd kind = together(gw, dx ? &gx : nullptr, isz, mm, x_a);
+      if (kind != gemm::LinearBwd::kApart) {
+        gw.sums = db ? static_cast<float *>(db->data) : nullptr;
+        return gemm::launch_linear_bwd(gw, dx ? &gx : nullptr, x_b, kind, as_stream(stream));
+      }
+    }
+    // the sums beside the weight gradient, in parts that a small reduction adds up
+    if (db && gemm::sums_of_large(gw, isz) && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= w.workspace_bytes(gw)) {
+      const chn_array parts = w.parts(gw, ws);
+      gw.partial = static_cast<float *>(ws);
+      gw.sums = static_cast<float *>(parts.shape[0] == 1 ? db->data : parts.data);
+      CHN_TRY(gemm::launch_with_sums(gw, w.transposed, isz, as_stream(stream)));
+      const size_t at = w.fold_offset(gw);
+      if (parts.shape[0] > 1) CHN_TRY(chn_reduce_axis(CHN_REDUCE_SUM, &parts, 0, 0, db, static_cast<char *>(ws) + at, ws_bytes - at, stream));
+      done = true;
     }
   }
-  CHN_TRY(chn_gemm(&dvt, x, dW, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, ws, ws_bytes, stream));
-  if (db) CHN_TRY(chn_reduce_axis(CHN_REDUCE_SUM, dv, 0, 0, db, ws, ws_bytes, stream));
+  if (!done) {
+    CHN_TRY(chn_gemm(&w.A, &w.B, &w.C, 1.0f, 0.0f, CHN_EPI_NONE, nullptr, nullptr, nullptr, ws, ws_bytes, stream));
+    if (db) CHN_TRY(chn_reduce_axis(CHN_REDUCE_SUM, dv, 0, 0, db, ws, ws_bytes, stream));
+  }
   return dx ? chn_gemm(dv, W, dx, 1.0f, 0.0f, epilogue, nullptr, aux, nullptr, ws, ws_bytes, stream) : CHN_OK;
 }
 

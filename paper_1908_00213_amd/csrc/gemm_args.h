@@ -36,8 +36,13 @@ struct GemmArgs {
   int parts;              // fp32 on the bfloat16 matrix cores (gemm_split.h): 0 no, 1 on 64x64 tiles, 2 on 128x128 tiles;
                           // 3: the latency-bound kernel for few tiles and a short K (gemm_tiny.h), whose blocks are
   int small;              // 16x16 or 32x32
-  float *sums;            // backward of a fully connected layer (linear_bwd.hip): [M] sums of A's rows over k, or NULL
+  float *sums;            // backward of a fully connected layer (linear_bwd.hip): sums over k of A's rows or B's columns, or NULL
 };
+
+// Which sums a product's kernel leaves beside C.  kRows: [M], A's rows, by the blocks of the first tile column.  kRowParts,
+// kColumnParts: [splits * tiles_n][M] of A's rows, [splits * tiles_m][N] of B's columns: the blocks that stage the same rows of
+// A (columns of B) take every tiles_n-th (tiles_m-th) tile step of it each, so that none has more to do than the others.
+enum class Sums { kNone, kRows, kRowParts, kColumnParts };
 
 }  // namespace gemm
 }  // namespace chn

@@ -1515,8 +1515,8 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
 // 11.0 -> 7.2 (13.6 -> 8.5 between other kernels); large tile: 2048x2048x2048 29, 37, 45 -> 24, 25, 26.
 template <int TM> constexpr int kSmallDmaStage = 2 * 64 * TM * 128;
 
-// Block `block` of the product (SUMS: and the row sums of A, by the blocks of the first tile column).
-template <int TM, bool A_KC, bool B_KC, bool SUMS>
+// Block `block` of the product, and its share of the sums.
+template <int TM, bool A_KC, bool B_KC, Sums SUMS>
 __device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, char *stage0, char *stage1, char *stage2, char *stage3) {
   using T = bf16_raw;
   constexpr int BM = 64 * TM, BK = 64, STAGES = 4;
@@ -1558,7 +1558,10 @@ __device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, ch
   float sum[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) sum[i] = 0.0f;
-  const bool summing = SUMS && g.sums && tp.tn == 0 && wn == 0;
+  constexpr bool kSums = SUMS != Sums::kNone, kSumB = SUMS == Sums::kColumnParts;
+  const int sharing = SUMS == Sums::kRowParts ? g.tiles_n : kSumB ? g.tiles_m : 1, share = SUMS == Sums::kRowParts ? tp.tn : kSumB ? tp.tm : 0;
+  const bool summing = kSums && g.sums && (SUMS != Sums::kRows || tp.tn == 0) && (kSumB ? wm : wn) == 0;
+  int due = share;                                         // steps until the next one that counts
   constexpr int kAhead = (STAGES - 2) * 4 * TM;            // copies of the two later tiles, per wave
   constexpr int kWait = (kAhead & 15) | (kAhead >> 4) << 14 | 0x70;   // vmcnt(kAhead), lgkmcnt(0)
   auto step = [&](const char *cur, char *before, int kt) __attribute__((always_inline)) {
@@ -1579,16 +1582,20 @@ __device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, ch
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) mma<T, TM, TM>(acc, f[ks]);
-    if constexpr (SUMS) {
-      if (summing) {
+    if constexpr (kSums) {
+      if (due == 0) {
+        if (summing) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          float t[4];
+          for (int i = 0; i < TM; ++i) {
+            float t[4];
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) t[ks] = sum8_bf16(f[ks].a[i]);
-          sum[i] += (t[0] + t[1]) + (t[2] + t[3]);
+            for (int ks = 0; ks < 4; ++ks) t[ks] = sum8_bf16(kSumB ? f[ks].b[i] : f[ks].a[i]);
+            sum[i] += (t[0] + t[1]) + (t[2] + t[3]);
+          }
         }
+        due = sharing;
       }
+      --due;
     }
   };
   int kt = kt0;
@@ -1604,31 +1611,32 @@ __device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, ch
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);                // the epilogue reuses the stages
   __syncthreads();
   static_assert(kEpiStageBytes<TM, TM> <= STAGE, "a wave stages its accumulators in one stage");
-  if constexpr (SUMS) {
+  if constexpr (kSums) {
     if (summing) {
+      const int first = kSumB ? n0 + wn * TM * 32 : m0 + wm * TM * 32, extent = kSumB ? g.N : g.M;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const float t = sum[i] + __shfl_xor(sum[i], 32, 64);      // (lanes l and l + 32 hold the two halves of every 16 k)
-        const int row = m0 + (wm * TM + i) * 32 + (lane & 31);
-        if (lane < 32 && row < g.M) g.sums[row] = t;
+        const int row = first + i * 32 + (lane & 31);
+        if (lane < 32 && row < extent) g.sums[(int64_t)(split * sharing + share) * extent + row] = t;
       }
     }
   }
   write_out<TM, TM>(g, acc, wave == 0 ? stage0 : wave == 1 ? stage1 : wave == 2 ? stage2 : stage3, m0, n0, split);
 }
 
-template <int TM, bool A_KC, bool B_KC>
+template <int TM, bool A_KC, bool B_KC, Sums SUMS = Sums::kNone>
 __global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
   __shared__ __align__(1024) char stage0[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage1[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage2[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage3[kSmallDmaStage<TM>];
-  small_dma_block<TM, A_KC, B_KC, false>(g, blockIdx.x, stage0, stage1, stage2, stage3);
+  small_dma_block<TM, A_KC, B_KC, SUMS>(g, blockIdx.x, stage0, stage1, stage2, stage3);
 }
 
-template <int TM, bool A_KC, bool B_KC>
+template <int TM, bool A_KC, bool B_KC, Sums SUMS = Sums::kNone>
 chn_status launch_small_dma(const GemmArgs &g, hipStream_t st) {
-  hipLaunchKernelGGL((gemm_kernel_small_dma<TM, A_KC, B_KC>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), 0, st, g);
+  hipLaunchKernelGGL((gemm_kernel_small_dma<TM, A_KC, B_KC, SUMS>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), 0, st, g);
   CHN_TRY(check_launch("gemm (small direct copy)"));
   if (g.splits > 1) {
     const int64_t n = (int64_t)g.M * (g.ldp / 4);

@@ -216,8 +216,8 @@ struct SplitLoader {
 template <int TM, int TN, int KG>
 constexpr int kSplitStage = (KG / 2) * (kSplitSub<64 * TM> + kSplitSub<64 * TN>);
 
-// Block `block` of the product (SUMS: and the row sums of A, by the blocks of the first tile column).  lds: two stages.
-template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, bool SUMS>
+// Block `block` of the product, and its share of the sums.  lds: two stages.
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, Sums SUMS>
 __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *lds, int &redo) {
   constexpr int BM = 64 * TM, BN = 64 * TN, BK = 16 * KG, SUBS = KG / 2;
   constexpr int A_BYTES = SUBS * kSplitSub<BM>, STAGE = kSplitStage<TM, TN, KG>;
@@ -260,21 +260,29 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
     }
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
-    // row sums of A: what this thread has staged of it, by its rows
+    // sums: what this thread has staged, by its rows of A (columns of B); `due`: stored tiles until the next one that counts
+    constexpr bool kSums = SUMS != Sums::kNone, kSumB = SUMS == Sums::kColumnParts;
+    static_assert(!kSums || (kHalves && (!kSumB || (kAlike && BM == BN))), "one loader stages what is summed");
     float sum[LA::NS];
 #pragma unroll
     for (int e = 0; e < LA::NS; ++e) sum[e] = 0.0f;
-    const bool summing = SUMS && g.sums && tp.tn == 0 && (do_a || !kHalves);
+    const bool sums = kSums && g.sums && (SUMS != Sums::kRows || tp.tn == 0), summing = sums && do_a != kSumB;
+    const int sharing = SUMS == Sums::kRowParts ? g.tiles_n : kSumB ? g.tiles_m : 1, share = SUMS == Sums::kRowParts ? tp.tn : kSumB ? tp.tm : 0;
+    int due = share;
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
       if constexpr (!kHalves) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }
       else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
       else if constexpr (kAlike) { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else la.template issue<PBB, kAlike>(xa, kt * BK); }
       else { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else lb.template issue<PBB, kAlike>(xa, kt * BK); }
     };
-    auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage) __attribute__((always_inline)) {
+    auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage, int tile) __attribute__((always_inline)) {
       constexpr bool any_a = PBA == kAnyPiece, any_b = PBB == kAnyPiece;
-      if constexpr (SUMS) {
-        if (summing) la.add_up(xa, sum, any_a);
+      if constexpr (kSums) {
+        if (due == 0) {                                   // (uniform)
+          if (summing && tile < nk) la.add_up(xa, sum, kSumB ? any_b : any_a);
+          due = sharing;
+        }
+        --due;
       }
       if constexpr (!kHalves) { la.store(xa, stage, any_a); lb.store(xb, stage + A_BYTES, any_b); }
       else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES), do_a ? any_a : any_b);
@@ -305,9 +313,9 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
     // the first two tiles are fetched together
     issue(ra, rb, kt0);
     issue(ra1, rb1, kt0 + 1);
-    store(ra, rb, lds);
+    store(ra, rb, lds, kt0);
     issue(ra, rb, kt0 + 2);
-    store(ra1, rb1, lds + STAGE);
+    store(ra1, rb1, lds + STAGE, kt0 + 1);
     if constexpr (SETS == 2) issue(ra1, rb1, kt0 + 3);
     __syncthreads();
 #pragma unroll
@@ -323,8 +331,8 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
       const char *nxt = lds + (SET == 0 ? STAGE : 0);
       const bool early = grp & 1;
       auto stage_next = [&]() __attribute__((always_inline)) {
-        if constexpr (SETS == 2 && SET == 1) { store(ra1, rb1, cur); issue(ra1, rb1, kt + 4); }
-        else { store(ra, rb, cur); issue(ra, rb, kt + SETS + 2); }
+        if constexpr (SETS == 2 && SET == 1) { store(ra1, rb1, cur, kt + 2); issue(ra1, rb1, kt + 4); }
+        else { store(ra, rb, cur, kt + 2); issue(ra, rb, kt + SETS + 2); }
       };
       __syncthreads();
       if (early) stage_next();
@@ -349,16 +357,17 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
     }
     if (kt < nk) step(S0{}, kt);
     __syncthreads();
-    if constexpr (SUMS) {
-      if (g.sums && tp.tn == 0) {                         // (uniform over the workgroup) the threads that share a row add up in LDS
+    if constexpr (kSums) {
+      if (sums) {                                         // (uniform over the workgroup) the threads that share a row add up in LDS
         float *rows = reinterpret_cast<float *>(lds);     // [part][BM]
         if (summing) la.put_sums(t, sum, rows);
         __syncthreads();
-        if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < g.M) {
+        const int first = kSumB ? n0 : m0, extent = kSumB ? g.N : g.M;
+        if ((int)threadIdx.x < BM && first + (int)threadIdx.x < extent) {
           float s = 0.0f;
 #pragma unroll
           for (int p = 0; p < LA::PARTS; ++p) s += rows[p * BM + threadIdx.x];
-          g.sums[m0 + threadIdx.x] = s;
+          g.sums[(int64_t)(split * sharing + share) * extent + first + threadIdx.x] = s;
         }
         __syncthreads();
       }
@@ -473,18 +482,18 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
   }
 }
 
-template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, Sums SUMS = Sums::kNone>
 __global__ __launch_bounds__(256 * KG) void gemm_split_kernel(GemmArgs g) {
   extern __shared__ __align__(16) char lds[];
   __shared__ int redo;
-  split_block<TM, TN, KG, A_KC, B_KC, PBA, PBB, false>(g, blockIdx.x, lds, redo);
+  split_block<TM, TN, KG, A_KC, B_KC, PBA, PBB, SUMS>(g, blockIdx.x, lds, redo);
 }
 
-template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB>
+template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, Sums SUMS = Sums::kNone>
 chn_status launch_split_piece(const GemmArgs &g, hipStream_t st) {
   constexpr int LDS = 2 * kSplitStage<TM, TN, KG>;
   static_assert(4 * KG * kEpiStageBytes<1, TN> <= LDS && (64 * TM + 64 * TN) * 128 <= LDS, "the stages are reused by what follows the loop");
-  auto kern = gemm_split_kernel<TM, TN, KG, A_KC, B_KC, PBA, PBB>;
+  auto kern = gemm_split_kernel<TM, TN, KG, A_KC, B_KC, PBA, PBB, SUMS>;
   static bool configured = false;  // per instantiation
   if (!configured) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);

@@ -11,5 +11,10 @@ enum class LinearBwd { kApart, kTiny, kSplit, kDma };
 // Both unsplit, on tiles of the kind's size.
 chn_status launch_linear_bwd(const GemmArgs &w, const GemmArgs *dx, bool w_kc, LinearBwd kind, hipStream_t st);
 
+// A larger product, both operands along M/N, planned as it may be, that leaves parts of the sums of A's rows or B's columns in g.sums:
+// splits * tiles_n of M or splits * tiles_m of N.  Not every kernel does.
+bool sums_of_large(const GemmArgs &g, int isz);
+chn_status launch_with_sums(const GemmArgs &g, bool of_b, int isz, hipStream_t st);
+
 }  // namespace gemm
 }  // namespace chn

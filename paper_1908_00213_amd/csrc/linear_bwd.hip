@@ -27,8 +27,8 @@ template <bool W_KC, int PB, int KG>
 __global__ __launch_bounds__(256 * KG, 4) void linear_bwd_split_kernel(GemmArgs w, GemmArgs x, int n_w) {
   extern __shared__ __align__(16) char lds[];
   __shared__ int redo;
-  if ((int)blockIdx.x < n_w) split_block<1, 1, KG, false, false, PB, PB, true>(w, blockIdx.x, lds, redo);
-  else split_block<1, 1, KG, true, W_KC, PB, PB, false>(x, blockIdx.x - n_w, lds, redo);
+  if ((int)blockIdx.x < n_w) split_block<1, 1, KG, false, false, PB, PB, Sums::kRows>(w, blockIdx.x, lds, redo);
+  else split_block<1, 1, KG, true, W_KC, PB, PB, Sums::kNone>(x, blockIdx.x - n_w, lds, redo);
 }
 
 template <bool W_KC>
@@ -37,8 +37,8 @@ __global__ __launch_bounds__(256) void linear_bwd_dma_kernel(GemmArgs w, GemmArg
   __shared__ __align__(1024) char stage1[kSmallDmaStage<1>];
   __shared__ __align__(1024) char stage2[kSmallDmaStage<1>];
   __shared__ __align__(1024) char stage3[kSmallDmaStage<1>];
-  if ((int)blockIdx.x < n_w) small_dma_block<1, false, false, true>(w, blockIdx.x, stage0, stage1, stage2, stage3);
-  else small_dma_block<1, true, W_KC, false>(x, blockIdx.x - n_w, stage0, stage1, stage2, stage3);
+  if ((int)blockIdx.x < n_w) small_dma_block<1, false, false, Sums::kRows>(w, blockIdx.x, stage0, stage1, stage2, stage3);
+  else small_dma_block<1, true, W_KC, Sums::kNone>(x, blockIdx.x - n_w, stage0, stage1, stage2, stage3);
 }
 
 namespace {
@@ -90,6 +90,25 @@ chn_status launch_linear_bwd(const GemmArgs &w, const GemmArgs *dx, bool w_kc, L
   const bool aligned = w.piece == 16 && x.piece == 16;
   if (w_kc) return aligned ? launch_split_pair<true, 16>(w, x, n_w, n_x, st) : launch_split_pair<true, kAnyPiece>(w, x, n_w, n_x, st);
   return aligned ? launch_split_pair<false, 16>(w, x, n_w, n_x, st) : launch_split_pair<false, kAnyPiece>(w, x, n_w, n_x, st);
+}
+
+bool sums_of_large(const GemmArgs &g, int isz) {
+  if (isz == 2) return g.tile < 2 && g.dma;
+  return (g.parts == 1 || g.parts == 2) && (g.piece == 16 || (g.any_a && g.any_b));
+}
+
+template <Sums SUMS>
+chn_status launch_large(const GemmArgs &g, int isz, hipStream_t st) {
+  if (isz == 2) return g.tile == 1 ? launch_small_dma<2, false, false, SUMS>(g, st) : launch_small_dma<1, false, false, SUMS>(g, st);
+  if (g.parts == 1) {
+    if (g.piece == 16) return launch_split_piece<1, 1, 4, false, false, 16, 16, SUMS>(g, st);
+    return launch_split_piece<1, 1, 4, false, false, kAnyPiece, kAnyPiece, SUMS>(g, st);
+  }
+  if (g.piece == 16) return launch_split_piece<2, 2, 2, false, false, 16, 16, SUMS>(g, st);
+  return launch_split_piece<2, 2, 2, false, false, kAnyPiece, kAnyPiece, SUMS>(g, st);
+}
+chn_status launch_with_sums(const GemmArgs &g, bool of_b, int isz, hipStream_t st) {
+  return of_b ? launch_large<Sums::kColumnParts>(g, isz, st) : launch_large<Sums::kRowParts>(g, isz, st);
 }
 
 }  // namespace gemm

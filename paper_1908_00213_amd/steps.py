@@ -287,16 +287,13 @@ class LSTMTrainer:
         fits = fits and self.whole_sequence and (not lowp or B.lstm_seq_bwd_in_xcd(Bn, Hp, T, adt))
         self.whole_sequence_bwd = fits if whole_sequence_bwd is None else bool(whole_sequence_bwd)
         self.ws_seq_bwd = torch.zeros(B.lstm_seq_bwd_workspace_bytes(Bn, Hp), dtype=torch.uint8, device="cuda") if self.whole_sequence_bwd else None
-        # fp32: the two backward products of the output layer read one operand along its strided
-        # dimension, which for fp32 goes through registers instead of straight to LDS; a transposed
-        # copy of that operand (10-12 us each) saves 50-60 us per product
+        # fp32: the output layer's input gradient reads its weights along their strided dimension, beside
+        # the logit gradients along theirs; a transposed copy of the weights (10 us) saves 24 us.  (The weight gradient reads both
+        # operands along their strided dimension and gains nothing from one copy: 475 us, 482 with it.)
         self._WoT = None if lowp else z(Hp, V)
-        self._HallT = None if lowp else z(Hp, n)
         self._g = {k: z(*v.shape) for k, v in self._P.items()}
         self.loss, self.lse = z(()), z(n)
         self.ws_ce = torch.empty(B.softmax_ce_workspace_bytes(n), dtype=torch.uint8, device="cuda")
-        need = max(B.reduce_axis_workspace_bytes(self._dlogits, 0), B.reduce_axis_workspace_bytes(self._dZ, 0), 256)
-        self.ws_red = torch.empty(need, dtype=torch.uint8, device="cuda")
         self._progs = {}
 
     # ---- views without the padding (for callers and tests; the step itself never uses them) ----------
@@ -360,13 +357,7 @@ class LSTMTrainer:
         wp, wn = p.ws(self.ws_ce)
         # loss and gradient in one visit of every row (in fp32 the logit gradients overwrite the logits)
         p.add(L.chn_softmax_ce_fwd_bwd, p.d(self.logits), p.d(tg_f), -1, p.d(self.loss), p.d(self.lse), C.c_float(1.0), p.d(dlog), wp, wn)
-        rp, rn = p.ws(self.ws_red)
-        if self.lowp:
-            _gemm(p, L, dlog.t(), Hall, self._g["W_out"])
-        else:
-            p.add(L.chn_elementwise_broadcast, B.OP["copy"], 1, p.ptrs([Hall.t()]), p.d(self._HallT), None, 0)
-            _gemm(p, L, dlog.t(), self._HallT.t(), self._g["W_out"])
-        p.add(L.chn_reduce_axis, B.REDUCE["sum"], p.d(dlog), 0, 0, p.d(self._g["b_out"]), rp, rn)
+        _linear_bwd(p, L, dlog, None, Hall, self._g["W_out"], self._g["b_out"])
         if self.lowp:
             _gemm(p, L, dlog, Pl["W_out"], self._dHs)
         else:
@@ -387,8 +378,7 @@ class LSTMTrainer:
             if t > 0:
                 _gemm(p, L, blk(self._dZ, t), Pl["U"].t(), blk(self._dHs, t - 1), beta=1.0)
         _gemm(p, L, Hprev.t(), self._dZ, self._g["U"])
-        _gemm(p, L, self._X.t(), self._dZ, self._g["W"])
-        p.add(L.chn_reduce_axis, B.REDUCE["sum"], p.d(self._dZ), 0, 0, p.d(self._g["b"]), rp, rn)
+        _linear_bwd(p, L, self._dZ, None, self._X, self._g["W"].t(), self._g["b"])
         _gemm(p, L, self._dZ, Pl["W"].t(), self._dX)
         p.add(L.chn_embed_bwd, p.d(ids_f), p.d(self._dX), p.d(self._g["E"]), 0)
         names = list(P.keys())

@@ -78,6 +78,17 @@ class GpuBackend:
         return self.B.gemm(A, Bm, Cm, alpha, beta, epilogue, bias, aux, preact_out,
                            ws=self._gemm_ws if need else None)
 
+    def linear_bwd_in_one_launch(self, gy, W, x, gW, gx):
+        return self.B.linear_bwd_in_one_launch(gy, W, x, gx, gW)
+
+    def linear_bwd(self, gy, W, x, gW, gb, gx=None):
+        """gW = gy^T x, gb = column sums of gy and, unless gx is None, gx = gy W, in one call."""
+        gy, W, x, gW, gx = (self.B.desc(a) for a in (gy, W, x, gW, gx))
+        need = self.B.linear_bwd_workspace_bytes(gy, W, x, gx, gW)
+        if need and (self._gemm_ws is None or self._gemm_ws.numel() < need):
+            self._gemm_ws = self._bytes(need)
+        self.B.linear_bwd(gy, W, x, gW, gb, gx, ws=self._gemm_ws if need else None)
+
     def elementwise_broadcast(self, op, inputs, out, scalars=()):
         return self.B.elementwise_broadcast(op, inputs, out, scalars)
 
@@ -683,15 +694,21 @@ class LinearFunction(FunctionNode):
             gz = F.empty(gy.shape, F.dtype(gy))
             F.elementwise_broadcast(self.act + "_bwd", [gy, ref], gz)
             gy = gz
+        gx = F.empty(x.shape, F.dtype(x)) if 0 in indexes else None
+        gW = F.empty(W.shape, "f32") if 1 in indexes and self.grad_slots[indexes.index(1)] is None else None
+        # small layers: both products and the column sums in one launch
+        if gW is not None and 2 in indexes and hasattr(F, "linear_bwd") and F.linear_bwd_in_one_launch(gy, W, x, gW, gx):
+            gb = F.empty((gy.shape[1],), "f32")
+            F.linear_bwd(gy, W, x, gW, gb, gx)
+            return (gW, gb) if gx is None else (gx, gW, gb)
         out = []
         for k, i in enumerate(indexes):
             if i == 0:
-                gx = F.empty(x.shape, F.dtype(x))
                 F.gemm(gy, W, gx)
             elif i == 1:
                 gx = self.grad_slots[k]
                 if gx is None:
-                    gx = F.empty(W.shape, "f32")
+                    gx = gW
                     F.gemm(_t(gy), x, gx)
                 else:
                     F.gemm(_t(gy), x, gx, beta=1.0)
@@ -1411,6 +1428,15 @@ class NStepLSTM(FunctionNode):
                 dc_next = dc[t & 1]
         if 1 in indexes:
             F.gemm(blk(dZ, 0), _t(U), dh0)
+        gU = F.empty(tuple(U.shape), "f32") if 3 in indexes else None
+        gb = F.empty((4 * H,), "f32") if 4 in indexes else None
+        if gU is not None and gb is not None and hasattr(F, "linear_bwd"):
+            F.linear_bwd(dZ, None, Hs[:T * Bn], _t(gU), gb)
+        else:
+            if gU is not None:
+                F.gemm(_t(Hs[:T * Bn]), dZ, gU)
+            if gb is not None:
+                F.reduce_axis("sum", dZ, 0, gb)
         out = []
         for i in indexes:
             if i == 0:
@@ -1419,14 +1445,8 @@ class NStepLSTM(FunctionNode):
                 out.append(dh0)
             elif i == 2:
                 out.append(dZ)
-            elif i == 3:
-                gU = F.empty(tuple(U.shape), "f32")
-                F.gemm(_t(Hs[:T * Bn]), dZ, gU)
-                out.append(gU)
             else:
-                gb = F.empty((4 * H,), "f32")
-                F.reduce_axis("sum", dZ, 0, gb)
-                out.append(gb)
+                out.append(gU if i == 3 else gb)
         return tuple(out)
 
 

@@ -14,7 +14,7 @@ RNG = np.random.default_rng(77)
 
 SHAPES = [(1, 1, 1), (2, 3, 5), (32, 10, 100), (32, 100, 784), (33, 17, 65), (31, 15, 16), (64, 64, 64), (257, 16, 48), (600, 24, 40), (1000, 20, 33),   # small kernel
           (1024, 1000, 1000), (1023, 997, 1001), (1025, 200, 1030), (700, 260, 520), (2000, 129, 190), (640, 1000, 784),                    # one 64x64 tile a unit or two
-          (1024, 10, 1000), (2500, 70, 3000)]                                                                                             # different kernels, or none
+          (1024, 10, 1000), (2500, 70, 3000), (1100, 1030, 1300), (4100, 515, 260), (3000, 650, 1999)]                                    # sums in parts, or none
 
 
 def _dev(a, dt):
@@ -48,6 +48,22 @@ def test_gradients_are_exact(shape, dt, w_layout):
                 assert np.array_equal(db.cpu().numpy(), dv.astype(np.float64).sum(0)), "db"
             if with_dx:
                 assert torch.equal(dx.cpu(), torch.from_numpy(want_dx).float().to(dt)), "dx"
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_weight_gradient_stored_by_columns(shape, dt):
+    # the gradient of weights kept as (inputs, outputs); with too little workspace as with enough
+    M, N, K = shape
+    dv, x = (RNG.integers(-4, 5, size=s).astype(np.float32) for s in ((M, N), (M, K)))
+    d, h = _dev(dv, dt), _dev(x, dt)
+    dW, db = torch.empty(K, N, device="cuda"), torch.empty(N, device="cuda")
+    need = B.linear_bwd_workspace_bytes(d, None, h, None, dW.t())
+    for size in {max(256, need), B.reduce_axis_workspace_bytes(d, 0) + 256}:
+        dW.fill_(7.0), db.fill_(7.0)
+        B.linear_bwd(d, None, h, dW.t(), db, ws=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        assert np.array_equal(dW.cpu().numpy(), x.T.astype(np.float64) @ dv), "dW"
+        assert np.array_equal(db.cpu().numpy(), dv.astype(np.float64).sum(0)), "db"
 
 
 @pytest.mark.parametrize("shape", [(32, 100, 784), (1024, 1000, 1000)])
