@@ -578,9 +578,9 @@ size_t bwd_exchange_bytes(int64_t B, int64_t H) {
 size_t bwd_counter_bytes(int64_t B) { return (size_t)((((B + kBwdRows - 1) / kBwdRows) * sizeof(unsigned) + 255) / 256 * 256); }
 // what the kernels here need by themselves, and with those of lstm_xcd.hip before them
 size_t fwd_workspace(int64_t B) { return 256 + (size_t)((B + 63) / 64) * sizeof(unsigned) + 256; }
-size_t fwd_workspace_xcd(int64_t B) { return xcd::kFwdWords * sizeof(unsigned) + xcd::fwd_messages(B); }
+size_t fwd_workspace_xcd(int64_t B) { return xcd::kWords * sizeof(unsigned) + xcd::fwd_messages(B); }
 size_t bwd_workspace(int64_t B, int64_t H) { return 256 + bwd_counter_bytes(B) + bwd_exchange_bytes(B, H); }
-size_t bwd_workspace_xcd(int64_t B, int64_t H) { return std::max(bwd_workspace(B, H), xcd::kBwdWords * sizeof(unsigned) + xcd::bwd_messages(B, H)); }
+size_t bwd_workspace_xcd(int64_t B, int64_t H) { return std::max(bwd_workspace(B, H), xcd::kWords * sizeof(unsigned) + xcd::bwd_messages(B, H)); }
 
 int patience(int spin_limit) {
   const int p = g_patience.load();
@@ -658,7 +658,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
   hipStream_t st = as_stream(stream);
   const int64_t extent = std::max({a.B * a.h_pitch, a.B * a.c_pitch, a.B * a.zx_pitch, a.B * a.g_pitch, 4 * a.H * a.ut_pitch, a.B * 4 * a.H});
   const bool in_xcd = exchanges_in_xcd(false, t == CHN_BF16, a.B, a.H, n_steps, extent, ws_bytes, fwd_workspace_xcd(a.B));
-  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kFwdWords : (int)(64 + nbb));
+  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq clear"));
   if (in_xcd) {
     xcd::FwdArgs x{};
@@ -671,7 +671,7 @@ chn_status chn_lstm_seq_fwd(const chn_array *zx, const chn_array *Ut, const chn_
     x.Cs = a.Cs; x.c_pitch = a.c_pitch;
     x.gates = a.gates; x.g_pitch = a.g_pitch;
     x.status = a.status; x.state = a.status + xcd::kStateWord; x.ids = a.status + xcd::kFirstId;
-    x.xbuf = reinterpret_cast<char *>(a.status + xcd::kFwdWords);
+    x.xbuf = reinterpret_cast<char *>(a.status + xcd::kWords);
     CHN_TRY(xcd::launch_fwd(x, t == CHN_BF16, st));
     a.state = x.state;
   }
@@ -747,11 +747,11 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
   // (pairs of bfloat16 gradients are read in one access there)
   const bool pairs = t == CHN_F32 || (reinterpret_cast<uintptr_t>(dHs->data) % 4 == 0 && a.dh_pitch % 2 == 0);
   const bool in_xcd = pairs && exchanges_in_xcd(true, t == CHN_BF16, a.B, a.H, n_steps, extent, ws_bytes, bwd_workspace_xcd(a.B, a.H));
-  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kBwdWords : (int)(64 + nbb));
+  hipLaunchKernelGGL(seq_clear_kernel, dim3(1), dim3(256), 0, st, a.status, in_xcd ? xcd::kWords : (int)(64 + nbb));
   CHN_TRY(check_launch("lstm_seq_bwd clear"));
   if (in_xcd) {
     xcd::BwdArgs x{};
-    x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_of(a.H);
+    x.B = (int)a.B; x.H = (int)a.H; x.n_steps = a.n_steps; x.peers = xcd::peers_bwd(a.H);
     x.spin_limit = a.spin_limit; x.patience = patience(a.spin_limit); x.share = g_share_l2.load() ? ~0u : 0u;
     x.U = a.U; x.u_pitch = a.u_pitch;
     x.dHs = a.dHs; x.dh_pitch = a.dh_pitch;
@@ -760,8 +760,8 @@ chn_status chn_lstm_seq_bwd(const chn_array *U, const chn_array *dHs, const chn_
     x.dc_last = a.dc_last; x.dcl_pitch = a.dcl_pitch;
     x.dZ = a.dZ; x.dz_pitch = a.dz_pitch;
     x.dc0 = a.dc0; x.dc0_pitch = a.dc0_pitch;
-    x.status = a.status; x.state = a.status + xcd::kStateWord; x.ids = a.status + xcd::kFirstId; x.flags = a.status + xcd::kFirstFlag;
-    x.xbuf = reinterpret_cast<float *>(a.status + xcd::kBwdWords);
+    x.status = a.status; x.state = a.status + xcd::kStateWord; x.ids = a.status + xcd::kFirstId;
+    x.xbuf = reinterpret_cast<char *>(a.status + xcd::kWords);
     CHN_TRY(xcd::launch_bwd(x, t == CHN_BF16, st));
     a.state = x.state;
   }

@@ -15,10 +15,8 @@ constexpr int kPatience = 1 << 14;                     // polls (about 0.6 us ea
 constexpr unsigned kOpen = 1u << 30, kCalledOff = 1u << 31;
 
 // The words of a workspace that are zero at launch: the status block of the kernels of lstm_seq.hip, with the state among it, their
-// counters, then what they use for messages and these kernels for the members' ids, the flags (backward: one per sender wave) and
-// messages of their own.
-constexpr int kStateWord = 32, kFirstId = 128, kIdWords = kXcds * kMaxPeers, kFirstFlag = kFirstId + kIdWords, kFlagWords = kXcds * 4 * kMaxPeers;
-constexpr int kFwdWords = kFirstFlag, kBwdWords = kFirstFlag + kFlagWords;
+// counters, then what they use for messages and these kernels for the members' ids, and messages of their own.
+constexpr int kStateWord = 32, kFirstId = 128, kIdWords = kXcds * kMaxPeers, kWords = kFirstId + kIdWords;
 
 struct FwdArgs {
   int B, H, n_steps, peers, spin_limit, patience;
@@ -42,16 +40,18 @@ struct BwdArgs {
   const float *dc_last; int64_t dcl_pitch;
   void *dZ; int64_t dz_pitch;
   float *dc0; int64_t dc0_pitch;
-  unsigned *status, *state, *ids, *flags;
-  float *xbuf;
+  unsigned *status, *state, *ids;
+  char *xbuf;
 };
 
 // units of a workgroup: eight per 256 of the hidden width, so that at most 32 workgroups share a group's units
 inline int units_of(int64_t H) { return H <= 256 ? 8 : H <= 512 ? 16 : 24; }
 inline int peers_of(int64_t H) { return (int)((H + units_of(H) - 1) / units_of(H)); }
+// the backward pass works in squares of four: members without units fill the last one
+inline int peers_bwd(int64_t H) { return (peers_of(H) + 3) / 4 * 4; }
 // whether the sizes fit
 inline bool sizes_fit(int64_t B, int64_t H) { return B <= kXcds * kRows && H <= kMaxHidden; }
-inline bool takes(int64_t B, int64_t H, int cus) { return sizes_fit(B, H) && cus >= kXcds * peers_of(H); }
+inline bool takes(int64_t B, int64_t H, int cus) { return sizes_fit(B, H) && cus >= kXcds * peers_bwd(H); }
 // Steps from which a walk pays: U has to come into the registers, the workgroups have to meet, and the kernels that would take over
 // are launched behind, which the first steps, cheaper each, have to earn back (us, the kernels of lstm_seq.hip against these: fp32
 // forward 96 x 560 at one step 13.9 and 29.7, 32 x 528 at three 30.4 and 36.9, at four 39.4 and 40.7, 128 x 672 at four 53.0 and 44.8;
@@ -65,11 +65,11 @@ inline int least_steps(bool backward, bool bf16, int64_t B, int64_t H) {
   return backward ? bwd[bf16][B <= 32 ? 0 : B <= 64 ? 1 : 2][s] : fwd[bf16][B > 64][s];
 }
 // bytes of the messages: fp32 exchanges the three parts of h through four blocks (of the widest row: the caller of the forward
-// pass names no width), the backward pass its partial sums through two
+// pass names no width), the backward pass dz (fp32: its three parts) and partial sums of dh through four blocks each
 inline size_t fwd_messages(int64_t B) { return (size_t)((B + kRows - 1) / kRows * 4 * (kMaxHidden / 32) * 3 * 1024); }
 inline size_t bwd_messages(int64_t B, int64_t H) {
-  const int64_t g = peers_of(H);
-  return 2 * (size_t)((B + kRows - 1) / kRows * g * g * units_of(H) * kRows) * sizeof(float);
+  const int64_t g = peers_bwd(H);
+  return 4 * (size_t)((B + kRows - 1) / kRows * (g * (units_of(H) / 8) * 3 * 1024 + (g / 4 + 1) / 2 * 2 * (H / 8) * 512));
 }
 
 chn_status launch_fwd(const FwdArgs &a, bool bf16, hipStream_t st);

@@ -31,7 +31,7 @@ constexpr int kThreads = 256;
 // Cache policies of a buffer access.  What a store leaves in the XCD's L2 is there for its other compute units; a load has to get
 // past the vector cache of its own, which the device scope does (sc1) and the workgroup scope (sc0) does not.
 constexpr int kLoadXcd = 16, kStoreXcd = 0, kLoadDevice = 17, kStoreDevice = 17;
-constexpr int kNowhere = 0x7ffffff0;                   // a byte offset past every resource: loads give zero
+constexpr int kNowhere = 0x7f000000;                   // a byte offset past every resource, whatever is added: loads give zero
 constexpr unsigned kAbsent = 0xffffffffu;              // what a word of h holds until its value arrives
 constexpr int kMayCross = 0x7f6;                       // sched_barrier: everything but matrix instructions
 constexpr float kUnscale = 1.0f / (kSplitScale * kSplitScale);
@@ -43,11 +43,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t resource(const void *p, int64_
 template <bool LOCAL> __device__ __forceinline__ chn_u32x4 load16(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, LOCAL ? kLoadXcd : kLoadDevice);
 }
-template <bool LOCAL> __device__ __forceinline__ u32x2 load8(__amdgpu_buffer_rsrc_t r, int off) {
-  return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, LOCAL ? kLoadXcd : kLoadDevice);
-}
-template <bool LOCAL> __device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, int off, const floatx4 &v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(chn_u32x4, v), r, off, 0, LOCAL ? kStoreXcd : kStoreDevice);
+template <bool LOCAL> __device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, int off, const chn_u32x4 &v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, LOCAL ? kStoreXcd : kStoreDevice);
 }
 template <bool LOCAL> __device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t r, int off, unsigned v) {
   __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, LOCAL ? kStoreXcd : kStoreDevice);
@@ -57,8 +54,9 @@ template <bool LOCAL> __device__ __forceinline__ void store_word(unsigned *p, un
   else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned load_word(const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-// two neighbouring bfloat16 values, the word never kAbsent (a NaN of another payload then)
+// two neighbouring bfloat16 values, or an fp32 one, the word never kAbsent (a NaN of another payload then)
 __device__ __forceinline__ unsigned present(unsigned v) { return v == kAbsent ? 0xffff7fffu : v; }
+__device__ __forceinline__ unsigned present_f32(float v) { return __float_as_uint(v) == kAbsent ? 0x7fffffffu : __float_as_uint(v); }
 
 // Eight k of one row or column as the matrix instruction reads them: one bfloat16 vector, or the three parts of eight fp32.
 template <typename T> struct Parts;
@@ -86,6 +84,20 @@ __device__ __forceinline__ void pin(Parts<float> &p, int i) {
   if (i < kPinned) asm volatile("" : "+a"(p.h), "+a"(p.m));
 }
 __device__ __forceinline__ floatx4 mma(const bf16x8 &a, const bf16x8 &b, const floatx4 &c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// Four words a lane, seen as rows of sixteen lanes by words: transposed, so that row i holds word i of rows 0 to 3.
+__device__ __forceinline__ void swap16(unsigned &a, unsigned &b) {       // odd rows of a change places with even rows of b
+  const auto v = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = v[0]; b = v[1];
+}
+__device__ __forceinline__ void swap32(unsigned &a, unsigned &b) {       // the upper half of a with the lower half of b
+  const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = v[0]; b = v[1];
+}
+__device__ __forceinline__ void transpose_rows(unsigned (&w)[4]) {
+  swap16(w[0], w[1]); swap16(w[2], w[3]);
+  swap32(w[0], w[2]); swap32(w[1], w[3]);
+}
 
 // s_barrier without waiting for vector memory: LDS writes before it are visible after it, stores and prefetches stay in flight
 __device__ __forceinline__ void lds_barrier() {
@@ -446,23 +458,31 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_fwd_kernel(FwdArgs a) {
 }
 
 // ---- backward ------------------------------------------------------------------------------------------------------------
-// dh_t = (gradient from above) + dz_{t+1} U^T, contracted over the 4 H gate columns.  A workgroup multiplies the dz it has just
-// produced itself (16 rows x 32 S gate columns, through LDS) with its columns of U, resident as in the forward pass:
-// a partial dh of all H units.  Each member of the group receives its units' part from every member and adds them in
-// the members' order.  The partial sums are too many to be marked and checked word by word: a wave waits until the L2 has
-// its stores, then raises a flag; a receiving wave looks at the flags of the waves that hold its units, 128 bytes in a row.
-// The layout of a message, [receiver][sender][unit / 4][16 rows][4 units], is what the result tiles give in 16-byte stores of
-// 256 bytes in a row, and what a receiver reads back in 512.
+// dh_t = (gradient from above) + dz_{t+1} U^T, contracted over the 4 H gate columns, for the group's sixteen rows.  A workgroup's
+// cell makes dz of its 8 S units; what it multiplies is another matter: the members stand in squares of four, a member gathers
+// the dz of its square (the contraction: 128 S gate columns, a member's by each wave) and multiplies it with a quarter of U^T's
+// units, by its place in the square.  So a step is two trips through the L2, dz to the four members of a square, then partial sums of dh
+// to the owners of the units, one from every square, which they add in the squares' order.
+// us a step at 128 rows, 672 units, bf16 / fp32: with every member multiplying its own dz with all of U^T and sending partial sums of all
+// units to all members (one trip, but 1.2 MB a step and XCD each way, a wait for acknowledged stores and a flag) 4.4 and 6.6.
+// Values are their own arrival, as in the forward pass: four blocks of either kind of message take turns, what a block's next use will
+// write holds kAbsent before.  Partial sums: the reader, the only one of those bytes, puts the marks back when it has read
+// them.  dz: the sender marks its own words of the block of two steps ago once it has partial sums of this step: they were made, square
+// by square, from dz of the step before, which a member sends when it has made its sums of two steps ago.  (A member without units
+// sends no dz, but the sums it made of that block have been needed since.)  A wave waits for its marks before it sends its next dz; a block
+// is used again two (dz) and four (sums) steps on, when everybody's dz of the step before has been waited for.
+// tests/test_sequence_marks.py is the protocol as a model.
 template <typename T, int S>
 __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   constexpr bool kSplit = sizeof(T) == 4;
-  constexpr int NT = 4 * S, E = (int)sizeof(T), PARTS = kSplit ? 3 : 1;
-  constexpr int NLO = !kSplit ? 0 : NT * S < 32 ? NT * S : 32;           // low parts that lie in LDS (beside the tiles of dz it holds 32 a wave)
-  constexpr int kLoBytes = 4 * NLO * 1024, kTile = S * 1024, kRaw = kSplit ? 2 * kTile : 0;
-  constexpr int kUse = kLoBytes + 2 * (PARTS * kTile + kRaw) + 16;
-  constexpr int kBytes = kUse > 84 * 1024 ? kUse : 84 * 1024;
+  constexpr int TILES = 4 * S, E = (int)sizeof(T), PARTS = kSplit ? 3 : 1, PAIRS = kMaxPeers / 8;
+  constexpr int NLO = !kSplit ? 0 : TILES * S < 27 ? TILES * S : 27;     // low parts that lie in LDS (beside the sums it holds 27 a wave)
+  constexpr int kLoBytes = 4 * NLO * 1024, kSumBytes = TILES * 4 * 1024, SETS = kSplit ? 1 : 2;   // (two sets of sums: no barrier behind their use)
+  constexpr int kUse = kLoBytes + SETS * kSumBytes + 16, kBytes = kUse > 84 * 1024 ? kUse : 84 * 1024;
+  constexpr int kMessage = S * PARTS * 1024;                            // dz of a member
   __shared__ __attribute__((aligned(1024))) char lds[kBytes];
   bf16x8 *const lo = reinterpret_cast<bf16x8 *>(lds);
+  floatx4 *const sums = reinterpret_cast<floatx4 *>(lds + kLoBytes);
   int *const word = reinterpret_cast<int *>(lds + kUse - 16);   // [0], [1]: a wait of an even, odd step ran out; [2]: how the group met
   const int group = blockIdx.x % kXcds, idx = blockIdx.x / kXcds;
   const int b0 = group * kRows;
@@ -470,18 +490,20 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 15, q = lane >> 4;
   const int B = a.B, H = a.H, u0 = idx * 8 * S, n_mt = H / 16, T_ = a.n_steps, G = a.peers, n_groups = (B + kRows - 1) / kRows;
+  const int square = idx >> 2, quarter = (n_mt + 3) / 4, mt0 = (idx & 3) * quarter, n_tiles = min(n_mt - mt0, quarter);   // (n_tiles may be < 1)
+  const int from = 4 * square + wave;                                    // the member whose dz this wave multiplies
 
-  // ---- U, once: rows = all units (tile 4 n + wave), k-step s = unit u0 + 8 s + e of gate q
-  Parts<T> u[NT][S];
+  // ---- U, once: rows = units of the quarter (tile n), k-step s = unit 8 S from + 8 s + e of gate q
+  Parts<T> u[TILES][S];
   {
     const __amdgpu_buffer_rsrc_t ur = resource(a.U, ((H - 1) * a.u_pitch + 4 * (int64_t)H) * E);
-    const float scale = idx & 1 ? -kSplitScale : kSplitScale;
+    const float scale = wave & 1 ? -kSplitScale : kSplitScale;
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < TILES; ++n)
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        const int row = 16 * (4 * n + wave) + r, unit = u0 + 8 * s;
-        const int off = row < H && unit < H ? (int)((row * a.u_pitch + q * H + unit) * E) : kNowhere;
+        const int row = 16 * (mt0 + n) + r, unit = from * 8 * S + 8 * s;
+        const int off = n < n_tiles && unit < H ? (int)((row * a.u_pitch + q * H + unit) * E) : kNowhere;
         if constexpr (kSplit) {
           u[n][s].set(load16<true>(ur, off), load16<true>(ur, off == kNowhere ? off : off + 16), scale);
           if (S == 3) pin(u[n][s], n * S + s);
@@ -499,24 +521,70 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   u32x2 gt[4], cprev;
   float cc[2] = {0.0f, 0.0f};
   Pair d_raw{};
-  const int g_off = live ? (int)(((int64_t)b * a.g_pitch + j) * 4) : kNowhere, c_off = live ? (int)(((int64_t)b * a.c_pitch + j) * 4) : kNowhere;
-  const int d_off = live ? (int)(((int64_t)b * a.dh_pitch + j) * E) : kNowhere;
-  auto fetch = [&](int t) __attribute__((always_inline)) {               // zeros in lanes that hold no unit
-    const __amdgpu_buffer_rsrc_t gr = resource(a.gates + (int64_t)t * B * a.g_pitch, ((int64_t)(B - 1) * a.g_pitch + 4 * (int64_t)H) * 4);
-    const __amdgpu_buffer_rsrc_t cr = resource(a.Cs + (int64_t)t * B * a.c_pitch, ((int64_t)(B - 1) * a.c_pitch + H) * 4);
-    const __amdgpu_buffer_rsrc_t dr = resource(static_cast<const T *>(a.dHs) + (int64_t)t * B * a.dh_pitch, ((int64_t)(B - 1) * a.dh_pitch + H) * E);
+  // Everything below is one wave a SIMD: an instruction costs five cycles whatever it does.  So what can be is an offset that stays
+  // (all of a lane's, and `place` below; a kernel whose registers are full of U makes them anew) or a pointer that moves on.
+  constexpr bool kFull = kSplit && S == 3;
+  auto fresh = [&](int x) __attribute__((always_inline)) { if constexpr (kFull) keep_here(x); return x; };
+  auto step_rows = [&](const void *p, int64_t pitch, int size, int t) __attribute__((always_inline)) { return static_cast<const char *>(p) + (int64_t)t * B * pitch * size; };
+  const char *gates_t = step_rows(a.gates, a.g_pitch, 4, T_ - 1), *cs_t = step_rows(a.Cs, a.c_pitch, 4, T_ - 1), *dhs_t = step_rows(a.dHs, a.dh_pitch, E, T_ - 1);
+  const char *dhs_out = dhs_t, *dz_out = step_rows(a.dZ, a.dz_pitch, E, T_ - 1);
+  const int64_t gates_step = (int64_t)B * a.g_pitch * 4, cs_step = (int64_t)B * a.c_pitch * 4, dhs_step = (int64_t)B * a.dh_pitch * E, dz_step = (int64_t)B * a.dz_pitch * E;
+  const int gates_bytes = (int)(((B - 1) * a.g_pitch + 4 * (int64_t)H) * 4), cs_bytes = (int)(((B - 1) * a.c_pitch + H) * 4);
+  const int dhs_bytes = (int)(((B - 1) * a.dh_pitch + H) * E), dz_bytes_t = (int)(((B - 1) * a.dz_pitch + 4 * (int64_t)H) * E);
+  auto lane_off = [&](int64_t pitch, int size) __attribute__((always_inline)) { return live ? (int)((b * pitch + fresh(j)) * size) : kNowhere; };
+  auto fetch = [&]() __attribute__((always_inline)) {                    // the inputs of the step that the pointers are at: zeros in lanes that hold no unit
+    const __amdgpu_buffer_rsrc_t gr = resource(gates_t, gates_bytes);
+    const int at = lane_off(a.g_pitch, 4);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) gt[g] = __builtin_amdgcn_raw_buffer_load_b64(gr, g_off, g * H * 4, 0);
-    cprev = __builtin_amdgcn_raw_buffer_load_b64(cr, c_off, 0, 0);
-    if constexpr (kSplit) d_raw = __builtin_amdgcn_raw_buffer_load_b64(dr, d_off, 0, 0);
-    else d_raw = __builtin_amdgcn_raw_buffer_load_b32(dr, d_off, 0, 0);
+    for (int g = 0; g < 4; ++g) gt[g] = __builtin_amdgcn_raw_buffer_load_b64(gr, at, g * H * 4, 0);
+    cprev = __builtin_amdgcn_raw_buffer_load_b64(resource(cs_t, cs_bytes), lane_off(a.c_pitch, 4), 0, 0);
+    if constexpr (kSplit) d_raw = __builtin_amdgcn_raw_buffer_load_b64(resource(dhs_t, dhs_bytes), lane_off(a.dh_pitch, E), 0, 0);
+    else d_raw = __builtin_amdgcn_raw_buffer_load_b32(resource(dhs_t, dhs_bytes), lane_off(a.dh_pitch, E), 0, 0);
+    gates_t -= gates_step; cs_t -= cs_step; dhs_t -= dhs_step;
   };
   if (live) {
     if (a.dc_last) { dc[0] = a.dc_last[b * a.dcl_pitch + j]; dc[1] = a.dc_last[b * a.dcl_pitch + j + 1]; }
     cc[0] = a.Cs[((int64_t)T_ * B + b) * a.c_pitch + j]; cc[1] = a.Cs[((int64_t)T_ * B + b) * a.c_pitch + j + 1];
   }
-  fetch(T_ - 1);
-  wait_vector_memory();
+  // ---- the messages of a step, [member][k-step][part][gate][16 rows][8 units] and [unit / 8][square][unit / 4 % 2][16 rows][4 units], an even number of squares (the one too many holds zeros), and this lane's
+  // places in them, sixteen bytes each; lanes without a unit, and k-steps and units past the width, lie outside.  Rows past the batch repeat its last one.
+  const int rows = B - b0 < kRows ? B - b0 : kRows, pairs = (G / 4 + 1) / 2;
+  const int64_t dz_bytes = (int64_t)G * kMessage, sum_bytes = (int64_t)(H / 8) * pairs * 1024;
+  auto dz_block = [&](int step) __attribute__((always_inline)) { return resource(a.xbuf + ((int64_t)(step & 3) * n_groups + group) * dz_bytes, dz_bytes); };
+  auto sum_block = [&](int step) __attribute__((always_inline)) {
+    return resource(a.xbuf + 4 * n_groups * dz_bytes + ((int64_t)(step & 3) * n_groups + group) * sum_bytes, sum_bytes);
+  };
+  const int j8 = u0 + 8 * wave;                                          // this wave's first unit
+  auto dz_to = [&]() __attribute__((always_inline)) { return live ? idx * kMessage + wave * PARTS * 1024 + fresh(lane) * 16 : kNowhere; };
+  // sums: lanes 16 q .. 16 q + 15 hold quad q / 2 of the squares of parity q % 2
+  auto sums_at = [&](int pair) __attribute__((always_inline)) {
+    const int l = fresh(lane);
+    return ((j8 >> 3) * pairs + pair) * 1024 + (l >> 4 & 1) * 512 + (l >> 5) * 256 + min(l & 15, rows - 1) * 16;
+  };
+  const chn_u32x4 absent = {kAbsent, kAbsent, kAbsent, kAbsent};
+  auto mark_dz = [&](int step, auto scope) __attribute__((always_inline)) {
+    constexpr bool LOCAL = decltype(scope)::value;
+    const __amdgpu_buffer_rsrc_t m = dz_block(step);
+    const int to = dz_to();
+#pragma unroll
+    for (int part = 0; part < PARTS; ++part) store16<LOCAL>(m, to + part * 1024, absent);
+  };
+  auto mark_sums = [&](int step, auto scope) __attribute__((always_inline)) {
+    constexpr bool LOCAL = decltype(scope)::value;
+    const __amdgpu_buffer_rsrc_t m = sum_block(step);
+    const int at = live ? sums_at(0) : kNowhere;
+#pragma unroll
+    for (int pair = 0; pair < PAIRS; ++pair) {
+      const unsigned mark = 2 * pair + (fresh(lane) >> 4 & 1) < G / 4 ? kAbsent : 0u;
+      store16<LOCAL>(m, pair < pairs ? at + pair * 1024 : kNowhere, chn_u32x4{mark, mark, mark, mark});
+    }
+  };
+  if (wave < S) {
+#pragma unroll 1
+    for (int block = 0; block < 4; ++block) { mark_dz(block, std::false_type{}); mark_sums(block, std::false_type{}); }
+  }
+  fetch();
+  wait_vector_memory();                                // U, the first inputs; the marks are in place
   __syncthreads();
   if (wave == 0) {
     const unsigned m = meet(a.state, a.ids, G, n_groups, group, idx, lane, a.patience, a.share);
@@ -524,18 +592,14 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   }
   __syncthreads();
   const unsigned met = (unsigned)__builtin_amdgcn_readfirstlane(word[2]);
-  if (met == kCalledOff) return;
-
-  const int64_t slot_floats = (int64_t)G * G * 8 * S * kRows;          // one step's messages of a group
-  unsigned *const flags = a.flags + group * 4 * kMaxPeers;
-  const int from_wave = ((u0 + 8 * wave) / 16) & 3;                    // the waves that hold this wave's eight units
+  if (met == kCalledOff || (u0 >= H && n_tiles < 1)) return;    // (a member that nobody waits for)
 
   auto walk = [&](auto scope) __attribute__((always_inline)) {
     constexpr bool LOCAL = decltype(scope)::value;
 #pragma unroll 1
     for (int step = 0; step < T_; ++step) {
       const int t = T_ - 1 - step;
-      float dzv[4][2], d[2] = {0.0f, 0.0f};
+      float dzv[4][2] = {}, d[2] = {0.0f, 0.0f};
       bool ok = true;
       if (wave < S) {
         // what of the cell's backward does not depend on dh
@@ -546,45 +610,47 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
           k_o[e] = tc;
           k_c[e] = 1.0f - tc * tc;
         }
-        u32x2 now[4], cp;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) now[g] = gt[g];
-        cp = cprev;
-        const Pair d_now = d_raw;
         if (step > 0) {
+          // ---- the partial sums for this wave's units, one from every square
+          const __amdgpu_buffer_rsrc_t xr = sum_block(step);
+          chn_u32x4 part[PAIRS];
+          const int at = j8 < H ? sums_at(0) : kNowhere;
           ok = false;
 #pragma unroll 1
           for (int spins = 0; spins < a.spin_limit; ++spins) {
-            const unsigned seen = lane < G ? load_word(flags + from_wave * kMaxPeers + lane) : (unsigned)step;
+#pragma unroll
+            for (int pair = 0; pair < PAIRS; ++pair) part[pair] = load16<LOCAL>(xr, pair < pairs ? at + pair * 1024 : kNowhere);
             asm volatile("" ::: "memory");
-            if (!__any(seen < (unsigned)step)) { ok = true; break; }
+            unsigned most = 0;
+#pragma unroll
+            for (int pair = 0; pair < PAIRS; ++pair) most = max(most, max(max(part[pair][0], part[pair][1]), max(part[pair][2], part[pair][3])));
+            if (!__any(most == kAbsent)) { ok = true; break; }
             if ((spins & 255) == 255 && given_up(a.status)) break;
           }
           if (!ok && lane == 0) { word[step & 1] = 1; give_up(a.status); }
-          // ---- the partial sums for this wave's units, one message per member, added in the members' order
-          const __amdgpu_buffer_rsrc_t xr = resource(a.xbuf + ((step & 1) * n_groups + group) * slot_floats, slot_floats * 4);
-          int off = (idx * G * 2 * S + 2 * wave + (q >> 1)) * 256 + r * 16 + (q & 1) * 8;
-          keep_here(off);
-          u32x2 part[kMaxPeers];
+          // the squares of each parity, then both: every lane keeps two of its four units
+          floatx4 half = __builtin_bit_cast(floatx4, part[0]);
 #pragma unroll
-          for (int s = 0; s < kMaxPeers; ++s) {
-            part[s] = u32x2{0, 0};
-            if (s < G) part[s] = load8<LOCAL>(xr, off + s * (2 * S * 256));
+          for (int pair = 1; pair < PAIRS; ++pair) half += __builtin_bit_cast(floatx4, part[pair]);
+          chn_u32x4 w = __builtin_bit_cast(chn_u32x4, half);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            unsigned even = w[e], odd = w[2 + e];
+            swap16(even, odd);
+            d[e] = __uint_as_float(even) + __uint_as_float(odd);
           }
-#pragma unroll
-          for (int s = 0; s < kMaxPeers; ++s) { d[0] += __uint_as_float(part[s][0]); d[1] += __uint_as_float(part[s][1]); }
         }
-        fetch(t > 0 ? t - 1 : 0);
-        if constexpr (kSplit) { d[0] += __uint_as_float(d_now[0]); d[1] += __uint_as_float(d_now[1]); }
-        else { d[0] += bf16_to_f32((bf16_raw)(d_now & 0xFFFFu)); d[1] += bf16_to_f32((bf16_raw)(d_now >> 16)); }
+        wait_vector_memory();                            // the marks of the step before are in place
+        if constexpr (kSplit) { d[0] += __uint_as_float(d_raw[0]); d[1] += __uint_as_float(d_raw[1]); }
+        else { d[0] += bf16_to_f32((bf16_raw)(d_raw & 0xFFFFu)); d[1] += bf16_to_f32((bf16_raw)(d_raw >> 16)); }
         // the total is what the cell sees and what is stored: in mixed precision that is the bf16 value
         if constexpr (!kSplit) {
           if (step > 0) { d[0] = bf16_to_f32(f32_to_bf16(d[0])); d[1] = bf16_to_f32(f32_to_bf16(d[1])); }
         }
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          const float i = __uint_as_float(now[0][e]), f = __uint_as_float(now[1][e]), g = __uint_as_float(now[2][e]), o = __uint_as_float(now[3][e]);
-          const float c_before = __uint_as_float(cp[e]);
+          const float i = __uint_as_float(gt[0][e]), f = __uint_as_float(gt[1][e]), g = __uint_as_float(gt[2][e]), o = __uint_as_float(gt[3][e]);
+          const float c_before = __uint_as_float(cprev[e]);
           const float d_o = d[e] * k_o[e];
           const float dcv = dc[e] + d[e] * o * k_c[e];
           const float di = dcv * g, dg = dcv * i, df = dcv * c_before;
@@ -594,102 +660,189 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
           dzv[1][e] = df * f * (1.0f - f);
           dzv[2][e] = dg * (1.0f - g * g);
           dzv[3][e] = d_o * o * (1.0f - o);
-          if (!live) dzv[0][e] = dzv[1][e] = dzv[2][e] = dzv[3][e] = 0.0f;
         }
-      }
-      // ---- dz as the operand of the next product, in the order the matrix instruction reads it
-      char *const tile = lds + kLoBytes + (step & 1) * (PARTS * kTile + kRaw);
-      if (wave < S) {
+        // ---- dz to the members of the square, in the order the matrix instruction reads it: lanes 16 g .. 16 g + 15 hold eight units of gate g
+        constexpr int WORDS = kSplit ? 2 : 1;
+        unsigned dzw[WORDS][4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          char *const p = tile + ((wave * 4 + g) * 16 + r) * 16 + q * 4;
-          if constexpr (kSplit) {
-            uint32_t h, m, l;
-            split2(dzv[g][0] * kSplitScale, dzv[g][1] * kSplitScale, h, m, l);
-            *reinterpret_cast<uint32_t *>(p) = h;
-            *reinterpret_cast<uint32_t *>(p + kTile) = m;
-            *reinterpret_cast<uint32_t *>(p + 2 * kTile) = l;
-            *reinterpret_cast<floatx2 *>(tile + 3 * kTile + ((wave * 4 + g) * 16 + r) * 32 + q * 8) = floatx2{dzv[g][0], dzv[g][1]};
-          } else {
-            *reinterpret_cast<uint32_t *>(p) = pack_bf16(dzv[g][0], dzv[g][1]);
+          if constexpr (kSplit) { dzw[0][g] = __float_as_uint(dzv[g][0]); dzw[WORDS - 1][g] = __float_as_uint(dzv[g][1]); }
+          else dzw[0][g] = pack_bf16(dzv[g][0], dzv[g][1]);
+        }
+#pragma unroll
+        for (int e = 0; e < WORDS; ++e) transpose_rows(dzw[e]);
+        const bool sends = ok && step + 1 < T_;
+        const __amdgpu_buffer_rsrc_t m = dz_block(step);
+        const int to = sends ? dz_to() : kNowhere;
+        if constexpr (kSplit) {
+          chn_u32x4 part[3];
+          float bad = 0.0f;                              // 0, or NaN
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            unsigned hi, mid, low;
+            split2(__uint_as_float(dzw[0][k]) * kSplitScale, __uint_as_float(dzw[1][k]) * kSplitScale, hi, mid, low);
+            bad = __builtin_fmaf(__uint_as_float(hi << 16), 0.0f, __builtin_fmaf(__uint_as_float(hi & 0xffff0000u), 0.0f, bad));
+            part[0][k] = hi; part[1][k] = mid; part[2][k] = low;
+          }
+          if (__builtin_expect(bad != 0.0f, 0)) {
+            // what the parts cannot hold: infinities, which make every sum that meets them be taken again, and the values' own halves in the
+            // place of the other parts (kAbsent, two neighbours whose halves are all ones: one bit less)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const unsigned upper = dzw[0][k] >> 16 | (dzw[1][k] & 0xffff0000u), lower = (dzw[0][k] & 0xffffu) | dzw[1][k] << 16;
+              part[0][k] = 0x7f807f80u;
+              part[1][k] = upper == kAbsent ? 0xfffeffffu : upper;
+              part[2][k] = lower == kAbsent ? 0xfffeffffu : lower;
+            }
+          }
+#pragma unroll
+          for (int p = 0; p < 3; ++p) store16<LOCAL>(m, to + p * 1024, part[p]);
+        } else {
+          store16<LOCAL>(m, to, chn_u32x4{present(dzw[0][0]), present(dzw[0][1]), present(dzw[0][2]), present(dzw[0][3])});
+        }
+        // what leaves the step, while dz is on its way; the marks are for steps two and four on
+        if (step > 0) {
+          const __amdgpu_buffer_rsrc_t dr = resource(dhs_out, dhs_bytes);
+          const int at = lane_off(a.dh_pitch, E);
+          if constexpr (kSplit) __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(d[0]), __float_as_uint(d[1])}, dr, at, 0, 0);
+          else __builtin_amdgcn_raw_buffer_store_b32(pack_bf16(d[0], d[1]), dr, at, 0, 0);
+        }
+        const __amdgpu_buffer_rsrc_t zr = resource(dz_out, dz_bytes_t);
+        const int out = live ? (int)((b * a.dz_pitch + (fresh(lane) >> 4) * H + j8) * E) : kNowhere;
+        if constexpr (kSplit) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e)
+            __builtin_amdgcn_raw_buffer_store_b128(chn_u32x4{dzw[0][2 * e], dzw[1][2 * e], dzw[0][2 * e + 1], dzw[1][2 * e + 1]}, zr, out + 16 * e, 0, 0);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b128(chn_u32x4{dzw[0][0], dzw[0][1], dzw[0][2], dzw[0][3]}, zr, out, 0, 0);
+        }
+        if (step > 0 && step + 2 < T_) {
+          mark_sums(step, scope);
+          mark_dz(step + 2, scope);
+        }
+        dhs_out -= dhs_step; dz_out -= dz_step;
+      }
+      if (step + 1 == T_) break;
+      // ---- the square's dz, as it arrives
+      const __amdgpu_buffer_rsrc_t xr = dz_block(step);
+      chn_u32x4 v[S][PARTS];
+      const int l = fresh(lane);
+      const int at = from * kMessage + (l >> 4) * 256 + min(l & 15, rows - 1) * 16;
+      bool here = false;
+#pragma unroll 1
+      for (int spins = 0; spins < a.spin_limit; ++spins) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+          for (int part = 0; part < PARTS; ++part) v[s][part] = load16<LOCAL>(xr, from * 8 * S + 8 * s < H ? at + (s * PARTS + part) * 1024 : kNowhere);
+        asm volatile("" ::: "memory");
+        unsigned most = 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+          for (int part = 0; part < PARTS; ++part) most = max(most, max(max(v[s][part][0], v[s][part][1]), max(v[s][part][2], v[s][part][3])));
+        if (!__any(most == kAbsent)) { here = true; break; }
+        if ((spins & 255) == 255 && given_up(a.status)) break;
+      }
+      if (!here && lane == 0) { word[step & 1] = 1; give_up(a.status); }
+      if (wave < S && t > 0) fetch();
+      // ---- partial sums of the quarter's units, as many tiles at a time as there are registers for: tile 4 i + w is finished by
+      // wave w
+      constexpr int AT_ONCE = kFull ? 2 : kSplit ? 4 : TILES;
+      floatx4 *const meet_at = sums + (SETS == 2 ? (step & 1) * (kSumBytes / 16) : 0);
+#pragma unroll
+      for (int n0 = 0; n0 < TILES; n0 += AT_ONCE) {
+        floatx4 acc[AT_ONCE];
+#pragma unroll
+        for (int n = 0; n < AT_ONCE; ++n) acc[n] = floatx4{0, 0, 0, 0};
+        if constexpr (kSplit) {
+          floatx4 acc1[AT_ONCE], acc2[AT_ONCE];          // (products with a low part, in two chains)
+#pragma unroll
+          for (int n = 0; n < AT_ONCE; ++n) acc1[n] = acc2[n] = floatx4{0, 0, 0, 0};
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const bf16x8 xh = __builtin_bit_cast(bf16x8, v[s][0]), xm = __builtin_bit_cast(bf16x8, v[s][1]), xl = __builtin_bit_cast(bf16x8, v[s][2]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc1[n] = mma(u[n0 + n][s].h, xm, acc1[n]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc2[n] = mma(u[n0 + n][s].m, xh, acc2[n]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc[n] = mma(u[n0 + n][s].h, xh, acc[n]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc1[n] = mma(u[n0 + n][s].m, xm, acc1[n]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc2[n] = mma(u[n0 + n][s].h, xl, acc2[n]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) {
+              const int f = (n0 + n) * S + s;
+              acc1[n] = mma(f < NLO ? lo[(wave * NLO + f) * 64 + lane] : u[n0 + n][s].l, xh, acc1[n]);
+            }
+            __builtin_amdgcn_sched_barrier(kMayCross);
+          }
+          const float unscale = wave & 1 ? -kUnscale : kUnscale;
+#pragma unroll
+          for (int n = 0; n < AT_ONCE; ++n) acc[n] = (acc[n] + (acc1[n] + acc2[n])) * unscale;
+        } else {
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            const bf16x8 xh = __builtin_bit_cast(bf16x8, v[s][0]);
+#pragma unroll
+            for (int n = 0; n < AT_ONCE; ++n) acc[n] = mma(u[n][s].h, xh, acc[n]);
           }
         }
+#pragma unroll
+        for (int n = 0; n < AT_ONCE; ++n) meet_at[((n0 + n) * 4 + wave) * 64 + lane] = acc[n];
       }
       lds_barrier();
       if (word[step & 1]) break;
-      if (step + 1 < T_) {
-        Parts<T> x[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          const bf16x8 *p = reinterpret_cast<const bf16x8 *>(tile) + s * 64 + lane;
-          x[s].h = p[0];
-          if constexpr (kSplit) { x[s].m = p[kTile / 16]; x[s].l = p[2 * kTile / 16]; }
-        }
-        const __amdgpu_buffer_rsrc_t xw = resource(a.xbuf + (((step + 1) & 1) * n_groups + group) * slot_floats, slot_floats * 4);
-        // rows of a result tile: units 16 mt + 4 q .., columns: batch rows r
-        auto send = [&](const floatx4 &acc, int mt) __attribute__((always_inline)) {
-          int quad = 4 * mt + q;
-          keep_here(quad);
-          const int to = (int)((unsigned)quad / (2 * S));
-          const int off = ((to * G + idx) * (2 * S) + quad - to * 2 * S) * 256 + r * 16;
-          store16<LOCAL>(xw, off, acc);
+      {
+        const __amdgpu_buffer_rsrc_t xw = sum_block(step + 1);
+        auto send = [&](floatx4 acc, int n) __attribute__((always_inline)) {
+          const int l = fresh(lane);
+          const int to = n < n_tiles ? (2 * (mt0 + n) + (l >> 5)) * pairs * 1024 + square * 512 + (l & 31) * 16 : kNowhere;
+          store16<LOCAL>(xw, to, chn_u32x4{present_f32(acc[0]), present_f32(acc[1]), present_f32(acc[2]), present_f32(acc[3])});
         };
-        unsigned again = 0;
+        floatx4 sum[S];
+        float bad = 0.0f;                                // 0, or NaN
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          const int mt = 4 * n + wave;
-          if (mt < n_mt) {
-            floatx4 acc = floatx4{0, 0, 0, 0};
+        for (int i = 0; i < S; ++i) {
+          const int n = 4 * i + wave;
+          sum[i] = meet_at[n * 256 + lane];
 #pragma unroll
-            for (int s = 0; s < S; ++s) acc = mma(u[n][s].h, x[s].h, acc);
-            if constexpr (kSplit) {
-              floatx4 acc1 = floatx4{0, 0, 0, 0};
+          for (int s = 1; s < 4; ++s) sum[i] += meet_at[n * 256 + s * 64 + lane];
+          if constexpr (kSplit) {
 #pragma unroll
-              for (int s = 0; s < S; ++s) {
-                acc1 = mma(u[n][s].h, x[s].m, acc1);
-                acc1 = mma(u[n][s].m, x[s].h, acc1);
-                acc1 = mma(u[n][s].m, x[s].m, acc1);
-                acc1 = mma(u[n][s].h, x[s].l, acc1);
-                if (n * S + s < NLO) acc1 = mma(lo[(wave * NLO + n * S + s) * 64 + lane], x[s].h, acc1);
-                else acc1 = mma(u[n][s].l, x[s].h, acc1);
-              }
-              acc = (acc + acc1) * (idx & 1 ? -kUnscale : kUnscale);
-              if (__any(0.0f * acc[0] + 0.0f * acc[1] + 0.0f * acc[2] + 0.0f * acc[3] != 0.0f)) again |= 1u << n;   // (0, or NaN)
-            }
-            send(acc, mt);
+            for (int e = 0; e < 4; ++e) bad = __builtin_fmaf(sum[i][e], 0.0f, bad);
           }
         }
-        if constexpr (kSplit) {
-          while (__builtin_expect(again != 0u, 0)) {     // such tiles again, on fp32 values
-            const int mt = 4 * __builtin_ctz(again) + wave;
-            again &= again - 1;
-            floatx4 acc = floatx4{0, 0, 0, 0};
+        if (!kSplit || __builtin_expect(!__any(bad != 0.0f), 1)) {
+#pragma unroll
+          for (int i = 0; i < S; ++i) send(sum[i], 4 * i + wave);
+        } else {
+          // this wave's tiles again, on fp32 values; c = (member of the square, k-step, gate, unit)
 #pragma unroll 1
-            for (int c = 0; c < 32 * S; ++c) {           // c = (k-step, gate, unit)
-              const int unit = u0 + 8 * (c >> 5) + (c & 7), gate = (c >> 3) & 3;
-              const float dz = *reinterpret_cast<const float *>(tile + 3 * kTile + (((c >> 3) * 16 + r) * 8 + (c & 7)) * 4);
-              if (unit < H) {
+          for (int n = wave; n < n_tiles; n += 4) {
+            floatx4 acc = floatx4{0, 0, 0, 0};
+            int at = min(r, rows - 1) * 16;
+            keep_here(at);
+#pragma unroll 1
+            for (int c = 0; c < 4 * 32 * S; ++c) {
+              const int m = 4 * square + c / (32 * S), k = c % (32 * S), unit = m * 8 * S + 8 * (k >> 5) + (k & 7), gate = (k >> 3) & 3, sh = k & 1 ? 0 : 16;
+              if (unit >= H) continue;
+              unsigned bits[3];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fmaf(dz, static_cast<const float *>(a.U)[(int64_t)(16 * mt + 4 * q + i) * a.u_pitch + gate * H + unit], acc[i]);
-              }
+              for (int p = 0; p < 3; ++p)
+                bits[p] = __builtin_amdgcn_raw_buffer_load_b32(xr, at, m * kMessage + ((k >> 5) * 3 + p) * 1024 + gate * 256 + (k & 6) * 2, LOCAL ? kLoadXcd : kLoadDevice) << sh & 0xffff0000u;
+              const float hi = __uint_as_float(bits[0]);
+              const float dz = hi * 0.0f != 0.0f ? __uint_as_float(bits[1] | bits[2] >> 16) : ((__uint_as_float(bits[2]) + __uint_as_float(bits[1])) + hi) * (1.0f / kSplitScale);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[e] = fmaf(dz, static_cast<const float *>(a.U)[(int64_t)(16 * (mt0 + n) + 4 * q + e) * a.u_pitch + gate * H + unit], acc[e]);
             }
-            send(acc, mt);
+            send(acc, n);
           }
         }
-        wait_vector_memory();                            // the L2 has them
-        if (lane == 0) store_word<LOCAL>(flags + wave * kMaxPeers + idx, (unsigned)(step + 1));
       }
-      // ---- dz and the total dh leave while the others' sums are on their way
-      if (live) {
-        T *const dhr = static_cast<T *>(a.dHs) + ((int64_t)t * B + b) * a.dh_pitch + j;
-        T *const dzr = static_cast<T *>(a.dZ) + ((int64_t)t * B + b) * a.dz_pitch + j;
-        if (step > 0) { Elem<T>::store(dhr, d[0]); Elem<T>::store(dhr + 1, d[1]); }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          if constexpr (kSplit) *reinterpret_cast<floatx2 *>(dzr + g * H) = floatx2{dzv[g][0], dzv[g][1]};
-          else *reinterpret_cast<uint32_t *>(dzr + g * H) = pack_bf16(dzv[g][0], dzv[g][1]);
-        }
-      }
+      if constexpr (SETS == 1) lds_barrier();            // the sums have been read
     }
   };
   if (met >> group & 1) walk(std::true_type{});
