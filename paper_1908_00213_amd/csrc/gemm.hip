@@ -218,14 +218,14 @@ bool plan_small(GemmArgs *g, int isz, bool big_unsplit) {
   return true;
 }
 
-// fp32 products on the bfloat16 matrix cores (gemm_split.h): the 128x128 tile in two groups of waves or the 64x64 tile
-// in four, against the best plan on the fp32 matrix instruction, by the same kind of model (microseconds, a launch not
-// counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 plus its tile
-// steps (32 k on the large tile, 64 on the small one); a step takes longer when all 256 compute units pull operands out of
+// fp32 products on the bfloat16 matrix cores (gemm_split.h, gemm_split_direct.h): the 128x128 tile in two groups of waves or the 64x64
+// tile in four or by eight waves, against the best plan on the fp32 matrix instruction, by the same kind of model (microseconds, a launch not
+// counted).  Figures measured on 64 to 4096 tiles, K 784 to 10000, all four layouts: a block costs 5.6 (loaded directly 4) plus
+// its tile steps (32 k on the large tile, 64 on the small one); a step takes longer when all 256 compute units pull operands out of
 // the L2s than when a quarter of them does, and element by element (an extent below four).  Each compute
 // unit holds one block at a time.  Where the lines cross (fp32 instruction -> this, us): 1024x1000x1000 27 -> 22 on the
 // small tile, 4480x2688x672 143 -> 101 and 4480x10000x672 499 -> 361 on the large one, 672x2688x4480 both stored along
-// M/N 178 -> 115 cut in two; 300x200x100 stays (7.2, would be 8.8), as does 32x100x784 cut in six (9.2 against 14.6).
+// M/N 178 -> 115 cut in two; 640x640x360 along M/N 12.6 -> 10.2 and 585x800x1472 31.0 -> 25.9 loaded directly.
 // Rows off the 16-byte grid cost little: against the 8-byte pieces of before, 4480x650x2600 159 -> 145 and 2600x650x4480 162 -> 136;
 // against single elements, 4097x2351x2041 556 -> 273 and 8192x4001x651 584 -> 295.
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
@@ -234,7 +234,8 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
   const bool other_forced = force_tile >= 0 || g_force_direct.load(std::memory_order_relaxed) >= 0 || g_force_w8.load(std::memory_order_relaxed) >= 0;
   if (isz != 4 || big_unsplit || g->K == 0 || g->lda >= kMaxLd || g->ldb >= kMaxLd || (other_forced && force != 1)) return;
-  static const double step_large[3] = {1.0, 1.25, 1.2}, step_small[3] = {0.78, 1.1, 0.95};   // both along K, one, none
+  static const double step_large[3] = {1.0, 1.25, 1.2}, step_direct[3] = {2.4, 2.3, 1.95};    // both along K, one, none
+  constexpr double step_small = 0.78;
   const int lay = (a_kc ? 0 : 1) + (b_kc ? 0 : 1);
   auto narrow = [&](bool any, bool kc, bool large) {
     if (g->piece == 16) return 1.0;
@@ -256,19 +257,25 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
     const int b = large ? 128 : 64, bk = large ? 32 : 64;
     const int64_t tiles = (int64_t)((g->M + b - 1) / b) * ((g->N + b - 1) / b);
     const int nk = (g->K + bk - 1) / bk;
-    const double na = narrow(g->any_a, a_kc, large), nb = narrow(g->any_b, b_kc, large);
-    const double step = (large ? step_large : step_small)[lay] * (na > nb ? na : nb);
+    const double na = narrow(g->any_a, a_kc, large), nb = narrow(g->any_b, b_kc, large), narrowed = na > nb ? na : nb;
     for (int s : split_choices) {
       if (s > 1 && (!allow_split || s > nk / 4)) break;
       if (forced_splits >= 1 && allow_split && forced_splits <= nk) s = forced_splits;
       const int64_t blocks = tiles * s, rounds = (blocks + 255) / 256;
       const double fill = blocks < 256 ? (double)blocks / 256 : 1.0;
       const int steps = (nk + s - 1) / s;
-      double t = (double)rounds * (5.6 + steps * step * (large ? 0.9 + 0.25 * fill : 0.8 + 0.2 * fill)) * 1e-6;
-      if (s > 1) t += 5e-6 + (double)(s + 1) * g->M * g->N * 4.0 / 4e12;
+      // The small tile loads its operands straight into registers (gemm_split_direct.h), unless both lie along K and K is long: through
+      // LDS they then come in whole lines.  Eight waves take 128 k a round; in the last one some may have nothing to do.
+      const bool direct = !large && (lay > 0 || (steps <= 7 && s == 1));
+      double t = direct ? 4.0 + 0.5 * ((steps + 1) / 2 + 0.5 * steps) * step_direct[lay] * (0.8 + 0.2 * fill)
+                        : 5.6 + steps * (large ? step_large[lay] * (0.9 + 0.25 * fill) : step_small * (0.8 + 0.2 * fill)) * narrowed;
+      t = (double)rounds * t * 1e-6;
+      if (direct) t -= 1.8e-6;                             // (the first round's blocks start together with the launch)
+      if (s > 1) t += (direct ? 5.7e-6 : 5e-6) + (double)(s + 1) * g->M * g->N * 4.0 / 4e12;
       if (t < best * 0.97) {
         best = t;
         p.parts = large ? 2 : 1;
+        p.direct = direct;
         p.splits = s;
         p.tiles_m = (g->M + b - 1) / b;
         p.tiles_n = (g->N + b - 1) / b;
@@ -464,10 +471,7 @@ gemm::LinearBwd together(const GemmArgs &w, const GemmArgs *dx, int isz, bool w_
   const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n + (dx ? (int64_t)dx->tiles_m * dx->tiles_n : 0);
   if (isz == 4) {
     if (both([](const GemmArgs &g) { return g.parts == 3 && g.small == 16; })) return LinearBwd::kTiny;
-    if (tiles <= 512 && both([](const GemmArgs &g) { return g.parts == 1; }) &&
-        (both([](const GemmArgs &g) { return g.piece == 16; }) || both([](const GemmArgs &g) { return g.any_a && g.any_b; })))
-      return LinearBwd::kSplit;
-    return LinearBwd::kApart;
+    return tiles <= 512 && both([](const GemmArgs &g) { return g.parts == 1 && g.direct; }) ? LinearBwd::kSplit : LinearBwd::kApart;
   }
   return tiles <= 512 && both([](const GemmArgs &g) { return g.tile == 0 && g.dma; }) ? LinearBwd::kDma : LinearBwd::kApart;
 }

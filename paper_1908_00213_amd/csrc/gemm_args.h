@@ -36,6 +36,7 @@ struct GemmArgs {
   int parts;              // fp32 on the bfloat16 matrix cores (gemm_split.h): 0 no, 1 on 64x64 tiles, 2 on 128x128 tiles;
                           // 3: the latency-bound kernel for few tiles and a short K (gemm_tiny.h), whose blocks are
   int small;              // 16x16 or 32x32
+  int direct;             // parts == 1: operands straight to the registers (gemm_split_direct.h)
   float *sums;            // backward of a fully connected layer (linear_bwd.hip): sums over k of A's rows or B's columns, or NULL
 };
 

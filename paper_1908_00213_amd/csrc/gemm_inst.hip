@@ -3,6 +3,7 @@
 // -DCHN_GEMM_NAME=<symbol>.
 #include "gemm_kernel.h"
 #include "gemm_split.h"
+#include "gemm_split_direct.h"
 #include "gemm_tiny.h"
 
 namespace chn {
@@ -12,7 +13,10 @@ chn_status CHN_GEMM_NAME(GemmArgs &g, hipStream_t st) {
   if constexpr (sizeof(CHN_GEMM_T) == 4) {
     if (g.parts == 3) return launch_tiny<CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
     if (g.parts == 2) return launch_split<2, 2, 2, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
-    if (g.parts == 1) return launch_split<1, 1, 4, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
+    if constexpr (CHN_GEMM_AKC && CHN_GEMM_BKC) {
+      if (g.parts == 1 && !g.direct) return launch_split<1, 1, 4, true, true>(g, st);
+    }
+    if (g.parts == 1) return launch_split_direct<CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
   }
   return launch_layout<CHN_GEMM_T, CHN_GEMM_AKC != 0, CHN_GEMM_BKC != 0>(g, st);
 }

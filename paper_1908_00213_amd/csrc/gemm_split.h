@@ -14,7 +14,8 @@
 // Measured (us, fp32 instruction -> here, both operands along K): 1024x1000x1000 27.2 -> 22.0, 4480x2688x672 142.8 -> 101.3,
 // 4480x10000x672 499 -> 361, 4096x4096x4096 961 -> 688 (200 TFLOP/s, where the instruction's peak is 157).  What bounds the
 // large tile is the vector work of the split beside the matrix work (13 instructions per pair of values staged: scaling
-// took it from 667 to 688 at 4096^3); the small tile, one per compute unit, waits for the chip-wide stream of operand tiles.
+// took it from 667 to 688 at 4096^3) and the chip's power limit (1.8 GHz); the small tile, whose waves read 1 KB of LDS for every
+// matrix instruction, LDS: it is left to operands that both lie along a long K (gemm_split_direct.h has the others).
 #pragma once
 #include "gemm_kernel.h"
 #include "split.h"
@@ -114,38 +115,20 @@ struct SplitLoader {
     }
   }
 
-  // Sums over k of what has been loaded, by row: NS of them a thread, to which PARTS threads contribute.
-  static constexpr int NS = KC ? NU : 4, PARTS = KC ? 4 * SUBS : 8 * SUBS * (4 / R);
-  __device__ __forceinline__ void add_up(const uint4 (&reg)[R], float (&s)[NS], bool any) const {
-    if constexpr (KC) {
+  // Sums over k of what has been loaded (along M/N), by row: four of them a thread, to which PARTS threads contribute.
+  static constexpr int PARTS = 8 * SUBS * (4 / R);
+  __device__ __forceinline__ void add_up(const uint4 (&reg)[R], float (&s)[4], bool any) const {
+    static_assert(!KC && R == 4, "the large tile, along M/N");
+    uint4 v[R];
 #pragma unroll
-      for (int u = 0; u < NU; ++u) s[u] += sum4(reg[2 * u]) + sum4(reg[2 * u + 1]);
-    } else {
-      uint4 v[R];
+    for (int j = 0; j < R; ++j) v[j] = any && cut ? move_down(reg[j], down) : reg[j];
 #pragma unroll
-      for (int j = 0; j < R; ++j) v[j] = any && cut ? move_down(reg[j], down) : reg[j];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float x = __uint_as_float((&v[0].x)[e]) + __uint_as_float((&v[1].x)[e]);
-        if constexpr (R == 4) x += __uint_as_float((&v[2].x)[e]) + __uint_as_float((&v[3].x)[e]);
-        s[e] += x;
-      }
-    }
-  }
-  static __device__ __forceinline__ float sum4(const uint4 &v) {
-    return (__uint_as_float(v.x) + __uint_as_float(v.y)) + (__uint_as_float(v.z) + __uint_as_float(v.w));
+    for (int e = 0; e < 4; ++e)
+      s[e] += (__uint_as_float((&v[0].x)[e]) + __uint_as_float((&v[1].x)[e])) + (__uint_as_float((&v[2].x)[e]) + __uint_as_float((&v[3].x)[e]));
   }
   // t: as for init; rows: PARTS x ROWS floats
-  __device__ __forceinline__ void put_sums(int t, const float (&s)[NS], float *rows) const {
-    if constexpr (KC) {
-      const int q = t & 3, row = (t >> 2) % ROWS, sub = t / (4 * ROWS);
-#pragma unroll
-      for (int u = 0; u < NU; ++u) rows[(sub * 4 + q) * ROWS + row + u * (T / 4)] = s[u];
-    } else {
-      constexpr int PAIRS = 4 / R;
-      const int part = t % (8 * PAIRS), mc = (t / (8 * PAIRS)) % (ROWS / 4), sub = t / (2 * PAIRS * ROWS);
-      *reinterpret_cast<float4 *>(rows + (sub * 8 * PAIRS + part) * ROWS + mc * 4) = make_float4(s[0], s[1], s[2], s[3]);
-    }
+  __device__ __forceinline__ void put_sums(int t, const float (&s)[4], float *rows) const {
+    *reinterpret_cast<float4 *>(rows + (t / (2 * ROWS) * 8 + t % 8) * ROWS + t / 8 % (ROWS / 4) * 4) = make_float4(s[0], s[1], s[2], s[3]);
   }
 
   // any: the pieces were read at any address
@@ -244,7 +227,8 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
   {
     // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
     // by all threads together, so that every wave has the same mixture of work.
-    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike || TM == 1;
+    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike;
+    static_assert(TM == 2 || (A_KC && B_KC), "other layouts of the small tile: gemm_split_direct.h");
     // (a mixed pair of aligned operands: steps of whole k without checks do not pay, 4480x2688x672 120 -> 123 us)
     using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
     using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
@@ -262,12 +246,10 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
     // sums: what this thread has staged, by its rows of A (columns of B); `due`: stored tiles until the next one that counts
     constexpr bool kSums = SUMS != Sums::kNone, kSumB = SUMS == Sums::kColumnParts;
-    static_assert(!kSums || (kHalves && (!kSumB || (kAlike && BM == BN))), "one loader stages what is summed");
-    float sum[LA::NS];
-#pragma unroll
-    for (int e = 0; e < LA::NS; ++e) sum[e] = 0.0f;
-    const bool sums = kSums && g.sums && (SUMS != Sums::kRows || tp.tn == 0), summing = sums && do_a != kSumB;
-    const int sharing = SUMS == Sums::kRowParts ? g.tiles_n : kSumB ? g.tiles_m : 1, share = SUMS == Sums::kRowParts ? tp.tn : kSumB ? tp.tm : 0;
+    static_assert(SUMS != Sums::kRows && (!kSums || (kHalves && BM == BN)), "parts, of what one loader stages");
+    float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bool sums = kSums && g.sums, summing = sums && do_a != kSumB;
+    const int sharing = kSumB ? g.tiles_m : g.tiles_n, share = kSumB ? tp.tm : tp.tn;
     int due = share;
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
       if constexpr (!kHalves) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }

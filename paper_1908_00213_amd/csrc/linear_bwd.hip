@@ -5,8 +5,9 @@
 // launch, the first trip to memory and its epilogue, and leaves most of a compute unit's waves unused meanwhile.  Here the blocks
 // of both products share a grid, and the blocks of the weight gradient's first tile column add up the rows of dv^T that pass through their
 // registers: the bias gradient.  Three kernels, each the body of one of chn_gemm's: the latency-bound one of gemm_tiny.h, the 64x64
-// tile of gemm_split.h (fp32) and of the direct-copy kernel (bfloat16).
+// tile of gemm_split_direct.h (fp32) and of the direct-copy kernel (bfloat16).
 #include "gemm_split.h"
+#include "gemm_split_direct.h"
 #include "gemm_tiny.h"
 #include "linear_bwd.h"
 
@@ -21,14 +22,12 @@ __global__ __launch_bounds__(64 * NW) void linear_bwd_tiny_kernel(GemmArgs w, Ge
   else tiny_block<16, true, W_KC, NW, false>(x, blockIdx.x - n_w, lds);
 }
 
-// KG groups of waves a tile.  With more tiles than compute units two, where chn_gemm takes four: two workgroups share a compute unit,
-// and their loads, splitting and matrix work overlap.
-template <bool W_KC, int PB, int KG>
-__global__ __launch_bounds__(256 * KG, 4) void linear_bwd_split_kernel(GemmArgs w, GemmArgs x, int n_w) {
+template <bool W_KC>
+__global__ __launch_bounds__(64 * kDirectWaves) void linear_bwd_split_kernel(GemmArgs w, GemmArgs x, int n_w) {
   extern __shared__ __align__(16) char lds[];
   __shared__ int redo;
-  if ((int)blockIdx.x < n_w) split_block<1, 1, KG, false, false, PB, PB, Sums::kRows>(w, blockIdx.x, lds, redo);
-  else split_block<1, 1, KG, true, W_KC, PB, PB, Sums::kNone>(x, blockIdx.x - n_w, lds, redo);
+  if ((int)blockIdx.x < n_w) split_direct_block<false, false, Sums::kRows>(w, blockIdx.x, lds, redo);
+  else split_direct_block<true, W_KC, Sums::kNone>(x, blockIdx.x - n_w, lds, redo);
 }
 
 template <bool W_KC>
@@ -43,26 +42,17 @@ __global__ __launch_bounds__(256) void linear_bwd_dma_kernel(GemmArgs w, GemmArg
 
 namespace {
 
-template <bool W_KC, int PB, int KG>
-chn_status launch_split_groups(const GemmArgs &w, const GemmArgs &x, int n_w, int n_x, hipStream_t st) {
-  constexpr int LDS = 2 * kSplitStage<1, 1, KG>;
-  static_assert(4 * KG * kEpiStageBytes<1, 1> <= LDS && 128 * 128 <= LDS, "the stages are reused by what follows the loop");
-  auto kern = linear_bwd_split_kernel<W_KC, PB, KG>;
-  if (LDS > 64 * 1024) {
-    static bool configured = false;  // per instantiation
-    if (!configured) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-      if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "linear_bwd: cannot reserve %d bytes of LDS: %s", LDS, hipGetErrorString(e));
-      configured = true;
-    }
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(n_w + n_x)), dim3(256 * KG), LDS, st, w, x, n_w);
-  return check_launch("linear_bwd (split fp32)");
-}
-template <bool W_KC, int PB>
+template <bool W_KC>
 chn_status launch_split_pair(const GemmArgs &w, const GemmArgs &x, int n_w, int n_x, hipStream_t st) {
-  if (n_w + n_x <= 256) return launch_split_groups<W_KC, PB, 4>(w, x, n_w, n_x, st);
-  return launch_split_groups<W_KC, PB, 2>(w, x, n_w, n_x, st);
+  auto kern = linear_bwd_split_kernel<W_KC>;
+  static bool configured = false;  // per instantiation
+  if (!configured) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kDirectLds);
+    if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "linear_bwd: cannot reserve %d bytes of LDS: %s", kDirectLds, hipGetErrorString(e));
+    configured = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(n_w + n_x)), dim3(64 * kDirectWaves), kDirectLds, st, w, x, n_w);
+  return check_launch("linear_bwd (split fp32)");
 }
 
 }  // namespace
@@ -87,23 +77,18 @@ chn_status launch_linear_bwd(const GemmArgs &w, const GemmArgs *dx, bool w_kc, L
     else hipLaunchKernelGGL((linear_bwd_dma_kernel<false>), grid, dim3(256), 0, st, w, x, n_w);
     return check_launch("linear_bwd (direct copy)");
   }
-  const bool aligned = w.piece == 16 && x.piece == 16;
-  if (w_kc) return aligned ? launch_split_pair<true, 16>(w, x, n_w, n_x, st) : launch_split_pair<true, kAnyPiece>(w, x, n_w, n_x, st);
-  return aligned ? launch_split_pair<false, 16>(w, x, n_w, n_x, st) : launch_split_pair<false, kAnyPiece>(w, x, n_w, n_x, st);
+  return w_kc ? launch_split_pair<true>(w, x, n_w, n_x, st) : launch_split_pair<false>(w, x, n_w, n_x, st);
 }
 
 bool sums_of_large(const GemmArgs &g, int isz) {
   if (isz == 2) return g.tile < 2 && g.dma;
-  return (g.parts == 1 || g.parts == 2) && (g.piece == 16 || (g.any_a && g.any_b));
+  return g.parts == 1 || (g.parts == 2 && (g.piece == 16 || (g.any_a && g.any_b)));
 }
 
 template <Sums SUMS>
 chn_status launch_large(const GemmArgs &g, int isz, hipStream_t st) {
   if (isz == 2) return g.tile == 1 ? launch_small_dma<2, false, false, SUMS>(g, st) : launch_small_dma<1, false, false, SUMS>(g, st);
-  if (g.parts == 1) {
-    if (g.piece == 16) return launch_split_piece<1, 1, 4, false, false, 16, 16, SUMS>(g, st);
-    return launch_split_piece<1, 1, 4, false, false, kAnyPiece, kAnyPiece, SUMS>(g, st);
-  }
+  if (g.parts == 1) return launch_split_direct<false, false, SUMS>(g, st);
   if (g.piece == 16) return launch_split_piece<2, 2, 2, false, false, 16, 16, SUMS>(g, st);
   return launch_split_piece<2, 2, 2, false, false, kAnyPiece, kAnyPiece, SUMS>(g, st);
 }
