@@ -55,13 +55,16 @@ inline bool takes(int64_t B, int64_t H, int cus) { return sizes_fit(B, H) && cus
 // Steps from which a walk pays: U has to come into the registers, the workgroups have to meet, and the kernels that would take over
 // are launched behind, which the first steps, cheaper each, have to earn back (us, the kernels of lstm_seq.hip against these: fp32
 // forward 96 x 560 at one step 13.9 and 29.7, 32 x 528 at three 30.4 and 36.9, at four 39.4 and 40.7, 128 x 672 at four 53.0 and 44.8;
-// fp32 backward 32 x 768 at five 55.0 and 57.7, at six 66.1 and 63.5; bf16 backward 16 x 528 at five 28.0 and 30.4, at six 33.2
-// and 33.6).  Measured at 8 to 128 rows, widths 64 to 768, one to twelve steps; few rows make those kernels' steps cheaper, more
-// units a workgroup (8, 16, 24) make the start of these longer.
+// fp32 backward 32 x 768 at five 56.2 and 58.8, at six 67.0 and 63.4, 8 x 384 at three 22.2 and 23.1, at four 28.5 and 26.4; bf16 backward
+// 32 x 544 at four 24.9 and 26.0, at five 30.5 and 29.1, 64 x 224 at two 11.9 and 12.2, at three 15.9 and 14.0).  Measured at 8 to 128 rows,
+// widths 64 to 768, one to twelve steps; few rows make those kernels' steps cheaper, more units a workgroup (8, 16, 24) make the start of
+// these longer.  bf16 backward also decides against a call a step, which is the better start where little has to come in (8 x 64 at four
+// steps 13.6 and 13.2, at three 12.1 and 9.3; 128 x 768 at three 29.9 and 28.6, at four 32.7 and 40.8).
 inline int least_steps(bool backward, bool bf16, int64_t B, int64_t H) {
   static const int fwd[2][2][3] = {{{2, 3, 4}, {2, 3, 4}}, {{2, 3, 4}, {2, 2, 3}}};                            // [bf16][more than 64 rows]
-  static const int bwd[2][3][3] = {{{3, 5, 6}, {3, 4, 5}, {3, 4, 4}}, {{5, 5, 6}, {4, 4, 4}, {4, 3, 4}}};      // [bf16][up to 32 rows, to 64, more]
+  static const int bwd[2][3][3] = {{{3, 4, 6}, {3, 4, 5}, {3, 4, 4}}, {{4, 4, 5}, {3, 3, 4}, {3, 3, 4}}};      // [bf16][up to 32 rows, to 64, more]
   const int s = units_of(H) / 8 - 1;
+  if (backward && bf16 && B <= 16 && H <= 64) return 5;
   return backward ? bwd[bf16][B <= 32 ? 0 : B <= 64 ? 1 : 2][s] : fwd[bf16][B > 64][s];
 }
 // bytes of the messages: fp32 exchanges the three parts of h through four blocks (of the widest row: the caller of the forward

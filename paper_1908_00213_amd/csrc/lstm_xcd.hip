@@ -464,14 +464,15 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_fwd_kernel(FwdArgs a) {
 // units, by its place in the square.  So a step is two trips through the L2, dz to the four members of a square, then partial sums of dh
 // to the owners of the units, one from every square, which they add in the squares' order.
 // us a step at 128 rows, 672 units, bf16 / fp32: with every member multiplying its own dz with all of U^T and sending partial sums of all
-// units to all members (one trip, but 1.2 MB a step and XCD each way, a wait for acknowledged stores and a flag) 4.4 and 6.6.
+// units to all members (one trip, but 1.2 MB a step and XCD each way, a wait for acknowledged stores and a flag) 4.4 and 6.6, now 3.1 and 6.3.
+// A step is bound by its instructions, one wave a SIMD and about five cycles each (product and messages about half each), and the two trips.
 // Values are their own arrival, as in the forward pass: four blocks of either kind of message take turns, what a block's next use will
 // write holds kAbsent before.  Partial sums: the reader, the only one of those bytes, puts the marks back when it has read
 // them.  dz: the sender marks its own words of the block of two steps ago once it has partial sums of this step: they were made, square
 // by square, from dz of the step before, which a member sends when it has made its sums of two steps ago.  (A member without units
 // sends no dz, but the sums it made of that block have been needed since.)  A wave waits for its marks before it sends its next dz; a block
 // is used again two (dz) and four (sums) steps on, when everybody's dz of the step before has been waited for.
-// tests/test_sequence_marks.py is the protocol as a model.
+// tests/test_sequence_marks_backward.py is the protocol as a model.
 template <typename T, int S>
 __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
   constexpr bool kSplit = sizeof(T) == 4;

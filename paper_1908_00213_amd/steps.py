@@ -238,7 +238,7 @@ class LSTMTrainer:
         of the recurrent matrix in LDS and exchange h through device memory.  None = wherever the library takes
         the shape (fused_step only).  Measured on workload 4, inside the XCDs: 5.1 us instead of 14.3 us per step
         in fp32, 2.5 instead of 8.0 us in mixed precision.  The T backward steps are one launch too
-        (chn_lstm_seq_bwd: 6.0 us per step in fp32, 4.0 in mixed precision, where the per-step fused call takes
+        (chn_lstm_seq_bwd: 6.3 us per step in fp32, 3.1 in mixed precision, where the per-step fused call takes
         11.6; in mixed precision only where the launch walks inside the XCDs, chn_lstm_seq_bwd_in_xcd).
         `whole_sequence_bwd` overrides that choice.  The kernels' waits are bounded;
         `sequence_complete()` tells whether one ran out (then the step's results and the parameters it
