@@ -393,6 +393,7 @@ chn_status launch_planned(GemmArgs &g, int isz, bool a_kc, bool b_kc, int epilog
     else plan(&g, isz, a_kc, b_kc, false);
   }
   g.w8 = eight_waves(g, isz, epilogue);
+  gemm::set_grid(g);
   if (isz == 4) {
     if (a_kc) return b_kc ? gemm::launch_f32_kk(g, st) : gemm::launch_f32_km(g, st);
     return b_kc ? gemm::launch_f32_mk(g, st) : gemm::launch_f32_mm(g, st);
@@ -597,6 +598,8 @@ chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_arr
       if (dx) plan(&gx, isz, x_a, x_b, true);
       const gemm::LinearBwd kind = together(gw, dx ? &gx : nullptr, isz, mm, x_a);
       if (kind != gemm::LinearBwd::kApart) {
+        gemm::set_grid(gw);
+        gemm::set_grid(gx);
         gw.sums = db ? static_cast<float *>(db->data) : nullptr;
         return gemm::launch_linear_bwd(gw, dx ? &gx : nullptr, x_b, kind, as_stream(stream));
       }
@@ -606,6 +609,7 @@ chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_arr
       const chn_array parts = w.parts(gw, ws);
       gw.partial = static_cast<float *>(ws);
       gw.sums = static_cast<float *>(parts.shape[0] == 1 ? db->data : parts.data);
+      gemm::set_grid(gw);
       CHN_TRY(gemm::launch_with_sums(gw, w.transposed, isz, as_stream(stream)));
       const size_t at = w.fold_offset(gw);
       if (parts.shape[0] > 1) CHN_TRY(chn_reduce_axis(CHN_REDUCE_SUM, &parts, 0, 0, db, static_cast<char *>(ws) + at, ws_bytes - at, stream));

@@ -726,20 +726,26 @@ static __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmArgs
 }
 
 // Which C tile (and which K split) a workgroup owns: XCD-aware renumbering, then grouped (8 tile rows
-// at a time) ordering.
+// at a time) ordering.  All of it stands before a workgroup's first load, and a division is twenty instructions that wait
+// for each other: three of them, and one for the length of a split, are multiplications (us, 1024x1000x784 bf16
+// 6.63 -> 6.45, its forward and two gradients one after the other 22.1 -> 21.6).
+// No branches: behind one the next arguments would be another trip to memory.
 struct TilePos { int tm, tn, split; };
-__device__ __forceinline__ TilePos tile_pos(const GemmArgs &g, int block) {
-  const int nb = g.tiles_m * g.tiles_n;
-  int pid = block % nb;
-  const int split = block / nb;
-  const int nb8 = nb & ~7;
-  if (pid < nb8) pid = (pid & 7) * (nb8 >> 3) + (pid >> 3);
-  constexpr int GROUP = 8;
-  const int width = GROUP * g.tiles_n;
-  const int first_m = (pid / width) * GROUP;
-  const int gsize = min(g.tiles_m - first_m, GROUP);
-  return TilePos{first_m + (pid % width) % gsize, (pid % width) / gsize, split};
+__device__ __forceinline__ unsigned divide(unsigned n, unsigned d, unsigned per) {
+  const unsigned q = __umulhi(n, per);
+  return q + (n - q * d >= d ? 1 : 0);
 }
+__device__ __forceinline__ TilePos tile_pos(const GemmArgs &g, unsigned block) {
+  const unsigned nb = g.tiles_m * g.tiles_n, nb8 = nb & ~7u, eight = 8 * g.tiles_n;
+  const unsigned split = divide(block, nb, g.per_tiles);
+  unsigned pid = block - split * nb;
+  pid = pid < nb8 ? (pid & 7) * (nb8 >> 3) + (pid >> 3) : pid;
+  const unsigned group = divide(pid, eight, g.per_eight), at = pid - group * eight, rest = g.tiles_m - 8 * group;
+  const unsigned rows = min(rest, 8u), tn = divide(at, rows, rest < 8 ? g.per_rest : reciprocal(8));
+  return TilePos{(int)(8 * group + at - tn * rows), (int)tn, (int)split};
+}
+// tile steps of a K split, of `all`
+__device__ __forceinline__ int split_steps(const GemmArgs &g, int all) { return (int)divide(all + g.splits - 1, g.splits, g.per_splits); }
 
 // Epilogue of one workgroup.  Each wave moves its accumulators through its own LDS area `stage`
 // (kEpiStageBytes<TM, TN> bytes; the caller has made sure that nobody uses that memory for anything
@@ -844,7 +850,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 
   // this block's range of tile steps along K (all of them unless the product is split)
   const int nk_all = (g.K + BK - 1) / BK;
-  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int per_split = split_steps(g, nk_all);
   const int kt0 = split * per_split;
   const int nk = min(nk_all, kt0 + per_split);
   la.issue(kt0 * BK);
@@ -1233,7 +1239,7 @@ __global__ __launch_bounds__(256) void gemm_kernel_dma(GemmArgs g) {
   };
 
   const int nk_all = (g.K + BK - 1) / BK;
-  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int per_split = split_steps(g, nk_all);
   const int kt0 = split * per_split;
   const int nk = min(nk_all, kt0 + per_split);
 
@@ -1408,7 +1414,7 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
   };
 
   const int nk_all = (g.K + BK - 1) / BK;
-  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int per_split = split_steps(g, nk_all);
   const int kt0 = split * per_split;
   const int nk = min(nk_all, kt0 + per_split);
   auto k_of = [&](int kt) { return kt * BK; };
@@ -1517,7 +1523,7 @@ template <int TM> constexpr int kSmallDmaStage = 2 * 64 * TM * 128;
 
 // Block `block` of the product, and its share of the sums.
 template <int TM, bool A_KC, bool B_KC, Sums SUMS>
-__device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, char *stage0, char *stage1, char *stage2, char *stage3) {
+__device__ __forceinline__ void small_dma_block(const GemmArgs &g, unsigned block, char *stage0, char *stage1, char *stage2, char *stage3) {
   using T = bf16_raw;
   constexpr int BM = 64 * TM, BK = 64, STAGES = 4;
   constexpr int A_BYTES = BM * 128, STAGE = kSmallDmaStage<TM>;
@@ -1530,7 +1536,7 @@ __device__ __forceinline__ void small_dma_block(const GemmArgs &g, int block, ch
   lb.init(static_cast<const T *>(g.B), g.ldb, g.N, n0, g.K);
 
   const int nk_all = (g.K + BK - 1) / BK;
-  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int per_split = split_steps(g, nk_all);
   const int kt0 = split * per_split;
   const int nk = min(nk_all, kt0 + per_split);
   auto copy = [&](int kt, char *stage) __attribute__((always_inline)) {   // (past the end of K: zeros, never used)

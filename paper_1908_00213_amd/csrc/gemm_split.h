@@ -201,7 +201,7 @@ constexpr int kSplitStage = (KG / 2) * (kSplitSub<64 * TM> + kSplitSub<64 * TN>)
 
 // Block `block` of the product, and its share of the sums.  lds: two stages.
 template <int TM, int TN, int KG, bool A_KC, bool B_KC, int PBA, int PBB, Sums SUMS>
-__device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *lds, int &redo) {
+__device__ __forceinline__ void split_block(const GemmArgs &g, unsigned block, char *lds, int &redo) {
   constexpr int BM = 64 * TM, BN = 64 * TN, BK = 16 * KG, SUBS = KG / 2;
   constexpr int A_BYTES = SUBS * kSplitSub<BM>, STAGE = kSplitStage<TM, TN, KG>;
   constexpr int SETS = TM == 1 ? 2 : 1, NT = 256 * KG;    // (the large tile has no registers for a second set)
@@ -212,7 +212,7 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, int block, char *
   const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
   const int r = lane & 31, h = lane >> 5;
   const int nk_all = (g.K + BK - 1) / BK;
-  const int per_split = (nk_all + g.splits - 1) / g.splits;
+  const int per_split = split_steps(g, nk_all);
   const int kt0 = split * per_split;
   const int nk = min(nk_all, kt0 + per_split);
 

@@ -66,12 +66,12 @@ struct DirectParts {
 
 // Block `block` of the product, and its share of the sums.
 template <bool A_KC, bool B_KC, Sums SUMS>
-__device__ __forceinline__ void split_direct_block(const GemmArgs &g, int block, char *lds, int &redo) {
+__device__ __forceinline__ void split_direct_block(const GemmArgs &g, unsigned block, char *lds, int &redo) {
   const TilePos tp = tile_pos(g, block);
   const int split = tp.split, m0 = tp.tm * 64, n0 = tp.tn * 64;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
-  const int nk_all = (g.K + 63) / 64, per_split = (nk_all + g.splits - 1) / g.splits;    // (cuts at whole steps of 64 k, as planned)
+  const int nk_all = (g.K + 63) / 64, per_split = split_steps(g, nk_all);    // (cuts at whole steps of 64 k, as planned)
   const int end = min(g.K, (split + 1) * per_split * 64), full = end / 16;               // slices that are whole
   if (threadIdx.x == 0) redo = 0;
 

@@ -66,7 +66,7 @@ __device__ __forceinline__ void tiny_block(const GemmArgs &g, int block, float *
   constexpr int NT = 64 * NW, OUT = TS * TS > NT ? TS * TS / NT : 1, PART = kTinyPart<TS>;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & (TS - 1), q = lane / TS;
-  const int tm = block / g.tiles_n, tn = block - tm * g.tiles_n, m0 = tm * TS, n0 = tn * TS;
+  const int tm = divide(block, g.tiles_n, g.per_column), tn = block - tm * g.tiles_n, m0 = tm * TS, n0 = tn * TS;
   const float *A = static_cast<const float *>(g.A), *Bm = static_cast<const float *>(g.B);
   const int ra = min(m0 + r, g.M - 1), rb = min(n0 + r, g.N - 1);      // (rows past the end repeat the last one: never stored)
   const int full = g.K / CHUNK;
