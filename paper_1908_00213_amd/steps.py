@@ -37,7 +37,6 @@ class _Program:
         self.gemm_ws = C.c_void_p(0)
         self.gemm_ws_bytes = C.c_size_t(0)
         self._gemm_need = 0
-        self.operations = 0                # library operations the calls stand for, when issued one by one
 
     def finish(self):
         if self._gemm_need:
@@ -63,9 +62,8 @@ class _Program:
     def ws(self, t):
         return (None, 0) if t is None else (C.c_void_p(t.data_ptr()), t.numel() * t.element_size())
 
-    def add(self, fn, *args, operations=1):
+    def add(self, fn, *args):
         self.calls.append((fn, args))
-        self.operations += operations
 
     def run(self, stream=None):
         s = B._stream() if stream is None else stream
@@ -99,7 +97,7 @@ def _linear_bwd(p, L, dv, W, x, dW, db, dx=None, epi="none", aux=None):
     """Weight, bias and (unless dx is None) input gradient of a fully connected layer."""
     a, w, b, c, d = p.d(dv), p.d(W), p.d(x), p.d(dx), p.d(dW)
     p._gemm_need = max(p._gemm_need, L.chn_linear_bwd_workspace_bytes(a, w, b, c, d))
-    p.add(L.chn_linear_bwd, a, w, b, B.EPI[epi], p.d(aux), c, d, p.d(db), p.gemm_ws, p.gemm_ws_bytes, operations=2 if dx is None else 3)
+    p.add(L.chn_linear_bwd, a, w, b, B.EPI[epi], p.d(aux), c, d, p.d(db), p.gemm_ws, p.gemm_ws_bytes)
 
 
 class MLPTrainer:
@@ -199,9 +197,9 @@ class MLPTrainer:
         return self.loss
 
     def n_launch_calls(self, x, t):
-        """Library operations of a step (a call that does a layer's whole backward counts as the three it replaces)."""
+        """Library calls of a step (a layer's whole backward may be one of them)."""
         self.step(x, t)
-        return self._progs[(x.data_ptr(), t.data_ptr())].operations
+        return len(self._progs[(x.data_ptr(), t.data_ptr())].calls)
 
 
 def _ceil32(n):
@@ -403,4 +401,4 @@ class LSTMTrainer:
 
     def n_launch_calls(self, ids, targets):
         self.step(ids, targets)
-        return self._progs[(ids.data_ptr(), targets.data_ptr())].operations
+        return len(self._progs[(ids.data_ptr(), targets.data_ptr())].calls)

@@ -48,8 +48,8 @@ def run_mlp(w, lowp, tol):
 
 def test_config1_tiny_mlp_step():
     tr, xd, td = run_mlp(W.config1(), False, 1e-4)
-    # library calls per step: 3 forward products, loss with its gradient, 3 dW + 3 db + 2 dx, 1 update
-    assert tr.n_launch_calls(xd, td) == 13
+    # library calls per step: 3 forward products, loss with its gradient, the backward of 3 layers (dW, db and dx in one call each), 1 update
+    assert tr.n_launch_calls(xd, td) == 8
 
 
 def test_config3_mlp_step_fp32_and_bf16():
@@ -219,4 +219,6 @@ def test_mlp_step_with_update_fused_into_the_weight_gradient_products(lowp):
     # and the second step starts from the updated weights in both
     l2f, l2p = float(fused.step(xd, td).cpu()), float(plain.step(xd, td).cpu())
     assert abs(l2f - l2p) <= 1e-5 * max(1.0, abs(l2p)) and l2f < lf
-    assert fused.n_launch_calls(xd, td) == plain.n_launch_calls(xd, td)
+    # the same calls, but for the last layer's backward: dW, db and dx are one call where the weights are not updated in between
+    # (the other layers' bias gradients come out of the input gradients' products)
+    assert fused.n_launch_calls(xd, td) == plain.n_launch_calls(xd, td) + 2
