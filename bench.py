@@ -116,16 +116,16 @@ def bench_array(torch, B, W, timer, quick):
 
 
 class GemmProbe:
-    """Brackets every GEMM launch of a recorded step with HIP events (same stream) so that the time of
-    each launch can be read back afterwards.  A measurement pass of its own, run after the timed
+    """Brackets every call of a recorded step that multiplies with HIP events (same stream) so that the time of
+    each can be read back afterwards.  A measurement pass of its own, run after the timed
     region of the step benchmark: recording two events per product costs host and device time that
     the step itself does not have.  The events exist before the pass starts."""
 
     def __init__(self, torch, B, prog, slots):
         self.torch = torch
-        self.fn = B.lib().chn_gemm
+        self.fns = (B.lib().chn_gemm, B.lib().chn_linear_bwd)
         self.prog = prog
-        self.n = sum(1 for fn, _ in prog.calls if fn is self.fn)
+        self.n = sum(1 for fn, _ in prog.calls if fn in self.fns)
         mk = lambda: torch.cuda.Event(enable_timing=True)
         self.events = [[(mk(), mk()) for _ in range(self.n)] for _ in range(slots)]
         self.used = set()
@@ -135,7 +135,7 @@ class GemmProbe:
         s = C.c_void_p(self.torch.cuda.current_stream().cuda_stream)
         ev = iter(self.events[slot])
         for fn, args in self.prog.calls:
-            if fn is self.fn:
+            if fn in self.fns:
                 e0, e1 = next(ev)
                 e0.record()
                 st = fn(*args, s)
@@ -166,15 +166,34 @@ class GemmProbe:
         return [x / max(1, len(self.used)) for x in tot]
 
 
-def gemm_shapes_mlp(sizes, batch, fused_update):
-    """(label, M, N, K) of every GEMM of one MLP step in issue order (see steps.MLPTrainer)."""
+def gemm_calls_mlp(sizes, batch, fused_update, backward_in_one_call):
+    """(label, [(M, N, K) of every product in it]) of every call of one MLP step that multiplies, in issue order (see
+    steps.MLPTrainer).  A layer's backward may be one call: its two products and the column sums of the bias gradient."""
     n = len(sizes) - 1
-    out = [("fwd%d" % l, batch, sizes[l + 1], sizes[l]) for l in range(n)]
+    out = [("fwd%d" % l, [(batch, sizes[l + 1], sizes[l])]) for l in range(n)]
     for l in range(n - 1, -1, -1):
-        dW = ("dW%d%s" % (l, "+sgd" if fused_update else ""), sizes[l + 1], sizes[l], batch)
-        dx = [("dx%d" % l, batch, sizes[l], sizes[l + 1])] if l > 0 else []
-        out += dx + [dW] if fused_update else [dW] + dx
+        dW = ("dW%d%s" % (l, "+sgd" if fused_update else ""), [(sizes[l + 1], sizes[l], batch)])
+        dx = [("dx%d" % l, [(batch, sizes[l], sizes[l + 1])])] if l > 0 else []
+        if backward_in_one_call[l]:
+            out.append(("+".join(["dW%d" % l, "db%d" % l] + [c[0] for c in dx]), dW[1] + (dx[0][1] if dx else [])))
+        else:
+            out += dx + [dW] if fused_update else [dW] + dx
     return out
+
+
+def gemm_report(calls, seconds, empty):
+    """What is reported of the calls that multiply.  "us": the event bracket as read; "us_net": minus what an empty bracket reads
+    (the launch itself; for a product of a few microseconds the bracket's own cost is a large part of "us")."""
+    if len(calls) != len(seconds):
+        raise RuntimeError("%d calls were timed, %d have a label" % (len(seconds), len(calls)))
+    flops = [sum(2.0 * M * N * K for M, N, K in products) for _, products in calls]
+    lines = []
+    for (lab, products), f, t in zip(calls, flops, seconds):
+        net = max(t - empty, 1e-7)
+        line = {"call": lab, "us": round(t * 1e6, 1), "TFLOP/s": round(f / t / 1e12, 1), "us_net": round(net * 1e6, 1), "TFLOP/s_net": round(f / net / 1e12, 1)}
+        line.update(zip("MNK", products[0]) if len(products) == 1 else {"products_MNK": [list(p) for p in products]}.items())
+        lines.append(line)
+    return {"gemm_calls": lines, "gemm_seconds_per_step": sum(seconds), "gemm_flops_per_step": sum(flops)}
 
 
 def bench_mlp(torch, B, steps_mod, w, lowp, timer, steps, warmup, probe=False, graph=False, fused_update=False, repeats=1,
@@ -220,15 +239,7 @@ def bench_mlp(torch, B, steps_mod, w, lowp, timer, steps, warmup, probe=False, g
             for i, v in enumerate(p.per_call_seconds()):
                 per[i] += v / len(probes)
         empty = probes[0].empty_pair_seconds()
-        # "us": the event bracket as read; "us_net": minus what an empty bracket reads (the launch itself;
-        # for a product of a few microseconds the bracket's own cost is a large part of "us")
-        res["gemm_calls"] = [{"call": lab, "M": M, "N": N, "K": K, "us": round(t_ * 1e6, 1),
-                              "TFLOP/s": round(2.0 * M * N * K / t_ / 1e12, 1),
-                              "us_net": round(max(t_ - empty, 1e-7) * 1e6, 1),
-                              "TFLOP/s_net": round(2.0 * M * N * K / max(t_ - empty, 1e-7) / 1e12, 1)}
-                             for (lab, M, N, K), t_ in zip(gemm_shapes_mlp(w.sizes, w.batch, fused_update), per)]
-        res["gemm_seconds_per_step"] = sum(per)
-        res["gemm_flops_per_step"] = sum(2.0 * M * N * K for _, M, N, K in gemm_shapes_mlp(w.sizes, w.batch, fused_update))
+        res.update(gemm_report(gemm_calls_mlp(w.sizes, w.batch, fused_update, tr.backward_in_one_call), per, empty))
         res["gemm_probe_steps"] = per_batch * nb
         res["event_pair_empty_us"] = round(empty * 1e6, 2)
     res.update({"ms_per_step": s * 1e3, "steps_per_s": 1.0 / s, "loss": float(tr.loss.cpu()),
@@ -531,7 +542,7 @@ def main():
                 r = bench_mlp(torch, B, steps_mod, w3, lowp, timer, 100, 10, graph=graph, probe=not graph)
                 tag = ("bf16" if lowp else "f32") + ("_hipgraph" if graph else "")
                 extra["cfg3_mlp_%s" % tag] = r
-                log("  %s: %.1f us/step  %.0f steps/s  %.2f TFLOP/s  (%d launches/step)" % (
+                log("  %s: %.1f us/step  %.0f steps/s  %.2f TFLOP/s  (%d library calls/step)" % (
                     tag, r["ms_per_step"] * 1e3, r["steps_per_s"], r["TFLOP/s"], r["launch_calls_per_step"]))
                 if "gemm_calls" in r:
                     log("    products (us, TFLOP/s; net of the event bracket): " + "  ".join(
@@ -548,7 +559,7 @@ def main():
         for graph in (False, True):
             r = bench_lstm(torch, B, steps_mod, w4, timer, 20, 3, graph=graph)
             extra["cfg4_lstm_lm_f32" + ("_hipgraph" if graph else "")] = r
-            log("  %s%.3f ms/step  %.1f steps/s  %.0f tokens/s  %.1f TFLOP/s (%.1f%% of six bf16 products per fp32 one at the bf16 MFMA peak; %d launches/step)" % (
+            log("  %s%.3f ms/step  %.1f steps/s  %.0f tokens/s  %.1f TFLOP/s (%.1f%% of six bf16 products per fp32 one at the bf16 MFMA peak; %d library calls/step)" % (
                 "HIP graph: " if graph else "", r["ms_per_step"], r["steps_per_s"], r["tokens_per_s"], r["TFLOP/s"],
                 100 * r["frac_split_peak_f32"], r["launch_calls_per_step"]))
         r = bench_lstm(torch, B, steps_mod, w4, timer, 20, 3, lowp=True)

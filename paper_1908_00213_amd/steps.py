@@ -138,6 +138,8 @@ class MLPTrainer:
         # bias gradient is the sum of those few rows instead of another pass over the gradient.
         self.rowsums = {l: mk(batch // 128, self.sizes[l]) for l in range(1, n)
                         if batch % 256 == 0 and self.sizes[l] % 256 == 0 and self.sizes[l + 1] % 8 == 0}
+        # the layers whose whole backward is one call: the others take or leave such sums, or update their weights on the way
+        self.backward_in_one_call = [not fused_update and l not in self.rowsums and l + 1 not in self.rowsums for l in range(n)]
         self._progs = {}
 
     def _build(self, x, t):
@@ -163,7 +165,7 @@ class MLPTrainer:
         for l in range(n - 1, -1, -1):
             dv = self.dv[l + 1]
             aux = (hs[l] if self.act == "relu" else self.z[l]) if l > 0 else None
-            if not self.fused_update and l not in self.rowsums and l + 1 not in self.rowsums:
+            if self.backward_in_one_call[l]:
                 _linear_bwd(p, L, dv, self.Wl[l], hs[l], self.dW[l], self.db[l], *((self.dv[l], bwd_epi, aux) if l > 0 else ()))
                 continue
             if not self.fused_update:
