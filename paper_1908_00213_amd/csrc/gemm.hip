@@ -300,8 +300,8 @@ bool eight_waves(const GemmArgs &g, int isz, int epilogue) {
   return f < 0 || f != 0;
 }
 
-// What chn_gemm would do with these operands.
-chn_status plan_of(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace, GemmArgs *g) {
+// The operands of a product that is only planned.
+chn_status check_operands(const chn_array *A, const chn_array *B, const chn_array *C, GemmArgs *g, bool *a_kc, bool *b_kc) {
   CHN_TRY(validate(A, "A", false));
   CHN_TRY(validate(B, "B", false));
   CHN_TRY(validate(C, "C", true));
@@ -309,8 +309,13 @@ chn_status plan_of(const chn_array *A, const chn_array *B, const chn_array *C, i
   if (!is_float(A->dtype) || A->dtype != B->dtype) return fail(CHN_ERR_DTYPE, "gemm: A and B must share F32 or BF16");
   if (A->shape[1] != B->shape[0] || C->shape[0] != A->shape[0] || C->shape[1] != B->shape[1]) return fail(CHN_ERR_SHAPE, "gemm: shapes do not match");
   if (A->shape[0] > 0x3fffffff || A->shape[1] > 0x3fffffff || B->shape[1] > 0x3fffffff) return fail(CHN_ERR_SHAPE, "gemm: dimension too large");
+  return classify(A, B, g, a_kc, b_kc);
+}
+
+// What chn_gemm would do with these operands.
+chn_status plan_of(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace, GemmArgs *g) {
   bool a_kc, b_kc;
-  CHN_TRY(classify(A, B, g, &a_kc, &b_kc));
+  CHN_TRY(check_operands(A, B, C, g, &a_kc, &b_kc));
   plan(g, dtype_size(A->dtype), a_kc, b_kc, have_workspace != 0);
   return CHN_OK;
 }
@@ -440,7 +445,8 @@ struct WeightGradient {
   size_t workspace_bytes() const {
     GemmArgs g{};
     bool a_kc, b_kc;
-    if (A.shape[0] <= 0 || A.shape[1] <= 0 || B.shape[1] <= 0 || plan_of(&A, &B, &C, 1, &g) != CHN_OK || classify(&A, &B, &g, &a_kc, &b_kc) != CHN_OK) return 0;
+    if (A.shape[0] <= 0 || A.shape[1] <= 0 || B.shape[1] <= 0 || check_operands(&A, &B, &C, &g, &a_kc, &b_kc) != CHN_OK) return 0;
+    plan(&g, dtype_size(A.dtype), a_kc, b_kc, true);
     return !a_kc && !b_kc && gemm::sums_of_large(g, dtype_size(A.dtype)) ? workspace_bytes(g) : split_bytes(g);
   }
 };
@@ -464,6 +470,14 @@ bool may_overlap(const chn_array *a, const chn_array *b) {
   return a0 < b1 && b0 < a1;
 }
 
+// What rules one launch out before anything is planned (which takes 1.3 us a product): the kernels that take both products work on
+// tiles of 64x64 or less, at most 512 of the larger ones, and in bfloat16 on operands that are copied straight to LDS.
+bool surely_apart(const GemmArgs &w, const GemmArgs *dx, int isz, bool w_mm, bool x_a_kc) {
+  auto tiles = [](const GemmArgs &g) { return (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64); };
+  if (!w_mm || (dx && !x_a_kc) || tiles(w) + (dx ? tiles(*dx) : 0) > 512) return true;
+  return isz == 2 && !(direct_copy_fits(w, isz, false, false) && (!dx || direct_copy_fits(*dx, isz, true, false)));
+}
+
 // Which of the one-launch kernels takes the two planned products (dx: NULL where there is none).
 gemm::LinearBwd together(const GemmArgs &w, const GemmArgs *dx, int isz, bool w_mm, bool x_a_kc) {
   using gemm::LinearBwd;
@@ -475,6 +489,18 @@ gemm::LinearBwd together(const GemmArgs &w, const GemmArgs *dx, int isz, bool w_
     return tiles <= 512 && both([](const GemmArgs &g) { return g.parts == 1 && g.direct; }) ? LinearBwd::kSplit : LinearBwd::kApart;
   }
   return tiles <= 512 && both([](const GemmArgs &g) { return g.tile == 0 && g.dma; }) ? LinearBwd::kDma : LinearBwd::kApart;
+}
+
+// ... planned here, no further than up to the answer.
+gemm::LinearBwd plan_together(GemmArgs &w, GemmArgs *dx, int isz, bool w_a, bool w_b, bool x_a, bool x_b) {
+  using gemm::LinearBwd;
+  const bool mm = !w_a && !w_b;
+  if (surely_apart(w, dx, isz, mm, x_a)) return LinearBwd::kApart;
+  plan(&w, isz, w_a, w_b, true);
+  const LinearBwd alone = together(w, nullptr, isz, mm, true);
+  if (!dx || alone == LinearBwd::kApart) return alone;
+  plan(dx, isz, x_a, x_b, true);
+  return together(w, dx, isz, mm, x_a);
 }
 
 }  // namespace
@@ -555,14 +581,10 @@ int chn_linear_bwd_plan(const chn_array *dv, const chn_array *W, const chn_array
   const WeightGradient w = weight_gradient(dv, x, dW);
   GemmArgs gw{}, gx{};
   bool w_a, w_b, x_a = true, x_b;
-  CHN_TRY(plan_of(&w.A, &w.B, &w.C, 1, &gw));
-  CHN_TRY(classify(&w.A, &w.B, &gw, &w_a, &w_b));
-  if (dx) {
-    CHN_TRY(plan_of(dv, W, dx, 1, &gx));
-    CHN_TRY(classify(dv, W, &gx, &x_a, &x_b));
-  }
+  CHN_TRY(check_operands(&w.A, &w.B, &w.C, &gw, &w_a, &w_b));
+  if (dx) CHN_TRY(check_operands(dv, W, dx, &gx, &x_a, &x_b));
   if (w.transposed || gw.M <= 0 || gw.N <= 0 || gw.K <= 0) return 0;
-  return together(gw, dx ? &gx : nullptr, dtype_size(dv->dtype), !w_a && !w_b, x_a) != gemm::LinearBwd::kApart;
+  return plan_together(gw, dx ? &gx : nullptr, dtype_size(dv->dtype), w_a, w_b, x_a, x_b) != gemm::LinearBwd::kApart;
 }
 
 chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_array *x, int epilogue, const chn_array *aux, const chn_array *dx,
@@ -589,14 +611,12 @@ chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_arr
   const bool mm = !w_a && !w_b;
   bool done = false;
   if (mm && gw.M > 0 && gw.N > 0 && gw.K > 0 && !(db && (may_overlap(db, dv) || may_overlap(db, x) || may_overlap(db, dW)))) {
-    plan(&gw, isz, w_a, w_b, true);
     // one launch: no product may write what another still reads
     const bool apart = may_overlap(dW, dv) || may_overlap(dW, x) ||
                        (dx && (may_overlap(dx, dv) || may_overlap(dx, x) || may_overlap(dx, dW) || (db && may_overlap(dx, db)) || may_overlap(dW, W) ||
                                (db && may_overlap(db, W)) || (aux && (may_overlap(aux, dW) || (db && may_overlap(aux, db))))));
     if (!w.transposed && !apart) {
-      if (dx) plan(&gx, isz, x_a, x_b, true);
-      const gemm::LinearBwd kind = together(gw, dx ? &gx : nullptr, isz, mm, x_a);
+      const gemm::LinearBwd kind = plan_together(gw, dx ? &gx : nullptr, isz, w_a, w_b, x_a, x_b);
       if (kind != gemm::LinearBwd::kApart) {
         gemm::set_grid(gw);
         gemm::set_grid(gx);
@@ -604,6 +624,7 @@ chn_status chn_linear_bwd(const chn_array *dv, const chn_array *W, const chn_arr
         return gemm::launch_linear_bwd(gw, dx ? &gx : nullptr, x_b, kind, as_stream(stream));
       }
     }
+    if (db && gw.tiles_m == 0) plan(&gw, isz, w_a, w_b, true);
     // the sums beside the weight gradient, in parts that a small reduction adds up
     if (db && gemm::sums_of_large(gw, isz) && ws && reinterpret_cast<uintptr_t>(ws) % 256 == 0 && ws_bytes >= w.workspace_bytes(gw)) {
       const chn_array parts = w.parts(gw, ws);
