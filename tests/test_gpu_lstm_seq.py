@@ -459,3 +459,28 @@ def test_overflowing_products_inside_the_xcds(meeting):
     """As test_sequence_values_that_three_parts_do_not_hold, whose three steps are left to the other kernels otherwise."""
     meeting(patience=1 << 14)
     test_sequence_values_that_three_parts_do_not_hold()
+
+
+@pytest.mark.parametrize("share_l2", [True, False])
+@pytest.mark.parametrize("Bn,H,T", [(17, 64, 10), (40, 272, 9), (128, 656, 12)])
+def test_backward_sums_taken_again_while_others_go_on(Bn, H, T, share_l2, meeting):
+    """fp32, more steps than blocks of messages: dz of three units of every third row exceeds what the parts hold, against small columns
+    of U, so that two squares at most multiply again in every step, from a block of dz that is marked for its next use two steps on, while
+    the others go on.  Every step from the dz that the GPU left for it."""
+    assert B.lstm_seq_bwd_in_xcd(Bn, H, T, torch.float32)
+    U, dh_in, gates, Cs, dc_last = bwd_inputs(Bn, H, T, "f32", 57)
+    for unit in (7, H // 2, H // 2 + 1):
+        dh_in[::3, unit] *= np.float32(2.0 ** 106)
+        U[:, unit::H] *= np.float32(2.0 ** -100)
+    meeting(share_l2=share_l2)
+    dHs, dZ, dc0, work = run_bwd(U, dh_in, gates, Cs, dc_last, T, "f32")
+    assert status_word(work) == 0 and torch.isfinite(dHs).all()
+    dH, dz, dc = host(dHs), host(dZ), dc_last.astype(np.float64)
+    for t in range(T - 1, -1, -1):
+        sl, nx = slice(t * Bn, (t + 1) * Bn), slice((t + 1) * Bn, (t + 2) * Bn)
+        if t < T - 1:
+            check(dH[sl], O.gemm(dz[nx], U.T, dh_in[sl], 1.0, 1.0), TOL_SUM, O.gemm(np.abs(dz[nx]), np.abs(U.T)) + np.abs(dh_in[sl]), "dh total %d" % t)
+        rdz, dc = O.lstm_bwd(gates[sl], Cs[sl].astype(np.float64), Cs[nx].astype(np.float64), dH[sl], dc)
+        Sdc = np.abs(dc) + np.abs(dH[sl]) + 1e-3
+        check(dz[sl], rdz, TOL_EW * 10 * (T - t), np.concatenate([Sdc, Sdc * (1 + np.abs(Cs[sl])), Sdc, np.abs(dH[sl])], axis=1), "dz %d" % t)
+    check(host(dc0), dc, TOL_EW * 10 * T, np.abs(dc) + 1.0, "dc0")

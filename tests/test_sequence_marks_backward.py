@@ -5,7 +5,8 @@ Members stand in squares of four.  A member has four waves; wave w < S owns one 
 load the partial sums of its units, one from every square, until no word is marked (not in step 0); wait for its own stores; send dz of
 its units; put the marks back on the sums it has read and mark its own words of the dz block of two steps ago; load dz of the square's
 member w until no word is marked; barrier; send the partial sums of every fourth tile (two groups of units) of the member's quarter.
-(In fp32 another barrier follows.)  Blocks of both kinds are four that take turns.  A wave's stores arrive in any order, those to one word in order, at the
+In fp32 sums that are not finite are taken again first, tile by tile, from the dz of the whole square as it lies in memory.  (There another
+barrier follows, for the sums in LDS; the messages do without.)  Blocks of both kinds are four that take turns.  A wave's stores arrive in any order, those to one word in order, at the
 latest at its next wait.  A member without units and without tiles takes no part."""
 import random
 
@@ -18,8 +19,9 @@ class Broken(Exception):
     pass
 
 
-def walk(groups, S, steps, rng, back, wait):
-    """One run under a random schedule.  back: of how many steps ago the dz block is that is marked; wait: whether marks are waited for."""
+def walk(groups, S, steps, rng, back, wait, again):
+    """One run under a random schedule.  back: of how many steps ago the dz block is that is marked; wait: whether marks are waited for;
+    again: whether some sums are taken again."""
     real = (groups + S - 1) // S
     members = (real + 3) // 4 * 4
     tiles = (groups + 1) // 2
@@ -32,6 +34,7 @@ def walk(groups, S, steps, rng, back, wait):
     def wave(m, w):
         unit = m * S + w if w < S and m * S + w < groups else None
         square, first = m // 4, m % 4 * quarter
+        whole = [g for g in range(4 * square * S, 4 * (square + 1) * S) if g < groups]
         mine = [t for t in range(first, min(first + quarter, tiles)) if (t - first) % 4 == w]
         peer = [g for g in range((4 * square + w) * S, (4 * square + w + 1) * S) if g < groups]
         if m * S >= groups and first >= tiles:
@@ -86,7 +89,14 @@ def walk(groups, S, steps, rng, back, wait):
             if any(v != step for v in seen):
                 raise Broken("step %d read dz of another step" % step)
             yield from barrier()
+            redo = again and rng.random() < 0.5
             for t in mine:
+                for g in whole if redo else ():
+                    if dz[step % BLOCKS][g] != step:
+                        raise Broken("step %d multiplied again dz of another step" % step)
+                    if rng.random() < 0.2:
+                        drain(False)
+                        yield True
                 for g in (2 * t, 2 * t + 1):
                     if g < groups:
                         pending.append((sums[(step + 1) % BLOCKS][square], g, step + 1))
@@ -112,13 +122,13 @@ def walk(groups, S, steps, rng, back, wait):
 SIZES = ((2, 1), (4, 1), (6, 1), (10, 1), (12, 1), (32, 1), (36, 2), (38, 2), (68, 3), (84, 3))      # groups of eight units, S
 
 
-def outcomes(seeds, back=2, wait=True):
+def outcomes(seeds, back=2, wait=True, again=False):
     bad = 0
     for seed in range(seeds):
         rng = random.Random(seed)
         groups, S = SIZES[seed % len(SIZES)]
         try:
-            walk(groups, S, 11, rng, back, wait)
+            walk(groups, S, 11, rng, back, wait, again)
         except Broken:
             bad += 1
     return bad
@@ -128,6 +138,11 @@ def test_no_word_is_marked_or_written_too_early():
     assert outcomes(60) == 0
 
 
+def test_sums_taken_again_find_the_dz_they_were_made_of():
+    assert outcomes(60, again=True) == 0
+
+
 def test_the_model_sees_marks_too_early_and_marks_not_waited_for():
     assert outcomes(40, back=1) > 0
     assert outcomes(40, wait=False) > 0
+    assert outcomes(40, back=1, again=True) > 0
