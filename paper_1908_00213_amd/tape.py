@@ -82,12 +82,10 @@ class GpuBackend:
         return self.B.linear_bwd_in_one_launch(gy, W, x, gx, gW)
 
     def linear_bwd(self, gy, W, x, gW, gb, gx=None):
-        """gW = gy^T x, gb = column sums of gy and, unless gx is None, gx = gy W, in one call."""
+        """gW = gy^T x, gb = column sums of gy and, unless gx is None, gx = gy W, in one call.  The workspace is the call's own, like that of
+        a reduction: parts of the sums lie in it even where no product is cut, and a layer on another stream may be under way."""
         gy, W, x, gW, gx = (self.B.desc(a) for a in (gy, W, x, gW, gx))
-        need = self.B.linear_bwd_workspace_bytes(gy, W, x, gx, gW)
-        if need and (self._gemm_ws is None or self._gemm_ws.numel() < need):
-            self._gemm_ws = self._bytes(need)
-        self.B.linear_bwd(gy, W, x, gW, gb, gx, ws=self._gemm_ws if need else None)
+        self.B.linear_bwd(gy, W, x, gW, gb, gx, ws=self._bytes(self.B.linear_bwd_workspace_bytes(gy, W, x, gx, gW)))
 
     def elementwise_broadcast(self, op, inputs, out, scalars=()):
         return self.B.elementwise_broadcast(op, inputs, out, scalars)

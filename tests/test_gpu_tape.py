@@ -440,3 +440,23 @@ def test_n_step_lstm_takes_the_recurrent_matrix_as_it_lies(layout, steps_):
     for got, want in zip(once(view), once(U)):
         cmp(got, host(want), 1e-5, layout)
     T.backend().check_sequences()
+
+
+def test_backward_calls_on_two_streams_share_no_workspace(monkeypatch):
+    F = T.backend()
+    M, N, K = 640, 1672, 2008                    # an uncut weight gradient that leaves parts of the bias gradient in the workspace
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    ints = lambda *s: torch.randint(-4, 5, s, generator=gen, device="cuda").float()
+    sets = [(ints(M, N), ints(M, K), torch.empty(N, K, device="cuda"), torch.empty(N, device="cuda")) for _ in range(2)]
+    torch.cuda.synchronize()
+    seen, call = [], F.B.linear_bwd
+    monkeypatch.setattr(F.B, "linear_bwd", lambda *a, ws=None, **k: (seen.append((ws.data_ptr(), ws.numel())), call(*a, ws=ws, **k)))
+    streams = [torch.cuda.Stream() for _ in sets]
+    for s, (gy, x, gW, gb) in zip(streams, sets):
+        with torch.cuda.stream(s):
+            F.linear_bwd(gy, None, x, gW, gb)
+    torch.cuda.synchronize()
+    (a, na), (b, nb) = seen
+    assert a + na <= b or b + nb <= a
+    for gy, x, gW, gb in sets:
+        assert torch.equal(gb.double(), gy.double().sum(0)) and torch.equal(gW.double(), gy.double().t() @ x.double())
