@@ -31,6 +31,7 @@
 //     so that bias / activation / activation-gradient run on 16-byte vectors and C, aux and preact
 //     are accessed as whole 512-byte (fp32) or 256-byte (bf16) row segments; one final rounding.
 #pragma once
+#include <atomic>
 #include <type_traits>
 
 #include "common.h"
@@ -1694,19 +1695,22 @@ chn_status launch_dma(const GemmArgs &g, hipStream_t st) {
   }
 }
 
+// Asks for a kernel's dynamic LDS beyond 64 KB before its first launch.  Threads may come here together: what they set is the same.
+inline chn_status reserve_lds(std::atomic<bool> &done, const void *kernel, int bytes) {
+  if (done.load(std::memory_order_acquire)) return CHN_OK;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "gemm: cannot reserve %d bytes of LDS: %s", bytes, hipGetErrorString(e));
+  done.store(true, std::memory_order_release);
+  return CHN_OK;
+}
+
 template <typename T, int TM, int TN, bool A_KC, bool B_KC, int PB, int PB2 = PB>
 chn_status launch_piece(const GemmArgs &g, hipStream_t st) {
   constexpr int LDS = 2 * (64 * TM + 64 * TN) * 128;
   static_assert(4 * kEpiStageBytes<TM, TN> <= LDS, "epilogue staging must fit in the operand stages");
   auto kern = gemm_kernel<T, TM, TN, A_KC, B_KC, PB, PB2>;
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    if (LDS > 64 * 1024) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-      if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "gemm: cannot reserve %d bytes of LDS: %s", LDS, hipGetErrorString(e));
-    }
-    configured = true;
-  }
+  static std::atomic<bool> configured{LDS <= 64 * 1024};  // per instantiation
+  CHN_TRY(reserve_lds(configured, reinterpret_cast<const void *>(kern), LDS));
   hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), LDS, st, g);
   CHN_TRY(check_launch("gemm"));
   if (g.splits > 1) {

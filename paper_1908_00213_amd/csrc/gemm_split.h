@@ -476,12 +476,8 @@ chn_status launch_split_piece(const GemmArgs &g, hipStream_t st) {
   constexpr int LDS = 2 * kSplitStage<TM, TN, KG>;
   static_assert(4 * KG * kEpiStageBytes<1, TN> <= LDS && (64 * TM + 64 * TN) * 128 <= LDS, "the stages are reused by what follows the loop");
   auto kern = gemm_split_kernel<TM, TN, KG, A_KC, B_KC, PBA, PBB, SUMS>;
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "gemm: cannot reserve %d bytes of LDS: %s", LDS, hipGetErrorString(e));
-    configured = true;
-  }
+  static std::atomic<bool> configured{false};  // per instantiation
+  CHN_TRY(reserve_lds(configured, reinterpret_cast<const void *>(kern), LDS));
   hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256 * KG), LDS, st, g);
   CHN_TRY(check_launch("gemm (split fp32)"));
   if (g.splits > 1) {

@@ -231,12 +231,8 @@ __global__ __launch_bounds__(64 * kDirectWaves) void gemm_split_direct_kernel(Ge
 template <bool A_KC, bool B_KC, Sums SUMS = Sums::kNone>
 chn_status launch_split_direct(const GemmArgs &g, hipStream_t st) {
   auto kern = gemm_split_direct_kernel<A_KC, B_KC, SUMS>;
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kDirectLds);
-    if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "gemm: cannot reserve %d bytes of LDS: %s", kDirectLds, hipGetErrorString(e));
-    configured = true;
-  }
+  static std::atomic<bool> configured{false};  // per instantiation
+  CHN_TRY(reserve_lds(configured, reinterpret_cast<const void *>(kern), kDirectLds));
   hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(64 * kDirectWaves), kDirectLds, st, g);
   CHN_TRY(check_launch("gemm (split fp32, 64x64)"));
   if (g.splits > 1) {

@@ -45,12 +45,8 @@ namespace {
 template <bool W_KC>
 chn_status launch_split_pair(const GemmArgs &w, const GemmArgs &x, int n_w, int n_x, hipStream_t st) {
   auto kern = linear_bwd_split_kernel<W_KC>;
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kDirectLds);
-    if (e != hipSuccess) return fail(CHN_ERR_LAUNCH, "linear_bwd: cannot reserve %d bytes of LDS: %s", kDirectLds, hipGetErrorString(e));
-    configured = true;
-  }
+  static std::atomic<bool> configured{false};  // per instantiation
+  CHN_TRY(reserve_lds(configured, reinterpret_cast<const void *>(kern), kDirectLds));
   hipLaunchKernelGGL(kern, dim3((unsigned)(n_w + n_x)), dim3(64 * kDirectWaves), kDirectLds, st, w, x, n_w);
   return check_launch("linear_bwd (split fp32)");
 }
