@@ -227,35 +227,34 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, unsigned block, c
   {
     // Operands that lie alike are staged by one half of the threads each, with one loader; a mixed pair is staged
     // by all threads together, so that every wave has the same mixture of work.
-    constexpr bool kAlike = A_KC == B_KC, kHalves = kAlike;
+    constexpr bool kAlike = A_KC == B_KC;
     static_assert(TM == 2 || (A_KC && B_KC), "other layouts of the small tile: gemm_split_direct.h");
     // (a mixed pair of aligned operands: steps of whole k without checks do not pay, 4480x2688x672 120 -> 123 us)
-    using LA = SplitLoader<BM, SUBS, A_KC, kHalves ? NT / 2 : NT>;
-    using LB = SplitLoader<BN, SUBS, B_KC, kHalves ? NT / 2 : NT>;
+    using LA = SplitLoader<BM, SUBS, A_KC, kAlike ? NT / 2 : NT>;
+    using LB = SplitLoader<BN, SUBS, B_KC, kAlike ? NT / 2 : NT>;
     LA la;
     LB lb;
     const bool do_a = wave < 2 * KG;                      // (uniform over a wave)
-    const int t = kHalves ? (int)threadIdx.x & (NT / 2 - 1) : (int)threadIdx.x;
+    const int t = kAlike ? (int)threadIdx.x & (NT / 2 - 1) : (int)threadIdx.x;
     if constexpr (kAlike) {
       la.init(t, static_cast<const float *>(do_a ? g.A : g.B), do_a ? g.lda : g.ldb, do_a ? g.M : g.N, do_a ? m0 : n0, g.K, do_a);
     } else {
-      if (do_a || !kHalves) la.init(t, static_cast<const float *>(g.A), g.lda, g.M, m0, g.K, true);
-      if (!do_a || !kHalves) lb.init(t, static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K, false);
+      la.init(t, static_cast<const float *>(g.A), g.lda, g.M, m0, g.K, true);
+      lb.init(t, static_cast<const float *>(g.B), g.ldb, g.N, n0, g.K, false);
     }
     // staging registers: with two sets taking turns (SETS) loads run two steps ahead of their use, else one
     uint4 ra[LA::R], ra1[LA::R], rb[LB::R], rb1[LB::R];    // (a thread with one role uses ra, ra1 only)
     // sums: what this thread has staged, by its rows of A (columns of B); `due`: stored tiles until the next one that counts
     constexpr bool kSums = SUMS != Sums::kNone, kSumB = SUMS == Sums::kColumnParts;
-    static_assert(SUMS != Sums::kRows && (!kSums || (kHalves && BM == BN)), "parts, of what one loader stages");
+    static_assert(SUMS != Sums::kRows && (!kSums || (kAlike && BM == BN)), "parts, of what one loader stages");
     float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     const bool sums = kSums && g.sums, summing = sums && do_a != kSumB;
     const int sharing = kSumB ? g.tiles_m : g.tiles_n, share = kSumB ? tp.tm : tp.tn;
     int due = share;
     auto issue = [&](uint4 (&xa)[LA::R], uint4 (&xb)[LB::R], int kt) __attribute__((always_inline)) {
-      if constexpr (!kHalves) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }
-      else if constexpr (kAlike && PBA == PBB) la.template issue<PBA, kAlike>(xa, kt * BK);
-      else if constexpr (kAlike) { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else la.template issue<PBB, kAlike>(xa, kt * BK); }
-      else { if (do_a) la.template issue<PBA, kAlike>(xa, kt * BK); else lb.template issue<PBB, kAlike>(xa, kt * BK); }
+      if constexpr (!kAlike) { la.template issue<PBA, false>(xa, kt * BK); lb.template issue<PBB, false>(xb, kt * BK); }
+      else if (PBA == PBB || do_a) la.template issue<PBA, true>(xa, kt * BK);
+      else la.template issue<PBB, true>(xa, kt * BK);
     };
     auto store = [&](const uint4 (&xa)[LA::R], const uint4 (&xb)[LB::R], char *stage, int tile) __attribute__((always_inline)) {
       constexpr bool any_a = PBA == kAnyPiece, any_b = PBB == kAnyPiece;
@@ -266,9 +265,8 @@ __device__ __forceinline__ void split_block(const GemmArgs &g, unsigned block, c
         }
         --due;
       }
-      if constexpr (!kHalves) { la.store(xa, stage, any_a); lb.store(xb, stage + A_BYTES, any_b); }
-      else if constexpr (kAlike) la.store(xa, stage + (do_a ? 0 : A_BYTES), do_a ? any_a : any_b);
-      else { if (do_a) la.store(xa, stage, any_a); else lb.store(xa, stage + A_BYTES, any_b); }
+      if constexpr (!kAlike) { la.store(xa, stage, any_a); lb.store(xb, stage + A_BYTES, any_b); }
+      else la.store(xa, stage + (do_a ? 0 : A_BYTES), do_a ? any_a : any_b);
     };
     // this group's 16 k inside a stage: sub-tile grp / 2, k-step grp % 2
     const int off = split_off(r, (grp & 1) * 2 + h);
