@@ -45,7 +45,7 @@ class GpuBackend:
         self.torch, self.B = torch, binding
         self._dt = {"f32": torch.float32, "bf16": torch.bfloat16, "i64": torch.int64, "i32": torch.int32}
         self._name = {v: k for k, v in self._dt.items()}
-        self._gemm_ws = None
+        self._gemm_ws = {}         # stream -> workspace of its products: launches on one stream follow each other, on two they do not
         self._seq_ws = []          # workspaces of whole-sequence recurrent launches whose status word is unread
         self._dev = torch.device("cuda", torch.cuda.current_device())
 
@@ -69,23 +69,31 @@ class GpuBackend:
     def _bytes(self, n):
         return None if n == 0 else self.torch.empty(n, dtype=self.torch.uint8, device="cuda")
 
+    def _workspace(self, need):
+        """The products' workspace of the current stream (one that is replaced by a larger one stays valid for launches already queued)."""
+        if not need:
+            return None
+        stream = self.B._stream().value
+        ws = self._gemm_ws.get(stream)
+        if ws is None or ws.numel() < need:
+            if len(self._gemm_ws) >= 64:
+                self._gemm_ws.clear()
+            ws = self._gemm_ws[stream] = self._bytes(need)
+        return ws
+
     # kernels: same names and argument order as the binding
     def gemm(self, A, Bm, Cm, alpha=1.0, beta=0.0, epilogue="none", bias=None, aux=None, preact_out=None):
         A, Bm, Cm = self.B.desc(A), self.B.desc(Bm), self.B.desc(Cm)     # marshalled once for both calls
-        need = self.B.gemm_workspace_bytes(A, Bm, Cm)
-        if need and (self._gemm_ws is None or self._gemm_ws.numel() < need):
-            self._gemm_ws = self._bytes(need)   # the old one stays valid for launches already queued
         return self.B.gemm(A, Bm, Cm, alpha, beta, epilogue, bias, aux, preact_out,
-                           ws=self._gemm_ws if need else None)
+                           ws=self._workspace(self.B.gemm_workspace_bytes(A, Bm, Cm)))
 
     def linear_bwd_in_one_launch(self, gy, W, x, gW, gx):
         return self.B.linear_bwd_in_one_launch(gy, W, x, gx, gW)
 
     def linear_bwd(self, gy, W, x, gW, gb, gx=None):
-        """gW = gy^T x, gb = column sums of gy and, unless gx is None, gx = gy W, in one call.  The workspace is the call's own, like that of
-        a reduction: parts of the sums lie in it even where no product is cut, and a layer on another stream may be under way."""
+        """gW = gy^T x, gb = column sums of gy and, unless gx is None, gx = gy W, in one call."""
         gy, W, x, gW, gx = (self.B.desc(a) for a in (gy, W, x, gW, gx))
-        self.B.linear_bwd(gy, W, x, gW, gb, gx, ws=self._bytes(self.B.linear_bwd_workspace_bytes(gy, W, x, gx, gW)))
+        self.B.linear_bwd(gy, W, x, gW, gb, gx, ws=self._workspace(self.B.linear_bwd_workspace_bytes(gy, W, x, gx, gW)))
 
     def elementwise_broadcast(self, op, inputs, out, scalars=()):
         return self.B.elementwise_broadcast(op, inputs, out, scalars)

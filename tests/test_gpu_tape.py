@@ -442,21 +442,25 @@ def test_n_step_lstm_takes_the_recurrent_matrix_as_it_lies(layout, steps_):
     T.backend().check_sequences()
 
 
-def test_backward_calls_on_two_streams_share_no_workspace(monkeypatch):
+@pytest.mark.parametrize("what", ["gemm", "linear_bwd"])
+def test_calls_on_two_streams_share_no_workspace(what, monkeypatch):
     F = T.backend()
-    M, N, K = 640, 1672, 2008                    # an uncut weight gradient that leaves parts of the bias gradient in the workspace
+    # a cut product, and an uncut weight gradient that leaves parts of the bias gradient in the workspace
+    M, N, K = (2048, 512, 512) if what == "gemm" else (640, 1672, 2008)
     gen = torch.Generator(device="cuda").manual_seed(5)
     ints = lambda *s: torch.randint(-4, 5, s, generator=gen, device="cuda").float()
     sets = [(ints(M, N), ints(M, K), torch.empty(N, K, device="cuda"), torch.empty(N, device="cuda")) for _ in range(2)]
     torch.cuda.synchronize()
-    seen, call = [], F.B.linear_bwd
-    monkeypatch.setattr(F.B, "linear_bwd", lambda *a, ws=None, **k: (seen.append((ws.data_ptr(), ws.numel())), call(*a, ws=ws, **k)))
+    seen, call = [], getattr(F.B, what)
+    monkeypatch.setattr(F.B, what, lambda *a, ws=None, **k: (seen.append((ws.data_ptr(), ws.numel())), call(*a, ws=ws, **k)))
     streams = [torch.cuda.Stream() for _ in sets]
-    for s, (gy, x, gW, gb) in zip(streams, sets):
-        with torch.cuda.stream(s):
-            F.linear_bwd(gy, None, x, gW, gb)
+    for _ in range(2):
+        for s, (gy, x, gW, gb) in zip(streams, sets):
+            with torch.cuda.stream(s):
+                F.gemm(gy.t(), x, gW) if what == "gemm" else F.linear_bwd(gy, None, x, gW, gb)
     torch.cuda.synchronize()
-    (a, na), (b, nb) = seen
-    assert a + na <= b or b + nb <= a
+    (a, na), (b, nb) = seen[:2]
+    assert (a + na <= b or b + nb <= a) and seen[2:] == seen[:2]      # (kept for the next call on the stream)
     for gy, x, gW, gb in sets:
-        assert torch.equal(gb.double(), gy.double().sum(0)) and torch.equal(gW.double(), gy.double().t() @ x.double())
+        assert torch.equal(gW.double(), gy.double().t() @ x.double())
+        assert what == "gemm" or torch.equal(gb.double(), gy.double().sum(0))
