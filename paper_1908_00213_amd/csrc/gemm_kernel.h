@@ -730,8 +730,8 @@ static __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmArgs
 // at a time) ordering.  All of it stands before a workgroup's first load, and a division is twenty instructions that wait
 // for each other: three of them, and one for the length of a split, are multiplications (us in a graph, bf16, divisions and
 // multiplications: 1024x1000x784 6.79 and 6.73, its input gradient 8.85 and 8.70, its weight gradient 8.61 and 8.65).  One after the other
-// three such kernels gain nothing by it (23.8 and 23.9): there the place of their code decides, which the instruction cache has to
-// hold (the first kernel's moved by 2, 4, 8 and 16 KB and nothing else changed: 24.2, 24.3, 24.7, 24.3).
+// three such kernels gain nothing by it (23.8 and 23.9): there the place of their code decides (the first kernel's moved by 2, 4, 8 and
+// 16 KB and nothing else changed: 24.2, 24.3, 24.7, 24.3).
 // No branches: behind one the next arguments would be another trip to memory.
 struct TilePos { int tm, tn, split; };
 __device__ __forceinline__ unsigned divide(unsigned n, unsigned d, unsigned per) {
