@@ -753,6 +753,7 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
       floatx4 *const meet_at = sums + (SETS == 2 ? (step & 1) * (kSumBytes / 16) : 0);
 #pragma unroll
       for (int n0 = 0; n0 < TILES; n0 += AT_ONCE) {
+        if (kFull && n0 + AT_ONCE == TILES && n0 >= n_tiles) break;      // (up to 640 units nobody has the last two tiles: 128 x 544, 35 steps, 203 -> 190 us)
         floatx4 acc[AT_ONCE];
 #pragma unroll
         for (int n = 0; n < AT_ONCE; ++n) acc[n] = floatx4{0, 0, 0, 0};
@@ -813,7 +814,7 @@ __global__ __launch_bounds__(kThreads, 1) void lstm_xcd_bwd_kernel(BwdArgs a) {
           for (int s = 1; s < 4; ++s) sum[i] += meet_at[n * 256 + s * 64 + lane];
           if constexpr (kSplit) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) bad = __builtin_fmaf(sum[i][e], 0.0f, bad);
+            for (int e = 0; e < 4; ++e) bad = n < n_tiles ? __builtin_fmaf(sum[i][e], 0.0f, bad) : bad;
           }
         }
         if (!kSplit || __builtin_expect(!__any(bad != 0.0f), 1)) {

@@ -462,7 +462,7 @@ def test_overflowing_products_inside_the_xcds(meeting):
 
 
 @pytest.mark.parametrize("share_l2", [True, False])
-@pytest.mark.parametrize("Bn,H,T", [(17, 64, 10), (40, 272, 9), (128, 656, 12)])
+@pytest.mark.parametrize("Bn,H,T", [(17, 64, 10), (40, 272, 9), (70, 528, 8), (33, 640, 9), (128, 656, 12)])
 def test_backward_sums_taken_again_while_others_go_on(Bn, H, T, share_l2, meeting):
     """fp32, more steps than blocks of messages: dz of three units of every third row exceeds what the parts hold, against small columns
     of U, so that two squares at most multiply again in every step, from a block of dz that is marked for its next use two steps on, while
