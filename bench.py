@@ -243,7 +243,7 @@ def bench_mlp(torch, B, steps_mod, w, lowp, timer, steps, warmup, probe=False, g
         res["gemm_probe_steps"] = per_batch * nb
         res["event_pair_empty_us"] = round(empty * 1e6, 2)
     res.update({"ms_per_step": s * 1e3, "steps_per_s": 1.0 / s, "loss": float(tr.loss.cpu()),
-                "TFLOP/s": w.flops_per_step() / s / 1e12, "launch_calls_per_step": tr.n_launch_calls(xs[0], ts[0])})
+                "TFLOP/s": w.flops_per_step() / s / 1e12, "launch_calls_per_step": tr.n_calls(xs[0], ts[0])})
     return res
 
 
@@ -256,7 +256,7 @@ def bench_lstm(torch, B, steps_mod, w, timer, steps, warmup, graph=False, lowp=F
     return {"ms_per_step": s * 1e3, "steps_per_s": 1.0 / s, "tokens_per_s": w.bptt * w.batch / s, "loss": float(tr.loss.cpu()),
             "forward_steps_in_one_launch": bool(tr.whole_sequence), "backward_steps_in_one_launch": bool(tr.whole_sequence_bwd),
             "TFLOP/s": w.flops_per_step() / s / 1e12, "frac_split_peak_f32": w.flops_per_step() / s / 1e12 / (MFMA_PEAK_TFLOPS["bf16"] / 6),
-            "launch_calls_per_step": tr.n_launch_calls(ids, tg)}
+            "launch_calls_per_step": tr.n_calls(ids, tg)}
 
 
 def bench_tape(torch, W, timer, quick):

@@ -37,6 +37,7 @@ class _Program:
         self.gemm_ws = C.c_void_p(0)
         self.gemm_ws_bytes = C.c_size_t(0)
         self._gemm_need = 0
+        self.operations = 0                # library operations the calls stand for, when issued one by one
 
     def finish(self):
         if self._gemm_need:
@@ -62,8 +63,9 @@ class _Program:
     def ws(self, t):
         return (None, 0) if t is None else (C.c_void_p(t.data_ptr()), t.numel() * t.element_size())
 
-    def add(self, fn, *args):
+    def add(self, fn, *args, operations=1):
         self.calls.append((fn, args))
+        self.operations += operations
 
     def run(self, stream=None):
         s = B._stream() if stream is None else stream
@@ -97,7 +99,7 @@ def _linear_bwd(p, L, dv, W, x, dW, db, dx=None, epi="none", aux=None):
     """Weight, bias and (unless dx is None) input gradient of a fully connected layer."""
     a, w, b, c, d = p.d(dv), p.d(W), p.d(x), p.d(dx), p.d(dW)
     p._gemm_need = max(p._gemm_need, L.chn_linear_bwd_workspace_bytes(a, w, b, c, d))
-    p.add(L.chn_linear_bwd, a, w, b, B.EPI[epi], p.d(aux), c, d, p.d(db), p.gemm_ws, p.gemm_ws_bytes)
+    p.add(L.chn_linear_bwd, a, w, b, B.EPI[epi], p.d(aux), c, d, p.d(db), p.gemm_ws, p.gemm_ws_bytes, operations=2 if dx is None else 3)
 
 
 class MLPTrainer:
@@ -199,7 +201,13 @@ class MLPTrainer:
         return self.loss
 
     def n_launch_calls(self, x, t):
-        """Library calls of a step (a layer's whole backward may be one of them)."""
+        """Library operations of a step: a call that does a layer's whole backward counts as the two or three it stands for, so this is
+        no count of calls (n_calls) nor of kernels."""
+        self.step(x, t)
+        return self._progs[(x.data_ptr(), t.data_ptr())].operations
+
+    def n_calls(self, x, t):
+        """Library calls of a step."""
         self.step(x, t)
         return len(self._progs[(x.data_ptr(), t.data_ptr())].calls)
 
@@ -402,5 +410,11 @@ class LSTMTrainer:
         return all(w is None or B.lstm_seq_status(w) == 0 for w in (self.ws_seq, self.ws_seq_bwd))
 
     def n_launch_calls(self, ids, targets):
+        """Library operations of a step (as MLPTrainer.n_launch_calls)."""
+        self.step(ids, targets)
+        return self._progs[(ids.data_ptr(), targets.data_ptr())].operations
+
+    def n_calls(self, ids, targets):
+        """Library calls of a step."""
         self.step(ids, targets)
         return len(self._progs[(ids.data_ptr(), targets.data_ptr())].calls)
