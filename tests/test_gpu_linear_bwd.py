@@ -12,9 +12,9 @@ from paper_1908_00213_amd import binding as B
 pytestmark = pytest.mark.gpu
 RNG = np.random.default_rng(77)
 
-SHAPES = [(1, 1, 1), (2, 3, 5), (32, 10, 100), (32, 100, 784), (33, 17, 65), (31, 15, 16), (64, 64, 64), (257, 16, 48), (600, 24, 40), (1000, 20, 33),   # few blocks (fp32: the small kernel)
-          (1024, 1000, 1000), (1023, 997, 1001), (1025, 200, 1030), (700, 260, 520), (2000, 129, 190), (640, 1000, 784),                    # one 64x64 tile a unit or two, cut or not
-          (1024, 10, 1000), (2500, 70, 3000), (1100, 1030, 1300), (4100, 515, 260), (3000, 650, 1999)]                                    # fp32: sums in parts; bf16, off the grid: three calls
+SHAPES = [(1, 1, 1), (2, 3, 5), (32, 10, 100), (32, 100, 784), (33, 17, 65), (31, 15, 16), (64, 64, 64), (257, 16, 48), (600, 24, 40), (1000, 20, 33),   # small kernel
+          (1024, 1000, 1000), (1023, 997, 1001), (1025, 200, 1030), (700, 260, 520), (2000, 129, 190), (640, 1000, 784),                    # one 64x64 tile a unit or two
+          (1024, 10, 1000), (2500, 70, 3000), (1100, 1030, 1300), (4100, 515, 260), (3000, 650, 1999)]                                    # sums in parts, or none
 
 
 def _dev(a, dt):

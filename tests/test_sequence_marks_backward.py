@@ -19,7 +19,7 @@ class Broken(Exception):
     pass
 
 
-def walk(groups, S, steps, rng, back, wait, again):
+def walk(groups, S, steps, rng, back, wait, again=False):
     """One run under a random schedule.  back: of how many steps ago the dz block is that is marked; wait: whether marks are waited for;
     again: whether some sums are taken again."""
     real = (groups + S - 1) // S
@@ -140,9 +140,9 @@ def test_no_word_is_marked_or_written_too_early():
 
 def test_sums_taken_again_find_the_dz_they_were_made_of():
     assert outcomes(60, again=True) == 0
+    assert outcomes(40, back=1, again=True) > 0
 
 
 def test_the_model_sees_marks_too_early_and_marks_not_waited_for():
     assert outcomes(40, back=1) > 0
     assert outcomes(40, wait=False) > 0
-    assert outcomes(40, back=1, again=True) > 0
