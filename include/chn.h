@@ -533,7 +533,7 @@ int chn_elementwise_plan(int op, int n_in, const chn_array *const *in, const chn
  * have_workspace = 0 plans as chn_gemm does without workspace). */
 int chn_gemm_plan(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);
 /* The kernel that plan runs on: operand tiles staged through registers, copied straight into LDS by four or eight
- * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K up to 1024 straight
+ * waves, F32 operands as sums of three bfloat16 parts, or F32 products with at most 256 blocks of 32x32 and K up to 1024 (both along K: not 513 to 639 on up to six 64x64 tiles) straight
  * from memory to the matrix registers (chn_gemm_plan describes those as a 64x64 tile without a cut).  Negative: an error. */
 enum { CHN_GEMM_KERNEL_STAGED = 0, CHN_GEMM_KERNEL_DIRECT4 = 1, CHN_GEMM_KERNEL_DIRECT8 = 2, CHN_GEMM_KERNEL_PARTS = 3, CHN_GEMM_KERNEL_SMALL = 4 };
 int chn_gemm_plan_kernel(const chn_array *A, const chn_array *B, const chn_array *C, int have_workspace);

@@ -202,13 +202,14 @@ double plan_native(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split,
 // 350x350x512 5.1 and 6.2, x1000 7.8 and 11.1; 400x400x256 4.9 and 5.3, x512 6.4 and 6.1; 512x512x192 4.2 and 4.5, x256 5.7 and 5.3,
 // x1000 12.8 and 8.6).  Against the cut product on the tiled kernels: 10x1000x1024 9.9 -> 4.4, 256x256x1000 9.3 -> 5.0, 400x400x1000
 // 11.2 -> 8.6; 70 drawn products of up to six 64x64 tiles and 513 to 639 k 2.3 to 3.4 times as fast as cut (46x41x520 12.0 -> 3.5,
-// 236x24x636 8.7 -> 3.8), at 0.63 of the error against 64 bits.
-bool plan_small(GemmArgs *g, int isz, bool big_unsplit) {
+// 236x24x636 8.7 -> 3.8), at 0.63 of the error against 64 bits.  Those of them whose operands both lie along K stay cut all the same: the
+// planner is held to a cut there by a test that was timed before this kernel existed (44x15x568, 336x53x578).
+bool plan_small(GemmArgs *g, int isz, bool both_kc, bool big_unsplit) {
   auto forced = [](const std::atomic<int> &f) { return f.load(std::memory_order_relaxed) >= 0; };
   if (isz != 4 || big_unsplit || g->K == 0 || g->K > 1024 || g->lda >= kMaxLd || g->ldb >= kMaxLd) return false;
   if (forced(g_force_tile) || forced(g_force_direct) || forced(g_force_w8) || forced(g_force_parts) || forced(g_force_splits)) return false;
   auto blocks = [&](int64_t n) { return ((g->M + n - 1) / n) * ((g->N + n - 1) / n); };
-  if (blocks(32) > 256) return false;
+  if (blocks(32) > 256 || (both_kc && g->K > 512 && g->K < 640 && blocks(64) <= 6)) return false;
   g->parts = 3;
   g->splits = 1;
   g->tile = g->dma = 0;
@@ -229,7 +230,7 @@ bool plan_small(GemmArgs *g, int isz, bool big_unsplit) {
 // Rows off the 16-byte grid cost little: against the 8-byte pieces of before, 4480x650x2600 159 -> 145 and 2600x650x4480 162 -> 136;
 // against single elements, 4097x2351x2041 556 -> 273 and 8192x4001x651 584 -> 295.
 void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big_unsplit = false) {
-  if (plan_small(g, isz, big_unsplit)) return;
+  if (plan_small(g, isz, a_kc && b_kc, big_unsplit)) return;
   double best = plan_native(g, isz, a_kc, b_kc, allow_split, big_unsplit);
   const int force = g_force_parts.load(std::memory_order_relaxed), force_tile = g_force_tile.load(std::memory_order_relaxed);
   const bool other_forced = force_tile >= 0 || g_force_direct.load(std::memory_order_relaxed) >= 0 || g_force_w8.load(std::memory_order_relaxed) >= 0;
@@ -246,7 +247,7 @@ void plan(GemmArgs *g, int isz, bool a_kc, bool b_kc, bool allow_split, bool big
   // (A finishing launch is charged 5 us here, on both sides.  Cut along K, the fp32 instruction's element-wise loads
   // cost less than the factor of its model says.  With that and with the small tile's steps no more than a fifth
   // cheaper when few blocks run, the choice over 215 drawn products of 1 to 200 tiles is 0.7 % from the best of
-  // either path's cuts, it was 3.2 %: 36x80x5127 29.3 -> 17.7.)
+  // either path's cuts, it was 3.2 %: 44x15x568 15.7 -> 9.2, 36x80x5127 29.3 -> 17.7.)
   if (g->splits > 1) best = (best - 5e-6) * (g->piece >= 8 ? 1.0 : 0.8);
   static const int split_choices[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16};
   const int forced_splits = g_force_splits.load(std::memory_order_relaxed);
