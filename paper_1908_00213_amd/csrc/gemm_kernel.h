@@ -625,14 +625,22 @@ __device__ __forceinline__ void epilogue_pass_vec(const GemmArgs &g, const float
   }
 }
 
+// An epilogue that a kernel is made for: its kind and whether C is bf16, without old C and of products that are not cut.
+constexpr int kAnyEpilogue = -1;
+constexpr int fixed_epilogue(int epi, bool c_bf16) { return epi | (c_bf16 ? 16 : 0); }
+
 // One pass of a wave's epilogue: RP rows x W columns of staged accumulators.  With K splits the raw
 // sums go to this split's slab of the workspace instead.
-template <int TN, int RP, int UMAX = 4>
+template <int TN, int RP, int UMAX = 4, int FIXED = kAnyEpilogue>
 __device__ __forceinline__ void epilogue_pass(const GemmArgs &g, const float *stage, int row0, int col0, int lane, float *slab, float *cs) {
   using L = StageLayout<TN>;
   constexpr int W = L::W, CPR = W / 4;
   auto passes = [&](auto edge_c) __attribute__((always_inline)) {
     constexpr bool EDGE = decltype(edge_c)::value;
+    if constexpr (FIXED != kAnyEpilogue) {
+      epilogue_pass_vec<(FIXED & 15), (FIXED & 16) != 0, false, TN, RP, false, UMAX, EDGE>(g, stage, row0, col0, lane);
+      return;
+    }
     auto run = [&](auto epi_c) __attribute__((always_inline)) {
       constexpr int EPI = decltype(epi_c)::value;
       constexpr bool kF32Only = EPI == CHN_EPI_BF16_COPY;   // (the host refuses a bf16 C for it)
@@ -729,9 +737,7 @@ static __global__ __launch_bounds__(256) void gemm_splitk_finish_kernel(GemmArgs
 // Which C tile (and which K split) a workgroup owns: XCD-aware renumbering, then grouped (8 tile rows
 // at a time) ordering.  All of it stands before a workgroup's first load, and a division is twenty instructions that wait
 // for each other: three of them, and one for the length of a split, are multiplications (us in a graph, bf16, divisions and
-// multiplications: 1024x1000x784 6.79 and 6.73, its input gradient 8.85 and 8.70, its weight gradient 8.61 and 8.65).  One after the other
-// three such kernels gain nothing by it (23.8 and 23.9): there the place of their code decides (the first kernel's moved by 2, 4, 8 and
-// 16 KB and nothing else changed: 24.2, 24.3, 24.7, 24.3).
+// multiplications: 1024x1000x784 6.79 and 6.73, its input gradient 8.85 and 8.70, its weight gradient 8.61 and 8.65).
 // No branches: behind one the next arguments would be another trip to memory.
 struct TilePos { int tm, tn, split; };
 __device__ __forceinline__ unsigned divide(unsigned n, unsigned d, unsigned per) {
@@ -763,7 +769,7 @@ template <int TM, int TN>
 constexpr int kEpiStageBytes = kEpiRows<TM, TN> * StageLayout<TN>::PITCH * 4;
 
 // WAVES_N: waves side by side along N (2 for the 2 x 2 arrangement of four waves, 4 for the 2 x 4 of eight).
-template <int TM, int TN, int WAVES_N = 2>
+template <int TM, int TN, int WAVES_N = 2, int FIXED = kAnyEpilogue>
 __device__ __forceinline__ void write_out(const GemmArgs &g, floatx16 (&acc)[TM][TN], char *stage_bytes, int m0, int n0, int split) {
   using L = StageLayout<TN>;
   constexpr int RP = kEpiRows<TM, TN>, IPP = RP / 32, NPASS = TM / IPP;   // 32-row blocks per pass, passes
@@ -774,7 +780,7 @@ __device__ __forceinline__ void write_out(const GemmArgs &g, floatx16 (&acc)[TM]
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int r = lane & 31, h = lane >> 5;
   float *stage = reinterpret_cast<float *>(stage_bytes);
-  float *slab = g.splits > 1 ? g.partial + (int64_t)split * g.M * g.ldp : nullptr;
+  float *slab = FIXED == kAnyEpilogue && g.splits > 1 ? g.partial + (int64_t)split * g.M * g.ldp : nullptr;
   auto put = [&](auto pc) {
     constexpr int P = decltype(pc)::value;
 #pragma unroll
@@ -793,7 +799,7 @@ __device__ __forceinline__ void write_out(const GemmArgs &g, floatx16 (&acc)[TM]
     if (p == 0) put(std::integral_constant<int, 0>{});
     else put(std::integral_constant<int, NPASS - 1>{});
     __builtin_amdgcn_wave_barrier();
-    epilogue_pass<TN, RP, WAVES_N == 4 ? 2 : 4>(g, stage, m0 + (wm * TM) * 32 + p * RP, n0 + wn * TN * 32, lane, slab, cs);
+    epilogue_pass<TN, RP, WAVES_N == 4 ? 2 : 4, FIXED>(g, stage, m0 + (wm * TM) * 32 + p * RP, n0 + wn * TN * 32, lane, slab, cs);
     __builtin_amdgcn_wave_barrier();
   }
   if constexpr (TM == 4 && (TN == 4 || TN == 2)) {
@@ -1525,7 +1531,7 @@ __global__ __launch_bounds__(512) void gemm_kernel_w8(GemmArgs g) {
 template <int TM> constexpr int kSmallDmaStage = 2 * 64 * TM * 128;
 
 // Block `block` of the product, and its share of the sums.
-template <int TM, bool A_KC, bool B_KC, Sums SUMS>
+template <int TM, bool A_KC, bool B_KC, Sums SUMS, int FIXED = kAnyEpilogue>
 __device__ __forceinline__ void small_dma_block(const GemmArgs &g, unsigned block, char *stage0, char *stage1, char *stage2, char *stage3) {
   using T = bf16_raw;
   constexpr int BM = 64 * TM, BK = 64, STAGES = 4;
@@ -1631,21 +1637,43 @@ __device__ __forceinline__ void small_dma_block(const GemmArgs &g, unsigned bloc
       }
     }
   }
-  write_out<TM, TM>(g, acc, wave == 0 ? stage0 : wave == 1 ? stage1 : wave == 2 ? stage2 : stage3, m0, n0, split);
+  write_out<TM, TM, 2, FIXED>(g, acc, wave == 0 ? stage0 : wave == 1 ? stage1 : wave == 2 ? stage2 : stage3, m0, n0, split);
 }
 
-template <int TM, bool A_KC, bool B_KC, Sums SUMS = Sums::kNone>
+template <int TM, bool A_KC, bool B_KC, Sums SUMS = Sums::kNone, int FIXED = kAnyEpilogue>
 __global__ __launch_bounds__(256) void gemm_kernel_small_dma(GemmArgs g) {
   __shared__ __align__(1024) char stage0[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage1[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage2[kSmallDmaStage<TM>];
   __shared__ __align__(1024) char stage3[kSmallDmaStage<TM>];
-  small_dma_block<TM, A_KC, B_KC, SUMS>(g, blockIdx.x, stage0, stage1, stage2, stage3);
+  small_dma_block<TM, A_KC, B_KC, SUMS, FIXED>(g, blockIdx.x, stage0, stage1, stage2, stage3);
 }
 
+// The 64x64 tile has a kernel for each of the usual epilogues (not cut, no old C; bf16 C, and fp32 C without bias or activation: a weight
+// gradient), everything else takes the one with all of them.  That one is 86 KB, of which a launch runs through 5 KB in pieces that
+// lie all over it; these are 7 to 12 KB in one piece.  A product of a few microseconds waits for its code: the three products of
+// a layer (1024x1000x784) and its bias gradient one after the other 27.5 us with all epilogues in one kernel, 26.2 so.  The 128x128
+// tile (153 KB with all), whose products take 20 us and more, was left as it is.
 template <int TM, bool A_KC, bool B_KC, Sums SUMS = Sums::kNone>
 chn_status launch_small_dma(const GemmArgs &g, hipStream_t st) {
-  hipLaunchKernelGGL((gemm_kernel_small_dma<TM, A_KC, B_KC, SUMS>), dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), 0, st, g);
+  auto kern = gemm_kernel_small_dma<TM, A_KC, B_KC, SUMS>;
+  if constexpr (TM == 1 && SUMS == Sums::kNone) {
+    if (g.splits == 1 && g.beta == 0.0f) {
+      switch (fixed_epilogue(g.epi, g.c_bf16 != 0)) {
+#define CHN_FIXED(epi, c_bf16) case fixed_epilogue(epi, c_bf16): kern = gemm_kernel_small_dma<TM, A_KC, B_KC, SUMS, fixed_epilogue(epi, c_bf16)>; break
+        CHN_FIXED(CHN_EPI_NONE, false);
+        CHN_FIXED(CHN_EPI_NONE, true);
+        CHN_FIXED(CHN_EPI_BIAS, true);
+        CHN_FIXED(CHN_EPI_BIAS_RELU, true);
+        CHN_FIXED(CHN_EPI_BIAS_GELU, true);
+        CHN_FIXED(CHN_EPI_RELU_BWD, true);
+        CHN_FIXED(CHN_EPI_GELU_BWD, true);
+#undef CHN_FIXED
+        default: break;
+      }
+    }
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n * g.splits)), dim3(256), 0, st, g);
   CHN_TRY(check_launch("gemm (small direct copy)"));
   if (g.splits > 1) {
     const int64_t n = (int64_t)g.M * (g.ldp / 4);
